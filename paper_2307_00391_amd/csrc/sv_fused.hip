@@ -347,86 +347,6 @@ __global__ __launch_bounds__(NT) void k_fused(cvec<R> *__restrict__ psi, const F
     }
 }
 
-// One group of the QFT cascade on the register [lo, lo+m): local qubits are
-// the low c bits and the r register bits starting at global position gpos0
-// (register-relative j0).  Each register qubit j of the group gets a
-// Hadamard fused with all controlled phases whose target is j:
-//   forward cascade (QFT without swaps): for j = j0+r-1 .. j0,
-//     H(j), then phase 2 pi (v mod 2^j) / 2^(j+1) on bit j = 1
-//   inverse cascade: for j = j0 .. j0+r-1, conjugate phase first, then H(j)
-// where v is the register value of the amplitude.  Phases are accumulated
-// as exact 64-bit fractions of a turn.
-struct QftPassArgs {
-    uint64_t nl_mask, fix_val;
-    int k, c, gpos0, r;     // local = [0,c) U [gpos0, gpos0 + r)   (r = 0: local = [0,c))
-    int lo, j0, jn;          // register base and the register bits of this group: [j0, j0 + jn)
-    int tpos0;               // tile position of register bit j0
-    int inverse;
-};
-
-template <typename R>
-__global__ __launch_bounds__(FUSE_BLOCK) void k_qft_pass(cvec<R> *__restrict__ psi, QftPassArgs A) {
-    extern __shared__ unsigned char smem_raw[];
-    cvec<R> *tile = reinterpret_cast<cvec<R> *>(smem_raw);
-    const uint32_t T = 1u << A.k;
-    const uint64_t tid = (uint64_t)blockIdx.x + (uint64_t)blockIdx.y * gridDim.x;
-    const uint64_t base = pdep64(tid, A.nl_mask) | A.fix_val;
-    const uint64_t cm = (1ull << A.c) - 1ull;
-    auto gidx = [&](uint32_t t) -> uint64_t {
-        return base | ((uint64_t)t & cm) | (A.r ? ((uint64_t)(t >> A.c) << A.gpos0) : 0ull);
-    };
-    constexpr int U = sizeof(R) == 4 ? 16 : 8;
-    if (T >= FUSE_BLOCK * U) {
-        for (uint32_t t0 = threadIdx.x; t0 < T; t0 += FUSE_BLOCK * U) {
-            cvec<R> buf[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) buf[u] = psi[gidx(t0 + u * FUSE_BLOCK)];
-#pragma unroll
-            for (int u = 0; u < U; ++u) tile[t0 + u * FUSE_BLOCK] = buf[u];
-        }
-    } else {
-        for (uint32_t t = threadIdx.x; t < T; t += FUSE_BLOCK) tile[t] = psi[gidx(t)];
-    }
-    __syncthreads();
-
-    const R h = (R)0.70710678118654752440;
-    for (int s = 0; s < A.jn; ++s) {
-        const int jr = A.inverse ? s : A.jn - 1 - s;       // position inside the group
-        const int j = A.j0 + jr;                            // register-relative qubit
-        const int pos = A.tpos0 + jr;                       // tile position
-        const uint32_t tb = 1u << pos;
-        const uint64_t lowmask = (1ull << j) - 1ull;
-        for (uint32_t p = threadIdx.x; p < T / 2; p += FUSE_BLOCK) {
-            const uint32_t t0 = insert0(p, pos);
-            cvec<R> a0 = tile[t0], a1 = tile[t0 | tb];
-            const uint64_t vlow = (gidx(t0) >> A.lo) & lowmask;
-            const uint64_t turns = j ? (vlow << (63 - j)) : 0ull;
-            if (A.inverse) {
-                if (turns) a1 = cmul<R>(a1, turn_phase<R>(0ull - turns));
-                tile[t0] = cmake<R>((a0.x + a1.x) * h, (a0.y + a1.y) * h);
-                tile[t0 | tb] = cmake<R>((a0.x - a1.x) * h, (a0.y - a1.y) * h);
-            } else {
-                cvec<R> b1 = cmake<R>((a0.x - a1.x) * h, (a0.y - a1.y) * h);
-                if (turns) b1 = cmul<R>(b1, turn_phase<R>(turns));
-                tile[t0] = cmake<R>((a0.x + a1.x) * h, (a0.y + a1.y) * h);
-                tile[t0 | tb] = b1;
-            }
-        }
-        __syncthreads();
-    }
-    if (T >= FUSE_BLOCK * U) {
-        for (uint32_t t0 = threadIdx.x; t0 < T; t0 += FUSE_BLOCK * U) {
-            cvec<R> buf[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) buf[u] = tile[t0 + u * FUSE_BLOCK];
-#pragma unroll
-            for (int u = 0; u < U; ++u) psi[gidx(t0 + u * FUSE_BLOCK)] = buf[u];
-        }
-    } else {
-        for (uint32_t t = threadIdx.x; t < T; t += FUSE_BLOCK) psi[gidx(t)] = tile[t];
-    }
-}
-
 // ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
@@ -448,10 +368,6 @@ static int lds_limit_bytes() {
                         (const void *)k_fused<float, 4, 512>, (const void *)k_fused<float, 3>,
                         (const void *)k_fused<double, 4>, (const void *)k_fused<double, 3>};
     for (const void *f : fk) ok &= hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lim) == hipSuccess;
-    ok &= hipFuncSetAttribute((const void *)k_qft_pass<float>, hipFuncAttributeMaxDynamicSharedMemorySize, lim) ==
-          hipSuccess;
-    ok &= hipFuncSetAttribute((const void *)k_qft_pass<double>, hipFuncAttributeMaxDynamicSharedMemorySize, lim) ==
-          hipSuccess;
     bool at0 = true;
     for (const void *f : fk) {
         hipFuncAttributes fa;
@@ -961,85 +877,6 @@ sv_status run_hadamards(sv_state s, int lo, int m, uint64_t fix_mask, uint64_t f
     return s->dt == SV_C64 ? launch_passes<float>(s, passes) : launch_passes<double>(s, passes);
 }
 
-template <typename R>
-static sv_status qft_cascade_impl(sv_state s, const QftSpec &q, int max_local) {
-    const int n = s->n;
-    const int kmax = clamp_k(s, max_local);
-    const int c0 = std::min(low_bits_for(s->dt), kmax - 1);
-    const uint64_t all = (1ull << n) - 1ull;
-    // group sizes: as many register bits per pass as fit next to the low bits
-    // a register that lies inside the lowest kmax bits is transformed in one pass
-    const int gmax = (q.lo + q.m <= kmax) ? q.m : std::max(1, kmax - c0);
-    std::vector<std::pair<int, int>> groups;   // (j0, count), in application order
-    if (!q.inverse) {
-        int top = q.m;
-        while (top > 0) {
-            int cnt = std::min(gmax, top);
-            groups.push_back({top - cnt, cnt});
-            top -= cnt;
-        }
-    } else {
-        int bot = 0;
-        while (bot < q.m) {
-            int cnt = std::min(gmax, q.m - bot);
-            groups.push_back({bot, cnt});
-            bot += cnt;
-        }
-    }
-    const int nfix = popcount64(q.fix_mask);
-    for (auto &gr : groups) {
-        QftPassArgs A;
-        memset(&A, 0, sizeof A);
-        A.lo = q.lo;
-        A.j0 = gr.first;
-        A.jn = gr.second;
-        A.inverse = q.inverse;
-        const int gpos0 = q.lo + gr.first;
-        // local set: [0, c) U [gpos0, gpos0 + jn) with |local| <= kmax
-        int c = std::min(kmax - gr.second, gpos0);
-        if (c < 0) c = 0;
-        uint64_t L;
-        const uint64_t lowm = (1ull << c) - 1ull;
-        if ((lowm | (((1ull << gr.second) - 1ull) << gpos0)) & q.fix_mask)
-            return fail(SV_EINVAL, "qft: a restricted bit overlaps the pass's local qubits");
-        if (c == gpos0) {
-            // contiguous: [0, gpos0 + jn)
-            A.c = gpos0 + gr.second;
-            A.r = 0;
-            A.gpos0 = 0;
-            A.tpos0 = gpos0;
-            L = (1ull << A.c) - 1ull;
-        } else {
-            A.c = c;
-            A.r = gr.second;
-            A.gpos0 = gpos0;
-            A.tpos0 = c;
-            L = ((1ull << c) - 1ull) | (((1ull << gr.second) - 1ull) << gpos0);
-        }
-        if (L & q.fix_mask) return fail(SV_EINVAL, "qft: restriction bit inside the register");
-        A.k = popcount64(L);
-        A.nl_mask = all & ~L & ~q.fix_mask;
-        A.fix_val = q.fix_val;
-        const uint64_t tiles = dim_of(n - A.k - nfix);
-        const size_t lds = ((size_t)1 << A.k) * sizeof(cvec<R>);
-        {
-            TraceScope _ts(s->stream, "qft_pass", 2.0 * (double)dim_of(n - nfix) * sizeof(cvec<R>), 0.0);
-            hipLaunchKernelGGL(k_qft_pass<R>, tile_grid(tiles), dim3(FUSE_BLOCK), lds, s->stream, (cvec<R> *)s->data, A);
-        }
-    }
-    SV_HIP(hipGetLastError());
-    return SV_OK;
-}
-
-sv_status run_qft_cascade(sv_state s, const QftSpec &q, int max_local) {
-    if (q.m < 1 || q.lo < 0 || q.lo + q.m > s->n) return fail(SV_EINVAL, "qft register out of range");
-    return s->dt == SV_C64 ? qft_cascade_impl<float>(s, q, max_local) : qft_cascade_impl<double>(s, q, max_local);
-}
-
-}  // namespace sv
-
-namespace sv {
-
 // The fusion autotuner (sv_apply_circuit with max_local = 0, states of 2^22
 // amplitudes and more): the candidates are k local qubits in {K-1, K} (K the
 // default, bounded by the LDS) times c contiguous low bits in {C-1, C, C+1}
@@ -1206,17 +1043,6 @@ sv_status sv_apply_circuit(sv_state s, const sv_gate *gates, int n_gates, int ma
     std::vector<HostPass> passes;
     plan(s->n, k, c, pg, passes);
     return s->dt == SV_C64 ? launch_passes<float>(s, passes, rb) : launch_passes<double>(s, passes, rb);
-}
-
-sv_status sv_qft(sv_state s, int q_lo, int m, int inverse, int swaps, int max_local) {
-    clear_error();
-    SV_TRY(check_state(s));
-    if (m < 1 || q_lo < 0 || q_lo + m > s->n) return fail(SV_EINVAL, "register [%d,%d) outside the state", q_lo, q_lo + m);
-    QftSpec q{q_lo, m, inverse ? 1 : 0, 0, 0};
-    if (inverse && swaps) SV_TRY(bitrev_register(s, q_lo, m, 0, 0));
-    SV_TRY(run_qft_cascade(s, q, max_local));
-    if (!inverse && swaps) SV_TRY(bitrev_register(s, q_lo, m, 0, 0));
-    return SV_OK;
 }
 
 }  // extern "C"

@@ -18,10 +18,6 @@
 //           two outside neighbours of every chunk (all select values) into
 //           scratch memory, so the in-place tile pass can read them after the
 //           neighbouring tiles have been overwritten.
-//
-// Spectral form.  Inverse QFT on the register, the wavenumber diagonal
-// Lambda_k as the |1> block of a rotation of one more qubit (controlled on the
-// register value; its table is computed in the kernel), then the QFT.
 #include <math.h>
 
 #include <vector>
@@ -257,34 +253,6 @@ static sv_status lcu_gates(sv_state s, int q_lo, int m, int sel_lo) {
     return sv_apply_gate(s, sel_lo + 1, H, nullptr, nullptr, 0);
 }
 
-// ----------------------------------------------------------- spectral diagonal
-
-// For each register value k: (a0, a1) on qubit anc <- e^{i arg Lambda_k} Ry(t_k) (a0, a1),
-// sin(t_k/2) = |k'| / (N/2 - 1), k' = k (k < N/2) or k - N (k > N/2); arg = +-pi/2, so the
-// phase is an exact multiplication by +-i.  k = 0 and k = N/2 are the identity.
-template <typename R>
-__global__ __launch_bounds__(256) void k_wavenumber_ry(cvec<R> *__restrict__ psi, uint64_t npairs, int anc,
-                                                       int q_lo, int m) {
-    const uint64_t N = 1ull << m, half = N >> 1;
-    const double den = (double)(half - 1);
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t p = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; p < npairs; p += stride) {
-        const uint64_t i0 = ((p >> anc) << (anc + 1)) | (p & ((1ull << anc) - 1ull));
-        const uint64_t k = (i0 >> q_lo) & (N - 1);
-        if (k == 0 || k == half) continue;
-        const uint64_t i1 = i0 | (1ull << anc);
-        const bool pos = k < half;
-        const double sd = (double)(pos ? k : N - k) / den;   // exactly 1 at the largest |k'|
-        const R sn = (R)sd, cs = (R)sqrt(fmax(0.0, 1.0 - sd * sd));
-        const cvec<R> a0 = psi[i0], a1 = psi[i1];
-        const cvec<R> b0 = cmake<R>(cs * a0.x - sn * a1.x, cs * a0.y - sn * a1.y);
-        const cvec<R> b1 = cmake<R>(sn * a0.x + cs * a1.x, sn * a0.y + cs * a1.y);
-        // times +i: (x, y) -> (-y, x); times -i: (x, y) -> (y, -x)
-        psi[i0] = pos ? cmake<R>(-b0.y, b0.x) : cmake<R>(b0.y, -b0.x);
-        psi[i1] = pos ? cmake<R>(-b1.y, b1.x) : cmake<R>(b1.y, -b1.x);
-    }
-}
-
 }  // namespace sv
 
 using namespace sv;
@@ -303,31 +271,6 @@ sv_status sv_lcu_derivative(sv_state s, int q_lo, int m, int sel_lo, int mode) {
     if (mode == 0) return lcu_gates(s, q_lo, m, sel_lo);
     if (mode == 1) return lcu_fused(s, q_lo, m, sel_lo);
     return fail(SV_EINVAL, "mode must be 0 or 1");
-}
-
-sv_status sv_spectral_derivative(sv_state s, int q_lo, int m, int anc, int max_local) {
-    clear_error();
-    SV_TRY(check_state(s));
-    if (m < 2 || q_lo < 0 || q_lo + m > s->n)
-        return fail(SV_EINVAL, "register [%d, %d) outside the state or narrower than 2 qubits", q_lo, q_lo + m);
-    if (m > 30) return fail(SV_EINVAL, "register wider than 30 qubits");
-    if (anc < 0 || anc >= s->n || (anc >= q_lo && anc < q_lo + m))
-        return fail(SV_EINVAL, "qubit %d is outside the state or inside the register", anc);
-    SV_TRY(sv_qft(s, q_lo, m, 1, 1, max_local));
-    {
-        const uint64_t np = dim_of(s->n - 1);
-        uint64_t g = (np + 1023) / 1024;
-        if (g > (1u << 20)) g = 1u << 20;
-        TraceScope ts(s->stream, "wavenumber_ry", 2.0 * (double)dim_of(s->n) * amp_bytes(s->dt), 0.0);
-        if (s->dt == SV_C64)
-            hipLaunchKernelGGL(k_wavenumber_ry<float>, dim3((unsigned)g), dim3(256), 0, s->stream, (float2 *)s->data,
-                               np, anc, q_lo, m);
-        else
-            hipLaunchKernelGGL(k_wavenumber_ry<double>, dim3((unsigned)g), dim3(256), 0, s->stream,
-                               (double2 *)s->data, np, anc, q_lo, m);
-        SV_HIP(hipGetLastError());
-    }
-    return sv_qft(s, q_lo, m, 0, 1, max_local);
 }
 
 }  // extern "C"
