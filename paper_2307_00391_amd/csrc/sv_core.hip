@@ -406,6 +406,25 @@ sv_status bitrev_register(sv_state s, int lo, int m, uint64_t fix_mask, uint64_t
     return SV_OK;
 }
 
+// the uniformly controlled Ry with its (cos, sin) table on the device, in the
+// state's precision; fm / fv: the target (0) and the restricting controls
+sv_status uniform_ry_table(sv_state s, int target, int reg_lo, int m, const void *table, uint64_t fm, uint64_t fv) {
+    const Ins f = make_ins(fm, fv);
+    const uint64_t count = dim_of(s->n - popcount64(fm)), rmask = dim_of(m) - 1;
+    const unsigned g = grid_for(count, 4);
+    if (s->dt == SV_C64) {
+        TraceScope _ts(s->stream, "uniform_ry_c64", (double)count * 32, 0.0);
+        hipLaunchKernelGGL(k_uniform_ry<float>, dim3(g), dim3(256), 0, s->stream, (float2 *)s->data, count, f,
+                           1ull << target, reg_lo, rmask, (const float2 *)table);
+    } else {
+        TraceScope _ts(s->stream, "uniform_ry_c128", (double)count * 64, 0.0);
+        hipLaunchKernelGGL(k_uniform_ry<double>, dim3(g), dim3(256), 0, s->stream, (double2 *)s->data, count, f,
+                           1ull << target, reg_lo, rmask, (const double2 *)table);
+    }
+    SV_HIP(hipGetLastError());
+    return SV_OK;
+}
+
 template <typename R>
 static sv_status launch_gate(sv_state s, int target, const double *u, uint64_t cmask, uint64_t cval) {
     const uint64_t tbit = 1ull << target;
@@ -657,22 +676,7 @@ sv_status sv_apply_uniform_ry(sv_state s, int target, int reg_lo, int m, const d
     } else {
         SV_TRY(upload(s, dt, cs, tb));
     }
-    const Ins f = make_ins(fm, fv);
-    const uint64_t count = dim_of(s->n - popcount64(fm));
-    const unsigned g = grid_for(count, 4);
-    if (s->dt == SV_C64)
-        {
-            TraceScope _ts(s->stream, "uniform_ry_c64", (double)count * 32, 0.0);
-            hipLaunchKernelGGL(k_uniform_ry<float>, dim3(g), dim3(256), 0, s->stream, (float2 *)s->data, count, f,
-                           1ull << target, reg_lo, M - 1, (const float2 *)dt);
-        }
-    else
-        {
-            TraceScope _ts(s->stream, "uniform_ry_c128", (double)count * 64, 0.0);
-            hipLaunchKernelGGL(k_uniform_ry<double>, dim3(g), dim3(256), 0, s->stream, (double2 *)s->data, count, f,
-                           1ull << target, reg_lo, M - 1, (const double2 *)dt);
-        }
-    SV_HIP(hipGetLastError());
+    SV_TRY(uniform_ry_table(s, target, reg_lo, m, dt, fm, fv));
     SV_HIP(hipStreamSynchronize(s->stream));   // the table lives in the small arena
     return SV_OK;
 }

@@ -64,6 +64,9 @@ sv_status check_qubits(sv_state s, const int *qs, int nq, const int *ctrls, cons
 // ---- launchers used across files -----------------------------------------
 // FP64 sum of |a_i|^2 over (i & mask) == value, result left in device memory at *dev_out
 sv_status norm2_device(sv_state s, uint64_t mask, uint64_t value, double *dev_out);
+// uniformly controlled Ry from a device table of (cos, sin) in the state's
+// precision; fm / fv: fixed bits (the target at 0, controls at their values)
+sv_status uniform_ry_table(sv_state s, int target, int reg_lo, int m, const void *table, uint64_t fm, uint64_t fv);
 // in-place bit reversal of the register [lo, lo+m)
 sv_status bitrev_register(sv_state s, int lo, int m, uint64_t fix_mask, uint64_t fix_val);
 

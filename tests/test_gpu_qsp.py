@@ -105,3 +105,29 @@ def test_qsp_errors():
         B.sv_qsp_prepare(st.h, np.array([1.0, np.nan]), 0, 1)
     assert e.value.status == B.SV_EINVAL
     st.close()
+
+
+@pytest.mark.parametrize("dt", ["c128", "c64"])
+@pytest.mark.parametrize("m", [8, 9, 10, 16, 17, 18, 19])
+def test_tables_at_block_and_chunk_edges(dt, m):
+    """The device-built tree around its blocks (2^9 leaves) and upload chunks
+    (2^16 entries: one, two and more than two), both modes, and a bad entry in
+    the last chunk, which leaves the state as it was."""
+    rng = np.random.default_rng(900 + m)
+    b = _b(rng, m, "complex")
+    ref = b / np.linalg.norm(b)
+    st = B.State(m, dt)
+    for mode in (0, 1):
+        B.sv_qsp_prepare(st.h, b, 0, mode)
+        assert np.abs(st.get() - ref).max() <= TOL[dt]
+    before = st.get()
+    for bad in (np.nan, np.inf):
+        b[-1] = bad
+        with pytest.raises(B.SvError) as e:
+            B.sv_qsp_prepare(st.h, b, 0, 1)
+        assert e.value.status == B.SV_EINVAL
+    with pytest.raises(B.SvError) as e:
+        B.sv_qsp_prepare(st.h, np.zeros(1 << m), 0, 1)
+    assert e.value.status == B.SV_EZERONORM
+    assert np.array_equal(st.get(), before)
+    st.close()
