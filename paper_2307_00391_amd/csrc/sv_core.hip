@@ -10,6 +10,7 @@
 #include <string>
 
 #include "sv_device.h"
+#include "sv_fused.h"
 #include "sv_internal.h"
 
 namespace sv {
@@ -72,6 +73,26 @@ sv_status upload(sv_state s, void *dst, const void *src, size_t bytes) {
     memcpy(s->pinned, src, bytes);
     SV_HIP(hipMemcpyAsync(dst, s->pinned, bytes, hipMemcpyHostToDevice, s->stream));
     SV_HIP(hipStreamSynchronize(s->stream));
+    return SV_OK;
+}
+
+// The copy is ordered on the stream; the host waits only for the previous
+// plan's copy out of the staging buffer, not for the passes behind it.
+sv_status upload_plan(sv_state s, void *dst, const void *src, size_t bytes) {
+    if (!bytes) return SV_OK;
+    if (!s->plan_ev) SV_HIP(hipEventCreateWithFlags(&s->plan_ev, hipEventDisableTiming));
+    else SV_HIP(hipEventSynchronize(s->plan_ev));
+    if (s->plan_bytes < bytes) {
+        if (s->plan_pinned) SV_HIP(hipHostFree(s->plan_pinned));
+        s->plan_pinned = nullptr;
+        s->plan_bytes = 0;
+        const size_t sz = std::max<size_t>(bytes + bytes / 2, 1 << 16);
+        SV_HIP(hipHostMalloc(&s->plan_pinned, sz, hipHostMallocDefault));
+        s->plan_bytes = sz;
+    }
+    memcpy(s->plan_pinned, src, bytes);
+    SV_HIP(hipMemcpyAsync(dst, s->plan_pinned, bytes, hipMemcpyHostToDevice, s->stream));
+    SV_HIP(hipEventRecord(s->plan_ev, s->stream));
     return SV_OK;
 }
 
@@ -524,6 +545,8 @@ sv_status sv_free(sv_state s) {
     if (s->scratch) hipFree(s->scratch);
     if (s->small) hipFree(s->small);
     if (s->pinned) hipHostFree(s->pinned);
+    if (s->plan_pinned) hipHostFree(s->plan_pinned);
+    if (s->plan_ev) hipEventDestroy(s->plan_ev);
     delete s;
     return SV_OK;
 }

@@ -24,15 +24,12 @@
 #include <string>
 #include <vector>
 
-#include "sv_device.h"
-#include "sv_internal.h"
+#include "sv_fused.h"
 
 namespace sv {
 
 constexpr int FUSE_BLOCK = 256;
 constexpr int MAX_HI = 20;
-
-enum OpType { OP_U = 0, OP_X = 1, OP_SWAP = 2, OP_PHASE = 3 };
 
 struct FOp {
     int type;
@@ -42,18 +39,6 @@ struct FOp {
     uint64_t gmask, gval;  // condition on non-local bits (global coordinates)
     uint64_t turns;        // OP_PHASE: phase as a fraction of a turn, 2^-64 units
     double u[8];           // OP_U
-};
-
-// an op as a segment runs it: targets as register bits, its local condition
-// split into the register part and the part fixed per thread
-struct ROp {
-    int type;
-    int j0, j1;            // register bits of the target(s)
-    uint32_t rmask, rval;  // condition on the register index
-    uint32_t tmask, tval;  // condition on the tile bits outside the segment's set
-    uint32_t onm;          // bit m set: register index m meets the register condition
-    uint64_t gmask, gval;  // condition on non-local bits
-    double u[8];           // OP_U matrix; OP_PHASE: (cos, sin) of the phase in u[0], u[1]
 };
 
 constexpr int MAX_RB = 5;
@@ -77,158 +62,6 @@ struct FPass {
     int nseg, seg_off;
     int hpos[MAX_HI];      // global positions of the gathered bits, ascending
 };
-
-// global offset of tile coordinate t
-__device__ __forceinline__ uint64_t scatter_t(uint32_t t, int c, int r, const int *__restrict__ hpos) {
-    uint64_t g = t & ((1u << c) - 1u);
-    uint32_t h = t >> c;
-    for (int i = 0; i < r; ++i)
-        if (h >> i & 1u) g |= 1ull << hpos[i];
-    return g;
-}
-
-__device__ __forceinline__ uint32_t insert0(uint32_t p, int pos) {
-    return ((p >> pos) << (pos + 1)) | (p & ((1u << pos) - 1u));
-}
-
-// LDS slot of tile coordinate t: the bank index (the low e = log2(256 B /
-// elem) bits) is XOR-ed with the folded higher bits.  The segment tables
-// are built on the host with the same function.
-__host__ __device__ __forceinline__ uint32_t swz_e(uint32_t t, int e) {
-    const uint32_t m = (1u << e) - 1u;
-    const uint32_t h = t >> e;
-    return t ^ ((h ^ (h >> e) ^ (h >> (2 * e))) & m);
-}
-template <typename R>
-__device__ __forceinline__ uint32_t swz(uint32_t t) {
-    return swz_e(t, sizeof(cvec<R>) == 8 ? 5 : 4);
-}
-
-__device__ __forceinline__ uint32_t pdep32(uint32_t v, uint32_t mask) {
-    uint32_t r = 0;
-    for (uint32_t b = 1; mask; b <<= 1) {
-        const uint32_t low = mask & (0u - mask);
-        if (v & b) r |= low;
-        mask ^= low;
-    }
-    return r;
-}
-
-template <typename R>
-__device__ __forceinline__ cvec<R> csel(bool c, cvec<R> a, cvec<R> b) {
-    return cmake<R>(c ? a.x : b.x, c ? a.y : b.y);
-}
-
-// The register-bit condition of an op is uniform.  Without one every pair
-// is updated (no branches, so the pairs interleave); with one, a uniform
-// branch per pair (on the op's precomputed mask of the register indices
-// that meet it) skips the pairs it leaves alone.
-template <typename R, int RB, int J>
-__device__ __forceinline__ void reg_u(cvec<R> (&v)[1 << RB], const ROp &f) {
-    const cvec<R> u00 = cmake<R>((R)f.u[0], (R)f.u[1]), u01 = cmake<R>((R)f.u[2], (R)f.u[3]);
-    const cvec<R> u10 = cmake<R>((R)f.u[4], (R)f.u[5]), u11 = cmake<R>((R)f.u[6], (R)f.u[7]);
-    if (f.rmask == 0) {
-#pragma unroll
-        for (int m = 0; m < (1 << RB); ++m) {
-            if (m & (1 << J)) continue;
-            const cvec<R> a0 = v[m], a1 = v[m | (1 << J)];
-            v[m] = cmac2<R>(u00, a0, u01, a1);
-            v[m | (1 << J)] = cmac2<R>(u10, a0, u11, a1);
-        }
-    } else {
-        const uint32_t on = f.onm;
-#pragma unroll
-        for (int m = 0; m < (1 << RB); ++m) {
-            if (m & (1 << J)) continue;
-            if (!(on >> m & 1u)) continue;
-            const cvec<R> a0 = v[m], a1 = v[m | (1 << J)];
-            v[m] = cmac2<R>(u00, a0, u01, a1);
-            v[m | (1 << J)] = cmac2<R>(u10, a0, u11, a1);
-        }
-    }
-}
-
-// A conditional swap in place on the bits, d = (a ^ b) & mask, a ^= d,
-// b ^= d: three instructions per pair of words (the AND folds into one
-// three-input bit op), where selects of both words into fresh registers and
-// moves back took four, with no register permutation for the compiler to resolve
-__device__ __forceinline__ void cswap_bits(float &a, float &b, uint32_t mask) {
-    const uint32_t x = __builtin_bit_cast(uint32_t, a), y = __builtin_bit_cast(uint32_t, b);
-    const uint32_t d = (x ^ y) & mask;
-    a = __builtin_bit_cast(float, x ^ d);
-    b = __builtin_bit_cast(float, y ^ d);
-}
-__device__ __forceinline__ void cswap_bits(double &a, double &b, uint32_t mask) {
-    const uint64_t m64 = mask ? ~0ull : 0ull;
-    const uint64_t x = __builtin_bit_cast(uint64_t, a), y = __builtin_bit_cast(uint64_t, b);
-    const uint64_t d = (x ^ y) & m64;
-    a = __builtin_bit_cast(double, x ^ d);
-    b = __builtin_bit_cast(double, y ^ d);
-}
-
-template <typename R, int RB, int J>
-__device__ __forceinline__ void reg_x(cvec<R> (&v)[1 << RB], const ROp &f) {
-    const uint32_t on = f.onm;
-#pragma unroll
-    for (int m = 0; m < (1 << RB); ++m) {
-        if (m & (1 << J)) continue;
-        const uint32_t mask = 0u - (on >> m & 1u);
-        cswap_bits(v[m].x, v[m | (1 << J)].x, mask);
-        cswap_bits(v[m].y, v[m | (1 << J)].y, mask);
-    }
-}
-
-template <typename R, int RB>
-__device__ __forceinline__ void reg_phase(cvec<R> (&v)[1 << RB], const ROp &f) {
-    const cvec<R> ph = cmake<R>((R)f.u[0], (R)f.u[1]);
-    const uint32_t on = f.onm;
-#pragma unroll
-    for (int m = 0; m < (1 << RB); ++m)
-        if (on >> m & 1u) v[m] = cmul<R>(v[m], ph);
-}
-
-template <typename R, int RB>
-__device__ __forceinline__ void reg_apply(cvec<R> (&v)[1 << RB], const ROp &f) {
-    switch (f.type) {
-    case OP_PHASE: reg_phase<R, RB>(v, f); break;
-    case OP_X:
-        switch (f.j0) {
-        case 0: reg_x<R, RB, 0>(v, f); break;
-        case 1: reg_x<R, RB, 1 < RB ? 1 : 0>(v, f); break;
-        case 2: reg_x<R, RB, 2 < RB ? 2 : 0>(v, f); break;
-        case 3: reg_x<R, RB, 3 < RB ? 3 : 0>(v, f); break;
-        default: reg_x<R, RB, 4 < RB ? 4 : 0>(v, f); break;
-        }
-        break;
-    default:
-        switch (f.j0) {
-        case 0: reg_u<R, RB, 0>(v, f); break;
-        case 1: reg_u<R, RB, 1 < RB ? 1 : 0>(v, f); break;
-        case 2: reg_u<R, RB, 2 < RB ? 2 : 0>(v, f); break;
-        case 3: reg_u<R, RB, 3 < RB ? 3 : 0>(v, f); break;
-        default: reg_u<R, RB, 4 < RB ? 4 : 0>(v, f); break;
-        }
-        break;
-    }
-}
-
-// LDS access by byte address.  The kernels that use these have no static LDS,
-// so their dynamic area starts at address 0 (the host checks this): a slot's
-// byte offset, formed by XOR, is then its address with no base added.
-template <typename R> using v2r = R __attribute__((ext_vector_type(2)));
-template <typename T> using lptr = __attribute__((address_space(3))) T *;
-template <typename R>
-__device__ __forceinline__ cvec<R> lds_ld(uint32_t a) {
-    const v2r<R> x = *(lptr<v2r<R>>)(uintptr_t)a;
-    return cmake<R>(x.x, x.y);
-}
-template <typename R>
-__device__ __forceinline__ void lds_st(uint32_t a, cvec<R> v) {
-    v2r<R> x;
-    x.x = v.x;
-    x.y = v.y;
-    *(lptr<v2r<R>>)(uintptr_t)a = x;
-}
 
 // One fused pass.  Blocks walk the tiles tile = block + i * (blocks in the
 // grid): the grid is what the device holds at once, or one tile per block
@@ -403,15 +236,6 @@ static inline dim3 tile_grid(uint64_t tiles) {
     return dim3(1u << 30, (unsigned)(tiles >> 30));
 }
 
-struct PGate {
-    int kind;          // 0 dense U, 1 X, 2 SWAP, 3 diagonal (phases)
-    int t0, t1;
-    uint64_t cmask, cval;
-    uint64_t qubits;   // all qubits touched (targets + controls)
-    uint64_t need;     // qubits that must be local
-    double u[8];
-};
-
 static bool unit_modulus(double re, double im) { return fabs(re * re + im * im - 1.0) < 1e-13; }
 
 static uint64_t angle_turns(double re, double im) {
@@ -463,7 +287,7 @@ struct HostPass {
     std::vector<FOp> ops;
 };
 
-static int ops_of(const PGate &g) {
+int ops_of(const PGate &g) {
     if (g.kind != 3) return 1;
     int c = 0;
     if (!(g.u[0] == 1 && g.u[1] == 0)) ++c;
@@ -530,46 +354,26 @@ static void emit_ops(const PGate &g, uint64_t L, std::vector<FOp> &ops) {
     ops.push_back(f);
 }
 
-constexpr int MAX_OPS_PER_PASS = 96;
+// A pass's ops are interpreted one by one, so their number costs nothing by
+// itself; the bound keeps the tables of a pass small.
+constexpr int MAX_OPS_PER_PASS = 256;
 
 static void plan(int n, int kmax, int c0, const std::vector<PGate> &gates, std::vector<HostPass> &passes) {
     passes.clear();
     // a gate needs at most two local bits besides the low run, so every pass
     // takes at least the first gate left (callers pass c0 <= kmax - 2)
     c0 = std::max(0, std::min(c0, kmax - 2));
-    std::vector<char> done(gates.size(), 0);
-    size_t left = gates.size();
-    const uint64_t low = (1ull << std::min(c0, n)) - 1ull;
-    while (left) {
-        uint64_t L = low, blocked = 0;
-        std::vector<int> take;
-        int nops = 0;
-        for (size_t i = 0; i < gates.size(); ++i) {
-            if (done[i]) continue;
-            const PGate &g = gates[i];
-            if (g.qubits & blocked) {
-                blocked |= g.qubits;
-                continue;
-            }
-            const uint64_t L2 = L | g.need;
-            const int no = ops_of(g);
-            if (popcount64(L2) <= kmax && nops + no <= MAX_OPS_PER_PASS) {
-                L = L2;
-                nops += no;
-                take.push_back((int)i);
-            } else {
-                blocked |= g.qubits;
-            }
-        }
+    std::vector<PlanItem> items;
+    items.reserve(gates.size());
+    for (const PGate &g : gates) items.push_back({g.qubits, g.need, 0, ops_of(g)});
+    std::vector<PlanWindow> wins;
+    plan_windows(items, kmax, (1ull << std::min(c0, n)) - 1ull, -1, -1, MAX_OPS_PER_PASS, wins);
+    const uint64_t all = n >= 64 ? ~0ull : (1ull << n) - 1ull;
+    for (const PlanWindow &w : wins) {
         HostPass hp;
         memset(&hp.hdr, 0, sizeof hp.hdr);
-        finish_layout(n, kmax, L, hp);
-        uint64_t Lfinal = ~hp.hdr.nl_mask & ((n >= 64) ? ~0ull : ((1ull << n) - 1ull));
-        for (int i : take) {
-            emit_ops(gates[i], Lfinal, hp.ops);
-            done[i] = 1;
-            --left;
-        }
+        finish_layout(n, kmax, w.set, hp);
+        for (int i : w.take) emit_ops(gates[i], ~hp.hdr.nl_mask & all, hp.ops);
         if (!hp.ops.empty()) passes.push_back(std::move(hp));
     }
 }
@@ -824,7 +628,7 @@ static sv_status launch_passes(sv_state s, std::vector<HostPass> &passes, int rb
     memcpy(blob.data() + ooff, rops.data(), rops.size() * sizeof(ROp));
     void *dev = nullptr;
     SV_HIP(hipMallocAsync(&dev, blob.size(), s->stream));
-    sv_status st = upload(s, dev, blob.data(), blob.size());
+    sv_status st = upload_plan(s, dev, blob.data(), blob.size());
     if (st != SV_OK) {
         hipFreeAsync(dev, s->stream);
         return st;

@@ -24,6 +24,10 @@ struct sv_state_s {
     size_t small_bytes = 0;
     void *pinned = nullptr;       // pinned host staging
     size_t pinned_bytes = 0;
+    // staging of the gate-list plans: pinned, reused once its event has passed
+    void *plan_pinned = nullptr;
+    size_t plan_bytes = 0;
+    hipEvent_t plan_ev = nullptr;
 };
 
 namespace sv {
