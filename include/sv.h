@@ -133,7 +133,10 @@ typedef struct {
  * it can there, so a run of g gates costs one read and one write of the
  * state instead of g.  Gates are only moved past gates on disjoint qubits;
  * the result equals the in-order product.  max_local <= 0 lets the
- * autotuner choose k.  A pass runs as many workgroups as the device holds at
+ * autotuner choose k.  With max_local = 0, a circuit whose gates touch at most
+ * four qubits each and not only permute or scale amplitudes may run its
+ * passes as blocks instead: the product of the gates on four qubits as one
+ * dense 16 x 16 matrix on the matrix cores.  A pass runs as many workgroups as the device holds at
  * once, each walking a strided run of tiles; SV_FUSED_PERSIST=0 launches one
  * workgroup per tile instead (same results, bit for bit). */
 sv_status sv_apply_circuit(sv_state s, const sv_gate *gates, int n_gates, int max_local);
@@ -384,8 +387,9 @@ int sv_trace_report(char *buf, int len);
  *       0 = 64 x 64 per workgroup, 1 = 16 x 16 per wavefront;
  *   fused/<dtype>/<n>/<circuit>  sv_apply_circuit with max_local = 0: (k
  *       local qubits, c contiguous low bits, rb register bits per segment
- *       line: 5 or 4 for complex64, 4 or 3 for complex128) per circuit
- *       structure; an entry of (k, c) takes the default rb.
+ *       line: 5 or 4 for complex64, 4 or 3 for complex128; 1: the circuit
+ *       runs as matrix-core blocks) per circuit structure; an entry of (k, c)
+ *       takes the default rb.
  * Returns the report length. */
 int sv_tune_report(char *buf, int len);
 /* Sets (n > 0: vals[0..n)) or removes (n == 0) one tuning entry, with the key

@@ -14,6 +14,27 @@ namespace sv {
 
 enum OpType { OP_U = 0, OP_X = 1, OP_SWAP = 2, OP_PHASE = 3 };
 
+constexpr int MAX_HI = 20;
+
+// a tile: the lowest c index bits and r gathered ones
+struct TileLayout {
+    uint64_t nl_mask;      // the other bits (the tile number is deposited here)
+    int k, c, r;           // k = c + r
+    int hpos[MAX_HI];      // index positions of the gathered bits, ascending
+};
+// the tile of a pass with the local bits L, filled up to k bits
+void tile_layout(int n, int k, uint64_t L, TileLayout &t);
+
+struct FOp {
+    int type;
+    int p0, p1;            // tile positions of the target(s)
+    int pad;
+    uint64_t lmask, lval;  // condition on local bits (tile coordinates)
+    uint64_t gmask, gval;  // condition on non-local bits (global coordinates)
+    uint64_t turns;        // OP_PHASE: phase as a fraction of a turn, 2^-64 units
+    double u[8];           // OP_U
+};
+
 // an op as a segment runs it: targets as register bits, its local condition
 // split into the register part and the part fixed per thread
 struct ROp {
@@ -172,6 +193,10 @@ struct PGate {
     double u[8];
 };
 
+// the ops of a gate on a tile with the local bits L
+void emit_ops(const PGate &g, uint64_t L, std::vector<FOp> &ops);
+// an op as ops on the register bits of the tile positions S; returns their number
+int to_rops(const FOp &f, uint32_t S, int RB, std::vector<ROp> &rops);
 // number of the ops a gate turns into (a diagonal gate: one phase per entry that is not 1)
 int ops_of(const PGate &g);
 
@@ -197,6 +222,9 @@ void plan_windows(const std::vector<PlanItem> &items, int cap, uint64_t base, in
 // ---- matrix-core passes (sv_blocks.hip) -------------------------------------
 // every gate fits a block of four qubits, and one at least mixes amplitudes
 bool blocks_eligible(sv_state s, const std::vector<PGate> &gates);
+// passes and blocks they come to on tiles of k qubits with the lowest c in them
+int count_block_passes(const std::vector<PGate> &gates, int k, int c);
+int count_blocks(sv_state s, const std::vector<PGate> &gates, int k, int c);
 // tiles of 2^k amplitudes with the lowest c index bits in them
 sv_status run_blocks(sv_state s, const std::vector<PGate> &gates, int k, int c);
 

@@ -29,17 +29,6 @@
 namespace sv {
 
 constexpr int FUSE_BLOCK = 256;
-constexpr int MAX_HI = 20;
-
-struct FOp {
-    int type;
-    int p0, p1;            // tile positions of the target(s)
-    int pad;
-    uint64_t lmask, lval;  // condition on local bits (tile coordinates)
-    uint64_t gmask, gval;  // condition on non-local bits (global coordinates)
-    uint64_t turns;        // OP_PHASE: phase as a fraction of a turn, 2^-64 units
-    double u[8];           // OP_U
-};
 
 constexpr int MAX_RB = 5;
 
@@ -56,11 +45,8 @@ struct FSeg {
 };
 
 struct FPass {
-    uint64_t nl_mask;      // non-local, non-fixed bits (the tile id is deposited here)
-    uint64_t fix_val;      // fixed non-local bits
-    int k, c, r;           // local count, low contiguous bits, gathered high bits
+    TileLayout t;
     int nseg, seg_off;
-    int hpos[MAX_HI];      // global positions of the gathered bits, ascending
 };
 
 // One fused pass.  Blocks walk the tiles tile = block + i * (blocks in the
@@ -74,10 +60,10 @@ __global__ __launch_bounds__(NT) void k_fused(cvec<R> *__restrict__ psi, const F
     extern __shared__ unsigned char smem_raw[];
     cvec<R> *tile = reinterpret_cast<cvec<R> *>(smem_raw);
     const FPass &P = passes[pi];
-    const int k = P.k, c = P.c, r = P.r;
+    const int k = P.t.k, c = P.t.c, r = P.t.r;
     const uint32_t T = 1u << k;
     const uint64_t tstride = (uint64_t)gridDim.x * gridDim.y;
-    const int *hpos = P.hpos;
+    const int *hpos = P.t.hpos;
 
     // HBM <-> LDS with U loads in flight per thread.  scatter_t is a bit
     // deposit, so the thread's part (bits below log2 NT), the part of
@@ -115,7 +101,7 @@ __global__ __launch_bounds__(NT) void k_fused(cvec<R> *__restrict__ psi, const F
         return w;
     };
     for (uint64_t tl = (uint64_t)blockIdx.x + (uint64_t)blockIdx.y * gridDim.x; tl < ntiles; tl += tstride) {
-        const uint64_t base = pdep64(tl, P.nl_mask) | P.fix_val;
+        const uint64_t base = pdep64(tl, P.t.nl_mask);
         if (big) {
             for (uint32_t t0 = 0; t0 < T; t0 += NT * U) {
                 const uint64_t g0 = base | gthr | scatter_t(t0, c, r, hpos);
@@ -295,19 +281,18 @@ int ops_of(const PGate &g) {
     return c;
 }
 
-static void finish_layout(int n, int k, uint64_t L, HostPass &hp) {
+void tile_layout(int n, int k, uint64_t L, TileLayout &t) {
     // fill the local set up to k with the lowest free bits
     for (int q = 0; q < n && popcount64(L) < k; ++q) L |= 1ull << q;
     int c = 0;
     while (c < n && (L >> c & 1)) ++c;
-    hp.hdr.c = c;
-    hp.hdr.k = popcount64(L);
-    hp.hdr.r = 0;
+    t.c = c;
+    t.k = popcount64(L);
+    t.r = 0;
     for (int q = c; q < n; ++q)
-        if (L >> q & 1) hp.hdr.hpos[hp.hdr.r++] = q;
+        if (L >> q & 1) t.hpos[t.r++] = q;
     const uint64_t all = (n >= 64) ? ~0ull : ((1ull << n) - 1ull);
-    hp.hdr.nl_mask = all & ~L;
-    hp.hdr.fix_val = 0;
+    t.nl_mask = all & ~L;
 }
 
 static int tile_pos(uint64_t L, int q) { return popcount64(L & ((1ull << q) - 1ull)); }
@@ -319,7 +304,7 @@ static uint64_t to_tile_mask(uint64_t L, uint64_t gm) {
     return r;
 }
 
-static void emit_ops(const PGate &g, uint64_t L, std::vector<FOp> &ops) {
+void emit_ops(const PGate &g, uint64_t L, std::vector<FOp> &ops) {
     FOp f;
     memset(&f, 0, sizeof f);
     const uint64_t lc = g.cmask & L, gc = g.cmask & ~L;
@@ -372,8 +357,8 @@ static void plan(int n, int kmax, int c0, const std::vector<PGate> &gates, std::
     for (const PlanWindow &w : wins) {
         HostPass hp;
         memset(&hp.hdr, 0, sizeof hp.hdr);
-        finish_layout(n, kmax, w.set, hp);
-        for (int i : w.take) emit_ops(gates[i], ~hp.hdr.nl_mask & all, hp.ops);
+        tile_layout(n, kmax, w.set, hp.hdr.t);
+        for (int i : w.take) emit_ops(gates[i], ~hp.hdr.t.nl_mask & all, hp.ops);
         if (!hp.ops.empty()) passes.push_back(std::move(hp));
     }
 }
@@ -402,6 +387,49 @@ static uint32_t on_mask(uint32_t rmask, uint32_t rval, int RB) {
     for (uint32_t m = 0; m < (1u << RB); ++m)
         if ((m & rmask) == rval) on |= 1u << m;
     return on;
+}
+
+// a tile-level op as ops on the register bits of the positions S (its local
+// conditions outside S become per-thread conditions); returns their number
+int to_rops(const FOp &f, uint32_t S, int RB, std::vector<ROp> &rops) {
+    ROp o;
+    memset(&o, 0, sizeof o);
+    o.type = f.type;
+    o.j0 = f.type == OP_PHASE ? 0 : __builtin_ctz(compress_bits(1u << f.p0, S));
+    o.j1 = f.type == OP_SWAP ? __builtin_ctz(compress_bits(1u << f.p1, S)) : 0;
+    o.rmask = compress_bits((uint32_t)f.lmask & S, S);
+    o.rval = compress_bits((uint32_t)f.lval & S, S);
+    o.tmask = (uint32_t)f.lmask & ~S;
+    o.tval = (uint32_t)f.lval & ~S;
+    o.onm = on_mask(o.rmask, o.rval, RB);
+    o.gmask = f.gmask;
+    o.gval = f.gval;
+    if (f.type == OP_PHASE) {
+        const long double a = ldexpl((long double)(int64_t)f.turns, -64) * 2.0L * 3.14159265358979323846264338327950288L;
+        o.u[0] = (double)cosl(a);
+        o.u[1] = (double)sinl(a);
+    } else {
+        memcpy(o.u, f.u, sizeof o.u);
+    }
+    if (f.type != OP_SWAP) {
+        rops.push_back(o);
+        return 1;
+    }
+    // SWAP(a, b) = CX(a -> b) CX(b -> a) CX(a -> b), each an X on
+    // a register bit controlled by the other
+    const int a = o.j0, b = o.j1;
+    ROp x = o;
+    x.type = OP_X;
+    for (int r = 0; r < 3; ++r) {
+        const int tgt = r == 1 ? a : b, ctl = r == 1 ? b : a;
+        x.j0 = tgt;
+        x.j1 = 0;
+        x.rmask = o.rmask | (1u << ctl);
+        x.rval = o.rval | (1u << ctl);
+        x.onm = on_mask(x.rmask, x.rval, RB);
+        rops.push_back(x);
+    }
+    return 3;
 }
 
 // Register-controlled NOTs at either end of a segment permute the register
@@ -461,7 +489,7 @@ static void fold_permutations(FSeg &g, std::vector<ROp> &rops, int RB) {
 // every gate that is ready (all earlier gates it does not commute with are
 // placed) and whose targets fit, in program order, not only a contiguous run.
 static void segment_pass(const HostPass &hp, int RB, int swz_bits, std::vector<FSeg> &segs, std::vector<ROp> &rops) {
-    const int k = hp.hdr.k;
+    const int k = hp.hdr.t.k;
     const std::vector<FOp> &ops = hp.ops;
     const size_t n = ops.size();
     // conflict: a target of one is a target or a local control of the other
@@ -512,48 +540,8 @@ static void segment_pass(const HostPass &hp, int RB, int swz_bits, std::vector<F
             g.off[m] = swz_e(o, swz_bits) * (swz_bits == 5 ? 8u : 16u);   // bytes
         }
         g.op_off = (int)rops.size();
-        g.nops = (int)seg.size();
-        for (int q : seg) {
-            const FOp &f = ops[q];
-            ROp o;
-            memset(&o, 0, sizeof o);
-            o.type = f.type;
-            o.j0 = f.type == OP_PHASE ? 0 : __builtin_ctz(compress_bits(1u << f.p0, S));
-            o.j1 = f.type == OP_SWAP ? __builtin_ctz(compress_bits(1u << f.p1, S)) : 0;
-            o.rmask = compress_bits((uint32_t)f.lmask & S, S);
-            o.rval = compress_bits((uint32_t)f.lval & S, S);
-            o.tmask = (uint32_t)f.lmask & ~S;
-            o.tval = (uint32_t)f.lval & ~S;
-            o.onm = on_mask(o.rmask, o.rval, RB);
-            o.gmask = f.gmask;
-            o.gval = f.gval;
-            if (f.type == OP_PHASE) {
-                const long double a = ldexpl((long double)(int64_t)f.turns, -64) * 2.0L * 3.14159265358979323846264338327950288L;
-                o.u[0] = (double)cosl(a);
-                o.u[1] = (double)sinl(a);
-            } else {
-                memcpy(o.u, f.u, sizeof o.u);
-            }
-            if (f.type == OP_SWAP) {
-                // SWAP(a, b) = CX(a -> b) CX(b -> a) CX(a -> b), each an X on
-                // a register bit controlled by the other
-                const int a = o.j0, b = o.j1;
-                ROp x = o;
-                x.type = OP_X;
-                for (int r = 0; r < 3; ++r) {
-                    const int tgt = r == 1 ? a : b, ctl = r == 1 ? b : a;
-                    x.j0 = tgt;
-                    x.j1 = 0;
-                    x.rmask = o.rmask | (1u << ctl);
-                    x.rval = o.rval | (1u << ctl);
-                    x.onm = on_mask(x.rmask, x.rval, RB);
-                    rops.push_back(x);
-                }
-                g.nops += 2;
-                continue;
-            }
-            rops.push_back(o);
-        }
+        g.nops = 0;
+        for (int q : seg) g.nops += to_rops(ops[q], S, RB, rops);
         fold_permutations(g, rops, RB);
         segs.push_back(g);
     }
@@ -604,16 +592,16 @@ static sv_status launch_passes(sv_state s, std::vector<HostPass> &passes, int rb
     if (passes.empty()) return SV_OK;
     lds_limit_bytes();
     if (!g_fused_lds_at_0) return fail(SV_EDEVICE, "the fused-pass kernels carry static LDS; their tile addressing needs none");
-    int RB = reg_bits_for(s->dt, passes[0].hdr.k);
+    int RB = reg_bits_for(s->dt, passes[0].hdr.t.k);
     if (rb_req > 0) {
         if (rb_req < 3 || rb_req > (sizeof(R) == 4 ? 5 : 4)) return fail(SV_EINVAL, "%d register bits per segment line", rb_req);
-        RB = std::min(rb_req, passes[0].hdr.k);
+        RB = std::min(rb_req, passes[0].hdr.t.k);
     }
     if (RB < 3) return fail(SV_EUNSUPPORTED, "state too small for fused passes");
     std::vector<FSeg> segs;
     std::vector<ROp> rops;
     for (auto &p : passes) {
-        if (p.hdr.k < RB) return fail(SV_EDEVICE, "pass with %d local qubits (< %d)", p.hdr.k, RB);
+        if (p.hdr.t.k < RB) return fail(SV_EDEVICE, "pass with %d local qubits (< %d)", p.hdr.t.k, RB);
         p.hdr.seg_off = (int)segs.size();
         segment_pass(p, RB, sizeof(R) == 4 ? 5 : 4, segs, rops);
         p.hdr.nseg = (int)segs.size() - p.hdr.seg_off;
@@ -638,15 +626,15 @@ static sv_status launch_passes(sv_state s, std::vector<HostPass> &passes, int rb
     const ROp *dops = (const ROp *)((unsigned char *)dev + ooff);
     for (size_t i = 0; i < passes.size(); ++i) {
         const FPass &h = passes[i].hdr;
-        const uint64_t tiles = dim_of(s->n - h.k);
-        const size_t lds = ((size_t)1 << h.k) * sizeof(cvec<R>);
+        const uint64_t tiles = dim_of(s->n - h.t.k);
+        const size_t lds = ((size_t)1 << h.t.k) * sizeof(cvec<R>);
         TraceScope _ts(s->stream, "fused_pass", 2.0 * (double)dim_of(s->n) * sizeof(cvec<R>), 0.0);
         cvec<R> *psi = (cvec<R> *)s->data;
         // complex64 lines of 16 amplitudes on tiles of 2^13 or more: 512
         // threads, so that each has one line per segment and two workgroups
         // of a 64 KiB tile keep four waves on every SIMD
         if (RB == 5 && sizeof(R) == 4) launch_fused<float, 5>(tiles, lds, s->stream, (cvec<float> *)psi, dp, (int)i, ds, dops);
-        else if (RB >= 4 && sizeof(R) == 4 && (1u << (h.k - 4)) >= 512u)
+        else if (RB >= 4 && sizeof(R) == 4 && (1u << (h.t.k - 4)) >= 512u)
             launch_fused<float, 4, 512>(tiles, lds, s->stream, (cvec<float> *)psi, dp, (int)i, ds, dops);
         else if (RB >= 4) launch_fused<R, 4>(tiles, lds, s->stream, psi, dp, (int)i, ds, dops);
         else launch_fused<R, 3>(tiles, lds, s->stream, psi, dp, (int)i, ds, dops);
@@ -681,6 +669,33 @@ sv_status run_hadamards(sv_state s, int lo, int m, uint64_t fix_mask, uint64_t f
     return s->dt == SV_C64 ? launch_passes<float>(s, passes) : launch_passes<double>(s, passes);
 }
 
+// rb of a configuration that runs as matrix-core blocks (sv_blocks.hip)
+constexpr int RB_BLOCKS = 1;
+
+// the environment names the vector passes' own parameters
+static bool fusion_pinned() { return getenv("SV_FUSED_LOWBITS") || getenv("SV_FUSED_RB"); }
+
+// The configuration without tuning, for states below 2^22 amplitudes (larger
+// ones: the vector passes).  Times here are launches, latencies and the
+// serial run of a tile's gates, and blocks shorten the last: 4 layers of U3 +
+// CNOT ladder take 56 against 134 us on 14 qubits and 119 against 251 us on 20
+// (complex64), 80 mixed gates 113 against 135 and 135 against 157 us.  In
+// complex128 a block costs four times as much, so from 19 qubits on blocks
+// with few gates lose (20 qubits, 80 mixed gates, two gates per block: 195
+// against 153 us; the layers, five per block: 150 against 226 us).
+// The tile grows with the state, so that small states still spread over many
+// compute units: 14 qubits, complex64, k = 8 .. 13: 72 71 54 56 57 71 us; 20
+// qubits: 337 243 179 122 119 117 us.
+static void fusion_default(sv_state s, const std::vector<PGate> &pg, int &k, int &c, int &rb) {
+    if (s->n >= 22 || !blocks_eligible(s, pg)) return;
+    const bool wide = s->dt == SV_C128;
+    const int bk = std::min(wide ? 12 : 13, std::max(std::min(s->n, 10), s->n / 2 + (wide ? 2 : 3)));
+    if (wide && s->n >= 19 && count_blocks(s, pg, bk, 3) * 3 > (int)pg.size()) return;
+    k = bk;
+    c = 3;
+    rb = RB_BLOCKS;
+}
+
 // The fusion autotuner (sv_apply_circuit with max_local = 0, states of 2^22
 // amplitudes and more): the candidates are k local qubits in {K-1, K} (K the
 // default, bounded by the LDS) times c contiguous low bits in {C-1, C, C+1}
@@ -691,7 +706,9 @@ sv_status run_hadamards(sv_state s, int lo, int m, uint64_t fix_mask, uint64_t f
 // others spread over the plan times their number.  When the two best
 // estimates are within 10 %, both run their whole plan, and the faster is kept.  Cached per dtype, size and circuit
 // structure (gate kinds and qubits, not angles) as (k, c, rb); an entry of
-// (k, c) takes the default rb.  SV_FUSED_LOWBITS pins c and skips the tuning.
+// (k, c) takes the default rb, rb = 1 stands for matrix-core blocks, which run
+// beside the candidates above where every gate fits one.  SV_FUSED_LOWBITS pins
+// c and skips the tuning.
 static uint64_t circuit_signature(const std::vector<PGate> &pg) {
     uint64_t h = 1469598103934665603ull;
     auto mix = [&](uint64_t v) {
@@ -713,7 +730,11 @@ static uint64_t circuit_signature(const std::vector<PGate> &pg) {
 }
 
 sv_status fusion_config(sv_state s, const std::vector<PGate> &pg, int &k, int &c, int &rb) {
-    if (s->n < 22 || getenv("SV_FUSED_LOWBITS")) return SV_OK;
+    if (s->n < 22) {
+        if (!fusion_pinned()) fusion_default(s, pg, k, c, rb);
+        return SV_OK;
+    }
+    if (getenv("SV_FUSED_LOWBITS")) return SV_OK;
     char sig[32];
     snprintf(sig, sizeof sig, "%016llx", (unsigned long long)circuit_signature(pg));
     const std::string key = std::string("fused/") + (s->dt == SV_C64 ? "c64/" : "c128/") + std::to_string(s->n) + "/" + sig;
@@ -781,6 +802,17 @@ sv_status fusion_config(sv_state s, const std::vector<PGate> &pg, int &k, int &c
             }
         }
     }
+    // matrix-core blocks: the whole circuit, or on large states a prefix of it
+    // (at least four gates per qubit), scaled
+    if (st == SV_OK && !fusion_pinned() && blocks_eligible(s, pg)) {
+        const size_t part = s->n <= 28 ? pg.size() : std::min(pg.size(), (size_t)(4 * s->n));
+        const std::vector<PGate> head(pg.begin(), pg.begin() + (long)part);
+        for (int cc = s->dt == SV_C64 ? 3 : 2, e = cc + 1; cc <= e && st == SV_OK && blocks_eligible(s, head); ++cc) {
+            float ms = 0.f;
+            st = time_stream(s->stream, 1, &ms, [&]() { return run_blocks(t, head, K, cc); });
+            if (st == SV_OK) cands.push_back({ms * (float)pg.size() / (float)part, K, cc, RB_BLOCKS});
+        }
+    }
     // the two best estimates, when within 10 % of each other (closer than the
     // sample can tell apart), both run their whole plan, and the faster is kept
     std::sort(cands.begin(), cands.end(), [](const Cand &x, const Cand &y) { return x.est < y.est; });
@@ -793,9 +825,10 @@ sv_status fusion_config(sv_state s, const std::vector<PGate> &pg, int &k, int &c
     for (size_t i = 0; i < cands.size() && i < nfull && nfull > 1 && st == SV_OK; ++i) {
         const Cand &cd = cands[i];
         std::vector<HostPass> passes;
-        plan(s->n, cd.k, cd.c, pg, passes);
+        if (cd.rb != RB_BLOCKS) plan(s->n, cd.k, cd.c, pg, passes);
         float ms = 0.f;
         st = time_stream(s->stream, 1, &ms, [&]() {
+            if (cd.rb == RB_BLOCKS) return run_blocks(t, pg, cd.k, cd.c);
             return s->dt == SV_C64 ? launch_passes<float>(t, passes, cd.rb) : launch_passes<double>(t, passes, cd.rb);
         });
         if (st == SV_OK && ms < best) {
@@ -828,8 +861,11 @@ int sv_plan_passes(int n_qubits, sv_dtype dt, const sv_gate *gates, int n_gates,
     if (to_pgates(&tmp, gates, n_gates, pg) != SV_OK) return -1;
     int k = max_local > 0 ? max_local : default_max_local(dt);
     if (k > n_qubits) k = n_qubits;
+    int c = std::min(low_bits_for(dt), k - 2), rb = 0;
+    if (max_local == 0 && !fusion_pinned()) fusion_default(&tmp, pg, k, c, rb);
+    if (rb == RB_BLOCKS) return count_block_passes(pg, k, c);
     std::vector<HostPass> passes;
-    plan(n_qubits, k, std::min(low_bits_for(dt), k - 2), pg, passes);
+    plan(n_qubits, k, c, pg, passes);
     return (int)passes.size();
 }
 
@@ -844,6 +880,7 @@ sv_status sv_apply_circuit(sv_state s, const sv_gate *gates, int n_gates, int ma
     if (k < 3) return fail(SV_EUNSUPPORTED, "state too small for fused passes");
     int c = std::max(0, std::min(low_bits_for(s->dt), k - 2)), rb = 0;
     if (max_local == 0) SV_TRY(fusion_config(s, pg, k, c, rb));
+    if (rb == RB_BLOCKS) return run_blocks(s, pg, k, c);
     std::vector<HostPass> passes;
     plan(s->n, k, c, pg, passes);
     return s->dt == SV_C64 ? launch_passes<float>(s, passes, rb) : launch_passes<double>(s, passes, rb);

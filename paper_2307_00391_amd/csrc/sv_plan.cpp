@@ -24,14 +24,17 @@ struct Scan {
     int ncand;
 };
 
-// what a window with the qubits `set` can run of the gates left
-void scan(const std::vector<PlanItem> &items, const std::vector<int> &left, uint64_t set, int cap, int item_out,
-          int window_out, int max_ops, bool want_cand, Scan &r, std::vector<int> *take) {
+// what a window with the qubits `set` can run of the gates left (packed in
+// program order); `take`: their places in `left`
+void scan(const std::vector<PlanItem> &left, uint64_t set, int cap, int item_out, int window_out, int max_ops,
+          bool want_cand, Scan &r, std::vector<int> *take) {
     uint64_t blocked = 0, ext = 0;
     r.ops = 0;
     r.ncand = 0;
-    for (int i : left) {
-        const PlanItem &g = items[i];
+    const PlanItem *it = left.data();
+    const int n = (int)left.size();
+    for (int i = 0; i < n; ++i) {
+        const PlanItem &g = it[i];
         if (g.order & blocked) {
             blocked |= g.order;
         } else {
@@ -42,17 +45,17 @@ void scan(const std::vector<PlanItem> &items, const std::vector<int> &left, uint
                 ext |= out;
                 r.ops += g.ops;
                 if (take) take->push_back(i);
-            } else {
-                if (want_cand && r.ncand < MAX_CAND) {
-                    const uint64_t m = (near ? g.need : g.need | g.order) & ~set;
-                    if (m && popcount64(set | m) <= cap) {
-                        bool seen = false;
-                        for (int j = 0; j < r.ncand; ++j) seen |= r.cand[j] == m;
-                        if (!seen) r.cand[r.ncand++] = m;
-                    }
-                }
-                blocked |= g.order;
+                continue;
             }
+            if (want_cand && r.ncand < MAX_CAND) {
+                const uint64_t m = (near ? g.need : g.need | g.order) & ~set;
+                if (m && popcount64(set | m) <= cap) {
+                    bool seen = false;
+                    for (int j = 0; j < r.ncand; ++j) seen |= r.cand[j] == m;
+                    if (!seen) r.cand[r.ncand++] = m;
+                }
+            }
+            blocked |= g.order;
         }
         // Once every qubit of the window waits, only gates that need none of
         // them (phases on other qubits) are left: they are taken, not counted.
@@ -65,20 +68,20 @@ void scan(const std::vector<PlanItem> &items, const std::vector<int> &left, uint
 void plan_windows(const std::vector<PlanItem> &items, int cap, uint64_t base, int item_out, int window_out,
                   int max_ops, std::vector<PlanWindow> &out) {
     out.clear();
-    std::vector<int> left(items.size()), rest;
-    for (size_t i = 0; i < left.size(); ++i) left[i] = (int)i;
-    std::vector<char> done(items.size(), 0);
+    std::vector<PlanItem> left(items);
+    std::vector<int> where(items.size()), take;
+    for (size_t i = 0; i < where.size(); ++i) where[i] = (int)i;
     Scan r, t;
     while (!left.empty()) {
-        const PlanItem &f = items[left[0]];
+        const PlanItem &f = left[0];
         uint64_t set = base | f.need;
         if (item_out >= 0 && popcount64(f.ext | (f.order & ~set)) > item_out) set |= f.order;
         while (popcount64(set) < cap) {
-            scan(items, left, set, cap, item_out, window_out, max_ops, true, r, nullptr);
+            scan(left, set, cap, item_out, window_out, max_ops, true, r, nullptr);
             if (!r.ncand) break;
             int best = -1, at = 0;
-            for (int j = 0; j < r.ncand; ++j) {
-                scan(items, left, set | r.cand[j], cap, item_out, window_out, max_ops, false, t, nullptr);
+            for (int j = 0; j < r.ncand && r.ncand > 1; ++j) {
+                scan(left, set | r.cand[j], cap, item_out, window_out, max_ops, false, t, nullptr);
                 if (t.ops > best) {
                     best = t.ops;
                     at = j;
@@ -86,15 +89,25 @@ void plan_windows(const std::vector<PlanItem> &items, int cap, uint64_t base, in
             }
             set |= r.cand[at];
         }
-        PlanWindow w;
+        out.emplace_back();
+        PlanWindow &w = out.back();
         w.set = set;
-        scan(items, left, set, cap, item_out, window_out, max_ops, false, r, &w.take);
-        for (int i : w.take) done[i] = 1;
-        rest.clear();
-        for (int i : left)
-            if (!done[i]) rest.push_back(i);
-        left.swap(rest);
-        out.push_back(std::move(w));
+        take.clear();
+        scan(left, set, cap, item_out, window_out, max_ops, false, r, &take);
+        // the rest moves up
+        size_t q = 0, e = 0;
+        w.take.reserve(take.size());
+        for (size_t i = 0; i < left.size(); ++i) {
+            if (e < take.size() && take[e] == (int)i) {
+                w.take.push_back(where[i]);
+                ++e;
+            } else {
+                left[q] = left[i];
+                where[q++] = where[i];
+            }
+        }
+        left.resize(q);
+        where.resize(q);
     }
 }
 
