@@ -384,7 +384,8 @@ int sv_trace_report(char *buf, int len);
  *   eigpipe/<dtype>/<n_s>/<n_c>  fused eigen-frame kernels: (log2 columns
  *       per tile, threads per workgroup) for each of the three kernels;
  *   cgemm/<dtype>/<M>/<N>/<K>/<trans>  the matrix-core GEMM's tile shape:
- *       0 = 64 x 64 per workgroup, 1 = 16 x 16 per wavefront;
+ *       0 = 64 x 64 per workgroup, 1 = 16 x 16 per wavefront, 2 = 16 x 16 with
+ *       k in four parts, 3 = 32 x 32 with k in two;
  *   fused/<dtype>/<n>/<circuit>  sv_apply_circuit with max_local = 0: (k
  *       local qubits, c contiguous low bits, rb register bits per segment
  *       line: 5 or 4 for complex64, 4 or 3 for complex128; 1: the circuit

@@ -10,7 +10,6 @@
 #include <string>
 
 #include "sv_device.h"
-#include "sv_fused.h"
 #include "sv_internal.h"
 
 namespace sv {
@@ -340,8 +339,10 @@ template <typename R> static inline cvec<R> hc(const double *u) {
 // Reduction partials of norm2_into: at most this many blocks.
 constexpr int NORM_MAX_PARTS = 4096;
 
+// 8 amplitudes per thread: 2^19 amplitudes on 256 workgroups take 5 us, where
+// 64 per thread (32 workgroups) took 16
 static uint64_t norm_blocks(uint64_t count) {
-    const uint64_t per_block = 256 * 64;
+    const uint64_t per_block = 256 * 8;
     const uint64_t nb = (count + per_block - 1) / per_block;
     return nb > (uint64_t)NORM_MAX_PARTS ? (uint64_t)NORM_MAX_PARTS : (nb ? nb : 1);
 }
@@ -423,6 +424,36 @@ sv_status bitrev_register(sv_state s, int lo, int m, uint64_t fix_mask, uint64_t
             TraceScope _ts(s->stream, "bitrev_c128", (double)count * 32, 0.0);
             hipLaunchKernelGGL(k_bitrev<double>, dim3(g), dim3(256), 0, s->stream, (double2 *)s->data, count, f, lo, m);
         }
+    SV_HIP(hipGetLastError());
+    return SV_OK;
+}
+
+sv_status init_b_device(sv_state s, const double2 *b, int n_s, int n_clock_superpose, double scale) {
+    const uint64_t dim = dim_of(s->n);
+    const unsigned g = grid_for(dim, 8);
+    if (s->dt == SV_C64) {
+        TraceScope _ts(s->stream, "init_b_c64", (double)dim * 8, 0.0);
+        hipLaunchKernelGGL(k_init_b<float>, dim3(g), dim3(256), 0, s->stream, (float2 *)s->data, dim, b, n_s,
+                           dim_of(n_clock_superpose), scale);
+    } else {
+        TraceScope _ts(s->stream, "init_b_c128", (double)dim * 16, 0.0);
+        hipLaunchKernelGGL(k_init_b<double>, dim3(g), dim3(256), 0, s->stream, (double2 *)s->data, dim, b, n_s,
+                           dim_of(n_clock_superpose), scale);
+    }
+    SV_HIP(hipGetLastError());
+    return SV_OK;
+}
+
+sv_status gather_device(sv_state s, uint64_t mask, uint64_t value, const double *prob, double2 *out) {
+    const uint64_t count = dim_of(s->n - popcount64(mask));
+    const Ins f = make_ins(mask, value);
+    const unsigned g = grid_for(count, 4);
+    if (s->dt == SV_C64)
+        hipLaunchKernelGGL(k_gather_f64<float>, dim3(g), dim3(256), 0, s->stream, out, (const float2 *)s->data, count, f,
+                           prob);
+    else
+        hipLaunchKernelGGL(k_gather_f64<double>, dim3(g), dim3(256), 0, s->stream, out, (const double2 *)s->data, count,
+                           f, prob);
     SV_HIP(hipGetLastError());
     return SV_OK;
 }
@@ -590,21 +621,7 @@ sv_status sv_init_b(sv_state s, const double *b, int n_s, int n_clock_superpose)
     double2 *db = (double2 *)((char *)s->small + 64);
     SV_TRY(upload(s, db, b, N * sizeof(double2)));
     const double scale = 1.0 / (nrm * sqrt((double)dim_of(n_clock_superpose)));
-    const uint64_t dim = dim_of(s->n);
-    const unsigned g = grid_for(dim, 8);
-    if (s->dt == SV_C64)
-        {
-            TraceScope _ts(s->stream, "init_b_c64", (double)dim * 8, 0.0);
-            hipLaunchKernelGGL(k_init_b<float>, dim3(g), dim3(256), 0, s->stream, (float2 *)s->data, dim,
-                           (const double2 *)db, n_s, dim_of(n_clock_superpose), scale);
-        }
-    else
-        {
-            TraceScope _ts(s->stream, "init_b_c128", (double)dim * 16, 0.0);
-            hipLaunchKernelGGL(k_init_b<double>, dim3(g), dim3(256), 0, s->stream, (double2 *)s->data, dim,
-                           (const double2 *)db, n_s, dim_of(n_clock_superpose), scale);
-        }
-    SV_HIP(hipGetLastError());
+    SV_TRY(init_b_device(s, db, n_s, n_clock_superpose, scale));
     SV_HIP(hipStreamSynchronize(s->stream));   // db lives in the small arena
     return SV_OK;
 }
@@ -743,13 +760,7 @@ sv_status sv_postselect(sv_state s, uint64_t mask, uint64_t value, double *prob,
         return SV_OK;
     }
     SV_TRY(ensure_scratch(s, count * sizeof(double2)));
-    if (s->dt == SV_C64)
-        hipLaunchKernelGGL(k_gather_f64<float>, dim3(g), dim3(256), 0, s->stream, (double2 *)s->scratch,
-                           (const float2 *)s->data, count, f, (const double *)dres);
-    else
-        hipLaunchKernelGGL(k_gather_f64<double>, dim3(g), dim3(256), 0, s->stream, (double2 *)s->scratch,
-                           (const double2 *)s->data, count, f, (const double *)dres);
-    SV_HIP(hipGetLastError());
+    SV_TRY(gather_device(s, mask, value, dres, (double2 *)s->scratch));
     return download(s, out, s->scratch, count * sizeof(double2));
 }
 

@@ -228,7 +228,4 @@ int count_blocks(sv_state s, const std::vector<PGate> &gates, int k, int c);
 // tiles of 2^k amplitudes with the lowest c index bits in them
 sv_status run_blocks(sv_state s, const std::vector<PGate> &gates, int k, int c);
 
-// stream-ordered copy of a plan to the device; returns without waiting
-sv_status upload_plan(sv_state s, void *dst, const void *src, size_t bytes);
-
 }  // namespace sv

@@ -190,6 +190,158 @@ __global__ __launch_bounds__(256) void k_cgemm_w(GemmArgs<R> A) {
     }
 }
 
+// Small products: a workgroup computes (16 TA) x (16 TB) outputs with KS groups
+// of TA TB wavefronts, each group one KS-th of the k range, so that products of
+// a few hundred rows and columns still give every SIMD a wavefront or more:
+//   16 x 16, k in four parts:   256 x 256 outputs are 256 workgroups;
+//   32 x 32, k in two parts:    1024 x 256 outputs are 256 workgroups of 8 waves.
+// Operands go through LDS (16 k at a time, whole amplitudes, one pad column so
+// that the k-major rows fall on different banks), two stages; the next two are
+// in registers while one is multiplied.  The parts are added in order.  A
+// wavefront per tile straight from memory (k_cgemm_w) leaves three SIMDs of
+// four idle at 256 x 256 and waits for its 64-byte pieces of 16 rows.  Bound:
+// the latency of the operand loads (a third of the FP64 matrix rate at 1024 x
+// 256 x 256).  Controlled unitary on the given rows, copy back included, N = K
+// = 256, complex128: 256 rows 36.4 -> 13.5 us, 512 rows 37.7 -> 17.3, 1024 rows
+// 40.0 -> 23.4; complex64: 23.9 -> 11.3, 24.5 -> 13.4, 25.8 -> 16.3.  At 2048 x
+// 1024 the 64 x 64 tiles are as fast.
+template <typename R, int TA, int TB, int KS>
+__global__ __launch_bounds__(64 * TA * TB * KS) void k_cgemm_k(GemmArgs<R> A) {
+    using M_ = MfmaT<R>;
+    using acc_t = typename M_::acc;
+    constexpr int PT = 64 * TA * TB, TM = 16 * TA, TN = 16 * TB, KC = 16;
+    constexpr int NA = TM * KC / PT, NB = TN * KC / PT;
+    struct Stage {
+        cvec<R> a[KC][TM + 1], b[KC][TN + 1];
+    };
+    constexpr int NW = TA * TB;
+    union Lds {
+        Stage st[2][KS];
+        R red[KS > 1 ? KS - 1 : 1][NW][8][64];
+    };
+    __shared__ Lds lds;
+    const int part = threadIdx.x / PT, pt = threadIdx.x % PT, lane = pt & 63, wave = pt >> 6;
+    const int wm = wave / TB, wn = wave % TB;
+    const uint64_t row0 = (uint64_t)blockIdx.x * TM;
+    const int n0 = blockIdx.y * TN;
+    const int chunks = (A.K + KC * KS - 1) / (KC * KS);
+    const int kbeg = part * chunks * KC, kend = kbeg + chunks * KC < A.K ? kbeg + chunks * KC : A.K;
+
+    // this thread's elements: lanes along k where k is contiguous in memory
+    // (16 of them: 128 or 256 bytes), along rows or columns otherwise
+    int a_row[NA], a_k[NA], b_n[NB], b_k[NB];
+    uint64_t a_base[NA];
+    bool a_ok[NA];
+#pragma unroll
+    for (int i = 0; i < NA; ++i) {
+        const int e = pt + i * PT;
+        a_row[i] = A.ksh ? e % TM : e / KC;
+        a_k[i] = A.ksh ? e / TM : e % KC;
+        const uint64_t r = row0 + (uint64_t)a_row[i];
+        a_ok[i] = r < A.M;
+        a_base[i] = a_ok[i] ? (pdep64(r, A.row_mask) | A.row_fix) : 0;
+    }
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+        const int e = pt + i * PT;
+        b_n[i] = A.trans ? e % TN : e / KC;
+        b_k[i] = A.trans ? e / TN : e % KC;
+    }
+    const R csgn = A.conjb ? (R)-1 : (R)1;
+    struct Regs {
+        cvec<R> a[NA], b[NB];
+    };
+    auto fetch = [&](int ch, Regs &p) {
+        const int k0 = kbeg + ch * KC;
+#pragma unroll
+        for (int i = 0; i < NA; ++i) {
+            const int kk = k0 + a_k[i];
+            p.a[i] = cmake<R>((R)0, (R)0);
+            if (a_ok[i] && kk < kend) p.a[i] = A.in[a_base[i] + ((uint64_t)kk << A.ksh)];
+        }
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            const int kk = k0 + b_k[i], nn = n0 + b_n[i];
+            p.b[i] = cmake<R>((R)0, (R)0);
+            if (kk < kend && nn < A.N) p.b[i] = A.trans ? A.U[(uint64_t)kk * A.N + nn] : A.U[(uint64_t)nn * A.K + kk];
+        }
+    };
+    auto stage = [&](Stage &S, const Regs &p) {
+#pragma unroll
+        for (int i = 0; i < NA; ++i) S.a[a_k[i]][a_row[i]] = p.a[i];
+#pragma unroll
+        for (int i = 0; i < NB; ++i) S.b[b_k[i]][b_n[i]] = cmake<R>(p.b[i].x, csgn * p.b[i].y);
+    };
+    acc_t acc_re, acc_im;
+    for (int v = 0; v < 4; ++v) acc_re[v] = acc_im[v] = (R)0;
+    auto multiply = [&](const Stage &S) {
+#pragma unroll
+        for (int kc = 0; kc < KC / 4; ++kc) {
+            const int kr = kc * 4 + (lane >> 4), li = lane & 15;
+            const cvec<R> a = S.a[kr][wm * 16 + li], b = S.b[kr][wn * 16 + li];
+            acc_re = M_::mfma(a.x, b.x, acc_re);
+            acc_im = M_::mfma(a.x, b.y, acc_im);
+            acc_re = M_::mfma(-a.y, b.y, acc_re);
+            acc_im = M_::mfma(a.y, b.x, acc_im);
+        }
+    };
+    // two chunks ahead in registers, one in LDS (fetches past the end read nothing)
+    Regs p0, p1;
+    fetch(0, p0);
+    fetch(1, p1);
+    stage(lds.st[0][part], p0);
+    __syncthreads();
+    for (int ch = 0; ch < chunks; ch += 2) {
+        fetch(ch + 2, p0);
+        multiply(lds.st[0][part]);
+        stage(lds.st[1][part], p1);
+        __syncthreads();
+        if (ch + 1 >= chunks) break;
+        fetch(ch + 3, p1);
+        multiply(lds.st[1][part]);
+        stage(lds.st[0][part], p0);
+        __syncthreads();
+    }
+    if (KS > 1) {
+        if (part > 0)
+            for (int v = 0; v < 4; ++v) {
+                lds.red[part - 1][wave][v][lane] = acc_re[v];
+                lds.red[part - 1][wave][4 + v][lane] = acc_im[v];
+            }
+        __syncthreads();
+        if (part > 0) return;
+        for (int p = 0; p < KS - 1; ++p)
+            for (int v = 0; v < 4; ++v) {
+                acc_re[v] += lds.red[p][wave][v][lane];
+                acc_im[v] += lds.red[p][wave][4 + v][lane];
+            }
+    }
+    for (int v = 0; v < 4; ++v) {
+        const uint64_t r = row0 + wm * 16 + M_::row(lane, v);
+        const int c = n0 + wn * 16 + (lane & 15);
+        if (r < A.M && c < A.N) A.out[r * A.N + c] = cmake<R>(acc_re[v], acc_im[v]);
+    }
+}
+
+// Rows of 256 elements and more, contiguous in the state: a workgroup copies
+// 256 elements of four rows, whose numbers (and so their bit deposits, a loop
+// over the row bits) are uniform.  With the deposit per element the copy of
+// 1024 rows of 256 took 6.5 us.
+template <typename R>
+__global__ __launch_bounds__(256) void k_scatter_long(cvec<R> *__restrict__ psi, const cvec<R> *__restrict__ src,
+                                                      int mbits, uint64_t row_mask, uint64_t row_fix) {
+    const int per = mbits - 8;                                     // log2 of a row's 256-element pieces
+    const uint64_t piece0 = (uint64_t)blockIdx.x * 4;              // (M is a power of two: four whole pieces)
+    cvec<R> v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = src[((piece0 + q) << 8) + threadIdx.x];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const uint64_t p = piece0 + q;
+        psi[(pdep64(p >> per, row_mask) | row_fix) + ((p & ((1ull << per) - 1ull)) << 8) + threadIdx.x] = v[q];
+    }
+}
+
 template <typename R>
 __global__ void k_scatter_rows(cvec<R> *__restrict__ psi, const cvec<R> *__restrict__ src, uint64_t M, int mbits,
                                uint64_t row_mask, uint64_t row_fix, int ksh) {
@@ -223,10 +375,11 @@ static sv_status cgemm_ks(hipStream_t st, const cvec<R> *in, cvec<R> *out, const
     if (gm > 0x7fffffffull) return fail(SV_EUNSUPPORTED, "GEMM with too many rows");
     const uint64_t wtiles = ((M + 15) / 16) * (uint64_t)((N + 15) / 16);
     const uint64_t wblocks = (wtiles + 3) / 4;
-    // the tile shape: 64 x 64 per workgroup (0) or 16 x 16 per wavefront (1).
-    // Tuned per shape by timing both on this call's operands (the product is
-    // out of place, so it can be run twice), cached; without tuning, the
-    // wavefront tiles wherever the workgroup tiles would not fill the chip.
+    // the tile shape: 64 x 64 per workgroup (0), 16 x 16 per wavefront (1), or
+    // k in parts: 16 x 16 in four (2), 32 x 32 in two (3).  Tuned per shape by
+    // timing all on this call's operands (the product is out of place, so it
+    // can be run again), cached; without tuning, parts wherever the 64 x 64
+    // tiles would not fill the chip, the smaller ones up to two per compute unit.
     const std::string key = std::string("cgemm/") + (sizeof(R) == 4 ? "c64/" : "c128/") + std::to_string(M) + "/" +
                             std::to_string(N) + "/" + std::to_string(K) + "/" + std::to_string(trans) +
                             (ksh ? "/s" + std::to_string(ksh) : std::string());
@@ -235,6 +388,12 @@ static sv_status cgemm_ks(hipStream_t st, const cvec<R> *in, cvec<R> *out, const
         if (shape == 1) {
             if (wblocks > 0x7fffffffull) return fail(SV_EUNSUPPORTED, "GEMM with too many tiles");
             hipLaunchKernelGGL(k_cgemm_w<R>, dim3((unsigned)wblocks), dim3(256), 0, st, a);
+        } else if (shape == 2) {
+            hipLaunchKernelGGL((k_cgemm_k<R, 1, 1, 4>), dim3((unsigned)((M + 15) / 16), (unsigned)((N + 15) / 16)), dim3(256),
+                               0, st, a);
+        } else if (shape == 3) {
+            hipLaunchKernelGGL((k_cgemm_k<R, 2, 2, 2>), dim3((unsigned)((M + 31) / 32), (unsigned)((N + 31) / 32)), dim3(512),
+                               0, st, a);
         } else {
             hipLaunchKernelGGL(k_cgemm<R>, dim3((unsigned)gm, gn), dim3(256), 0, st, a);
         }
@@ -242,12 +401,17 @@ static sv_status cgemm_ks(hipStream_t st, const cvec<R> *in, cvec<R> *out, const
         return SV_OK;
     };
     std::vector<int> cached;
-    int shape = gm * gn < 256 ? 1 : 0;
-    if (tune_lookup(key, cached) && cached.size() == 1 && (cached[0] == 0 || cached[0] == 1)) {
+    // (grids of at most 2^23 workgroups in x: threads per launch stay below 2^32)
+    const bool parts_ok = (M + 15) / 16 <= (1ull << 22) && N <= (1 << 19);
+    int shape = gm * gn < 256 && parts_ok ? (wtiles <= 512 ? 2 : 3) : 0;
+    if (tune_lookup(key, cached) && cached.size() == 1 && (cached[0] == 0 || cached[0] == 1 ||
+                                                           (parts_ok && (cached[0] == 2 || cached[0] == 3)))) {
         shape = cached[0];
     } else if (autotune_enabled() && wblocks <= 0x7fffffffull) {
         float best = 1e30f;
-        for (int c = 0; c < 2; ++c) {
+        // the small shapes only where the large one leaves compute units short
+        // of work: on a large product a wavefront per tile takes many times longer
+        for (int c = 0; c < (gm * gn <= 4096 && parts_ok ? 4 : 2); ++c) {
             float ms = 0.f;
             SV_TRY(time_stream(st, 2, &ms, [&]() { return launch(c); }));
             if (ms < best) {
@@ -289,8 +453,13 @@ static sv_status ctrl_mask_unitary_at(sv_state s, const cvec<R> *U, int lo, int 
     if (g > (1u << 20)) g = 1u << 20;
     {
         TraceScope _ts(s->stream, "scatter_rows", 2.0 * (double)total * sizeof(cvec<R>), 0.0);
-        hipLaunchKernelGGL(k_scatter_rows<R>, dim3((unsigned)g), dim3(256), 0, s->stream, (cvec<R> *)s->data,
-                       (const cvec<R> *)out, M, m, row_mask, row_fix, lo);
+        const uint64_t gl = total / 1024;
+        if (lo == 0 && m >= 8 && gl >= 1 && gl <= (1u << 23))       // (threads per launch stay below 2^32)
+            hipLaunchKernelGGL(k_scatter_long<R>, dim3((unsigned)gl), dim3(256), 0, s->stream, (cvec<R> *)s->data,
+                               (const cvec<R> *)out, m, row_mask, row_fix);
+        else
+            hipLaunchKernelGGL(k_scatter_rows<R>, dim3((unsigned)g), dim3(256), 0, s->stream, (cvec<R> *)s->data,
+                               (const cvec<R> *)out, M, m, row_mask, row_fix, lo);
     }
     SV_HIP(hipGetLastError());
     return SV_OK;

@@ -61,13 +61,15 @@ __global__ void k_transpose_c128(double2 *__restrict__ out, const double2 *__res
     }
 }
 
-// W[r][j] = V[r][j] * E[j]
-__global__ void k_scale_cols(double2 *__restrict__ W, const double2 *__restrict__ V, const double2 *__restrict__ E,
-                             int N) {
-    const uint64_t total = (uint64_t)N * N;
+// W_k[r][j] = V[r][j] exp(2 pi i frac(phi_j 2^k)) for `cnt` clock bits from k0,
+// stacked; F: the turn table [N][n_c]
+__global__ void k_scale_phases(double2 *__restrict__ W, const double2 *__restrict__ V, const uint64_t *__restrict__ F,
+                               uint64_t N, int n_c, int k0, int cnt) {
+    const uint64_t NN = N * N, total = NN * (uint64_t)cnt;
     for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (uint64_t)gridDim.x * blockDim.x) {
-        const double2 v = V[i], e = E[i % N];
-        W[i] = make_double2(v.x * e.x - v.y * e.y, v.x * e.y + v.y * e.x);
+        const uint64_t e = i % NN;
+        const double2 v = V[e], p = turn_phase_f64(F[(e % N) * (uint64_t)n_c + (uint64_t)k0 + i / NN]);
+        W[i] = make_double2(v.x * p.x - v.y * p.y, v.x * p.y + v.y * p.x);
     }
 }
 
@@ -1017,46 +1019,62 @@ __global__ void k_kron_matrix(double2 *__restrict__ V, const double2 *__restrict
     }
 }
 
+// Host work between the launches is one staged copy in (b^ and the rotation
+// table) and one copy out (the three sums and x): everything else is ordered on
+// the stream.  The n_c controlled unitaries are formed by one stacked product
+// each GATE_BATCH bytes of them.
+constexpr uint64_t GATE_BATCH = 64ull << 20;
+
 template <typename R>
-static sv_status gate_faithful_run(sv_state s, const double2 *dV, const std::vector<double> &lam, Workspace &w, bool sgn,
+static sv_status gate_faithful_run(sv_state s, const double2 *dV, const double *lam_dev, Workspace &w, bool sgn,
                                    uint64_t gcut, int n_s, int n_c, double T0, const double *b, sv_hhl_result *res,
                                    double *x_out) {
-    const int N = 1 << n_s;
+    const uint64_t N = dim_of(n_s), NN = N * N, M = dim_of(n_c);
     const hipStream_t st = s->stream;
     // U_k = V diag(E_k) V^H for k = 0..n_c-1, FP64, then rounded to the state's precision
-    std::vector<double> Ek(2 * (size_t)N * n_c);
-    for (int k = 0; k < n_c; ++k)
-        for (int j = 0; j < N; ++j) {
-            const double phi = lam[j] * T0 / (2.0 * M_PI);
-            const double x = ldexp(phi, k), f = x - floor(x);
-            Ek[2 * ((size_t)k * N + j)] = cos(2.0 * M_PI * f);
-            Ek[2 * ((size_t)k * N + j) + 1] = sin(2.0 * M_PI * f);
-        }
-    const uint64_t NN = (uint64_t)N * N;
-    SV_TRY(need(w.E, Ek.size() * sizeof(double)));
-    SV_TRY(need(w.W, NN * sizeof(double2)));
-    SV_TRY(need(w.U64, NN * sizeof(double2)));
+    const int kb = (int)std::max<uint64_t>(1, std::min<uint64_t>((uint64_t)n_c, GATE_BATCH / (NN * sizeof(double2))));
+    constexpr bool wide = std::is_same<R, double>::value;
+    SV_TRY(need(w.F, N * n_c * sizeof(uint64_t)));
+    SV_TRY(need(w.W, (size_t)kb * NN * sizeof(double2)));
+    if (!wide) SV_TRY(need(w.U64, (size_t)kb * NN * sizeof(double2)));
     SV_TRY(need(w.Uk, (size_t)n_c * NN * sizeof(cvec<R>)));
-    SV_TRY(upload(s, w.E.p, Ek.data(), Ek.size() * sizeof(double)));
-    for (int k = 0; k < n_c; ++k) {
-        hipLaunchKernelGGL(k_scale_cols, dim3(grid1(NN)), dim3(256), 0, st, (double2 *)w.W.p, dV,
-                           (const double2 *)w.E.p + (size_t)k * N, N);
-        double2 *dst = std::is_same<R, double>::value ? (double2 *)w.Uk.p + (size_t)k * NN : (double2 *)w.U64.p;
-        SV_TRY(cgemm<double>(st, (const double2 *)w.W.p, dst, dV, (uint64_t)N, N, N, (uint64_t)(N - 1) << n_s, 0, 0,
-                             1));
-        if (!std::is_same<R, double>::value)
-            hipLaunchKernelGGL(k_c128_to_c64, dim3(grid1(NN)), dim3(256), 0, st, (float2 *)w.Uk.p + (size_t)k * NN,
-                               (const double2 *)w.U64.p, NN);
+    SV_TRY(need(w.cs, N * sizeof(double2) + M * sizeof(cvec<R>)));
+    SV_TRY(need(w.x, 8 * sizeof(double) + N * sizeof(double2)));
+
+    // b and the rotation table, staged together
+    std::vector<double> cs;
+    inversion_table(n_c, cs, sgn, gcut);
+    std::vector<unsigned char> in(N * sizeof(double2) + M * sizeof(cvec<R>));
+    memcpy(in.data(), b, N * sizeof(double2));
+    R *tab = (R *)(in.data() + N * sizeof(double2));
+    for (size_t i = 0; i < cs.size(); ++i) tab[i] = (R)cs[i];
+    SV_TRY(upload_plan(s, w.cs.p, in.data(), in.size()));
+    const double2 *db = (const double2 *)w.cs.p;
+    const void *dcs = (const char *)w.cs.p + N * sizeof(double2);
+
+    hipLaunchKernelGGL(k_turn_table, dim3(grid1(N * n_c)), dim3(256), 0, st, (uint64_t *)w.F.p, lam_dev, T0, n_c, N);
+    for (int k = 0; k < n_c; k += kb) {
+        const int cnt = std::min(kb, n_c - k);
+        const uint64_t rows = (uint64_t)cnt * N;
+        hipLaunchKernelGGL(k_scale_phases, dim3(grid1(rows * N)), dim3(256), 0, st, (double2 *)w.W.p, dV,
+                           (const uint64_t *)w.F.p, N, n_c, k, cnt);
+        double2 *dst = wide ? (double2 *)w.Uk.p + (size_t)k * NN : (double2 *)w.U64.p;
+        uint64_t pow2 = 1;
+        while (pow2 < rows) pow2 <<= 1;
+        SV_TRY(cgemm<double>(st, (const double2 *)w.W.p, dst, dV, rows, (int)N, (int)N, (pow2 - 1) << n_s, 0, 0, 1));
+        if (!wide)
+            hipLaunchKernelGGL(k_c128_to_c64, dim3(grid1(rows * N)), dim3(256), 0, st, (float2 *)w.Uk.p + (size_t)k * NN,
+                               (const double2 *)w.U64.p, rows * N);
     }
     SV_HIP(hipGetLastError());
     const cvec<R> *U = (const cvec<R> *)w.Uk.p;
 
-    SV_TRY(sv_init_b(s, b, n_s, n_c));
+    double nrm = 0.0;
+    for (uint64_t j = 0; j < 2 * N; ++j) nrm += b[j] * b[j];
+    SV_TRY(init_b_device(s, db, n_s, n_c, 1.0 / (sqrt(nrm) * sqrt((double)M))));
     for (int k = 0; k < n_c; ++k) SV_TRY(ctrl_unitary_impl<R>(s, U + (size_t)k * NN, n_s, n_s + (n_c - 1 - k), 1, 0));
     SV_TRY(run_qft_cascade(s, QftSpec{n_s, n_c, 1, 0, 0}, 0));
-    std::vector<double> cs;
-    inversion_table(n_c, cs, sgn, gcut);
-    SV_TRY(sv_apply_uniform_ry(s, n_s + n_c, n_s, n_c, cs.data(), -1, 0));
+    SV_TRY(uniform_ry_table(s, n_s + n_c, n_s, n_c, dcs, 1ull << (n_s + n_c), 0));
     SV_TRY(run_qft_cascade(s, QftSpec{n_s, n_c, 0, 0, 0}, 0));
     for (int k = n_c - 1; k >= 0; --k)
         SV_TRY(ctrl_unitary_impl<R>(s, U + (size_t)k * NN, n_s, n_s + (n_c - 1 - k), 1, 1));
@@ -1064,9 +1082,20 @@ static sv_status gate_faithful_run(sv_state s, const double2 *dV, const std::vec
     SV_TRY(bitrev_register(s, n_s, n_c, 0, 0));
 
     const uint64_t abit = 1ull << (n_s + n_c), cmask = ((1ull << n_c) - 1ull) << n_s;
-    SV_TRY(sv_norm2(s, abit, abit, &res->p_anc));
-    SV_TRY(sv_norm2(s, 0, 0, &res->norm_total));
-    return sv_postselect(s, abit | cmask, abit, &res->p_post, x_out, 0);
+    double *sums = (double *)w.x.p;
+    double2 *dx = (double2 *)(sums + 8);
+    SV_TRY(norm2_device(s, abit, abit, sums));
+    SV_TRY(norm2_device(s, 0, 0, sums + 1));
+    SV_TRY(norm2_device(s, abit | cmask, abit, sums + 2));
+    SV_TRY(gather_device(s, abit | cmask, abit, sums + 2, dx));
+    std::vector<double> out(8 + (x_out ? 2 * N : 0));
+    SV_TRY(download(s, out.data(), sums, out.size() * sizeof(double)));
+    res->p_anc = out[0];
+    res->norm_total = out[1];
+    res->p_post = out[2];
+    if (!(out[2] > 0.0)) return fail(SV_EZERONORM, "post-selected outcome has probability 0");
+    if (x_out) memcpy(x_out, out.data() + 8, 2 * N * sizeof(double));
+    return SV_OK;
 }
 
 static sv_status check_params(sv_state s, const sv_hhl_params *prm, sv_hhl_result *res) {
@@ -1281,11 +1310,11 @@ static sv_status hhl_run_impl(sv_hhl_plan p, sv_state s, const double *b, const 
         }
         dV = (const double2 *)p->V_dense.p;
     }
-    if (s->dt == SV_C64)
-        return gate_faithful_run<float>(s, dV, p->E.lam, p->w, sgn, gcut, p->E.n_s, prm->n_c, prm->T0, bhat.data(),
-                                        res, x_out);
-    return gate_faithful_run<double>(s, dV, p->E.lam, p->w, sgn, gcut, p->E.n_s, prm->n_c, prm->T0, bhat.data(), res,
-                                     x_out);
+    const double *lam_dev = (const double *)p->E.lam_dev.p;
+    return s->dt == SV_C64 ? gate_faithful_run<float>(s, dV, lam_dev, p->w, sgn, gcut, p->E.n_s, prm->n_c, prm->T0,
+                                                      bhat.data(), res, x_out)
+                           : gate_faithful_run<double>(s, dV, lam_dev, p->w, sgn, gcut, p->E.n_s, prm->n_c, prm->T0,
+                                                       bhat.data(), res, x_out);
 }
 
 sv_status sv_hhl_run(sv_hhl_plan p, sv_state s, const double *b, const sv_hhl_params *prm, sv_hhl_result *res,

@@ -68,6 +68,12 @@ sv_status check_qubits(sv_state s, const int *qs, int nq, const int *ctrls, cons
 // ---- launchers used across files -----------------------------------------
 // FP64 sum of |a_i|^2 over (i & mask) == value, result left in device memory at *dev_out
 sv_status norm2_device(sv_state s, uint64_t mask, uint64_t value, double *dev_out);
+// the initial state of sv_init_b from a device vector b, amplitudes scaled by `scale`
+sv_status init_b_device(sv_state s, const double2 *b, int n_s, int n_clock_superpose, double scale);
+// the amplitudes with (i & mask) == value divided by sqrt(*prob), as FP64 on the device
+sv_status gather_device(sv_state s, uint64_t mask, uint64_t value, const double *prob, double2 *out);
+// stream-ordered copy to the device through the state's plan staging; returns without waiting
+sv_status upload_plan(sv_state s, void *dst, const void *src, size_t bytes);
 // uniformly controlled Ry from a device table of (cos, sin) in the state's
 // precision; fm / fv: fixed bits (the target at 0, controls at their values)
 sv_status uniform_ry_table(sv_state s, int target, int reg_lo, int m, const void *table, uint64_t fm, uint64_t fv);

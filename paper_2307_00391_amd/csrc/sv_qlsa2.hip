@@ -43,6 +43,16 @@ sv_status ctrl_unitary_impl(sv_state s, const cvec<R> *U, int m, int ctrl, int c
 template <typename R>
 sv_status ctrl_mask_unitary_impl(sv_state s, const cvec<R> *U, int m, uint64_t cmask, uint64_t cval, int adjoint);
 
+// W[r][j] = V[r][j] * E[j]
+__global__ void k_scale_cols(double2 *__restrict__ W, const double2 *__restrict__ V, const double2 *__restrict__ E,
+                             int N) {
+    const uint64_t total = (uint64_t)N * N;
+    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (uint64_t)gridDim.x * blockDim.x) {
+        const double2 v = V[i], e = E[i % N];
+        W[i] = make_double2(v.x * e.x - v.y * e.y, v.x * e.y + v.y * e.x);
+    }
+}
+
 static unsigned grid_for(uint64_t items) {
     uint64_t g = (items + 255) / 256;
     if (g < 1) g = 1;
