@@ -123,10 +123,10 @@ __global__ void k_axis_transform(double2 *__restrict__ out, const double2 *__res
 // F[j][k] = frac(phi_j 2^k) as a 64-bit fraction of a turn, phi_j = lam_j T0 / 2 pi:
 // the same IEEE operations as the host-side table (product, quotient, exact
 // scaling by 2^k, exact floor), so both give the same bits
-__global__ void k_turn_table(uint64_t *__restrict__ F, const double *__restrict__ lam, double T0, int n_c,
-                             uint64_t N) {
+__device__ __forceinline__ void turn_table_body(uint64_t *__restrict__ F, const double *__restrict__ lam, double T0,
+                                                int n_c, uint64_t N, uint64_t block, uint64_t blocks) {
     const uint64_t total = N * (uint64_t)n_c;
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (uint64_t)gridDim.x * blockDim.x) {
+    for (uint64_t i = block * blockDim.x + threadIdx.x; i < total; i += blocks * blockDim.x) {
         const uint64_t j = i / n_c;
         const int k = (int)(i % n_c);
         const double phi = lam[j] * T0 / (2.0 * M_PI);
@@ -135,6 +135,11 @@ __global__ void k_turn_table(uint64_t *__restrict__ F, const double *__restrict_
         const double sc = ldexp(f, 64);
         F[i] = sc >= 18446744073709551616.0 ? 0ull : (uint64_t)sc;
     }
+}
+
+__global__ void k_turn_table(uint64_t *__restrict__ F, const double *__restrict__ lam, double T0, int n_c,
+                             uint64_t N) {
+    turn_table_body(F, lam, T0, n_c, N, blockIdx.x, gridDim.x);
 }
 
 // ---- eigen-frame kernels ---------------------------------------------------
@@ -248,9 +253,9 @@ __global__ __launch_bounds__(256) void k_eig_project(const cvec<R> *__restrict__
 // z[j] = scale * sum over the partial rows of column j: four interleaved
 // accumulators (rows r = k mod 4) keep four loads in flight per thread, and
 // are combined in a fixed order
-__global__ void k_sum_cols(double2 *__restrict__ z, const double2 *__restrict__ part, uint64_t N, int rows,
-                           double scale) {
-    for (uint64_t j = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; j < N; j += (uint64_t)gridDim.x * blockDim.x) {
+__device__ __forceinline__ void sum_cols_body(double2 *__restrict__ z, const double2 *__restrict__ part, uint64_t N,
+                                              int rows, double scale, uint64_t block, uint64_t blocks) {
+    for (uint64_t j = block * blockDim.x + threadIdx.x; j < N; j += blocks * blockDim.x) {
         double re[4] = {0.0, 0.0, 0.0, 0.0}, im[4] = {0.0, 0.0, 0.0, 0.0};
         int r = 0;
         for (; r + 4 <= rows; r += 4) {
@@ -268,6 +273,48 @@ __global__ void k_sum_cols(double2 *__restrict__ z, const double2 *__restrict__ 
         }
         z[j] = make_double2(((re[0] + re[1]) + (re[2] + re[3])) * scale, ((im[0] + im[1]) + (im[2] + im[3])) * scale);
     }
+}
+
+__global__ void k_sum_cols(double2 *__restrict__ z, const double2 *__restrict__ part, uint64_t N, int rows,
+                           double scale) {
+    sum_cols_body(z, part, N, rows, scale, blockIdx.x, gridDim.x);
+}
+
+// The pipeline's sums in one launch: workgroups [0, nc) add nc stretches of the
+// (P(a=1), norm) partials into head[0..nc), which the host adds up in order; the
+// others add the columns.  Bound by the launch: 6.4 us on the 26-qubit complex128
+// solve (32 768 partials), where five launches took 25; one workgroup for all
+// partials takes longer than the gap it saves above about 2048 of them.
+constexpr int EIG_CHUNKS = 64;
+constexpr int EIG_HEAD = 8 + 2 * EIG_CHUNKS;     // doubles in front of x: scalars, then the stretches' sums
+
+static int eig_chunks(uint64_t nparts) { return nparts <= 2048 ? 1 : EIG_CHUNKS; }
+
+__global__ __launch_bounds__(256) void k_eig_sums(double2 *__restrict__ z, const double2 *__restrict__ zpart, uint64_t N,
+                                                  int rows, double scale, const double2 *__restrict__ part,
+                                                  uint64_t nparts, int nc, double2 *__restrict__ head) {
+    __shared__ double ws[2][4];
+    if ((int)blockIdx.x >= nc) {
+        sum_cols_body(z, zpart, N, rows, scale, blockIdx.x - nc, gridDim.x - nc);
+        return;
+    }
+    const uint64_t len = (nparts + nc - 1) / nc, beg = (uint64_t)blockIdx.x * len;
+    const uint64_t end = beg + len < nparts ? beg + len : nparts;
+    double a = 0.0, n = 0.0;
+    for (uint64_t i = beg + threadIdx.x; i < end; i += 256) {
+        a += part[i].x;
+        n += part[i].y;
+    }
+    a = wave_sum_f64(a);
+    n = wave_sum_f64(n);
+    if ((threadIdx.x & 63) == 0) {
+        ws[0][threadIdx.x >> 6] = a;
+        ws[1][threadIdx.x >> 6] = n;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0)
+        head[blockIdx.x] = make_double2((ws[0][0] + ws[0][1]) + (ws[0][2] + ws[0][3]),
+                                        (ws[1][0] + ws[1][1]) + (ws[1][2] + ws[1][3]));
 }
 
 // --------------------------------------------------------------------------
@@ -741,8 +788,8 @@ __global__ __launch_bounds__(256) void k_gemv_cols2(double2 *__restrict__ out, c
 }
 
 template <typename VT>
-__global__ __launch_bounds__(256) void k_gemv_cols(double2 *__restrict__ out, const VT *__restrict__ V,
-                                                   const double2 *__restrict__ b, uint64_t N) {
+__device__ __forceinline__ void gemv_cols_body(double2 *__restrict__ out, const VT *__restrict__ V,
+                                               const double2 *__restrict__ b, uint64_t N) {
     __shared__ double2 part[3][64];
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -759,6 +806,22 @@ __global__ __launch_bounds__(256) void k_gemv_cols(double2 *__restrict__ out, co
         const double2 p1 = part[0][lane], p2 = part[1][lane], p3 = part[2][lane];
         out[j] = make_double2((acc.x + p1.x) + (p2.x + p3.x), (acc.y + p1.y) + (p2.y + p3.y));
     }
+}
+
+template <typename VT>
+__global__ __launch_bounds__(256) void k_gemv_cols(double2 *__restrict__ out, const VT *__restrict__ V,
+                                                   const double2 *__restrict__ b, uint64_t N) {
+    gemv_cols_body<VT>(out, V, b, N);
+}
+
+// The head of a solve on a dense plan: workgroups [0, gcols) form beta = V^H b^,
+// the others the turn table (for small systems every launch counts)
+__global__ __launch_bounds__(256) void k_eig_head(double2 *__restrict__ beta, const double2 *__restrict__ V,
+                                                  const double2 *__restrict__ b, uint64_t N, unsigned gcols,
+                                                  uint64_t *__restrict__ F, const double *__restrict__ lam, double T0,
+                                                  int n_c) {
+    if (blockIdx.x < gcols) gemv_cols_body<double2>(beta, V, b, N);
+    else turn_table_body(F, lam, T0, n_c, N, blockIdx.x - gcols, gridDim.x - gcols);
 }
 
 // the dense basis change: out = V in (forward) or V^H in (adjoint), V N x N
@@ -780,9 +843,11 @@ static sv_status gemv_apply(hipStream_t st, double2 *out, const double2 *in, con
         const int nseg = (int)((N + GV_SEG - 1) / GV_SEG);
         const uint64_t blocks = ((N + GV_ROWS - 1) / GV_ROWS) * (uint64_t)nseg;
         if (blocks > 0x7fffffffull) return fail(SV_EUNSUPPORTED, "GEMV of %llu rows", (unsigned long long)N);
+        if (nseg == 1) part = out;       // one segment per row: its sum is the result
         if (Vr) hipLaunchKernelGGL(k_gemv_rows<double>, dim3((unsigned)blocks), dim3(256), 0, st, part, Vr, in, N, nseg);
         else hipLaunchKernelGGL(k_gemv_rows<double2>, dim3((unsigned)blocks), dim3(256), 0, st, part, Vc, in, N, nseg);
-        hipLaunchKernelGGL(k_gemv_reduce, dim3(grid1(N)), dim3(256), 0, st, out, (const double2 *)part, N, nseg);
+        if (nseg > 1)
+            hipLaunchKernelGGL(k_gemv_reduce, dim3(grid1(N)), dim3(256), 0, st, out, (const double2 *)part, N, nseg);
     }
     SV_HIP(hipGetLastError());
     return SV_OK;
@@ -828,11 +893,11 @@ static int pick_log_len(uint64_t N, int n_c) {
 
 // device workspaces of a plan, grown on demand and reused by every solve
 struct Workspace {
-    DevBuf F, cs, beta, tmp, tmp2, z, x, part, zpart, sum, E, W, U64, Uk, gpart;
+    DevBuf F, cs, beta, tmp, tmp2, z, x, part, zpart, out, W, U64, Uk, gpart;
 };
 
 static sv_status need(DevBuf &b, size_t bytes) { return b.ensure(bytes); }
-static sv_status eig_finish(sv_state s, const EigFrame &E, Workspace &w, uint64_t N, sv_hhl_result *res,
+static sv_status eig_finish(sv_state s, const EigFrame &E, Workspace &w, uint64_t N, int nc, sv_hhl_result *res,
                             double *x_out, bool dev, double2 *x_dev);
 
 // |v|^2 of an FP64 complex device vector, first level: block b sums the
@@ -850,21 +915,25 @@ __global__ __launch_bounds__(256) void k_vec_norm2(const double2 *__restrict__ v
     if (threadIdx.x == 0) tmp[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-// out[0] = |v|^2 in a fixed order: 64 chunk sums (tmp holds >= 64 doubles),
-// then their sum in one workgroup
-static void vec_norm2(hipStream_t st, const double2 *v, uint64_t n, double *tmp, double *out) {
-    const unsigned nb = 64;
-    const uint64_t chunk = (n + nb - 1) / nb;
-    hipLaunchKernelGGL(k_vec_norm2, dim3(nb), dim3(256), 0, st, v, n, chunk, tmp);
-    hipLaunchKernelGGL(k_sum_partials_strided, dim3(1), dim3(256), 0, st, (const double *)tmp, (int)nb, 1, out);
-}
-
-// out = in / sqrt(nrm[0]) (nrm on the device)
-__global__ void k_vec_normalise(double2 *__restrict__ out, const double2 *__restrict__ in, uint64_t n,
-                                const double *__restrict__ nrm) {
-    const double sc = 1.0 / sqrt(nrm[0]);
+// out = v / |v| (and |v|^2 into nrm[0]) in two launches: 64 chunk sums, then
+// every workgroup adds those in the same order and scales (out may be NULL:
+// the norm alone); tmp holds 64 doubles
+__global__ __launch_bounds__(256) void k_vec_scale(double2 *__restrict__ out, const double2 *__restrict__ in, uint64_t n,
+                                                   const double *__restrict__ tmp, int nb, double *__restrict__ nrm) {
+    const int lane = threadIdx.x & 63;
+    const double p = wave_sum_f64(lane < nb ? tmp[lane] : 0.0);
+    if (blockIdx.x == 0 && threadIdx.x == 0) nrm[0] = p;
+    if (!out) return;
+    const double sc = 1.0 / sqrt(p);
     for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x)
         out[i] = make_double2(in[i].x * sc, in[i].y * sc);
+}
+
+static void vec_normalise(hipStream_t st, double2 *out, const double2 *v, uint64_t n, double *tmp, double *nrm) {
+    const int nb = n <= 4096 ? 1 : 64;      // small: one workgroup, 16 terms per thread
+    const uint64_t chunk = (n + nb - 1) / nb;
+    hipLaunchKernelGGL(k_vec_norm2, dim3(nb), dim3(256), 0, st, v, n, chunk, tmp);
+    hipLaunchKernelGGL(k_vec_scale, dim3(out ? grid1(n) : 1), dim3(256), 0, st, out, v, n, (const double *)tmp, nb, nrm);
 }
 
 template <typename R>
@@ -892,23 +961,31 @@ static sv_status eig_frame_run(sv_state s, const EigFrame &E, Workspace &w, cons
     SV_TRY(need(w.x, N * sizeof(double2)));
     SV_TRY(need(w.part, 2 * nb * sizeof(double)));
     SV_TRY(need(w.zpart, (size_t)g2.y * 4 * N * sizeof(double2)));
-    SV_TRY(need(w.sum, 4 * sizeof(double)));
-    hipLaunchKernelGGL(k_turn_table, dim3(grid1(N * n_c)), dim3(256), 0, st, (uint64_t *)w.F.p,
-                       (const double *)E.lam_dev.p, T0, n_c, N);
-    SV_HIP(hipGetLastError());
+    SV_TRY(need(w.out, EIG_HEAD * sizeof(double) + N * sizeof(double2)));
+    double *sums = (double *)w.out.p;
     const bool dev = b_dev != nullptr;
     if (dev) {
-        // b on the device: its norm (w.sum[2]) and b^ there
+        // b on the device: its norm (sums[2]) and b^ there
         SV_TRY(need(w.tmp2, 512 * sizeof(double)));
-        vec_norm2(st, b_dev, N, (double *)w.tmp2.p, (double *)w.sum.p + 2);
-        hipLaunchKernelGGL(k_vec_normalise, dim3(grid1(N)), dim3(256), 0, st, (double2 *)w.x.p, b_dev, N,
-                           (const double *)w.sum.p + 2);
+        vec_normalise(st, (double2 *)w.x.p, b_dev, N, (double *)w.tmp2.p, sums + 2);
         SV_HIP(hipGetLastError());
     } else {
-        SV_TRY(upload(s, w.x.p, bhat.data(), N * sizeof(double2)));
+        SV_TRY(upload_plan(s, w.x.p, bhat.data(), N * sizeof(double2)));
     }
-    // beta = V^H b^
-    SV_TRY(kron_apply_frame(s, (double2 *)w.beta.p, (const double2 *)w.x.p, (double2 *)w.tmp.p, E, 1, w.gpart));
+    // the turn table, and beta = V^H b^
+    if (!E.Vr && E.n_lo <= 1) {
+        const unsigned gc = (unsigned)((N + 63) / 64);
+        TraceScope _ts(st, "gemv_vh", (double)N * (double)N * sizeof(double2), 8.0 * (double)N * (double)N);
+        hipLaunchKernelGGL(k_eig_head, dim3(gc + grid1(N * n_c)), dim3(256), 0, st, (double2 *)w.beta.p,
+                           (const double2 *)E.V_hi.p, (const double2 *)w.x.p, N, gc, (uint64_t *)w.F.p,
+                           (const double *)E.lam_dev.p, T0, n_c);
+        SV_HIP(hipGetLastError());
+    } else {
+        hipLaunchKernelGGL(k_turn_table, dim3(grid1(N * n_c)), dim3(256), 0, st, (uint64_t *)w.F.p,
+                           (const double *)E.lam_dev.p, T0, n_c, N);
+        SV_HIP(hipGetLastError());
+        SV_TRY(kron_apply_frame(s, (double2 *)w.beta.p, (const double2 *)w.x.p, (double2 *)w.tmp.p, E, 1, w.gpart));
+    }
 
     if (fused && pipe_supported(n_s, n_c)) {
         // fused three-kernel pipeline: (state + inverse QFT on the low clock bits),
@@ -921,16 +998,15 @@ static sv_status eig_frame_run(sv_state s, const EigFrame &E, Workspace &w, cons
         SV_TRY(pipe_run<R>(s, n_s, n_c, sgn, gcut, (const double2 *)w.beta.p, (const uint64_t *)w.F.p, (double *)w.part.p,
                            (double2 *)w.zpart.p, &nparts));
         if (nparts > nbp) return fail(SV_EDEVICE, "pipeline partial count exceeds its buffer");
-        SV_TRY(need(w.tmp2, 512 * sizeof(double)));
-        sum_partials(st, (const double *)w.part.p, nparts, 2, (double *)w.tmp2.p, (double *)w.sum.p);
-        sum_partials(st, (const double *)w.part.p + 1, nparts, 2, (double *)w.tmp2.p + 256, (double *)w.sum.p + 1);
         // 2^(-n_c/2) of the final Hadamard layer, and 2^(-g1/2) the fused forward
         // transform on the low clock group leaves out of its butterflies
         const int g1 = (n_c + 1) / 2;
-        hipLaunchKernelGGL(k_sum_cols, dim3(grid1(N)), dim3(256), 0, st, (double2 *)w.z.p,
-                           (const double2 *)w.zpart.p, N, rows, exp2(-0.5 * (n_c + g1)));
+        const int nc = eig_chunks(nparts);
+        hipLaunchKernelGGL(k_eig_sums, dim3(nc + grid1(N)), dim3(256), 0, st, (double2 *)w.z.p, (const double2 *)w.zpart.p,
+                           N, rows, exp2(-0.5 * (n_c + g1)), (const double2 *)w.part.p, nparts, nc,
+                           (double2 *)(sums + 8));
         SV_HIP(hipGetLastError());
-        return eig_finish(s, E, w, N, res, x_out, dev, x_dev);
+        return eig_finish(s, E, w, N, nc, res, x_out, dev, x_dev);
     }
     std::vector<double> cs;
     inversion_table(n_c, cs, sgn, gcut);
@@ -952,9 +1028,9 @@ static sv_status eig_frame_run(sv_state s, const EigFrame &E, Workspace &w, cons
                            (const double2 *)w.cs.p, half, n_s, (1ull << n_c) - 1ull, abit, chunk, (double *)w.part.p);
     }
     hipLaunchKernelGGL(k_sum_partials_strided, dim3(1), dim3(256), 0, st, (const double *)w.part.p, (int)nb, 2,
-                       (double *)w.sum.p);
+                       sums);
     hipLaunchKernelGGL(k_sum_partials_strided, dim3(1), dim3(256), 0, st, (const double *)w.part.p + 1, (int)nb, 2,
-                       (double *)w.sum.p + 1);
+                       sums + 1);
     SV_HIP(hipGetLastError());
     // 4. QFT cascade on the clock, ancilla = 1 half
     SV_TRY(run_qft_cascade(s, QftSpec{n_s, n_c, 0, abit, abit}, 0));
@@ -967,39 +1043,45 @@ static sv_status eig_frame_run(sv_state s, const EigFrame &E, Workspace &w, cons
     hipLaunchKernelGGL(k_sum_cols, dim3(grid1(N)), dim3(256), 0, st, (double2 *)w.z.p, (const double2 *)w.zpart.p, N,
                        (int)(g2.y * 4), 1.0 / sqrt((double)(1ull << n_c)));
     SV_HIP(hipGetLastError());
-    return eig_finish(s, E, w, N, res, x_out, dev, x_dev);
+    return eig_finish(s, E, w, N, 0, res, x_out, dev, x_dev);
 }
 
-// x = V z on the device, then P(a=1, clock=0) = |z|^2 and the normalised x on the host
-static sv_status eig_finish(sv_state s, const EigFrame &E, Workspace &w, uint64_t N, sv_hhl_result *res,
+// x = V z on the device, then P(a=1, clock=0) = |z|^2 and the normalised x, on
+// the host or in x_dev.  P(a=1) and the norm: sums[0], sums[1] (nc = 0), or nc
+// stretches behind the scalars.
+static sv_status eig_finish(sv_state s, const EigFrame &E, Workspace &w, uint64_t N, int nc, sv_hhl_result *res,
                             double *x_out, bool dev, double2 *x_dev) {
     const hipStream_t st = s->stream;
-    SV_TRY(kron_apply_frame(s, (double2 *)w.x.p, (const double2 *)w.z.p, (double2 *)w.tmp.p, E, 0, w.gpart));
+    double *sums = (double *)w.out.p;
+    double2 *x = (double2 *)(sums + EIG_HEAD);   // behind the sums: one copy brings both back
+    SV_TRY(kron_apply_frame(s, x, (const double2 *)w.z.p, (double2 *)w.tmp.p, E, 0, w.gpart));
     if (dev) {
-        // p = |x|^2 (w.sum[3]) and the normalised x on the device; only the scalars come back
+        // p = |x|^2 (sums[3]) and the normalised x on the device; only the sums come back
         SV_TRY(need(w.tmp2, 512 * sizeof(double)));
-        vec_norm2(st, (const double2 *)w.x.p, N, (double *)w.tmp2.p, (double *)w.sum.p + 3);
-        if (x_dev)
-            hipLaunchKernelGGL(k_vec_normalise, dim3(grid1(N)), dim3(256), 0, st, x_dev, (const double2 *)w.x.p, N,
-                               (const double *)w.sum.p + 3);
+        vec_normalise(st, x_dev, x, N, (double *)w.tmp2.p, sums + 3);
         SV_HIP(hipGetLastError());
-        std::vector<double> sums(4);
-        SV_TRY(download(s, sums.data(), w.sum.p, 4 * sizeof(double)));
-        res->p_post = sums[3];
-        res->p_anc = sums[0];
-        res->norm_total = sums[1];
-        if (!(sums[2] > 0.0) || !isfinite(sums[2])) return fail(SV_EZERONORM, "|b| = 0 or not finite");
-        if (!(sums[3] > 0.0)) return fail(SV_EZERONORM, "post-selected outcome has probability 0");
+    }
+    std::vector<double> out(EIG_HEAD + (dev ? 0 : 2 * N));
+    SV_TRY(download(s, out.data(), sums, out.size() * sizeof(double)));
+    res->p_anc = out[0];
+    res->norm_total = out[1];
+    if (nc) {
+        res->p_anc = res->norm_total = 0.0;
+        for (int i = 0; i < nc; ++i) {
+            res->p_anc += out[8 + 2 * i];
+            res->norm_total += out[9 + 2 * i];
+        }
+    }
+    if (dev) {
+        res->p_post = out[3];
+        if (!(out[2] > 0.0) || !isfinite(out[2])) return fail(SV_EZERONORM, "|b| = 0 or not finite");
+        if (!(out[3] > 0.0)) return fail(SV_EZERONORM, "post-selected outcome has probability 0");
         return SV_OK;
     }
-    std::vector<double> sums(2), xz(2 * N);
-    SV_TRY(download(s, sums.data(), w.sum.p, 2 * sizeof(double)));
-    SV_TRY(download(s, xz.data(), w.x.p, N * sizeof(double2)));
+    const double *xz = out.data() + EIG_HEAD;
     double p = 0.0;
     for (uint64_t j = 0; j < N; ++j) p += xz[2 * j] * xz[2 * j] + xz[2 * j + 1] * xz[2 * j + 1];
     res->p_post = p;
-    res->p_anc = sums[0];
-    res->norm_total = sums[1];
     if (!(p > 0.0)) return fail(SV_EZERONORM, "post-selected outcome has probability 0");
     if (x_out) {
         const double inv = 1.0 / sqrt(p);
