@@ -226,9 +226,9 @@ typedef struct {
                       1: eigen-frame, fused: the system register is held in the eigenbasis
                       of A, so the controlled-U_k are diagonal; the state after phase
                       estimation is generated inside the first inverse-QFT kernel, the
-                      rotation sits between the two halves of the clock transforms, and
-                      the uncompute ends in the clock = 0 projection: three passes over
-                      half the state (n_c <= 20; larger n_c runs as mode 2);
+                      rotation and the uncompute's projection on clock = 0 sit in the
+                      second: one pass over half the state (n_c <= 20; larger n_c runs
+                      as mode 2);
                       2: eigen-frame, one kernel per step (state write, inverse QFT on
                       the ancilla = 0 half, rotation into the ancilla = 1 half, QFT there,
                       projection) */
@@ -382,7 +382,8 @@ int sv_trace_report(char *buf, int len);
  * "op/dtype/shape... values".  Tuning runs on first use of a shape
  * (SV_AUTOTUNE=0: defaults); SV_TUNE_CACHE=<file> persists the choices.
  *   eigpipe/<dtype>/<n_s>/<n_c>  fused eigen-frame kernels: (log2 columns
- *       per tile, threads per workgroup) for each of the three kernels;
+ *       per tile, threads per workgroup) for each of the two kernels, and a
+ *       third pair that is not read;
  *   cgemm/<dtype>/<M>/<N>/<K>/<trans>  the matrix-core GEMM's tile shape:
  *       0 = 64 x 64 per workgroup, 1 = 16 x 16 per wavefront, 2 = 16 x 16 with
  *       k in four parts, 3 = 32 x 32 with k in two;

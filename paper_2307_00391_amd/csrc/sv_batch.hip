@@ -84,7 +84,7 @@ struct sv_batch_s {
     const FinishJob *d_finish_q = nullptr;   // the same for the work-queue form (its own partial counts)
     double *d_out = nullptr;
     struct Class {
-        int n_s, n_c, cl[3], nt[3];
+        int n_s, n_c, cl[2], nt[2];
         const PipeSolve *d_solves;
         int count;
         uint64_t nparts;      // k_pipe_b partial pairs per solve, as laid out for the finish
@@ -303,7 +303,7 @@ sv_status sv_batch_prepare(sv_batch *out, sv_dtype dt, void *hip_stream, const s
             L.F = take(N * I.n_c * sizeof(uint64_t));
             L.nparts_max = pipe_b_blocks(I.n_s, I.n_c, e);
             L.part = take(2 * L.nparts_max * sizeof(double));
-            L.zpart = take((size_t)pipe_c_rows(I.n_c) * N * sizeof(double2));
+            L.zpart = take((size_t)pipe_rows(I.n_c) * N * sizeof(double));
             lay.push_back(L);
         }
     }
@@ -374,7 +374,7 @@ sv_status sv_batch_prepare(sv_batch *out, sv_dtype dt, void *hip_stream, const s
         for (int k : class_members[c]) {
             const SolveLay &L = lay[k];
             ps.push_back(PipeSolve{base + L.psi, (const double2 *)beta[L.inst]->p, (const uint64_t *)(base + L.F),
-                                   (double *)(base + L.part), (double2 *)(base + L.zpart)});
+                                   (double *)(base + L.part), (double *)(base + L.zpart)});
         }
         sv_batch_s::Class C;
         C.n_s = n_s;
@@ -394,14 +394,13 @@ sv_status sv_batch_prepare(sv_batch *out, sv_dtype dt, void *hip_stream, const s
         for (size_t q = 0; q < class_members[c].size(); ++q) {
             const int k = class_members[c][q];
             const SolveLay &L = lay[k];
-            const int g1 = (n_c + 1) / 2;
-            fin[k] = FinishJob{(const double *)(base + L.part), np, (const double2 *)(base + L.zpart),
-                               pipe_c_rows(n_c), dim_of(n_s), exp2(-0.5 * (n_c + g1)),
+            fin[k] = FinishJob{(const double *)(base + L.part), np, (const double *)(base + L.zpart),
+                               pipe_rows(n_c), dim_of(n_s), (const double2 *)beta[L.inst]->p,
                                (const double2 *)cex[L.inst]->p, b->d_out + 4 * (size_t)k};
             qsolve_cls[k] = (int)c;
             qsolves[k] = ps[q];
         }
-        qcls.push_back(QueueClassIn{n_s, n_c, {C.cl[0], C.cl[1], C.cl[2]}});
+        qcls.push_back(QueueClassIn{n_s, n_c, {C.cl[0], C.cl[1]}});
         b->classes.push_back(C);
     }
     if ((st = upload(&b->ctx, (void *)b->d_finish, fin.data(), total * sizeof(FinishJob))) != SV_OK)
@@ -424,7 +423,7 @@ sv_status sv_batch_prepare(sv_batch *out, sv_dtype dt, void *hip_stream, const s
     }
     // side streams (default priority) and the fork/join events; classes go to
     // the least-loaded stream, largest first, weighed by amplitudes plus a
-    // fixed cost per class for its three launches
+    // fixed cost per class for its two launches
     {
         for (int i = 0; i < sv_batch_s::kSide; ++i) {
             hipError_t e1 = hipStreamCreateWithFlags(&b->side[i], hipStreamNonBlocking);

@@ -1,4 +1,4 @@
-// Eigen-frame HHL as three fused column-tile kernels.
+// Eigen-frame HHL as two fused column-tile kernels.
 //
 // The clock register [n_s, n_s + n_c) is split into a low group G1 =
 // register bits [0, g1) and a high group G2 = [g1, n_c) (g1, g2 <= 10).  A
@@ -11,26 +11,26 @@
 //             the inverse-QFT cascade on G1 (butterflies in registers, RA
 //             bits at a time, one LDS exchange).  The G1 stages act on G1
 //             qubits only, so the result is still a product between the
-//             groups: psi(j, y1, y2) = T_j(y1) * B_j(y2), with T_j the G1
+//             groups: psi(j, y1, y2) = beta_j T_j(y1) B_j(y2), with T_j the G1
 //             transform of the column's G1 factor and B_j(y2) the product of
 //             the phases of the set G2 bits.  k_pipe_a therefore runs for
 //             y2 = 0 only and leaves T in the clock rows y1 < 2^g1 of the
-//             ancilla = 0 half, and stages every column's clock-bit phases.
+//             ancilla = 0 half, and stages every column's G2 phases.
 //   k_pipe_b: the inverse-QFT cascade on G2 of T_j(y1) B_j(y2): each stage
 //             maps a product state over the G2 bits to another, so the
-//             cascade's output is T_j(y1) times a product of one factor per
+//             cascade's output P is T_j(y1) times a product of one factor per
 //             G2 bit, formed directly; then eigenvalue inversion
 //             a1 = (1/y) a0 (FP64 sums of P(a=1) and the norm)
 //                                                     -> ancilla = 1 half
-//   k_pipe_c: the uncompute projected on clock 0 (the QFT on the whole
-//             clock, the conjugate phases, the Hadamard layer onto |0>), as
-//             a contraction of the half against the transposed QFT applied
-//             to the phase product state, itself a closed-form product
+//             and, while a line is in registers, the uncompute projected on
+//             clock 0 (the QFT on the whole clock, the conjugate phases, the
+//             Hadamard layer onto |0>).  That is the inner product with the
+//             column phase estimation leaves, conj(P) up to the group
+//             normalisations, so z_j = beta_j sum_y s_y |P_j(y)|^2
 //                                                     -> FP64 partial sums
 //
-// Cascade stages on register qubit j (relative to the clock register):
-//   inverse: a1 *= conj(phase), then (a0 + a1, a0 - a1)/sqrt 2
-//   forward: (a0 + a1, (a0 - a1) * phase)/sqrt 2
+// Inverse cascade stage on register qubit j (relative to the clock register):
+//   a1 *= conj(phase), then (a0 + a1, a0 - a1)/sqrt 2
 // with phase = exp(2 pi i (v mod 2^j) / 2^(j+1)), v the register value: the
 // controlled phases of the textbook QFT circuit that target qubit j.  The
 // local part comes from a table of 2^g roots of unity, the part due to bits
@@ -82,9 +82,8 @@ __device__ __forceinline__ void gst(cvec<R> *p, uint64_t i, cvec<R> v) {
     ((gptr<v2_t<R>>)p)[i] = x;
 }
 
-// non-temporal forms for the ancilla = 1 half, written by k_pipe_b and read
-// back only by k_pipe_c after every tile is written: far more than the L2
-// and MALL hold, so they are streamed (the nt bit) instead of cached
+// non-temporal store for the ancilla = 1 half, which k_pipe_b writes once: far more than the L2 and MALL hold, so they are streamed (the nt bit)
+// instead of cached
 template <typename R>
 __device__ __forceinline__ void gst_nt(cvec<R> *p, uint64_t i, cvec<R> v) {
     v2_t<R> x;
@@ -92,12 +91,6 @@ __device__ __forceinline__ void gst_nt(cvec<R> *p, uint64_t i, cvec<R> v) {
     x.y = v.y;
     __builtin_nontemporal_store(x, &((gptr<v2_t<R>>)p)[i]);
 }
-template <typename R>
-__device__ __forceinline__ cvec<R> gld_nt(const cvec<R> *p, uint64_t i) {
-    const v2_t<R> x = __builtin_nontemporal_load(&((gptr<const v2_t<R>>)p)[i]);
-    return cmake<R>(x.x, x.y);
-}
-
 // the solve of this block: the kernel argument, or entry blockIdx.z of a batch
 __device__ __forceinline__ PipeSolve solve_of(const PipeSolve &one, const PipeSolve *many) {
     if (!many) return one;
@@ -119,15 +112,15 @@ __device__ __forceinline__ cvec<R> cconjmul(cvec<R> a, cvec<R> b) {   // a * con
 __device__ __forceinline__ float ffma(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double ffma(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
-// One cascade stage on a register line v[0..2^RL): pairs differ in bit kb of
-// the register index.  tw is the stage's twiddle table (entry m = phase for
-// the register bits below the stage's qubit equal to m); tidx(k) gives that
+// One inverse cascade stage on a register line v[0..2^RL): pairs differ in bit
+// kb of the register index.  tw is the stage's twiddle table (entry m = phase
+// for the register bits below the stage's qubit equal to m); tidx(k) gives that
 // m for element k.  The 1/sqrt(2) of the Hadamard is left out here and
 // applied once per group by the caller (butterflies are add/sub only).
 // has_tw = false for the lowest qubit of the register (phase 1).
-// The inverse butterfly forms v0 = a0 + a1 conj(w) with four FMAs and
+// The butterfly forms v0 = a0 + a1 conj(w) with four FMAs and
 // v1 = 2 a0 - v0 with two more (six operations instead of eight).
-template <typename R, int RL, bool INV, typename TIDX>
+template <typename R, int RL, typename TIDX>
 __device__ __forceinline__ void stage(cvec<R> (&v)[1 << RL], int kb, const cvec<R> *__restrict__ tw, bool has_tw,
                                       TIDX tidx) {
 #pragma unroll
@@ -135,66 +128,15 @@ __device__ __forceinline__ void stage(cvec<R> (&v)[1 << RL], int kb, const cvec<
         if (k0 & (1 << kb)) continue;
         const int k1 = k0 | (1 << kb);
         cvec<R> a0 = v[k0], a1 = v[k1];
-        if (INV) {
-            if (has_tw) {
-                const cvec<R> w = tw[tidx(k0)];
-                const R rx = ffma(a1.x, w.x, ffma(a1.y, w.y, a0.x));
-                const R ry = ffma(a1.y, w.x, ffma(-a1.x, w.y, a0.y));
-                v[k0] = cmake<R>(rx, ry);
-                v[k1] = cmake<R>(ffma((R)2, a0.x, -rx), ffma((R)2, a0.y, -ry));
-            } else {
-                v[k0] = cmake<R>(a0.x + a1.x, a0.y + a1.y);
-                v[k1] = cmake<R>(a0.x - a1.x, a0.y - a1.y);
-            }
+        if (has_tw) {
+            const cvec<R> w = tw[tidx(k0)];
+            const R rx = ffma(a1.x, w.x, ffma(a1.y, w.y, a0.x));
+            const R ry = ffma(a1.y, w.x, ffma(-a1.x, w.y, a0.y));
+            v[k0] = cmake<R>(rx, ry);
+            v[k1] = cmake<R>(ffma((R)2, a0.x, -rx), ffma((R)2, a0.y, -ry));
         } else {
-            const cvec<R> d = cmake<R>(a0.x - a1.x, a0.y - a1.y);
             v[k0] = cmake<R>(a0.x + a1.x, a0.y + a1.y);
-            v[k1] = has_tw ? cmul<R>(d, tw[tidx(k0)]) : d;
-        }
-    }
-}
-
-// Two forward stages at once (radix 4): the stage on bit kb + 1, then the
-// stage on bit kb, for every group of four elements that differ in those two
-// bits.  With m the group's twiddle index (the same for both stages: the
-// bit-kb-clear entry of the upper stage), t = tlo[m], T = thi[m], and the
-// upper stage's twiddle for bit kb set equal to i T, the four outputs are
-//   z00 = s0 + s1, z01 = (s0 - s1) t, z10 = T (d0 + i d1), z11 = T t (d0 - i d1)
-// with s0, d0 = x00 +- x10 and s1, d1 = x01 +- x11 (x_ab: bit kb + 1 = a,
-// bit kb = b); tt[m] = T t.  Three twiddle products per four elements
-// instead of four.
-template <typename R, int RL, typename TIDX>
-__device__ __forceinline__ void stage4f(cvec<R> (&v)[1 << RL], int kb, const cvec<R> *__restrict__ tlo,
-                                        const cvec<R> *__restrict__ thi, const cvec<R> *__restrict__ tt, TIDX tidx) {
-    const int b0 = 1 << kb, b1 = 2 << kb;
-#pragma unroll
-    for (int k = 0; k < (1 << RL); ++k) {
-        if (k & (b0 | b1)) continue;
-        const cvec<R> x00 = v[k], x01 = v[k | b0], x10 = v[k | b1], x11 = v[k | b0 | b1];
-        const int m = tidx(k);
-        const cvec<R> s0 = cmake<R>(x00.x + x10.x, x00.y + x10.y), d0 = cmake<R>(x00.x - x10.x, x00.y - x10.y);
-        const cvec<R> s1 = cmake<R>(x01.x + x11.x, x01.y + x11.y), d1 = cmake<R>(x01.x - x11.x, x01.y - x11.y);
-        v[k] = cmake<R>(s0.x + s1.x, s0.y + s1.y);
-        v[k | b0] = cmul<R>(cmake<R>(s0.x - s1.x, s0.y - s1.y), tlo[m]);
-        v[k | b1] = cmul<R>(cmake<R>(d0.x - d1.y, d0.y + d1.x), thi[m]);
-        v[k | b0 | b1] = cmul<R>(cmake<R>(d0.x + d1.y, d0.y - d1.x), tt[m]);
-    }
-}
-
-// The forward cascade over stages hi down to lo of a register line, in
-// radix-4 pairs from the top (a last single stage when the count is odd);
-// tables at tw_off(jb) of TW (twiddles) and TT (pair products), with stage
-// jb acting on line bit jb - lo_bit and tidx(jb, k) its twiddle index.
-template <typename R, int RL, int HI, int LO, int LOBIT, typename TIDX>
-__device__ __forceinline__ void fwd_cascade(cvec<R> (&v)[1 << RL], const cvec<R> *TW, const cvec<R> *TT, TIDX tidx) {
-#pragma unroll
-    for (int jb = HI; jb >= LO; jb -= 2) {
-        if (jb - 1 >= LO) {
-            const int lo = jb - 1;
-            stage4f<R, RL>(v, lo - LOBIT, TW + ((1 << lo) - 1), TW + ((1 << jb) - 1), TT + ((1 << lo) - 1),
-                           [&](int k) { return tidx(lo, k); });
-        } else {
-            stage<R, RL, false>(v, jb - LOBIT, TW + ((1 << jb) - 1), true, [&](int k) { return tidx(jb, k); });
+            v[k1] = cmake<R>(a0.x - a1.x, a0.y - a1.y);
         }
     }
 }
@@ -214,20 +156,6 @@ __device__ __forceinline__ void fill_twiddles(cvec<R> *TW, int g, int gbase, uin
 }
 __device__ __forceinline__ int tw_off(int jb) { return (1 << jb) - 1; }
 
-// The radix-4 pair products at offset 2^jb - 1 for jb <= g - 2: entry m is
-// (stage jb + 1 twiddle m) x (stage jb twiddle m), formed as one exact turn count
-template <typename R>
-__device__ __forceinline__ void fill_pair_twiddles(cvec<R> *TT, int g, int gbase, uint64_t vlow) {
-    for (int i = threadIdx.x; i < (1 << (g - 1)) - 1; i += blockDim.x) {
-        int jb = 0;
-        while ((2 << jb) - 1 <= i) ++jb;
-        const uint64_t m = (uint64_t)(i - ((1 << jb) - 1));
-        const int j = gbase + jb;
-        const uint64_t X = vlow + (m << gbase);
-        TT[i] = turn_phase<R>((X << (63 - j)) + (X << (62 - j)));
-    }
-}
-
 // tile decomposition: column block and the setting of the other group's bits
 __device__ __forceinline__ void tile_coords(const PipeArgs &A, uint64_t &j0, uint64_t &o) {
     const uint64_t nb = A.N >> A.cl;
@@ -239,20 +167,24 @@ __device__ __forceinline__ void tile_coords(const PipeArgs &A, uint64_t &j0, uin
 // ---------------------------------------------------------------------------
 // k_pipe_a: phase-estimation state + inverse cascade on G1
 // ---------------------------------------------------------------------------
+// In FP64 for both types, rounded once on the store: the table is small (2^g1 of
+// the 2^n_c clock rows), and its errors enter |P|^2 of k_pipe_b twice, alike
+// (complex64 solves of 10 + 10 qubits: rms error of p_post 4.9e-8, 2.0e-7 with a
+// complex64 table).  39 -> 75 us of a 32-qubit solve.
 template <typename R, int RA, int RB, int NT>
 __device__ __forceinline__ void pipe_a_body(const PipeArgs &A, const PipeSolve &S, uint64_t j0, uint64_t o) {
     constexpr int G = RA + RB;
     cvec<R> *__restrict__ psi = (cvec<R> *)S.psi;
-    const double2 *__restrict__ beta = S.beta;
     const gptr<const uint64_t> __restrict__ F = (gptr<const uint64_t>)S.F;
     extern __shared__ unsigned char smem_raw[];
     const int C = 1 << A.cl;
-    cvec<R> *tile = reinterpret_cast<cvec<R> *>(smem_raw);          // [2^G][C]
-    cvec<R> *TW = tile + ((size_t)C << G);                           // [2^G - 1] (+1 pad)
-    cvec<R> *om = TW + (1 << G);                                     // [G][C] exp(2 pi i F) of the local bits
-    cvec<R> *cc = om + G * C;                                        // [C] column constants
+    using D = double;
+    cvec<D> *tile = reinterpret_cast<cvec<D> *>(smem_raw);          // [2^G][C]
+    cvec<D> *TW = tile + ((size_t)C << G);                           // [2^G - 1] (+1 pad)
+    cvec<D> *om = TW + (1 << G);                                     // [G][C] exp(2 pi i F) of the local bits
+    cvec<D> *cc = om + G * C;                                        // [C] column constants
     const int n_c = A.n_c;
-    fill_twiddles<R>(TW, G, 0, 0);
+    fill_twiddles<D>(TW, G, 0, 0);
     // the tile holds clock index s = (o << G) | l; bit b of s carries F[j][n_c-1-b].
     // The G Hadamards below omit their 1/sqrt(2): 2^(-G/2) joins the amplitude scale.
     const double sc = A.scale * exp2(-0.5 * G);
@@ -261,42 +193,39 @@ __device__ __forceinline__ void pipe_a_body(const PipeArgs &A, const PipeSolve &
         uint64_t th = 0;
         for (int b = G; b < n_c; ++b)
             if (o >> (b - G) & 1) th += F[j * n_c + (n_c - 1 - b)];
-        const cvec<R> ph = turn_phase<R>(th);
-        const double2 bj = gld<double>(beta, j);
-        cc[c] = cmul<R>(cmake<R>((R)(bj.x * sc), (R)(bj.y * sc)), ph);
-        for (int b = 0; b < G; ++b) om[b * C + c] = turn_phase<R>(F[j * n_c + (n_c - 1 - b)]);
+        const cvec<D> ph = turn_phase<D>(th);
+        cc[c] = cmake<D>(sc * ph.x, sc * ph.y);
+        for (int b = 0; b < G; ++b) om[b * C + c] = turn_phase<D>(F[j * n_c + (n_c - 1 - b)]);
     }
-    // the clock-bit phases of every column for k_pipe_b and k_pipe_c, staged in
-    // clock rows 2^g1 + r (r < n_c) of the ancilla = 0 half, which the solve
-    // leaves unused otherwise (only the rows below 2^g1 hold the G1 table):
-    // row 2^g1 + r holds G2 bit r for r < g2 and G1 bit r - g2 after that
+    // the phases of the G2 bits of every column for k_pipe_b, staged in clock
+    // rows 2^g1 + r (r < g2) of the ancilla = 0 half, which the solve leaves
+    // unused otherwise (only the rows below 2^g1 hold the G1 table)
     const int g2 = n_c - G;
-    for (int e = threadIdx.x; e < n_c * C; e += NT) {
+    for (int e = threadIdx.x; e < g2 * C; e += NT) {
         const int r = e / C, c = e - r * C;
         const uint64_t j = j0 + c;
-        const int q = r < g2 ? n_c - 1 - (G + r) : n_c - 1 - (r - g2);
-        gst<R>(psi, ((((uint64_t)1 << G) + (uint64_t)r) << A.n_s) + j, turn_phase<R>(F[j * n_c + q]));
+        gst<R>(psi, ((((uint64_t)1 << G) + (uint64_t)r) << A.n_s) + j, turn_phase<R>(F[j * n_c + (n_c - 1 - (G + r))]));
     }
     __syncthreads();
     // phase A: line = (c, l_hi), register index = bits [0, RA)
     const int nla = C << RB;
     for (int line = threadIdx.x; line < nla; line += NT) {
         const int c = line & (C - 1), lhi = line >> A.cl;
-        cvec<R> v[1 << RA];
-        cvec<R> base = cc[c];
+        cvec<D> v[1 << RA];
+        cvec<D> base = cc[c];
         for (int b = 0; b < RB; ++b)
-            if (lhi >> b & 1) base = cmul<R>(base, om[(RA + b) * C + c]);
+            if (lhi >> b & 1) base = cmul<D>(base, om[(RA + b) * C + c]);
         v[0] = base;
 #pragma unroll
         for (int b = 0; b < RA; ++b) {
-            const cvec<R> w = om[b * C + c];
+            const cvec<D> w = om[b * C + c];
 #pragma unroll
-            for (int k = 0; k < (1 << b); ++k) v[k | (1 << b)] = cmul<R>(v[k], w);
+            for (int k = 0; k < (1 << b); ++k) v[k | (1 << b)] = cmul<D>(v[k], w);
         }
 #pragma unroll
         for (int jb = 0; jb < RA; ++jb)
-            stage<R, RA, true>(v, jb, TW + tw_off(jb), jb > 0, [&](int k) { return k & ((1 << jb) - 1); });
-        cvec<R> *lt = tile + ((lhi << RA) << A.cl) + c;
+            stage<D, RA>(v, jb, TW + tw_off(jb), jb > 0, [&](int k) { return k & ((1 << jb) - 1); });
+        cvec<D> *lt = tile + ((lhi << RA) << A.cl) + c;
 #pragma unroll
         for (int k = 0; k < (1 << RA); ++k) lt[k << A.cl] = v[k];
     }
@@ -305,19 +234,19 @@ __device__ __forceinline__ void pipe_a_body(const PipeArgs &A, const PipeSolve &
     const int nlb = C << RA;
     for (int line = threadIdx.x; line < nlb; line += NT) {
         const int c = line & (C - 1), llo = line >> A.cl;
-        cvec<R> v[1 << RB];
-        cvec<R> *lt = tile + (llo << A.cl) + c;
+        cvec<D> v[1 << RB];
+        cvec<D> *lt = tile + (llo << A.cl) + c;
 #pragma unroll
         for (int k = 0; k < (1 << RB); ++k) v[k] = lt[(k << RA) << A.cl];
 #pragma unroll
         for (int jb = RA; jb < G; ++jb)
-            stage<R, RB, true>(v, jb - RA, TW + tw_off(jb), true,
+            stage<D, RB>(v, jb - RA, TW + tw_off(jb), true,
                                [&](int k) { return llo + ((k & ((1 << (jb - RA)) - 1)) << RA); });
         // clock index (o << G) + (k << RA) + llo: a base for the line and a stride for k
         cvec<R> *p = psi + (((((o << G) + (uint64_t)llo) << A.n_s)) + j0 + c);
         const uint64_t ks = 1ull << (RA + A.n_s);
 #pragma unroll
-        for (int k = 0; k < (1 << RB); ++k) gst<R>(p, k * ks, v[k]);
+        for (int k = 0; k < (1 << RB); ++k) gst<R>(p, k * ks, cmake<R>((R)v[k].x, (R)v[k].y));
     }
 }
 
@@ -332,12 +261,28 @@ __global__ __launch_bounds__(NT) void k_pipe_a(PipeArgs A, PipeSolve one, const 
 // k_pipe_b: inverse cascade on G2 and the inversion rotation
 // ---------------------------------------------------------------------------
 // Writes the state after the rotation (the ancilla = 1 half), as
-// 2^-G2 s_y a(y): the forward cascade of the uncompute that follows is left
-// to k_pipe_c, which needs only its projection.  In the half the clock's two
+// 2^-G2 s_y a(y).  In the half the clock's two
 // groups trade places: clock value y1 + (y2 << g1) is row y2 + (y1 << g2), so
 // the rows of a tile (one G1 value) form one block of 2^g2 rows, which
 // streams faster than rows 2^g1 apart (a relabelling of the clock qubits in
-// memory; both kernels use it).  Tile: columns [j0, j0 + C)
+// memory).
+//
+// The projection.  Only the clock sum of each transformed column is needed,
+//   z = sum_y ph(y) (F v)(y),
+// F the forward cascade on the whole clock (the QFT of the uncompute, from
+// the top bit down) and ph(y) = prod_b om_b^(y_b) the conjugate phases of
+// the controlled powers, a product over the clock bits.  Moved onto the
+// input, z = sum_y v(y) K(y) with K the transposed cascade applied to ph,
+//   K(y) = prod_b (1 + (-1)^(y_b) t_b(y mod 2^b) om_b),
+// t_b the stage's twiddle: factor by factor the conjugate of the amplitudes
+// formed here, K = conj(P) 2^((n_c + g1)/2).  With v = 2^-G2 s beta P and the
+// 2^(-(n_c + g1)/2) of the Hadamards left out, z_j = beta_j sum_y 2^-G2 s_y |P|^2:
+// a real sum per column, taken while the line is in registers.  A third kernel
+// that read the half back and contracted it with K took 2.5 of the 5.8 ms of a
+// 32-qubit complex64 solve, and 90 of the 247 us of a 26-qubit complex128 one.
+// Bound by the stores: 17.2 GB in 3.02-3.07 ms, 5.6-5.7 TB/s (a plain fill: 6.9).
+//
+// Tile: columns [j0, j0 + C)
 // at G1 value o; a work-queue item (PERS) runs A.iters column blocks j0 + it 2^(pslog + cl).
 // The FP64 partial pair goes to slot `slot`.
 template <typename R, int RA, int RB, int NT, bool PERS>
@@ -345,23 +290,31 @@ __device__ __forceinline__ void pipe_b_body(const PipeArgs &A, const PipeSolve &
                                             uint64_t slot) {
     constexpr int G = RA + RB;
     cvec<R> *__restrict__ psi = (cvec<R> *)S.psi;
+    const double2 *__restrict__ beta = S.beta;
     const gptr<double> __restrict__ part = (gptr<double>)S.part;
+    const gptr<double> __restrict__ zpart = (gptr<double>)S.zpart;
     extern __shared__ unsigned char smem_raw[];
     const int C = 1 << A.cl;
     cvec<R> *TW = reinterpret_cast<cvec<R> *>(smem_raw);            // [2^G] twiddles of G2 at G1 value o
     R *s2t = reinterpret_cast<R *>(TW + (1 << G));                  // [2^G] s_y^2 2^-G
     R *srt = s2t + (1 << G);                                         // [2^G] s_y 2^-G
     // two sets (alternate tiles) of the column data: om[G][C] the phases of
-    // the G2 bits (staged by k_pipe_a in clock rows 2^g1 + b), then tT[C] the
-    // G1 table entries T_j(o)
-    const int ncd = (G + 1) * C;
+    // the G2 bits (staged by k_pipe_a in clock rows 2^g1 + b), tT[C] the
+    // G1 table entries T_j(o), be[C] the columns' beta; then two sets of the
+    // lines' sums of s_y |P|^2
+    const int ncd = (G + 2) * C;
     cvec<R> *cd = reinterpret_cast<cvec<R> *>(srt + (1 << G));
+    R *zl = reinterpret_cast<R *>(cd + 2 * ncd);
     __shared__ double red[2][NT / 64];
     const int iters = PERS ? A.iters : 1;
     const uint64_t jstep = PERS ? 1ull << (A.pslog + A.cl) : 0;
     const int g1 = A.g1, n_c = A.n_c;
     auto col_data = [&](int e, uint64_t j) -> cvec<R> {
         const int b = e / C, cq = e - b * C;
+        if (b > G) {
+            const double2 bj = gld<double>(beta, j + cq);
+            return cmake<R>((R)bj.x, (R)bj.y);
+        }
         return b < G ? gld<R>(psi, ((((uint64_t)1 << g1) + (uint64_t)b) << A.n_s) + j + cq)
                      : gld<R>(psi, (o << A.n_s) | (j + cq));
     };
@@ -389,7 +342,8 @@ __device__ __forceinline__ void pipe_b_body(const PipeArgs &A, const PipeSolve &
     double pa = 0.0, nt = 0.0;
     for (int it = 0; it < iters; ++it) {
         const bool more = PERS && it + 1 < iters;
-        const cvec<R> *om = cd + (it & 1) * ncd, *tT = om + G * C;
+        const cvec<R> *om = cd + (it & 1) * ncd, *tT = om + G * C, *be = tT + C;
+        R *zt = zl + (it & 1) * nl;
         // the inverse-QFT output on the G2 register of column j at
         // y = o + l 2^g1, l = llo + (k << RA), from its closed form.  The
         // input of the G2 stages is T_j(o) times a product state over the G2
@@ -429,22 +383,27 @@ __device__ __forceinline__ void pipe_b_body(const PipeArgs &A, const PipeSolve &
                     v[m + (1 << bb)] = cmul<R>(a, cmake<R>((R)1 - q.x, -q.y));
                 }
             }
-            // |a|^2 summed over the line in the amplitude precision (weighted by
-            // s_y^2 for P(a = 1); the rotation keeps each pair's norm, so the
-            // total is the plain sum), then accumulated in FP64
-            R lpa = 0, lnt = 0;
+            // |P|^2 summed over the line in the amplitude precision, weighted by
+            // s_y^2 for P(a = 1), by s_y for z and by one for the norm (the
+            // rotation keeps each pair's norm); |beta|^2 and the sums over lines
+            // and tiles in FP64
+            R lpa = 0, lnt = 0, lz = 0;
             const R *s2l = s2t + llo, *srl = srt + llo;
+            const cvec<R> bc = be[c];
             cvec<R> *ps = psi + (A.abit + (((uint64_t)llo + (o << G)) << A.n_s) + j0 + c);
 #pragma unroll
             for (int k = 0; k < (1 << RB); ++k) {
                 const R a2 = v[k].x * v[k].x + v[k].y * v[k].y;
-                lpa += s2l[k << RA] * a2;
-                lnt += a2;
                 const R sr = srl[k << RA];
-                gst_nt<R>(ps, k * ks, cmake<R>(v[k].x * sr, v[k].y * sr));
+                lpa += s2l[k << RA] * a2;
+                lz += sr * a2;
+                lnt += a2;
+                gst_nt<R>(ps, k * ks, cmul<R>(cmake<R>(v[k].x * sr, v[k].y * sr), bc));
             }
-            pa += (double)lpa;
-            nt += (double)lnt * fold;
+            const double b2 = (double)bc.x * (double)bc.x + (double)bc.y * (double)bc.y;
+            pa += b2 * (double)lpa;
+            nt += b2 * ((double)lnt * fold);
+            zt[(llo << A.cl) + c] = lz;
         }
         // an item's run: the next tile's column data go to the other set, last
         // read in the previous tile (before the last barrier).  (Reading them
@@ -453,7 +412,13 @@ __device__ __forceinline__ void pipe_b_body(const PipeArgs &A, const PipeSolve &
         if (more) {
             cvec<R> *nxt = cd + ((it + 1) & 1) * ncd;
             for (int e = threadIdx.x; e < ncd; e += NT) nxt[e] = col_data(e, j0 + jstep);
-            __syncthreads();
+        }
+        __syncthreads();
+        for (int cq = threadIdx.x; cq < C; cq += NT) {
+            double z = 0.0;
+#pragma unroll
+            for (int l = 0; l < (1 << RA); ++l) z += (double)zt[(l << A.cl) + cq];
+            zpart[o * A.N + j0 + cq] = z;
         }
         j0 += jstep;
     }
@@ -485,189 +450,17 @@ __global__ __launch_bounds__(NT) void k_pipe_b(PipeArgs A, PipeSolve one, const 
 
 
 // ---------------------------------------------------------------------------
-// k_pipe_c: forward cascade on the clock, conjugate phases, clock sum
-// (the missing 2^(-G/2) of the G1 Hadamards is applied with the final scale)
-// ---------------------------------------------------------------------------
-// Only the clock sum of each transformed column is needed,
-//   z = sum_y ph(y) (F v)(y),
-// F the forward cascade on the whole clock (the QFT of the uncompute, from
-// the top bit down) and ph(y) = prod_b om_b^(y_b) the conjugate phases of
-// the controlled powers, a product over the clock bits.  Moved onto the
-// input, z = sum_y v(y) K(y) with K the transposed cascade applied to ph.  A
-// transposed stage on bit b maps the pair (p0, p1) to (p0 + t p1, p0 - t p1),
-// t = exp(2 pi i (y mod 2^b) / 2^(b+1)) its twiddle; run from bit 0 upwards
-// on a product state it leaves
-//   K(y) = prod_b (1 + (-1)^(y_b) t_b(y mod 2^b) om_b),
-// so no transform is formed.  A thread takes a line: one column, one value lo
-// of the clock bits below L = n_c - RB, the 2^RB values of the top RB bits.
-// It contracts the line from its top bit down, each step halving it,
-//   u(m) = (v(m) + v(m + h)) + q (v(m) - v(m + h)),  q = t_b(lo + m 2^L) om_b,
-// and multiplies what is left by the factors of the bits below L.  With
-// lo = llo + (o << RA): the tile is columns [j0, j0 + C) at o (< 2^g2), its
-// lines the 2^RA values llo; a work-queue item (PERS) runs A.iters column
-// blocks j0 + it 2^(pslog + cl).  The threads exchange only the column sums.
-// cos(2 pi k / 32) and sin(2 pi k / 32): the roots of the line bits in
-// k_pipe_c (RB <= 5), folded into the code as constants
-__device__ constexpr double cos32(int k) {
-    // cos(j pi / 16), j = 0..8
-    constexpr double c[9] = {1.0,
-                             0.98078528040323044913,
-                             0.92387953251128675613,
-                             0.83146961230254523708,
-                             0.70710678118654752440,
-                             0.55557023301960222474,
-                             0.38268343236508977173,
-                             0.19509032201612826785,
-                             0.0};
-    k &= 31;
-    return k <= 8 ? c[k] : k <= 16 ? -c[16 - k] : k <= 24 ? -c[k - 16] : c[32 - k];
-}
-__device__ constexpr double sin32(int k) { return cos32(k - 8); }
-
-template <typename R, int RA, int RB, int NT, bool PERS>
-__device__ __forceinline__ void pipe_c_body(const PipeArgs &A, const PipeSolve &S, uint64_t j0, uint64_t o) {
-    constexpr int G = RA + RB;           // = g1
-    static_assert(RB <= 5, "the line bits' roots are 32nd roots of unity");
-    const cvec<R> *__restrict__ psi = (const cvec<R> *)S.psi;
-    double2 *__restrict__ zpart = S.zpart;
-    extern __shared__ unsigned char smem_raw[];
-    const int C = 1 << A.cl;
-    const int n_c = A.n_c, g2 = n_c - G, L = n_c - RB;
-    // LDS: the twiddles of the low bits t_b(x) (b < RA), per o the twiddles
-    // of the bits [RA, L) and the line's base phases exp(2 pi i lo / 2^(b+1))
-    // (b >= L), then two sets (alternate tiles) of the column phases
-    // om[n_c][C] and of the threads' partial sums
-    cvec<R> *TWa = reinterpret_cast<cvec<R> *>(smem_raw);           // [2^RA]
-    cvec<R> *T2 = TWa + (1 << RA);                                   // [g2][2^RA]
-    cvec<R> *T3 = T2 + (g2 << RA);                                   // [RB][2^RA]
-    const int nph = n_c * C;
-    cvec<R> *phs = T3 + (RB << RA);                                  // [2][n_c][C]
-    const size_t zoff = (((size_t)((unsigned char *)(phs + 2 * nph) - smem_raw)) + 15) & ~(size_t)15;
-    double2 *zs = reinterpret_cast<double2 *>(smem_raw + zoff);      // [2][NT]
-    const int iters = PERS ? A.iters : 1;
-    const uint64_t jstep = PERS ? 1ull << (A.pslog + A.cl) : 0;
-    const int nl = C << RA;
-    // every line of a thread has the thread's column (the line stride NT is a multiple of C)
-    const int c = threadIdx.x & (C - 1);
-    // clock value y = lo + (k << L) is row (y >> g1) + ((y mod 2^g1) << g2) of
-    // the half (k_pipe_b's layout); k's bits lie above g1, so a line is a
-    // base row and a stride for k
-    const uint64_t ks = 1ull << (L - G + A.n_s);
-    // conjugate phase of clock bit b (= e / C) of the column at j: staged by
-    // k_pipe_a in clock row 2^g1 + g2 + b (G1 bits) or 2^g1 + b - g1 (G2
-    // bits) of the ancilla = 0 half
-    auto col_phase = [&](int e, uint64_t j) -> cvec<R> {
-        const int b = e / C, cq = e - b * C;
-        const int r = b < G ? g2 + b : b - G;
-        const cvec<R> w = gld<R>(psi, ((((uint64_t)1 << G) + (uint64_t)r) << A.n_s) + j + cq);
-        return cmake<R>(w.x, -w.y);
-    };
-    for (int e = threadIdx.x; e < nph; e += NT) phs[e] = col_phase(e, j0);
-    fill_twiddles<R>(TWa, RA, 0, 0);
-    for (int e = threadIdx.x; e < ((g2 + RB) << RA); e += NT) {
-        const int i = e >> RA, llo = e & ((1 << RA) - 1);
-        if (i < g2) {
-            // bit b = RA + i: t_b(lo mod 2^b), lo mod 2^b = llo + ((o mod 2^i) << RA)
-            const int b = RA + i;
-            const uint64_t x = (uint64_t)llo + ((o & ((1ull << i) - 1)) << RA);
-            T2[e] = turn_phase<R>(x << (63 - b));
-        } else {
-            // bit b = L + kb: exp(2 pi i lo / 2^(b+1))
-            const int b = L + (i - g2);
-            T3[((i - g2) << RA) + llo] = turn_phase<R>(((uint64_t)llo + (o << RA)) << (63 - b));
-        }
-    }
-    __syncthreads();
-    for (int it = 0; it < iters; ++it) {
-        const bool more = PERS && it + 1 < iters;
-        const cvec<R> *om = phs + (it & 1) * nph;
-        // lines are read where they are used: lines held in registers across
-        // the table set-up or the previous tile cost more in occupancy than
-        // they hide
-        double zr = 0.0, zi = 0.0;
-        for (int line = threadIdx.x; line < nl; line += NT) {
-            const int llo = line >> A.cl;
-            cvec<R> v[1 << RB];
-            const uint64_t y = (o << RA) + (uint64_t)llo;
-            const uint64_t row = (y >> G) + ((y & ((1ull << G) - 1)) << g2);
-            const cvec<R> *p = psi + (A.abit + (row << A.n_s) + j0 + c);
-#pragma unroll
-            for (int k = 0; k < (1 << RB); ++k) v[k] = gld_nt<R>(p, k * ks);
-            // the line's bits, top first: q = om_b exp(2 pi i lo / 2^(b+1)) times
-            // the root exp(2 pi i m / 2^(kb+1)) of the line bits below
-#pragma unroll
-            for (int kb = RB - 1; kb >= 0; --kb) {
-                const int h = 1 << kb;
-                const cvec<R> Q = cmul<R>(om[(L + kb) * C + c], T3[(kb << RA) + llo]);
-#pragma unroll
-                for (int m = 0; m < h; ++m) {
-                    const int r = m << (4 - kb);
-                    const cvec<R> q = r == 0   ? Q
-                                      : r == 8 ? cmake<R>(-Q.y, Q.x)
-                                               : cmul<R>(Q, cmake<R>((R)cos32(r), (R)sin32(r)));
-                    const cvec<R> a = v[m], b = v[m + h];
-                    const R sx = a.x + b.x, sy = a.y + b.y, dx = a.x - b.x, dy = a.y - b.y;
-                    v[m] = cmake<R>(ffma(q.x, dx, ffma(-q.y, dy, sx)), ffma(q.x, dy, ffma(q.y, dx, sy)));
-                }
-            }
-            // the factors of the bits below L: the low RA bits (bit 0: twiddle
-            // 1), then the g2 bits of o
-            cvec<R> f = cmake<R>((R)1, (R)0);
-#pragma unroll
-            for (int b = 0; b < RA; ++b) {
-                const cvec<R> w = om[b * C + c];
-                const cvec<R> q = b == 0 ? w : cmul<R>(w, TWa[tw_off(b) + (llo & ((1 << b) - 1))]);
-                f = cmul<R>(f, (llo >> b & 1) ? cmake<R>((R)1 - q.x, -q.y) : cmake<R>((R)1 + q.x, q.y));
-            }
-            for (int i = 0; i < g2; ++i) {
-                const cvec<R> q = cmul<R>(om[(RA + i) * C + c], T2[(i << RA) + llo]);
-                f = cmul<R>(f, (o >> i & 1) ? cmake<R>((R)1 - q.x, -q.y) : cmake<R>((R)1 + q.x, q.y));
-            }
-            const cvec<R> u = cmul<R>(v[0], f);
-            zr += (double)u.x;
-            zi += (double)u.y;
-        }
-        // an item's run: the next tile's phases go to the other set, last read
-        // in the previous tile (before the last barrier)
-        if (more) {
-            cvec<R> *nxt = phs + ((it + 1) & 1) * nph;
-            for (int e = threadIdx.x; e < nph; e += NT) nxt[e] = col_phase(e, j0 + jstep);
-        }
-        double2 *zt = zs + (it & 1) * NT;
-        zt[threadIdx.x] = make_double2(zr, zi);
-        __syncthreads();
-        for (int cq = threadIdx.x; cq < C; cq += NT) {
-            double r = 0.0, i = 0.0;
-            for (int t = cq; t < NT; t += C) {
-                r += zt[t].x;
-                i += zt[t].y;
-            }
-            gst<double>(zpart, o * A.N + j0 + cq, make_double2(r, i));
-        }
-        j0 += jstep;
-    }
-}
-
-template <typename R, int RA, int RB, int NT>
-__global__ __launch_bounds__(NT) void k_pipe_c(PipeArgs A, PipeSolve one, const PipeSolve *__restrict__ many) {
-    uint64_t j0, o;
-    tile_coords(A, j0, o);               // o = value of the G2 bits
-    pipe_c_body<R, RA, RB, NT, false>(A, solve_of(one, many), j0, o);
-}
-
-
-// ---------------------------------------------------------------------------
 // a batch as one persistent kernel over device work queues
 // ---------------------------------------------------------------------------
 struct QClass {
-    PipeArgs A[3];            // launch parameters of the three kernels' items
-    int g[3];                 // the group each transforms: g1, g2, g1
-    uint32_t per_o[3];        // items per value of the other clock group
+    PipeArgs A[2];            // launch parameters of the two kernels' items
+    int g[2];                 // the group each transforms: g1, g2
+    uint32_t per_o[2];        // items per value of the other clock group
 };
 struct QSolve {
     PipeSolve S;
     uint32_t cls;
-    uint32_t items[3];        // items of the three kernels (the finish waits for the last)
+    uint32_t items[2];        // items of the two kernels (the finish waits for the last)
 };
 constexpr int kMaxQueues = 8;
 struct QueueArgs {
@@ -675,7 +468,7 @@ struct QueueArgs {
     const QSolve *solves;
     const uint64_t *items;    // the queues' item codes, queue after queue
     const FinishJob *fin;
-    unsigned *cnt;            // [3 nsolves] done counters, [kMaxQueues] heads, finished solves
+    unsigned *cnt;            // [2 nsolves] done counters, [kMaxQueues] heads, finished solves
     unsigned *flag;
     uint64_t wait_ticks;      // bound of one dependency wait, in wall-clock ticks
     uint32_t nsolves;
@@ -721,16 +514,14 @@ __device__ __forceinline__ void queue_item(int ph, const PipeArgs &A, const Pipe
     constexpr int RA = (G + 1) / 2, RB = G / 2;     // the register split of dispatch_g
     if (ph == 0)
         pipe_a_body<R, RA, RB, 256>(A, S, j0, o);
-    else if (ph == 1)
-        pipe_b_body<R, RA, RB, 256, true>(A, S, j0, o, slot);
     else
-        pipe_c_body<R, RA, RB, 256, true>(A, S, j0, o);
+        pipe_b_body<R, RA, RB, 256, true>(A, S, j0, o, slot);
 }
 
 // Every block serves one queue and takes its items from the queue's head
 // until it is empty; the next item's code and the position of the one after
-// it are fetched while the current one runs.  An item code holds the phase (bits 62-63: 0-2 the three
-// kernels, 3 the finish), the solve (bits 42-61), the number of items of the
+// it are fetched while the current one runs.  An item code holds the phase (bits 62-63: 0 and 1 the two
+// kernels, 2 the finish), the solve (bits 42-61), the number of items of the
 // previous phase of the solve that it waits for (bits 21-41) and the item's
 // index within its phase of the solve (bits 0-20).  With one queue per XCC, a block reads the XCC it runs on and
 // serves that XCC's queue: every producer and consumer of a solve then
@@ -748,8 +539,8 @@ k_pipe_queue(QueueArgs Q) {
     const bool local = Q.local != 0;
     const int q = local ? Q.qof[xcc_id()] : 0;
     if (q < 0) return;
-    unsigned *const head = Q.cnt + 3 * (size_t)Q.nsolves + q;
-    unsigned *const finished = Q.cnt + 3 * (size_t)Q.nsolves + kMaxQueues;
+    unsigned *const head = Q.cnt + 2 * (size_t)Q.nsolves + q;
+    unsigned *const finished = Q.cnt + 2 * (size_t)Q.nsolves + kMaxQueues;
     const uint32_t base = Q.qstart[q], nitems = Q.qstart[q + 1] - base;
     // thread 0: the code of the block's next item (~0: none left) and the
     // queue position of the one after, both in flight during an item
@@ -768,7 +559,7 @@ k_pipe_queue(QueueArgs Q) {
                 if (pend < nitems) pend = __hip_atomic_fetch_add(head, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 const unsigned ph = (unsigned)(code >> 62), sv = (unsigned)(code >> 42) & 0xFFFFFu;
                 if (ph > 0)
-                    queue_wait(Q.cnt + 3 * (size_t)sv + ph - 1, (unsigned)(code >> 21) & 0x1FFFFFu, Q.flag,
+                    queue_wait(Q.cnt + 2 * (size_t)sv + ph - 1, (unsigned)(code >> 21) & 0x1FFFFFu, Q.flag,
                                Q.wait_ticks, local);
             }
             sh_code = code;
@@ -780,7 +571,7 @@ k_pipe_queue(QueueArgs Q) {
         const int ph = (int)(code >> 62);
         const uint32_t sv = (uint32_t)(code >> 42) & 0xFFFFFu;
         const uint64_t t = code & 0x1FFFFFu;
-        if (ph == 3) {
+        if (ph == 2) {
             batch_finish_body(Q.fin[sv]);
             if (threadIdx.x == 0) __hip_atomic_fetch_add(finished, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             continue;
@@ -817,7 +608,7 @@ k_pipe_queue(QueueArgs Q) {
         }
         __syncthreads();
         if (threadIdx.x == 0)
-            __hip_atomic_fetch_add(Q.cnt + 3 * (size_t)sv + ph, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_fetch_add(Q.cnt + 2 * (size_t)sv + ph, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 
@@ -842,10 +633,8 @@ static sv_status launch_pipe(int which, hipStream_t st, const PipeSolve &one, co
                                             hipFuncAttributeMaxDynamicSharedMemorySize, kLim);
         hipError_t e1 = hipFuncSetAttribute((const void *)k_pipe_b<R, RA, RB, NT>,
                                             hipFuncAttributeMaxDynamicSharedMemorySize, kLim);
-        hipError_t e2 = hipFuncSetAttribute((const void *)k_pipe_c<R, RA, RB, NT>,
-                                            hipFuncAttributeMaxDynamicSharedMemorySize, kLim);
         (void)hipGetLastError();
-        if (e0 != hipSuccess || e1 != hipSuccess || e2 != hipSuccess)
+        if (e0 != hipSuccess || e1 != hipSuccess)
             return fail(SV_EDEVICE, "cannot raise the LDS limit of the pipeline kernels");
         attr_done = true;
     }
@@ -857,12 +646,9 @@ static sv_status launch_pipe(int which, hipStream_t st, const PipeSolve &one, co
     if (which == 0) {
         TraceScope ts(st, "pipe_a_init_iqft", table, 0.0);
         hipLaunchKernelGGL((k_pipe_a<R, RA, RB, NT>), grid, dim3(NT), lds, st, A, one, many);
-    } else if (which == 1) {
+    } else {
         TraceScope ts(st, "pipe_b_iqft_ry", half + table, 0.0);
         hipLaunchKernelGGL((k_pipe_b<R, RA, RB, NT>), grid, dim3(NT), lds, st, A, one, many);
-    } else {
-        TraceScope ts(st, "pipe_c_qft_project", half, 0.0);
-        hipLaunchKernelGGL((k_pipe_c<R, RA, RB, NT>), grid, dim3(NT), lds, st, A, one, many);
     }
     SV_HIP(hipGetLastError());
     return SV_OK;
@@ -908,25 +694,23 @@ static int default_cl(int n_s, int g, size_t elem) {
     return cl;
 }
 
-static size_t pipe_lds(int which, int cl, int g, int n_c, size_t e, int nt) {
+static size_t pipe_lds(int which, int cl, int g, size_t e) {
     const size_t C = (size_t)1 << cl;
-    const size_t RA = (size_t)(g + 1) / 2, RB = (size_t)g / 2, g2 = (size_t)(n_c - g);
-    if (which == 0)        // the tile, the twiddles, the column phases and constants
-        return ((C << g) + ((size_t)1 << g) + (size_t)(g + 1) * C) * e;
-    if (which == 1)        // the twiddles, two rotation tables, two sets of column data
-        return ((size_t)1 << g) * e + 2 * ((size_t)1 << g) * (e / 2) + 2 * (size_t)(g + 1) * C * e;
-    // k_pipe_c: the twiddle tables, two sets of column phases and of partial sums
-    return (((size_t)1 << RA) + ((g2 + RB) << RA) + 2 * (size_t)n_c * C) * e + 2 * (size_t)nt * sizeof(double2) + 16;
+    if (which == 0)        // the tile, the twiddles, the column phases and constants (FP64)
+        return ((C << g) + ((size_t)1 << g) + (size_t)(g + 1) * C) * sizeof(double2);
+    // the twiddles, two rotation tables, two sets of column data and of line sums
+    return ((size_t)1 << g) * e + 2 * ((size_t)1 << g) * (e / 2) + 2 * (size_t)(g + 2) * C * e +
+           2 * (C << ((g + 1) / 2)) * (e / 2);
 }
 
 struct PipePlan {
-    PipeArgs A[3];
-    int nt[3];
-    dim3 grid[3];
-    size_t lds[3];
+    PipeArgs A[2];
+    int nt[2];
+    dim3 grid[2];
+    size_t lds[2];
 };
 
-static void make_plan(PipePlan &P, int n_s, int n_c, size_t e, const int cl[3], const int nt[3], int nsolves) {
+static void make_plan(PipePlan &P, int n_s, int n_c, size_t e, const int cl[2], const int nt[2], int nsolves) {
     PipeArgs A;
     A.N = dim_of(n_s);
     A.n_s = n_s;
@@ -939,16 +723,19 @@ static void make_plan(PipePlan &P, int n_s, int n_c, size_t e, const int cl[3], 
     A.gcut = 0;
     A.pslog = 0;
     A.iters = 1;
-    for (int w = 0; w < 3; ++w) {
+    for (int w = 0; w < 2; ++w) {
         const int g = w == 1 ? A.g2 : A.g1;
         P.A[w] = A;
-        P.A[w].cl = cl[w];
+        int c = cl[w];
+        // saved entries may hold wider k_pipe_a tiles than fit in FP64
+        while (w == 0 && c > 0 && pipe_lds(0, c, g, e) > (size_t)PIPE_LDS_LIMIT) --c;
+        P.A[w].cl = c;
         P.nt[w] = nt[w];
         // k_pipe_a writes the G1 table only (G2 value 0)
-        const uint64_t tiles = w == 0 ? (A.N >> cl[w]) : (A.N >> cl[w]) << (n_c - g);
+        const uint64_t tiles = w == 0 ? (A.N >> c) : (A.N >> c) << (n_c - g);
         P.grid[w] = tiles <= 0x7fffffffull ? dim3((unsigned)tiles, 1, nsolves)
                                            : dim3(1u << 30, (unsigned)(tiles >> 30), nsolves);
-        P.lds[w] = pipe_lds(w, cl[w], g, n_c, e, nt[w]);
+        P.lds[w] = pipe_lds(w, c, g, e);
     }
 }
 
@@ -959,22 +746,20 @@ static sv_status run_one(hipStream_t st, const PipePlan &P, int w, const PipeSol
 }
 
 // The autotuner: per (dtype, n_s, n_c) time every feasible (columns per
-// tile, threads per workgroup) for each of the three kernels on the real
+// tile, threads per workgroup) for each of the two kernels on the real
 // operands of one solve (each kernel is idempotent given its input half)
 // and keep the fastest; results live in the process-wide tuning cache.
 template <typename R>
-static sv_status tune_pipe(hipStream_t st, int n_s, int n_c, const PipeSolve &one, int cl_out[3],
-                           int nt_out[3]) {
+static sv_status tune_pipe(hipStream_t st, int n_s, int n_c, const PipeSolve &one, int cl_out[2],
+                           int nt_out[2]) {
     const size_t e = sizeof(cvec<R>);
     const int g1 = (n_c + 1) / 2, g2 = n_c - g1;
-    for (int w = 0; w < 3; ++w) {
+    for (int w = 0; w < 2; ++w) {
         cl_out[w] = default_cl(n_s, w == 1 ? g2 : g1, e);
         nt_out[w] = 256;
     }
-    for (int w = 0; w < 3; ++w) {
+    for (int w = 0; w < 2; ++w) {
         const int g = w == 1 ? g2 : g1;
-        // up to 128 columns: k_pipe_c's loads then cover 1 KiB of a row per
-        // instruction (its 64-column tiles read the half about 3 % more slowly).
         // Every candidate is timed in two alternating rounds and keeps its
         // faster one: single timings of a few-millisecond kernel differ by
         // more than the candidates do.
@@ -982,12 +767,12 @@ static sv_status tune_pipe(hipStream_t st, int n_s, int n_c, const PipeSolve &on
         for (int cl = 3; cl <= 7; ++cl) {
             if (cl > n_s) break;
             for (int nt : {256, 512})
-                if (pipe_lds(w, cl, g, n_c, e, nt) <= (size_t)PIPE_LDS_LIMIT) cand.push_back({cl, nt});
+                if (pipe_lds(w, cl, g, e) <= (size_t)PIPE_LDS_LIMIT) cand.push_back({cl, nt});
         }
         std::vector<float> tbest(cand.size(), 1e30f);
         for (int round = 0; round < 2; ++round)
             for (size_t i = 0; i < cand.size(); ++i) {
-                int cls[3] = {cl_out[0], cl_out[1], cl_out[2]}, nts[3] = {nt_out[0], nt_out[1], nt_out[2]};
+                int cls[2] = {cl_out[0], cl_out[1]}, nts[2] = {nt_out[0], nt_out[1]};
                 cls[w] = cand[i].first;
                 nts[w] = cand[i].second;
                 PipePlan P;
@@ -1016,15 +801,17 @@ static sv_status tune_pipe(hipStream_t st, int n_s, int n_c, const PipeSolve &on
 
 // launch parameters for a shape: cached, tuned on `one` if allowed, else defaults
 template <typename R>
-static sv_status pipe_config_impl(hipStream_t st, int n_s, int n_c, const PipeSolve *tune_on, int cl[3],
-                                  int nt[3]) {
+static sv_status pipe_config_impl(hipStream_t st, int n_s, int n_c, const PipeSolve *tune_on, int cl[2],
+                                  int nt[2]) {
     const size_t e = sizeof(cvec<R>);
     const int g1 = (n_c + 1) / 2, g2 = n_c - g1;
     const std::string key = std::string("eigpipe/") + (e == 8 ? "c64/" : "c128/") + std::to_string(n_s) + "/" +
                             std::to_string(n_c);
     std::vector<int> cached;
+    // an entry's third pair belonged to a third kernel; it is kept as zeros so
+    // that saved entries of either kind serve
     if (tune_lookup(key, cached) && cached.size() == 6) {
-        for (int w = 0; w < 3; ++w) {
+        for (int w = 0; w < 2; ++w) {
             cl[w] = cached[2 * w];
             nt[w] = cached[2 * w + 1];
         }
@@ -1032,10 +819,10 @@ static sv_status pipe_config_impl(hipStream_t st, int n_s, int n_c, const PipeSo
     }
     if (tune_on && autotune_enabled()) {
         SV_TRY(tune_pipe<R>(st, n_s, n_c, *tune_on, cl, nt));
-        tune_store(key, {cl[0], nt[0], cl[1], nt[1], cl[2], nt[2]});
+        tune_store(key, {cl[0], nt[0], cl[1], nt[1], 0, 0});
         return SV_OK;
     }
-    for (int w = 0; w < 3; ++w) {
+    for (int w = 0; w < 2; ++w) {
         cl[w] = default_cl(n_s, w == 1 ? g2 : g1, e);
         nt[w] = 256;
     }
@@ -1043,35 +830,35 @@ static sv_status pipe_config_impl(hipStream_t st, int n_s, int n_c, const PipeSo
 }
 
 template <typename R>
-sv_status pipe_config(hipStream_t st, int n_s, int n_c, const PipeSolve *tune_on, int cl[3], int nt[3]) {
+sv_status pipe_config(hipStream_t st, int n_s, int n_c, const PipeSolve *tune_on, int cl[2], int nt[2]) {
     return pipe_config_impl<R>(st, n_s, n_c, tune_on, cl, nt);
 }
 
 template <typename R>
 sv_status pipe_run(sv_state s, int n_s, int n_c, bool sgn, uint64_t gcut, const double2 *beta, const uint64_t *F,
-                   double *part, double2 *zpart, uint64_t *nparts) {
+                   double *part, double *zpart, uint64_t *nparts) {
     const size_t e = sizeof(cvec<R>);
     PipeSolve one{s->data, beta, F, part, zpart};
-    int cl[3], nt[3];
+    int cl[2], nt[2];
     SV_TRY(pipe_config_impl<R>(s->stream, n_s, n_c, &one, cl, nt));
     PipePlan P;
     make_plan(P, n_s, n_c, e, cl, nt, 1);
-    for (int w = 0; w < 3; ++w) {
+    for (int w = 0; w < 2; ++w) {
         P.A[w].sgn = sgn ? 1 : 0;
         P.A[w].gcut = gcut;
     }
     *nparts = (uint64_t)P.grid[1].x * P.grid[1].y;
-    for (int w = 0; w < 3; ++w) SV_TRY(run_one<R>(s->stream, P, w, one, nullptr));
+    for (int w = 0; w < 2; ++w) SV_TRY(run_one<R>(s->stream, P, w, one, nullptr));
     return SV_OK;
 }
 template sv_status pipe_run<float>(sv_state, int, int, bool, uint64_t, const double2 *, const uint64_t *, double *,
-                                   double2 *, uint64_t *);
+                                   double *, uint64_t *);
 template sv_status pipe_run<double>(sv_state, int, int, bool, uint64_t, const double2 *, const uint64_t *,
-                                    double *, double2 *, uint64_t *);
+                                    double *, double *, uint64_t *);
 
-// a class of solves sharing (n_s, n_c): the three kernels once each, blockIdx.z = solve
+// a class of solves sharing (n_s, n_c): the two kernels once each, blockIdx.z = solve
 template <typename R>
-sv_status pipe_run_batch(hipStream_t st, int n_s, int n_c, const int cl[3], const int nt[3],
+sv_status pipe_run_batch(hipStream_t st, int n_s, int n_c, const int cl[2], const int nt[2],
                          const PipeSolve *dev_solves, int nsolves, uint64_t *nparts) {
     const size_t e = sizeof(cvec<R>);
     if (nsolves < 1 || nsolves > 65535) return fail(SV_EINVAL, "batch of %d solves", nsolves);
@@ -1079,7 +866,7 @@ sv_status pipe_run_batch(hipStream_t st, int n_s, int n_c, const int cl[3], cons
     make_plan(P, n_s, n_c, e, cl, nt, nsolves);
     *nparts = (uint64_t)P.grid[1].x * P.grid[1].y;
     PipeSolve none{};
-    for (int w = 0; w < 3; ++w) SV_TRY(run_one<R>(st, P, w, none, dev_solves));
+    for (int w = 0; w < 2; ++w) SV_TRY(run_one<R>(st, P, w, none, dev_solves));
     return SV_OK;
 }
 template sv_status pipe_run_batch<float>(hipStream_t, int, int, const int *, const int *, const PipeSolve *, int,
@@ -1091,7 +878,7 @@ template sv_status pipe_config<double>(hipStream_t, int, int, const PipeSolve *,
 
 // ---------------------------------------------------------------------------
 // the work queues' plan: items of about 2^15 amplitudes (runs of consecutive
-// column blocks for k_pipe_b and k_pipe_c); the solves spread over one
+// column blocks for k_pipe_b); the solves spread over one
 // queue per XCC, each queue numbered phase-major, its solves largest first
 // ---------------------------------------------------------------------------
 template <typename R>
@@ -1119,10 +906,10 @@ sv_status pipe_queue_build(sv_state ctx, hipStream_t st, PipeQueue &q, DevBuf &d
     int gmax = 1;
     for (size_t k = 0; k < cls.size(); ++k) {
         const QueueClassIn &ci = cls[k];
-        const int nt[3] = {256, 256, 256};
+        const int nt[2] = {256, 256};
         PipePlan P;
         make_plan(P, ci.n_s, ci.n_c, e, ci.cl, nt, 1);
-        for (int w = 0; w < 3; ++w) {
+        for (int w = 0; w < 2; ++w) {
             PipeArgs A = P.A[w];
             const int g = w == 1 ? A.g2 : A.g1;
             // tiles of at most 2^11 amplitudes: LDS for four blocks per CU
@@ -1138,7 +925,7 @@ sv_status pipe_queue_build(sv_state ctx, hipStream_t st, PipeQueue &q, DevBuf &d
             qc[k].g[w] = g;
             if (g > gmax) gmax = g;
             qc[k].per_o[w] = (uint32_t)(nb / (uint64_t)iters);
-            const size_t b = pipe_lds(w, A.cl, g, A.n_c, e, 256);
+            const size_t b = pipe_lds(w, A.cl, g, e);
             if (b > lds) lds = b;
         }
     }
@@ -1151,16 +938,15 @@ sv_status pipe_queue_build(sv_state ctx, hipStream_t st, PipeQueue &q, DevBuf &d
         const QClass &c = qc[solve_cls[k]];
         qs[k].S = solves[k];
         qs[k].cls = (uint32_t)solve_cls[k];
-        const int g1 = c.A[0].g1, g2 = c.A[0].g2;
+        const int g1 = c.A[0].g1;
         qs[k].items[0] = c.per_o[0];
         qs[k].items[1] = c.per_o[1] << g1;
-        qs[k].items[2] = c.per_o[2] << g2;
         q.nparts[k] = qs[k].items[1];
         if (q.nparts[k] > pipe_b_blocks(c.A[0].n_s, c.A[0].n_c, e))
             return fail(SV_EDEVICE, "queue partials exceed their buffer");
         const double half = (double)c.A[0].N * (double)(1ull << c.A[0].n_c) * e;
         const double table = (double)c.A[0].N * (double)(1ull << g1) * e;
-        cost[k] = 2.0 * half + 2.0 * table;
+        cost[k] = half + 2.0 * table;
         bytes += cost[k];
     }
     // resident blocks, and the XCC each of them lands on
@@ -1227,24 +1013,24 @@ sv_status pipe_queue_build(sv_state ctx, hipStream_t st, PipeQueue &q, DevBuf &d
     // each queue phase-major, its solves largest first; a code carries the
     // item count its wait targets (that of the solve's previous phase)
     for (int k = 0; k < ns; ++k)
-        for (int ph = 0; ph < 3; ++ph)
+        for (int ph = 0; ph < 2; ++ph)
             if (qs[k].items[ph] >= (1u << 21))
                 return fail(SV_EUNSUPPORTED, "%u items in one phase of a solve", qs[k].items[ph]);
     std::vector<uint64_t> items;
     for (int i = 0; i < q.nq; ++i) {
         q.qstart[i] = (uint32_t)items.size();
-        for (int ph = 0; ph < 3; ++ph)
+        for (int ph = 0; ph < 2; ++ph)
             for (int k : members[i]) {
                 q.items_per_phase[ph] += qs[k].items[ph];
                 const uint64_t wait = ph > 0 ? qs[k].items[ph - 1] : 0;
                 for (uint64_t t = 0; t < qs[k].items[ph]; ++t)
                     items.push_back(((uint64_t)ph << 62) | ((uint64_t)k << 42) | (wait << 21) | t);
             }
-        for (int k : members[i]) items.push_back((3ull << 62) | ((uint64_t)k << 42) | ((uint64_t)qs[k].items[2] << 21));
+        for (int k : members[i]) items.push_back((2ull << 62) | ((uint64_t)k << 42) | ((uint64_t)qs[k].items[1] << 21));
         if (items.size() >= 0xffffffffull) return fail(SV_EUNSUPPORTED, "work queue of %zu items", items.size());
     }
     q.qstart[q.nq] = (uint32_t)items.size();
-    q.items_per_phase[3] = (uint64_t)ns;
+    q.items_per_phase[2] = (uint64_t)ns;
     // descriptors: classes, solves, item codes
     const size_t o_cls = 0, o_sol = (qc.size() * sizeof(QClass) + 255) & ~(size_t)255;
     const size_t o_items = o_sol + ((qs.size() * sizeof(QSolve) + 255) & ~(size_t)255);
@@ -1304,11 +1090,11 @@ uint64_t pipe_b_blocks_for(int n_s, int n_c, int cl) {
 }
 
 // upper bounds of the k_pipe_b block count (one FP64 partial pair each) and
-// the k_pipe_c partial rows, over every configuration the tuner may pick
+// the rows of column sums, over every configuration the tuner may pick
 uint64_t pipe_b_blocks(int n_s, int n_c, size_t elem) {
     (void)elem;
     return pipe_b_blocks_for(n_s, n_c, n_s < 3 ? n_s : 3);
 }
-int pipe_c_rows(int n_c) { return 1 << (n_c - (n_c + 1) / 2); }
+int pipe_rows(int n_c) { return 1 << ((n_c + 1) / 2); }
 
 }  // namespace sv

@@ -47,7 +47,7 @@ sv_status ctrl_unitary_impl(sv_state s, const cvec<R> *U, int m, int ctrl, int c
 template <typename R>
 sv_status pipe_run(sv_state s, int n_s, int n_c, bool sgn, uint64_t gcut, const double2 *beta, const uint64_t *F,
                    double *part,
-                   double2 *zpart, uint64_t *nparts);
+                   double *zpart, uint64_t *nparts);
 
 // --------------------------------------------------------------------------
 // small FP64 kernels
@@ -253,9 +253,9 @@ __global__ __launch_bounds__(256) void k_eig_project(const cvec<R> *__restrict__
 // z[j] = scale * sum over the partial rows of column j: four interleaved
 // accumulators (rows r = k mod 4) keep four loads in flight per thread, and
 // are combined in a fixed order
-__device__ __forceinline__ void sum_cols_body(double2 *__restrict__ z, const double2 *__restrict__ part, uint64_t N,
-                                              int rows, double scale, uint64_t block, uint64_t blocks) {
-    for (uint64_t j = block * blockDim.x + threadIdx.x; j < N; j += blocks * blockDim.x) {
+__global__ void k_sum_cols(double2 *__restrict__ z, const double2 *__restrict__ part, uint64_t N, int rows,
+                           double scale) {
+    for (uint64_t j = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; j < N; j += (uint64_t)gridDim.x * blockDim.x) {
         double re[4] = {0.0, 0.0, 0.0, 0.0}, im[4] = {0.0, 0.0, 0.0, 0.0};
         int r = 0;
         for (; r + 4 <= rows; r += 4) {
@@ -275,14 +275,9 @@ __device__ __forceinline__ void sum_cols_body(double2 *__restrict__ z, const dou
     }
 }
 
-__global__ void k_sum_cols(double2 *__restrict__ z, const double2 *__restrict__ part, uint64_t N, int rows,
-                           double scale) {
-    sum_cols_body(z, part, N, rows, scale, blockIdx.x, gridDim.x);
-}
-
 // The pipeline's sums in one launch: workgroups [0, nc) add nc stretches of the
 // (P(a=1), norm) partials into head[0..nc), which the host adds up in order; the
-// others add the columns.  Bound by the launch: 6.4 us on the 26-qubit complex128
+// others add the columns (z = beta times the column's sum).  Bound by the launch: 6.4 us on the 26-qubit complex128
 // solve (32 768 partials), where five launches took 25; one workgroup for all
 // partials takes longer than the gap it saves above about 2048 of them.
 constexpr int EIG_CHUNKS = 64;
@@ -290,12 +285,30 @@ constexpr int EIG_HEAD = 8 + 2 * EIG_CHUNKS;     // doubles in front of x: scala
 
 static int eig_chunks(uint64_t nparts) { return nparts <= 2048 ? 1 : EIG_CHUNKS; }
 
-__global__ __launch_bounds__(256) void k_eig_sums(double2 *__restrict__ z, const double2 *__restrict__ zpart, uint64_t N,
-                                                  int rows, double scale, const double2 *__restrict__ part,
+__global__ __launch_bounds__(256) void k_eig_sums(double2 *__restrict__ z, const double *__restrict__ zpart,
+                                                  const double2 *__restrict__ beta, uint64_t N, int rows,
+                                                  const double2 *__restrict__ part,
                                                   uint64_t nparts, int nc, double2 *__restrict__ head) {
-    __shared__ double ws[2][4];
+    __shared__ double ws[2][4], wz[3][64];
     if ((int)blockIdx.x >= nc) {
-        sum_cols_body(z, zpart, N, rows, scale, blockIdx.x - nc, gridDim.x - nc);
+        // 64 columns per workgroup, its four waves a quarter of the rows each
+        const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+        const int per = (rows + 3) / 4, r0 = wv * per, r1 = r0 + per < rows ? r0 + per : rows;
+        const uint64_t j = (uint64_t)(blockIdx.x - nc) * 64 + lane;
+        double w[4] = {0.0, 0.0, 0.0, 0.0};
+        if (j < N) {
+            int r = r0;
+            for (; r + 4 <= r1; r += 4)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) w[k] += zpart[(uint64_t)(r + k) * N + j];
+            for (; r < r1; ++r) w[0] += zpart[(uint64_t)r * N + j];
+        }
+        const double f = (w[0] + w[1]) + (w[2] + w[3]);
+        if (wv) wz[wv - 1][lane] = f;
+        __syncthreads();
+        if (wv || j >= N) return;
+        const double t = (f + wz[0][lane]) + (wz[1][lane] + wz[2][lane]);
+        z[j] = make_double2(t * beta[j].x, t * beta[j].y);
         return;
     }
     const uint64_t len = (nparts + nc - 1) / nc, beg = (uint64_t)blockIdx.x * len;
@@ -988,22 +1001,19 @@ static sv_status eig_frame_run(sv_state s, const EigFrame &E, Workspace &w, cons
     }
 
     if (fused && pipe_supported(n_s, n_c)) {
-        // fused three-kernel pipeline: (state + inverse QFT on the low clock bits),
-        // (inverse QFT high + rotation), (uncompute projected on clock 0)
+        // fused two-kernel pipeline: (state + inverse QFT on the low clock bits),
+        // (inverse QFT high + rotation + the uncompute projected on clock 0)
         const uint64_t nbp = pipe_b_blocks(n_s, n_c, sizeof(cvec<R>));
-        const int rows = pipe_c_rows(n_c);
+        const int rows = pipe_rows(n_c);
         SV_TRY(need(w.part, 2 * nbp * sizeof(double)));
-        SV_TRY(need(w.zpart, (size_t)rows * N * sizeof(double2)));
+        SV_TRY(need(w.zpart, (size_t)rows * N * sizeof(double)));
         uint64_t nparts = 0;
         SV_TRY(pipe_run<R>(s, n_s, n_c, sgn, gcut, (const double2 *)w.beta.p, (const uint64_t *)w.F.p, (double *)w.part.p,
-                           (double2 *)w.zpart.p, &nparts));
+                           (double *)w.zpart.p, &nparts));
         if (nparts > nbp) return fail(SV_EDEVICE, "pipeline partial count exceeds its buffer");
-        // 2^(-n_c/2) of the final Hadamard layer, and 2^(-g1/2) the fused forward
-        // transform on the low clock group leaves out of its butterflies
-        const int g1 = (n_c + 1) / 2;
         const int nc = eig_chunks(nparts);
-        hipLaunchKernelGGL(k_eig_sums, dim3(nc + grid1(N)), dim3(256), 0, st, (double2 *)w.z.p, (const double2 *)w.zpart.p,
-                           N, rows, exp2(-0.5 * (n_c + g1)), (const double2 *)w.part.p, nparts, nc,
+        hipLaunchKernelGGL(k_eig_sums, dim3((unsigned)(nc + (N + 63) / 64)), dim3(256), 0, st, (double2 *)w.z.p, (const double *)w.zpart.p,
+                           (const double2 *)w.beta.p, N, rows, (const double2 *)w.part.p, nparts, nc,
                            (double2 *)(sums + 8));
         SV_HIP(hipGetLastError());
         return eig_finish(s, E, w, N, nc, res, x_out, dev, x_dev);

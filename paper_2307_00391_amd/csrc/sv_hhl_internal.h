@@ -30,7 +30,7 @@ struct PipeSolve {
     const double2 *beta;    // V^H b^ (FP64)
     const uint64_t *F;      // turn table [N][n_c]
     double *part;           // k_pipe_b partial sums (2 per block)
-    double2 *zpart;         // k_pipe_c partial column sums [2^g2][N]
+    double *zpart;          // k_pipe_b partial column sums [2^g1][N], over beta
 };
 
 // the last step of a batched solve: FP64 sums of P(a=1) and the norm, the
@@ -39,10 +39,10 @@ struct PipeSolve {
 struct FinishJob {
     const double *part;     // k_pipe_b partials, 2 per block (or queue item)
     uint64_t nparts;
-    const double2 *zpart;   // [rows][N]
+    const double *zpart;    // [rows][N]
     int rows;
     uint64_t N;
-    double scale;           // 2^(-(n_c + g1)/2)
+    const double2 *beta;    // z_j = beta_j times its column sum
     const double2 *cexact;  // normalised eigen-coefficients of A^{-1} b
     double *out;            // p_post, p_anc, norm_total, fidelity
 };
@@ -64,14 +64,10 @@ __device__ __forceinline__ void batch_finish_body(const FinishJob &J) {
         nt += J.part[2 * i + 1];
     }
     for (uint64_t j = threadIdx.x; j < J.N; j += blockDim.x) {
-        double zr = 0.0, zi = 0.0;
-        for (int r = 0; r < J.rows; ++r) {
-            const double2 v = J.zpart[(uint64_t)r * J.N + j];
-            zr += v.x;
-            zi += v.y;
-        }
-        zr *= J.scale;
-        zi *= J.scale;
+        double w = 0.0;
+        for (int r = 0; r < J.rows; ++r) w += J.zpart[(uint64_t)r * J.N + j];
+        const double2 b = J.beta[j];
+        const double zr = w * b.x, zi = w * b.y;
         pp += zr * zr + zi * zi;
         const double2 c = J.cexact[j];
         orr += c.x * zr + c.y * zi;      // conj(c) z
@@ -91,15 +87,14 @@ __device__ __forceinline__ void batch_finish_body(const FinishJob &J) {
 }
 
 // A batch as one persistent kernel over device work queues.  Every solve
-// has four phases: the k_pipe_a tiles, the k_pipe_b tiles, the k_pipe_c
-// tiles (each item a run of consecutive column blocks of one clock-group
-// value) and the finish; an item of phase p > 0 waits until every item of
+// has three phases: the k_pipe_a tiles, the k_pipe_b tiles (each item a run of
+// consecutive column blocks of one clock-group value) and the finish; an item of phase p > 0 waits until every item of
 // phase p - 1 of its solve is done (one counter per solve and phase).  The
 // solves are spread over one queue per XCC; a queue's items are numbered
 // phase-major, so a wait only ever targets items taken before.
 struct QueueClassIn {
     int n_s, n_c;
-    int cl[3];              // log2 columns per tile of the three kernels
+    int cl[2];              // log2 columns per tile of the two kernels
 };
 struct PipeQueue {
     const void *d_cls = nullptr;        // class table (launch parameters per phase)
@@ -116,12 +111,12 @@ struct PipeQueue {
     uint64_t wait_ticks = 0;            // bound of one dependency wait (wall-clock ticks)
     size_t lds = 0;
     std::vector<uint64_t> nparts;       // k_pipe_b partial pairs of every solve
-    uint64_t items_per_phase[4] = {0, 0, 0, 0};
+    uint64_t items_per_phase[3] = {0, 0, 0};
     double bytes = 0.0;                 // algorithmic HBM bytes of one run
 };
-// counters the queue needs for `nsolves` solves: three per solve, eight
+// counters the queue needs for `nsolves` solves: two per solve, eight
 // queue heads, the count of finished solves (the last)
-inline size_t pipe_queue_counters(int nsolves) { return 3 * (size_t)nsolves + 8 + 1; }
+inline size_t pipe_queue_counters(int nsolves) { return 2 * (size_t)nsolves + 8 + 1; }
 // plan and upload the queue (descriptors into `desc`); solve k uses class solve_cls[k]
 template <typename R>
 sv_status pipe_queue_build(sv_state ctx, hipStream_t st, PipeQueue &q, DevBuf &desc,
@@ -132,14 +127,14 @@ template <typename R>
 sv_status pipe_queue_launch(hipStream_t st, const PipeQueue &q, const FinishJob *d_fin);
 
 template <typename R>
-sv_status pipe_config(hipStream_t st, int n_s, int n_c, const PipeSolve *tune_on, int cl[3], int nt[3]);
+sv_status pipe_config(hipStream_t st, int n_s, int n_c, const PipeSolve *tune_on, int cl[2], int nt[2]);
 template <typename R>
-sv_status pipe_run_batch(hipStream_t st, int n_s, int n_c, const int cl[3], const int nt[3],
+sv_status pipe_run_batch(hipStream_t st, int n_s, int n_c, const int cl[2], const int nt[2],
                          const PipeSolve *dev_solves, int nsolves, uint64_t *nparts);
 int pipe_supported(int n_s, int n_c);
 uint64_t pipe_b_blocks_for(int n_s, int n_c, int cl);
 uint64_t pipe_b_blocks(int n_s, int n_c, size_t elem);
-int pipe_c_rows(int n_c);
+int pipe_rows(int n_c);
 
 
 // F[j][k] = frac(lam_j T0 / 2 pi 2^k) as 64-bit turn fractions (sv_hhl.hip)
