@@ -384,6 +384,8 @@ int sv_trace_report(char *buf, int len);
  *   eigpipe/<dtype>/<n_s>/<n_c>  fused eigen-frame kernels: (log2 columns
  *       per tile, threads per workgroup) for each of the two kernels, and a
  *       third pair that is not read;
+ *   eigbatch/<dtype>/<n_s>/<n_c>  the same two pairs for batched solves (an
+ *       eigpipe entry of the shape serves them too);
  *   cgemm/<dtype>/<M>/<N>/<K>/<trans>  the matrix-core GEMM's tile shape:
  *       0 = 64 x 64 per workgroup, 1 = 16 x 16 per wavefront, 2 = 16 x 16 with
  *       k in four parts, 3 = 32 x 32 with k in two;

@@ -7,11 +7,11 @@
 // A^{-1} b (beta_j / lambda_j, normalised) for the fidelity.
 // Per solve (instance, T0), inside the graph:
 //   turn tables (all solves, one kernel; it also clears the queue counters)
-//   -> the three pipeline kernels' tiles and the finish, in one of two forms:
+//   -> the two pipeline kernels' tiles and the finish, in one of two forms:
 //      * work queues: one persistent kernel; the solves are spread over one
 //        queue per XCC, each item a run of tiles of one phase of one solve,
 //        ordered by a done counter per solve and phase
-//      * side streams: per (n_s, n_c) class the three pipeline kernels with
+//      * side streams: per (n_s, n_c) class the two pipeline kernels with
 //        blockIdx.z = solve, the classes over four streams (parallel branches
 //        of the graph) so that small classes overlap instead of each paying
 //        its launch latency in series, then one finishing kernel
@@ -61,6 +61,10 @@ __global__ void k_turn_batch(const TurnJob *__restrict__ jobs, unsigned *__restr
         J.F[i] = sc >= 18446744073709551616.0 ? 0ull : (uint64_t)sc;
     }
 }
+
+// workgroups per solve: 64 for a few solves, but no more than about 8192 in all
+// (1024 solves at 64 each took 29 us, nearly all of it idle workgroups)
+static unsigned turn_blocks(int n_solves) { return (unsigned)std::min(64, std::max(8, 8192 / n_solves)); }
 
 // the finish of every solve, one block each (the stream path)
 __global__ __launch_bounds__(256) void k_batch_finish(const FinishJob *__restrict__ jobs) {
@@ -137,7 +141,7 @@ namespace sv {
 template <typename R>
 static sv_status enqueue_batch(sv_batch b) {
     const hipStream_t st = b->stream;
-    hipLaunchKernelGGL(k_turn_batch, dim3(64, b->n_solves), dim3(256), 0, st, b->d_turn, b->d_cnt, b->n_cnt);
+    hipLaunchKernelGGL(k_turn_batch, dim3(turn_blocks(b->n_solves), b->n_solves), dim3(256), 0, st, b->d_turn, b->d_cnt, b->n_cnt);
     SV_HIP(hipGetLastError());
     if (b->use_queue) return pipe_queue_launch<R>(st, b->queue, b->d_finish_q);
     SV_HIP(hipEventRecord(b->fork, st));
@@ -278,7 +282,9 @@ sv_status sv_batch_prepare(sv_batch *out, sv_dtype dt, void *hip_stream, const s
         for (auto &v : bt) v /= cn;
         if ((st = upload(&b->ctx, cex[i]->p, bt.data(), bt.size() * sizeof(double))) != SV_OK) return fail_del(st);
     }
-    // --- arena layout: per solve state, F, part, zpart, out
+    // --- arena layout: per solve the clock tables, F, part, zpart, out.  No call
+    // shows a batch's states, so their amplitudes are formed, rotated and
+    // projected in registers and not stored
     struct SolveLay {
         int inst, t;
         size_t psi, F, part, zpart;
@@ -299,7 +305,7 @@ sv_status sv_batch_prepare(sv_batch *out, sv_dtype dt, void *hip_stream, const s
             SolveLay L;
             L.inst = i;
             L.t = t;
-            L.psi = take(dim_of(I.n_s + I.n_c + 1) * e);
+            L.psi = take((size_t)pipe_table_rows(I.n_c) * N * e);
             L.F = take(N * I.n_c * sizeof(uint64_t));
             L.nparts_max = pipe_b_blocks(I.n_s, I.n_c, e);
             L.part = take(2 * L.nparts_max * sizeof(double));
@@ -359,7 +365,7 @@ sv_status sv_batch_prepare(sv_batch *out, sv_dtype dt, void *hip_stream, const s
     b->d_finish_q = (const FinishJob *)((const char *)b->d_finish + ((total * sizeof(FinishJob) + 255) & ~(size_t)255));
     char *dsol = (char *)b->d_finish_q + ((total * sizeof(FinishJob) + 255) & ~(size_t)255);
     if ((st = upload(&b->ctx, (void *)b->d_turn, turn.data(), total * sizeof(TurnJob))) != SV_OK) return fail_del(st);
-    hipLaunchKernelGGL(k_turn_batch, dim3(64, total), dim3(256), 0, b->stream, b->d_turn, b->d_cnt, b->n_cnt);
+    hipLaunchKernelGGL(k_turn_batch, dim3(turn_blocks(total), total), dim3(256), 0, b->stream, b->d_turn, b->d_cnt, b->n_cnt);
     {
         const hipError_t ke = hipGetLastError();
         if (ke != hipSuccess) return fail_del(hip_fail(ke, "k_turn_batch"));
@@ -385,8 +391,8 @@ sv_status sv_batch_prepare(sv_batch *out, sv_dtype dt, void *hip_stream, const s
         if ((st = upload(&b->ctx, (void *)C.d_solves, ps.data(), ps.size() * sizeof(PipeSolve))) != SV_OK)
             return fail_del(st);
         // launch configuration: cached or tuned on the first solve of the class
-        st = dt == SV_C64 ? pipe_config<float>(b->stream, n_s, n_c, &ps[0], C.cl, C.nt)
-                          : pipe_config<double>(b->stream, n_s, n_c, &ps[0], C.cl, C.nt);
+        st = dt == SV_C64 ? pipe_config_batch<float>(b->stream, n_s, n_c, &ps[0], C.cl, C.nt)
+                          : pipe_config_batch<double>(b->stream, n_s, n_c, &ps[0], C.cl, C.nt);
         if (st != SV_OK) return fail_del(st);
         const uint64_t np = pipe_b_blocks_for(n_s, n_c, C.cl[1]);
         if (np > pipe_b_blocks(n_s, n_c, e)) return fail_del(fail(SV_EDEVICE, "partials exceed their buffer"));
@@ -535,13 +541,18 @@ sv_status sv_batch_run(sv_batch b, int use_graph, double *results) {
         SV_TRY(b->dt == SV_C64 ? enqueue_batch<float>(b) : enqueue_batch<double>(b));
     }
     if (results) {
-        SV_TRY(download(&b->ctx, results, b->d_out, (size_t)b->n_solves * 4 * sizeof(double)));
+        // results, queue counters and flag lie in this order: one copy
+        const size_t nr = (size_t)b->n_solves * 4 * sizeof(double);
+        const size_t nb = b->use_queue ? (size_t)((const char *)(b->d_flag + 1) - (const char *)b->d_out) : nr;
+        std::vector<char> got(nb);
+        SV_TRY(download(&b->ctx, got.data(), b->d_out, nb));
+        memcpy(results, got.data(), nr);
         // a wait of the work queue that expired (this run or an earlier one
         // without results) leaves the flag set: the results are not trusted
         if (b->use_queue) {
             unsigned flag = 0, finished = 0;
-            SV_TRY(download(&b->ctx, &flag, b->d_flag, sizeof(unsigned)));
-            SV_TRY(download(&b->ctx, &finished, b->d_cnt + b->n_cnt - 1, sizeof(unsigned)));
+            memcpy(&flag, got.data() + nb - sizeof(unsigned), sizeof(unsigned));
+            memcpy(&finished, got.data() + ((const char *)(b->d_cnt + b->n_cnt - 1) - (const char *)b->d_out), sizeof(unsigned));
             if (flag) return fail(SV_EDEVICE, "a work-queue dependency wait expired; the results are invalid");
             if (finished != (unsigned)b->n_solves)
                 return fail(SV_EDEVICE, "the work queues finished %u of %d solves", finished, b->n_solves);

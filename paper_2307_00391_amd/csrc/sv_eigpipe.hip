@@ -260,8 +260,8 @@ __global__ __launch_bounds__(NT) void k_pipe_a(PipeArgs A, PipeSolve one, const 
 // ---------------------------------------------------------------------------
 // k_pipe_b: inverse cascade on G2 and the inversion rotation
 // ---------------------------------------------------------------------------
-// Writes the state after the rotation (the ancilla = 1 half), as
-// 2^-G2 s_y a(y).  In the half the clock's two
+// Writes the state after the rotation (the ancilla = 1 half; STORE, a single
+// solve's register), as 2^-G2 s_y a(y).  In the half the clock's two
 // groups trade places: clock value y1 + (y2 << g1) is row y2 + (y1 << g2), so
 // the rows of a tile (one G1 value) form one block of 2^g2 rows, which
 // streams faster than rows 2^g1 apart (a relabelling of the clock qubits in
@@ -285,7 +285,7 @@ __global__ __launch_bounds__(NT) void k_pipe_a(PipeArgs A, PipeSolve one, const 
 // Tile: columns [j0, j0 + C)
 // at G1 value o; a work-queue item (PERS) runs A.iters column blocks j0 + it 2^(pslog + cl).
 // The FP64 partial pair goes to slot `slot`.
-template <typename R, int RA, int RB, int NT, bool PERS>
+template <typename R, int RA, int RB, int NT, bool PERS, bool STORE>
 __device__ __forceinline__ void pipe_b_body(const PipeArgs &A, const PipeSolve &S, uint64_t j0, uint64_t o,
                                             uint64_t slot) {
     constexpr int G = RA + RB;
@@ -398,7 +398,7 @@ __device__ __forceinline__ void pipe_b_body(const PipeArgs &A, const PipeSolve &
                 lpa += s2l[k << RA] * a2;
                 lz += sr * a2;
                 lnt += a2;
-                gst_nt<R>(ps, k * ks, cmul<R>(cmake<R>(v[k].x * sr, v[k].y * sr), bc));
+                if (STORE) gst_nt<R>(ps, k * ks, cmul<R>(cmake<R>(v[k].x * sr, v[k].y * sr), bc));
             }
             const double b2 = (double)bc.x * (double)bc.x + (double)bc.y * (double)bc.y;
             pa += b2 * (double)lpa;
@@ -440,11 +440,11 @@ __device__ __forceinline__ void pipe_b_body(const PipeArgs &A, const PipeSolve &
     }
 }
 
-template <typename R, int RA, int RB, int NT>
+template <typename R, int RA, int RB, int NT, bool STORE>
 __global__ __launch_bounds__(NT) void k_pipe_b(PipeArgs A, PipeSolve one, const PipeSolve *__restrict__ many) {
     uint64_t j0, o;
     tile_coords(A, j0, o);               // o = value of the G1 bits
-    pipe_b_body<R, RA, RB, NT, false>(A, solve_of(one, many), j0, o,
+    pipe_b_body<R, RA, RB, NT, false, STORE>(A, solve_of(one, many), j0, o,
                                       (uint64_t)blockIdx.x + (uint64_t)blockIdx.y * gridDim.x);
 }
 
@@ -515,7 +515,7 @@ __device__ __forceinline__ void queue_item(int ph, const PipeArgs &A, const Pipe
     if (ph == 0)
         pipe_a_body<R, RA, RB, 256>(A, S, j0, o);
     else
-        pipe_b_body<R, RA, RB, 256, true>(A, S, j0, o, slot);
+        pipe_b_body<R, RA, RB, 256, true, false>(A, S, j0, o, slot);
 }
 
 // Every block serves one queue and takes its items from the queue's head
@@ -622,7 +622,7 @@ __global__ void k_xcc_probe(int *__restrict__ out) {
 // ---------------------------------------------------------------------------
 
 template <typename R, int RA, int RB, int NT>
-static sv_status launch_pipe(int which, hipStream_t st, const PipeSolve &one, const PipeSolve *many,
+static sv_status launch_pipe(int which, hipStream_t st, const PipeSolve &one, const PipeSolve *many, bool store,
                              const PipeArgs &A, dim3 grid, size_t lds) {
     // tiles above 64 KiB need a larger dynamic LDS limit; the request plus the
     // kernels' static LDS must stay within the 160 KiB of a workgroup
@@ -631,10 +631,12 @@ static sv_status launch_pipe(int which, hipStream_t st, const PipeSolve &one, co
     if (!attr_done) {
         hipError_t e0 = hipFuncSetAttribute((const void *)k_pipe_a<R, RA, RB, NT>,
                                             hipFuncAttributeMaxDynamicSharedMemorySize, kLim);
-        hipError_t e1 = hipFuncSetAttribute((const void *)k_pipe_b<R, RA, RB, NT>,
+        hipError_t e1 = hipFuncSetAttribute((const void *)k_pipe_b<R, RA, RB, NT, true>,
+                                            hipFuncAttributeMaxDynamicSharedMemorySize, kLim);
+        hipError_t e2 = hipFuncSetAttribute((const void *)k_pipe_b<R, RA, RB, NT, false>,
                                             hipFuncAttributeMaxDynamicSharedMemorySize, kLim);
         (void)hipGetLastError();
-        if (e0 != hipSuccess || e1 != hipSuccess)
+        if (e0 != hipSuccess || e1 != hipSuccess || e2 != hipSuccess)
             return fail(SV_EDEVICE, "cannot raise the LDS limit of the pipeline kernels");
         attr_done = true;
     }
@@ -646,35 +648,38 @@ static sv_status launch_pipe(int which, hipStream_t st, const PipeSolve &one, co
     if (which == 0) {
         TraceScope ts(st, "pipe_a_init_iqft", table, 0.0);
         hipLaunchKernelGGL((k_pipe_a<R, RA, RB, NT>), grid, dim3(NT), lds, st, A, one, many);
-    } else {
+    } else if (store) {
         TraceScope ts(st, "pipe_b_iqft_ry", half + table, 0.0);
-        hipLaunchKernelGGL((k_pipe_b<R, RA, RB, NT>), grid, dim3(NT), lds, st, A, one, many);
+        hipLaunchKernelGGL((k_pipe_b<R, RA, RB, NT, true>), grid, dim3(NT), lds, st, A, one, many);
+    } else {
+        TraceScope ts(st, "pipe_b_batch", table, 0.0);
+        hipLaunchKernelGGL((k_pipe_b<R, RA, RB, NT, false>), grid, dim3(NT), lds, st, A, one, many);
     }
     SV_HIP(hipGetLastError());
     return SV_OK;
 }
 
 template <typename R, int RA, int RB>
-static sv_status launch_nt(int which, hipStream_t st, const PipeSolve &one, const PipeSolve *many,
+static sv_status launch_nt(int which, hipStream_t st, const PipeSolve &one, const PipeSolve *many, bool store,
                            const PipeArgs &A, int nt, dim3 grid, size_t lds) {
-    if (nt == 512) return launch_pipe<R, RA, RB, 512>(which, st, one, many, A, grid, lds);
-    return launch_pipe<R, RA, RB, 256>(which, st, one, many, A, grid, lds);
+    if (nt == 512) return launch_pipe<R, RA, RB, 512>(which, st, one, many, store, A, grid, lds);
+    return launch_pipe<R, RA, RB, 256>(which, st, one, many, store, A, grid, lds);
 }
 
 template <typename R>
-static sv_status dispatch_g(int which, hipStream_t st, const PipeSolve &one, const PipeSolve *many,
+static sv_status dispatch_g(int which, hipStream_t st, const PipeSolve &one, const PipeSolve *many, bool store,
                             const PipeArgs &A, int g, int nt, dim3 grid, size_t lds) {
     switch (g) {
-    case 1: return launch_nt<R, 1, 0>(which, st, one, many, A, nt, grid, lds);
-    case 2: return launch_nt<R, 1, 1>(which, st, one, many, A, nt, grid, lds);
-    case 3: return launch_nt<R, 2, 1>(which, st, one, many, A, nt, grid, lds);
-    case 4: return launch_nt<R, 2, 2>(which, st, one, many, A, nt, grid, lds);
-    case 5: return launch_nt<R, 3, 2>(which, st, one, many, A, nt, grid, lds);
-    case 6: return launch_nt<R, 3, 3>(which, st, one, many, A, nt, grid, lds);
-    case 7: return launch_nt<R, 4, 3>(which, st, one, many, A, nt, grid, lds);
-    case 8: return launch_nt<R, 4, 4>(which, st, one, many, A, nt, grid, lds);
-    case 9: return launch_nt<R, 5, 4>(which, st, one, many, A, nt, grid, lds);
-    case 10: return launch_nt<R, 5, 5>(which, st, one, many, A, nt, grid, lds);
+    case 1: return launch_nt<R, 1, 0>(which, st, one, many, store, A, nt, grid, lds);
+    case 2: return launch_nt<R, 1, 1>(which, st, one, many, store, A, nt, grid, lds);
+    case 3: return launch_nt<R, 2, 1>(which, st, one, many, store, A, nt, grid, lds);
+    case 4: return launch_nt<R, 2, 2>(which, st, one, many, store, A, nt, grid, lds);
+    case 5: return launch_nt<R, 3, 2>(which, st, one, many, store, A, nt, grid, lds);
+    case 6: return launch_nt<R, 3, 3>(which, st, one, many, store, A, nt, grid, lds);
+    case 7: return launch_nt<R, 4, 3>(which, st, one, many, store, A, nt, grid, lds);
+    case 8: return launch_nt<R, 4, 4>(which, st, one, many, store, A, nt, grid, lds);
+    case 9: return launch_nt<R, 5, 4>(which, st, one, many, store, A, nt, grid, lds);
+    case 10: return launch_nt<R, 5, 5>(which, st, one, many, store, A, nt, grid, lds);
     }
     return fail(SV_EUNSUPPORTED, "clock group of %d bits", g);
 }
@@ -740,9 +745,10 @@ static void make_plan(PipePlan &P, int n_s, int n_c, size_t e, const int cl[2], 
 }
 
 template <typename R>
-static sv_status run_one(hipStream_t st, const PipePlan &P, int w, const PipeSolve &one, const PipeSolve *many) {
+static sv_status run_one(hipStream_t st, const PipePlan &P, int w, const PipeSolve &one, const PipeSolve *many,
+                         bool store) {
     const int g = w == 1 ? P.A[w].g2 : P.A[w].g1;
-    return dispatch_g<R>(w, st, one, many, P.A[w], g, P.nt[w], P.grid[w], P.lds[w]);
+    return dispatch_g<R>(w, st, one, many, store, P.A[w], g, P.nt[w], P.grid[w], P.lds[w]);
 }
 
 // The autotuner: per (dtype, n_s, n_c) time every feasible (columns per
@@ -750,7 +756,7 @@ static sv_status run_one(hipStream_t st, const PipePlan &P, int w, const PipeSol
 // operands of one solve (each kernel is idempotent given its input half)
 // and keep the fastest; results live in the process-wide tuning cache.
 template <typename R>
-static sv_status tune_pipe(hipStream_t st, int n_s, int n_c, const PipeSolve &one, int cl_out[2],
+static sv_status tune_pipe(hipStream_t st, int n_s, int n_c, const PipeSolve &one, bool store, int cl_out[2],
                            int nt_out[2]) {
     const size_t e = sizeof(cvec<R>);
     const int g1 = (n_c + 1) / 2, g2 = n_c - g1;
@@ -778,7 +784,7 @@ static sv_status tune_pipe(hipStream_t st, int n_s, int n_c, const PipeSolve &on
                 PipePlan P;
                 make_plan(P, n_s, n_c, e, cls, nts, 1);
                 float ms = 0.f;
-                SV_TRY(time_stream(st, 2, &ms, [&]() { return run_one<R>(st, P, w, one, nullptr); }));
+                SV_TRY(time_stream(st, 2, &ms, [&]() { return run_one<R>(st, P, w, one, nullptr, store); }));
                 if (ms < tbest[i]) tbest[i] = ms;
             }
         int bcl = cl_out[w], bnt = nt_out[w];
@@ -794,23 +800,25 @@ static sv_status tune_pipe(hipStream_t st, int n_s, int n_c, const PipeSolve &on
         // the next kernel reads what this one writes: leave its output in place
         PipePlan P;
         make_plan(P, n_s, n_c, e, cl_out, nt_out, 1);
-        SV_TRY(run_one<R>(st, P, w, one, nullptr));
+        SV_TRY(run_one<R>(st, P, w, one, nullptr, store));
     }
     return SV_OK;
 }
 
-// launch parameters for a shape: cached, tuned on `one` if allowed, else defaults
+// launch parameters for a shape: cached, tuned on `one` if allowed, else defaults.
+// A batch's k_pipe_b does not store and is tuned by itself (eigbatch); an entry
+// of the storing kernels serves it too
 template <typename R>
-static sv_status pipe_config_impl(hipStream_t st, int n_s, int n_c, const PipeSolve *tune_on, int cl[2],
+static sv_status pipe_config_impl(hipStream_t st, int n_s, int n_c, const PipeSolve *tune_on, bool store, int cl[2],
                                   int nt[2]) {
     const size_t e = sizeof(cvec<R>);
     const int g1 = (n_c + 1) / 2, g2 = n_c - g1;
-    const std::string key = std::string("eigpipe/") + (e == 8 ? "c64/" : "c128/") + std::to_string(n_s) + "/" +
-                            std::to_string(n_c);
+    const std::string shape = std::string(e == 8 ? "c64/" : "c128/") + std::to_string(n_s) + "/" + std::to_string(n_c);
     std::vector<int> cached;
-    // an entry's third pair belonged to a third kernel; it is kept as zeros so
-    // that saved entries of either kind serve
-    if (tune_lookup(key, cached) && cached.size() == 6) {
+    // an eigpipe entry's third pair belonged to a third kernel; it is kept as
+    // zeros so that saved entries of either kind serve
+    if ((!store && tune_lookup("eigbatch/" + shape, cached) && cached.size() == 4) ||
+        (tune_lookup("eigpipe/" + shape, cached) && cached.size() == 6)) {
         for (int w = 0; w < 2; ++w) {
             cl[w] = cached[2 * w];
             nt[w] = cached[2 * w + 1];
@@ -818,8 +826,9 @@ static sv_status pipe_config_impl(hipStream_t st, int n_s, int n_c, const PipeSo
         return SV_OK;
     }
     if (tune_on && autotune_enabled()) {
-        SV_TRY(tune_pipe<R>(st, n_s, n_c, *tune_on, cl, nt));
-        tune_store(key, {cl[0], nt[0], cl[1], nt[1], 0, 0});
+        SV_TRY(tune_pipe<R>(st, n_s, n_c, *tune_on, store, cl, nt));
+        if (store) tune_store("eigpipe/" + shape, {cl[0], nt[0], cl[1], nt[1], 0, 0});
+        else tune_store("eigbatch/" + shape, {cl[0], nt[0], cl[1], nt[1]});
         return SV_OK;
     }
     for (int w = 0; w < 2; ++w) {
@@ -830,8 +839,8 @@ static sv_status pipe_config_impl(hipStream_t st, int n_s, int n_c, const PipeSo
 }
 
 template <typename R>
-sv_status pipe_config(hipStream_t st, int n_s, int n_c, const PipeSolve *tune_on, int cl[2], int nt[2]) {
-    return pipe_config_impl<R>(st, n_s, n_c, tune_on, cl, nt);
+sv_status pipe_config_batch(hipStream_t st, int n_s, int n_c, const PipeSolve *tune_on, int cl[2], int nt[2]) {
+    return pipe_config_impl<R>(st, n_s, n_c, tune_on, false, cl, nt);
 }
 
 template <typename R>
@@ -840,7 +849,7 @@ sv_status pipe_run(sv_state s, int n_s, int n_c, bool sgn, uint64_t gcut, const 
     const size_t e = sizeof(cvec<R>);
     PipeSolve one{s->data, beta, F, part, zpart};
     int cl[2], nt[2];
-    SV_TRY(pipe_config_impl<R>(s->stream, n_s, n_c, &one, cl, nt));
+    SV_TRY(pipe_config_impl<R>(s->stream, n_s, n_c, &one, true, cl, nt));
     PipePlan P;
     make_plan(P, n_s, n_c, e, cl, nt, 1);
     for (int w = 0; w < 2; ++w) {
@@ -848,7 +857,7 @@ sv_status pipe_run(sv_state s, int n_s, int n_c, bool sgn, uint64_t gcut, const 
         P.A[w].gcut = gcut;
     }
     *nparts = (uint64_t)P.grid[1].x * P.grid[1].y;
-    for (int w = 0; w < 2; ++w) SV_TRY(run_one<R>(s->stream, P, w, one, nullptr));
+    for (int w = 0; w < 2; ++w) SV_TRY(run_one<R>(s->stream, P, w, one, nullptr, true));
     return SV_OK;
 }
 template sv_status pipe_run<float>(sv_state, int, int, bool, uint64_t, const double2 *, const uint64_t *, double *,
@@ -856,7 +865,8 @@ template sv_status pipe_run<float>(sv_state, int, int, bool, uint64_t, const dou
 template sv_status pipe_run<double>(sv_state, int, int, bool, uint64_t, const double2 *, const uint64_t *,
                                     double *, double *, uint64_t *);
 
-// a class of solves sharing (n_s, n_c): the two kernels once each, blockIdx.z = solve
+// a class of solves sharing (n_s, n_c): the two kernels once each, blockIdx.z =
+// solve; the states are not stored (psi holds the clock rows of k_pipe_a alone)
 template <typename R>
 sv_status pipe_run_batch(hipStream_t st, int n_s, int n_c, const int cl[2], const int nt[2],
                          const PipeSolve *dev_solves, int nsolves, uint64_t *nparts) {
@@ -866,15 +876,15 @@ sv_status pipe_run_batch(hipStream_t st, int n_s, int n_c, const int cl[2], cons
     make_plan(P, n_s, n_c, e, cl, nt, nsolves);
     *nparts = (uint64_t)P.grid[1].x * P.grid[1].y;
     PipeSolve none{};
-    for (int w = 0; w < 2; ++w) SV_TRY(run_one<R>(st, P, w, none, dev_solves));
+    for (int w = 0; w < 2; ++w) SV_TRY(run_one<R>(st, P, w, none, dev_solves, false));
     return SV_OK;
 }
 template sv_status pipe_run_batch<float>(hipStream_t, int, int, const int *, const int *, const PipeSolve *, int,
                                          uint64_t *);
 template sv_status pipe_run_batch<double>(hipStream_t, int, int, const int *, const int *, const PipeSolve *, int,
                                           uint64_t *);
-template sv_status pipe_config<float>(hipStream_t, int, int, const PipeSolve *, int *, int *);
-template sv_status pipe_config<double>(hipStream_t, int, int, const PipeSolve *, int *, int *);
+template sv_status pipe_config_batch<float>(hipStream_t, int, int, const PipeSolve *, int *, int *);
+template sv_status pipe_config_batch<double>(hipStream_t, int, int, const PipeSolve *, int *, int *);
 
 // ---------------------------------------------------------------------------
 // the work queues' plan: items of about 2^15 amplitudes (runs of consecutive
@@ -946,8 +956,8 @@ sv_status pipe_queue_build(sv_state ctx, hipStream_t st, PipeQueue &q, DevBuf &d
             return fail(SV_EDEVICE, "queue partials exceed their buffer");
         const double half = (double)c.A[0].N * (double)(1ull << c.A[0].n_c) * e;
         const double table = (double)c.A[0].N * (double)(1ull << g1) * e;
-        cost[k] = half + 2.0 * table;
-        bytes += cost[k];
+        cost[k] = half + 2.0 * table;      // as if stored: the balance of the queues
+        bytes += 2.0 * table;
     }
     // resident blocks, and the XCC each of them lands on
     // the queue kernel carries bodies for clock groups of up to 8 bits; a
@@ -1096,5 +1106,6 @@ uint64_t pipe_b_blocks(int n_s, int n_c, size_t elem) {
     return pipe_b_blocks_for(n_s, n_c, n_s < 3 ? n_s : 3);
 }
 int pipe_rows(int n_c) { return 1 << ((n_c + 1) / 2); }
+int pipe_table_rows(int n_c) { return pipe_rows(n_c) + n_c - (n_c + 1) / 2; }
 
 }  // namespace sv

@@ -26,7 +26,7 @@ struct DevBuf {
 // per-solve operands of the fused eigen-frame kernels (one solve: passed by
 // value; a batch: a device array indexed by blockIdx.z)
 struct PipeSolve {
-    void *psi;              // the state
+    void *psi;              // the state; of a batched solve, its first pipe_table_rows clock rows
     const double2 *beta;    // V^H b^ (FP64)
     const uint64_t *F;      // turn table [N][n_c]
     double *part;           // k_pipe_b partial sums (2 per block)
@@ -127,7 +127,7 @@ template <typename R>
 sv_status pipe_queue_launch(hipStream_t st, const PipeQueue &q, const FinishJob *d_fin);
 
 template <typename R>
-sv_status pipe_config(hipStream_t st, int n_s, int n_c, const PipeSolve *tune_on, int cl[2], int nt[2]);
+sv_status pipe_config_batch(hipStream_t st, int n_s, int n_c, const PipeSolve *tune_on, int cl[2], int nt[2]);
 template <typename R>
 sv_status pipe_run_batch(hipStream_t st, int n_s, int n_c, const int cl[2], const int nt[2],
                          const PipeSolve *dev_solves, int nsolves, uint64_t *nparts);
@@ -135,6 +135,7 @@ int pipe_supported(int n_s, int n_c);
 uint64_t pipe_b_blocks_for(int n_s, int n_c, int cl);
 uint64_t pipe_b_blocks(int n_s, int n_c, size_t elem);
 int pipe_rows(int n_c);
+int pipe_table_rows(int n_c);     // clock rows k_pipe_a writes: the G1 table and the G2 phases
 
 
 // F[j][k] = frac(lam_j T0 / 2 pi 2^k) as 64-bit turn fractions (sv_hhl.hip)
