@@ -384,8 +384,6 @@ int sv_trace_report(char *buf, int len);
  *   eigpipe/<dtype>/<n_s>/<n_c>  fused eigen-frame kernels: (log2 columns
  *       per tile, threads per workgroup) for each of the two kernels, and a
  *       third pair that is not read;
- *   eigbatch/<dtype>/<n_s>/<n_c>  the same two pairs for batched solves (an
- *       eigpipe entry of the shape serves them too);
  *   cgemm/<dtype>/<M>/<N>/<K>/<trans>  the matrix-core GEMM's tile shape:
  *       0 = 64 x 64 per workgroup, 1 = 16 x 16 per wavefront, 2 = 16 x 16 with
  *       k in four parts, 3 = 32 x 32 with k in two;
@@ -595,8 +593,8 @@ sv_status sv_qlsa2_fourier(sv_state s, const double *A, const double *b, const s
  * as a hipGraph that is replayed.  Two launch forms (the Quantum Flow
  * Simulator section's many parallel runs): one persistent kernel that takes
  * every solve's tiles from per-XCC device work queues, with a dependency
- * counter per solve and phase; or one launch per kernel and shape class on
- * side streams.
+ * counter per solve and phase; or one launch over every eigen-column of
+ * every solve.
  * --------------------------------------------------------------------- */
 typedef struct {
     int n_s, n_c;          /* 1 <= n_s <= 13, 2 <= n_c <= 20, n_s + n_c + 1 <= 32 */
@@ -610,26 +608,26 @@ typedef struct sv_batch_s *sv_batch;
 
 /* Classical preprocessing for every instance (FP64 eigen-decomposition,
  * beta = V^H b^, the eigen-coefficients of the exact solution A^{-1} b),
- * device buffers for every (instance, T0) state, launch configurations per
- * shape class (autotuned on first use), and the captured graph.  All inputs
+ * the device buffers of every (instance, T0) solve, and the captured graph.
+ * No call shows a batch's states: their amplitudes are formed, rotated and
+ * projected in registers and not stored.  All inputs
  * are copied; the caller's arrays may be freed on return.  hip_stream NULL:
  * the batch creates and owns a stream.  The launch form is the faster of
  * the two in graph replays (both forms captured, replayed alternately after
  * an untimed replay each, best of three rounds of two), remembered in
  * the tuning cache under key "batchform/<c64|c128>/<n_s>.<n_c>x<solves>/..."
  * (one entry per shape class, in increasing (n_s, n_c)); with autotuning
- * off (SV_AUTOTUNE=0) and no cached choice, the side streams.  The
- * environment variable SV_BATCH_QUEUE = 1 (the work queues) or 0 (the side
- * streams) overrides both.  The queue
+ * off (SV_AUTOTUNE=0) and no cached choice, the columns.  The
+ * environment variable SV_BATCH_QUEUE = 1 (the work queues) or 0 (the
+ * columns) overrides both.  The column form takes every eigen-column of every
+ * solve in one launch, one per lane, and a finishing launch.  The queue
  * kernel serves one queue per XCC with that XCC's blocks, so the producers
  * and consumers of a solve share one L2; a dependency wait is bounded (a
  * quarter second), and an expired wait or an undrained queue makes
  * sv_batch_run fail with SV_EDEVICE instead of hanging.  SV_QUEUE_LOCAL=0
  * forces a single queue for all blocks with device-scope synchronisation
- * (the fallback for an XCC layout the probe does not recognise).  In the stream form
- * the shape classes run on four side streams of default priority that the
- * batch owns, forked from and joined back into its stream (parallel branches
- * of the graph).  Either way the batch's work stays ordered on its stream.
+ * (the fallback for an XCC layout the probe does not recognise).  Either way
+ * the batch's work stays ordered on its stream.
  * Errors: SV_EINVAL, SV_EUNSUPPORTED, SV_ENOTHERMITIAN, SV_ENOTPOSDEF,
  * SV_EZERONORM, SV_ENOMEM, SV_EDEVICE. */
 sv_status sv_batch_prepare(sv_batch *out, sv_dtype dt, void *hip_stream, const sv_batch_instance *inst,
@@ -642,7 +640,7 @@ sv_status sv_batch_prepare(sv_batch *out, sv_dtype dt, void *hip_stream, const s
  * all accumulated in FP64.  Synchronises the batch's stream. */
 sv_status sv_batch_run(sv_batch b, int use_graph, double *results);
 int sv_batch_num_solves(sv_batch b);
-/* The batch's launch form: 1 the work-queue kernel, 0 the side streams, -1
+/* The batch's launch form: 1 the work-queue kernel, 0 the columns, -1
  * for a NULL batch.  ms_streams / ms_queue (may be NULL): the graph
  * replay times of the two forms measured at prepare (0 when not timed: pinned,
  * cached, or tuning off). */

@@ -14,7 +14,7 @@ CSRC = os.path.join(PKG, "csrc")
 OUT = os.path.join(PKG, "libsv.so")
 BUILD_DIR = os.path.join(PKG, "_build")
 
-SOURCES = ["sv_core.hip", "sv_fused.hip", "sv_blocks.hip", "sv_qft.hip", "sv_gemm.hip", "sv_hhl.hip", "sv_eigpipe.hip",
+SOURCES = ["sv_core.hip", "sv_fused.hip", "sv_blocks.hip", "sv_qft.hip", "sv_gemm.hip", "sv_hhl.hip", "sv_eigpipe.hip", "sv_columns.hip",
            "sv_batch.hip", "sv_mlp.hip", "sv_spectrum.hip", "sv_qsp.hip", "sv_qpp.hip", "sv_qlsa2.hip", "sv_qadc.hip",
            "sv_plan.cpp", "sv_tune.cpp", "sv_trace.cpp"]
 

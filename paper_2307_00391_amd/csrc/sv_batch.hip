@@ -6,17 +6,15 @@
 // beta = V^H b^, and the eigen-basis coefficients of the exact solution
 // A^{-1} b (beta_j / lambda_j, normalised) for the fidelity.
 // Per solve (instance, T0), inside the graph:
-//   turn tables (all solves, one kernel; it also clears the queue counters)
-//   -> the two pipeline kernels' tiles and the finish, in one of two forms:
-//      * work queues: one persistent kernel; the solves are spread over one
-//        queue per XCC, each item a run of tiles of one phase of one solve,
-//        ordered by a done counter per solve and phase
-//      * side streams: per (n_s, n_c) class the two pipeline kernels with
-//        blockIdx.z = solve, the classes over four streams (parallel branches
-//        of the graph) so that small classes overlap instead of each paying
-//        its launch latency in series, then one finishing kernel
-//      prepare times both and keeps the faster (or the one SV_BATCH_QUEUE
-//      names)
+//   one of two forms (prepare times both and keeps the faster, or the one
+//   SV_BATCH_QUEUE names):
+//   * columns: every eigen-column of every solve in one launch, a column per
+//     lane (sv_columns.hip), then one finishing kernel
+//   * work queues: turn tables (one kernel; it also clears the queue counters),
+//     then the two pipeline kernels' tiles and the finish in one persistent
+//     kernel; the solves are spread over one queue per XCC, each item a run of
+//     tiles of one phase of one solve, ordered by a done counter per solve and
+//     phase
 //   the finish: FP64 sums of P(a=1) and the norm, the post-selected
 //   eigen-coefficients z_j (column sums of the clock projection),
 //   p_post = |z|^2 and F = |<x_C|x_Q>| = |sum conj(c_j) z_j| / |z|, all in
@@ -84,50 +82,31 @@ struct sv_batch_s {
     DevBuf *arena = nullptr;              // states, tables, partials
     DevBuf *desc = nullptr;               // descriptor arrays
     const TurnJob *d_turn = nullptr;
-    const FinishJob *d_finish = nullptr;     // the finish jobs of the stream form
+    const FinishJob *d_finish = nullptr;     // the finish jobs of the column form
     const FinishJob *d_finish_q = nullptr;   // the same for the work-queue form (its own partial counts)
     double *d_out = nullptr;
-    struct Class {
-        int n_s, n_c, cl[2], nt[2];
-        const PipeSolve *d_solves;
-        int count;
-        uint64_t nparts;      // k_pipe_b partial pairs per solve, as laid out for the finish
-    };
-    std::vector<Class> classes;
     // the launch form: every solve in one persistent kernel over per-XCC
-    // work queues, or the classes' kernels on side streams; chosen by timing
-    // both at prepare unless SV_BATCH_QUEUE is 1 or 0
+    // work queues, or every column in one launch; chosen by timing both at
+    // prepare unless SV_BATCH_QUEUE is 1 or 0
     bool use_queue = true;
     bool have_queue = false;
-    float form_ms[2] = {0.f, 0.f};           // timed graph replays: streams, queue (0: not timed)
+    float form_ms[2] = {0.f, 0.f};           // timed graph replays: columns, queue (0: not timed)
     PipeQueue queue;
     DevBuf qdesc;
+    ColPlan cols;
+    DevBuf cdesc;
     unsigned *d_cnt = nullptr;            // queue counters (cleared by the turn-table kernel)
     uint64_t n_cnt = 0;
     unsigned *d_flag = nullptr;           // set if a queue wait expired
-    // the classes are independent: they run on kSide streams forked after the
-    // turn tables and joined before the finish (in the graph: parallel branches)
-    static constexpr int kSide = 4;
-    hipStream_t side[kSide] = {};
-    hipEvent_t fork = nullptr, join[kSide] = {};
-    std::vector<int> lane[kSide];          // class indices per side stream
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     hipStream_t own_stream = nullptr;
     ~sv_batch_s() {
-        // a replayed graph with side-stream branches kept the batch's memory
-        // from being released unless the device was idle when the graph and
-        // then the buffers went (prepare/replay/free loops lost one arena per
-        // batch otherwise)
+        // the device is idle when the graph and then the buffers go
         hipDeviceSynchronize();
         if (exec) hipGraphExecDestroy(exec);
         if (graph) hipGraphDestroy(graph);
         hipDeviceSynchronize();
-        for (int i = 0; i < kSide; ++i) {
-            if (join[i]) hipEventDestroy(join[i]);
-            if (side[i]) hipStreamDestroy(side[i]);
-        }
-        if (fork) hipEventDestroy(fork);
         if (own_stream) hipStreamDestroy(own_stream);
         for (auto *b : bufs) delete b;
         if (ctx.pinned) hipHostFree(ctx.pinned);
@@ -141,23 +120,13 @@ namespace sv {
 template <typename R>
 static sv_status enqueue_batch(sv_batch b) {
     const hipStream_t st = b->stream;
-    hipLaunchKernelGGL(k_turn_batch, dim3(turn_blocks(b->n_solves), b->n_solves), dim3(256), 0, st, b->d_turn, b->d_cnt, b->n_cnt);
-    SV_HIP(hipGetLastError());
-    if (b->use_queue) return pipe_queue_launch<R>(st, b->queue, b->d_finish_q);
-    SV_HIP(hipEventRecord(b->fork, st));
-    for (int i = 0; i < sv_batch_s::kSide; ++i) {
-        if (b->lane[i].empty()) continue;
-        SV_HIP(hipStreamWaitEvent(b->side[i], b->fork, 0));
-        for (int ci : b->lane[i]) {
-            const auto &c = b->classes[ci];
-            uint64_t np = 0;
-            SV_TRY(pipe_run_batch<R>(b->side[i], c.n_s, c.n_c, c.cl, c.nt, c.d_solves, c.count, &np));
-            if (np != c.nparts) return fail(SV_EDEVICE, "partial count %llu != %llu", (unsigned long long)np,
-                                            (unsigned long long)c.nparts);
-        }
-        SV_HIP(hipEventRecord(b->join[i], b->side[i]));
-        SV_HIP(hipStreamWaitEvent(st, b->join[i], 0));
+    if (b->use_queue) {
+        hipLaunchKernelGGL(k_turn_batch, dim3(turn_blocks(b->n_solves), b->n_solves), dim3(256), 0, st, b->d_turn,
+                           b->d_cnt, b->n_cnt);
+        SV_HIP(hipGetLastError());
+        return pipe_queue_launch<R>(st, b->queue, b->d_finish_q);
     }
+    SV_TRY(cols_launch<R>(st, b->cols));
     hipLaunchKernelGGL(k_batch_finish, dim3(b->n_solves), dim3(256), 0, st, b->d_finish);
     SV_HIP(hipGetLastError());
     return SV_OK;
@@ -282,12 +251,12 @@ sv_status sv_batch_prepare(sv_batch *out, sv_dtype dt, void *hip_stream, const s
         for (auto &v : bt) v /= cn;
         if ((st = upload(&b->ctx, cex[i]->p, bt.data(), bt.size() * sizeof(double))) != SV_OK) return fail_del(st);
     }
-    // --- arena layout: per solve the clock tables, F, part, zpart, out.  No call
-    // shows a batch's states, so their amplitudes are formed, rotated and
-    // projected in registers and not stored
+    // --- arena layout: per solve the sums of the column form; the clock tables,
+    // F and the sums of the queue form; out.  No call shows a batch's states, so
+    // their amplitudes are formed, rotated and projected in registers and not stored
     struct SolveLay {
         int inst, t;
-        size_t psi, F, part, zpart;
+        size_t cpart, czpart, psi, F, part, zpart;
         uint64_t nparts_max;
     };
     std::vector<SolveLay> lay;
@@ -298,6 +267,14 @@ sv_status sv_batch_prepare(sv_batch *out, sv_dtype dt, void *hip_stream, const s
         off += bytes;
         return o;
     };
+    std::map<int, uint64_t> ncols;
+    for (int i = 0; i < n_inst; ++i) ncols[inst[i].n_c] += dim_of(inst[i].n_s) * (uint64_t)inst[i].n_t0;
+    const std::map<int, int> splits = cols_splits(ncols);
+    int form = -1;     // -1: time both
+    {
+        const char *qe = getenv("SV_BATCH_QUEUE");
+        if (qe && *qe) form = atoi(qe) != 0 ? 1 : 0;
+    }
     for (int i = 0; i < n_inst; ++i) {
         const sv_batch_instance &I = inst[i];
         const uint64_t N = dim_of(I.n_s);
@@ -305,11 +282,15 @@ sv_status sv_batch_prepare(sv_batch *out, sv_dtype dt, void *hip_stream, const s
             SolveLay L;
             L.inst = i;
             L.t = t;
-            L.psi = take((size_t)pipe_table_rows(I.n_c) * N * e);
-            L.F = take(N * I.n_c * sizeof(uint64_t));
+            const uint64_t ns = 1ull << splits.at(I.n_c);
+            L.cpart = take(2 * ns * N * sizeof(double));
+            L.czpart = take(ns * N * sizeof(double));
             L.nparts_max = pipe_b_blocks(I.n_s, I.n_c, e);
-            L.part = take(2 * L.nparts_max * sizeof(double));
-            L.zpart = take((size_t)pipe_rows(I.n_c) * N * sizeof(double));
+            const size_t q = form == 0 ? 0 : 1;
+            L.psi = take(q * (size_t)pipe_table_rows(I.n_c) * N * e);
+            L.F = take(q * N * I.n_c * sizeof(uint64_t));
+            L.part = take(q * 2 * L.nparts_max * sizeof(double));
+            L.zpart = take(q * (size_t)pipe_rows(I.n_c) * N * sizeof(double));
             lay.push_back(L);
         }
     }
@@ -330,88 +311,63 @@ sv_status sv_batch_prepare(sv_batch *out, sv_dtype dt, void *hip_stream, const s
         const hipError_t me = hipMemsetAsync(b->d_flag, 0, sizeof(unsigned), b->stream);
         if (me != hipSuccess) return fail_del(hip_fail(me, "hipMemsetAsync"));
     }
-    int form = -1;     // -1: time both
-    {
-        const char *qe = getenv("SV_BATCH_QUEUE");
-        if (qe && *qe) form = atoi(qe) != 0 ? 1 : 0;
-    }
     // --- classes by (n_s, n_c)
     std::map<std::pair<int, int>, std::vector<int>> cls;
     for (int k = 0; k < total; ++k) cls[{inst[lay[k].inst].n_s, inst[lay[k].inst].n_c}].push_back(k);
-    // host descriptors
-    std::vector<TurnJob> turn(total);
-    std::vector<FinishJob> fin(total);
-    std::vector<PipeSolve> solves;
-    for (int k = 0; k < total; ++k) {
-        const SolveLay &L = lay[k];
-        const sv_batch_instance &I = inst[L.inst];
-        turn[k] = TurnJob{(const double *)lamd[L.inst]->p, (uint64_t *)(base + L.F), I.t0[L.t], I.n_c,
-                          dim_of(I.n_s)};
-    }
-    std::vector<std::pair<int, int>> class_keys;
-    std::vector<std::vector<int>> class_members;
-    for (auto &kv : cls) {
-        class_keys.push_back(kv.first);
-        class_members.push_back(kv.second);
-    }
-    // descriptor arena: turn jobs, finish jobs, per-class solve arrays
+    // descriptor arena: turn jobs, finish jobs of the two forms
     b->desc = new DevBuf();
     b->bufs.push_back(b->desc);
-    const size_t dbytes = total * (sizeof(TurnJob) + 2 * sizeof(FinishJob) + sizeof(PipeSolve)) + 4096;
-    if ((st = b->desc->alloc(dbytes)) != SV_OK) return fail_del(st);
+    const size_t tb = (total * sizeof(TurnJob) + 255) & ~(size_t)255, fb = (total * sizeof(FinishJob) + 255) & ~(size_t)255;
+    if ((st = b->desc->alloc(tb + 2 * fb)) != SV_OK) return fail_del(st);
     char *dbase = (char *)b->desc->p;
     b->d_turn = (const TurnJob *)dbase;
-    b->d_finish = (const FinishJob *)(dbase + ((total * sizeof(TurnJob) + 255) & ~(size_t)255));
-    b->d_finish_q = (const FinishJob *)((const char *)b->d_finish + ((total * sizeof(FinishJob) + 255) & ~(size_t)255));
-    char *dsol = (char *)b->d_finish_q + ((total * sizeof(FinishJob) + 255) & ~(size_t)255);
-    if ((st = upload(&b->ctx, (void *)b->d_turn, turn.data(), total * sizeof(TurnJob))) != SV_OK) return fail_del(st);
-    hipLaunchKernelGGL(k_turn_batch, dim3(turn_blocks(total), total), dim3(256), 0, b->stream, b->d_turn, b->d_cnt, b->n_cnt);
+    b->d_finish = (const FinishJob *)(dbase + tb);
+    b->d_finish_q = (const FinishJob *)(dbase + tb + fb);
+    // --- the column form
+    std::vector<FinishJob> fin(total);
     {
-        const hipError_t ke = hipGetLastError();
-        if (ke != hipSuccess) return fail_del(hip_fail(ke, "k_turn_batch"));
-    }
-    size_t sol_off = 0;
-    std::vector<QueueClassIn> qcls;
-    std::vector<int> qsolve_cls(total, 0);
-    std::vector<PipeSolve> qsolves(total);
-    for (size_t c = 0; c < class_keys.size(); ++c) {
-        const int n_s = class_keys[c].first, n_c = class_keys[c].second;
-        std::vector<PipeSolve> ps;
-        for (int k : class_members[c]) {
+        std::vector<ColSolve> cs(total);
+        std::vector<int> ns(total), nc(total);
+        for (int k = 0; k < total; ++k) {
             const SolveLay &L = lay[k];
-            ps.push_back(PipeSolve{base + L.psi, (const double2 *)beta[L.inst]->p, (const uint64_t *)(base + L.F),
-                                   (double *)(base + L.part), (double *)(base + L.zpart)});
-        }
-        sv_batch_s::Class C;
-        C.n_s = n_s;
-        C.n_c = n_c;
-        C.count = (int)ps.size();
-        C.d_solves = (const PipeSolve *)(dsol + sol_off);
-        sol_off += ps.size() * sizeof(PipeSolve);
-        if ((st = upload(&b->ctx, (void *)C.d_solves, ps.data(), ps.size() * sizeof(PipeSolve))) != SV_OK)
-            return fail_del(st);
-        // launch configuration: cached or tuned on the first solve of the class
-        st = dt == SV_C64 ? pipe_config_batch<float>(b->stream, n_s, n_c, &ps[0], C.cl, C.nt)
-                          : pipe_config_batch<double>(b->stream, n_s, n_c, &ps[0], C.cl, C.nt);
-        if (st != SV_OK) return fail_del(st);
-        const uint64_t np = pipe_b_blocks_for(n_s, n_c, C.cl[1]);
-        if (np > pipe_b_blocks(n_s, n_c, e)) return fail_del(fail(SV_EDEVICE, "partials exceed their buffer"));
-        C.nparts = np;
-        for (size_t q = 0; q < class_members[c].size(); ++q) {
-            const int k = class_members[c][q];
-            const SolveLay &L = lay[k];
-            fin[k] = FinishJob{(const double *)(base + L.part), np, (const double *)(base + L.zpart),
-                               pipe_rows(n_c), dim_of(n_s), (const double2 *)beta[L.inst]->p,
+            const sv_batch_instance &I = inst[L.inst];
+            const uint64_t N = dim_of(I.n_s), sp = 1ull << splits.at(I.n_c);
+            ns[k] = I.n_s;
+            nc[k] = I.n_c;
+            cs[k] = ColSolve{(const double *)lamd[L.inst]->p, (const double2 *)beta[L.inst]->p,
+                             (double *)(base + L.cpart), (double *)(base + L.czpart), I.t0[L.t], N};
+            fin[k] = FinishJob{cs[k].part, sp * N, cs[k].zpart, (int)sp, N, cs[k].beta,
                                (const double2 *)cex[L.inst]->p, b->d_out + 4 * (size_t)k};
-            qsolve_cls[k] = (int)c;
-            qsolves[k] = ps[q];
         }
-        qcls.push_back(QueueClassIn{n_s, n_c, {C.cl[0], C.cl[1]}});
-        b->classes.push_back(C);
+        st = dt == SV_C64 ? cols_build<float>(&b->ctx, b->cols, b->cdesc, ns, nc, splits, cs)
+                          : cols_build<double>(&b->ctx, b->cols, b->cdesc, ns, nc, splits, cs);
+        if (st != SV_OK) return fail_del(st);
+        if ((st = upload(&b->ctx, (void *)b->d_finish, fin.data(), total * sizeof(FinishJob))) != SV_OK)
+            return fail_del(st);
     }
-    if ((st = upload(&b->ctx, (void *)b->d_finish, fin.data(), total * sizeof(FinishJob))) != SV_OK)
-        return fail_del(st);
+    // --- the work queues
     if (form != 0) {
+        std::vector<TurnJob> turn(total);
+        std::vector<QueueClassIn> qcls;
+        std::vector<int> qsolve_cls(total, 0);
+        std::vector<PipeSolve> qsolves(total);
+        for (const auto &kv : cls) {
+            const int n_s = kv.first.first, n_c = kv.first.second;
+            QueueClassIn q{n_s, n_c, {0, 0}};
+            pipe_config_batch(n_s, n_c, e, q.cl);
+            for (int k : kv.second) {
+                const SolveLay &L = lay[k];
+                turn[k] = TurnJob{(const double *)lamd[L.inst]->p, (uint64_t *)(base + L.F), inst[L.inst].t0[L.t], n_c,
+                                  dim_of(n_s)};
+                qsolves[k] = PipeSolve{base + L.psi, (const double2 *)beta[L.inst]->p, (const uint64_t *)(base + L.F),
+                                       (double *)(base + L.part), (double *)(base + L.zpart)};
+                qsolve_cls[k] = (int)qcls.size();
+                fin[k].part = qsolves[k].part;
+                fin[k].zpart = qsolves[k].zpart;
+                fin[k].rows = pipe_rows(n_c);
+            }
+            qcls.push_back(q);
+        }
         st = dt == SV_C64 ? pipe_queue_build<float>(&b->ctx, b->stream, b->queue, b->qdesc, qcls, qsolve_cls,
                                                     qsolves, b->d_cnt, b->d_flag)
                           : pipe_queue_build<double>(&b->ctx, b->stream, b->queue, b->qdesc, qcls, qsolve_cls,
@@ -419,41 +375,13 @@ sv_status sv_batch_prepare(sv_batch *out, sv_dtype dt, void *hip_stream, const s
         if (st == SV_OK) {
             b->have_queue = true;
             for (int k = 0; k < total; ++k) fin[k].nparts = b->queue.nparts[k];
-            if ((st = upload(&b->ctx, (void *)b->d_finish_q, fin.data(), total * sizeof(FinishJob))) != SV_OK)
+            if ((st = upload(&b->ctx, (void *)b->d_finish_q, fin.data(), total * sizeof(FinishJob))) != SV_OK ||
+                (st = upload(&b->ctx, (void *)b->d_turn, turn.data(), total * sizeof(TurnJob))) != SV_OK)
                 return fail_del(st);
         } else if (form == 1 || st != SV_EUNSUPPORTED) {
             return fail_del(st);
         } else {
-            clear_error();      // a shape the queue does not carry: the stream form
-        }
-    }
-    // side streams (default priority) and the fork/join events; classes go to
-    // the least-loaded stream, largest first, weighed by amplitudes plus a
-    // fixed cost per class for its two launches
-    {
-        for (int i = 0; i < sv_batch_s::kSide; ++i) {
-            hipError_t e1 = hipStreamCreateWithFlags(&b->side[i], hipStreamNonBlocking);
-            if (e1 != hipSuccess) return fail_del(hip_fail(e1, "hipStreamCreateWithFlags"));
-            e1 = hipEventCreateWithFlags(&b->join[i], hipEventDisableTiming);
-            if (e1 != hipSuccess) return fail_del(hip_fail(e1, "hipEventCreateWithFlags"));
-        }
-        hipError_t e2 = hipEventCreateWithFlags(&b->fork, hipEventDisableTiming);
-        if (e2 != hipSuccess) return fail_del(hip_fail(e2, "hipEventCreateWithFlags"));
-        std::vector<int> order(b->classes.size());
-        std::vector<double> wgt(b->classes.size());
-        for (size_t i = 0; i < order.size(); ++i) {
-            const auto &c = b->classes[i];
-            order[i] = (int)i;
-            wgt[i] = (double)c.count * (double)dim_of(c.n_s + c.n_c) + (double)(1u << 20);
-        }
-        std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return wgt[x] > wgt[y]; });
-        double load[sv_batch_s::kSide] = {};
-        for (int ci : order) {
-            int best = 0;
-            for (int i = 1; i < sv_batch_s::kSide; ++i)
-                if (load[i] < load[best]) best = i;
-            b->lane[best].push_back(ci);
-            load[best] += wgt[ci];
+            clear_error();      // a shape the queue does not carry: the column form
         }
     }
     // record the whole sweep in a graph, in the given launch form (event
@@ -479,14 +407,15 @@ sv_status sv_batch_prepare(sv_batch *out, sv_dtype dt, void *hip_stream, const s
     // the launch form: as asked; else the cached choice for this mix of
     // shape classes; else the faster graph replay (both forms captured and
     // replayed alternately, after an untimed replay each; best of three
-    // rounds), cached; with tuning off, the side streams
+    // rounds), cached; with tuning off, the columns
     bool timed = false;
     if (form >= 0 || !b->have_queue) {
         b->use_queue = form != 0 && b->have_queue;
     } else {
         std::string key = std::string("batchform/") + (dt == SV_C64 ? "c64" : "c128");
-        for (const auto &c : b->classes)
-            key += "/" + std::to_string(c.n_s) + "." + std::to_string(c.n_c) + "x" + std::to_string(c.count);
+        for (const auto &kv : cls)
+            key += "/" + std::to_string(kv.first.first) + "." + std::to_string(kv.first.second) + "x" +
+                   std::to_string(kv.second.size());
         std::vector<int> cached;
         if (tune_lookup(key, cached) && cached.size() == 1) {
             b->use_queue = cached[0] == 1;

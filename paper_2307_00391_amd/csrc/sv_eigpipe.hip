@@ -91,19 +91,6 @@ __device__ __forceinline__ void gst_nt(cvec<R> *p, uint64_t i, cvec<R> v) {
     x.y = v.y;
     __builtin_nontemporal_store(x, &((gptr<v2_t<R>>)p)[i]);
 }
-// the solve of this block: the kernel argument, or entry blockIdx.z of a batch
-__device__ __forceinline__ PipeSolve solve_of(const PipeSolve &one, const PipeSolve *many) {
-    if (!many) return one;
-    const gptr<const PipeSolve> m = (gptr<const PipeSolve>)many + blockIdx.z;
-    PipeSolve r;
-    r.psi = m->psi;
-    r.beta = m->beta;
-    r.F = m->F;
-    r.part = m->part;
-    r.zpart = m->zpart;
-    return r;
-}
-
 template <typename R>
 __device__ __forceinline__ cvec<R> cconjmul(cvec<R> a, cvec<R> b) {   // a * conj(b)
     return cmake<R>(a.x * b.x + a.y * b.y, a.y * b.x - a.x * b.y);
@@ -251,17 +238,17 @@ __device__ __forceinline__ void pipe_a_body(const PipeArgs &A, const PipeSolve &
 }
 
 template <typename R, int RA, int RB, int NT>
-__global__ __launch_bounds__(NT) void k_pipe_a(PipeArgs A, PipeSolve one, const PipeSolve *__restrict__ many) {
+__global__ __launch_bounds__(NT) void k_pipe_a(PipeArgs A, PipeSolve one) {
     uint64_t j0, o;
     tile_coords(A, j0, o);
-    pipe_a_body<R, RA, RB, NT>(A, solve_of(one, many), j0, o);
+    pipe_a_body<R, RA, RB, NT>(A, one, j0, o);
 }
 
 // ---------------------------------------------------------------------------
 // k_pipe_b: inverse cascade on G2 and the inversion rotation
 // ---------------------------------------------------------------------------
-// Writes the state after the rotation (the ancilla = 1 half; STORE, a single
-// solve's register), as 2^-G2 s_y a(y).  In the half the clock's two
+// Writes the state after the rotation (the ancilla = 1 half; not for a
+// batch's work-queue items, PERS: no call shows a batch's states), as 2^-G2 s_y a(y).  In the half the clock's two
 // groups trade places: clock value y1 + (y2 << g1) is row y2 + (y1 << g2), so
 // the rows of a tile (one G1 value) form one block of 2^g2 rows, which
 // streams faster than rows 2^g1 apart (a relabelling of the clock qubits in
@@ -285,7 +272,7 @@ __global__ __launch_bounds__(NT) void k_pipe_a(PipeArgs A, PipeSolve one, const 
 // Tile: columns [j0, j0 + C)
 // at G1 value o; a work-queue item (PERS) runs A.iters column blocks j0 + it 2^(pslog + cl).
 // The FP64 partial pair goes to slot `slot`.
-template <typename R, int RA, int RB, int NT, bool PERS, bool STORE>
+template <typename R, int RA, int RB, int NT, bool PERS>
 __device__ __forceinline__ void pipe_b_body(const PipeArgs &A, const PipeSolve &S, uint64_t j0, uint64_t o,
                                             uint64_t slot) {
     constexpr int G = RA + RB;
@@ -398,7 +385,7 @@ __device__ __forceinline__ void pipe_b_body(const PipeArgs &A, const PipeSolve &
                 lpa += s2l[k << RA] * a2;
                 lz += sr * a2;
                 lnt += a2;
-                if (STORE) gst_nt<R>(ps, k * ks, cmul<R>(cmake<R>(v[k].x * sr, v[k].y * sr), bc));
+                if (!PERS) gst_nt<R>(ps, k * ks, cmul<R>(cmake<R>(v[k].x * sr, v[k].y * sr), bc));
             }
             const double b2 = (double)bc.x * (double)bc.x + (double)bc.y * (double)bc.y;
             pa += b2 * (double)lpa;
@@ -440,11 +427,11 @@ __device__ __forceinline__ void pipe_b_body(const PipeArgs &A, const PipeSolve &
     }
 }
 
-template <typename R, int RA, int RB, int NT, bool STORE>
-__global__ __launch_bounds__(NT) void k_pipe_b(PipeArgs A, PipeSolve one, const PipeSolve *__restrict__ many) {
+template <typename R, int RA, int RB, int NT>
+__global__ __launch_bounds__(NT) void k_pipe_b(PipeArgs A, PipeSolve one) {
     uint64_t j0, o;
     tile_coords(A, j0, o);               // o = value of the G1 bits
-    pipe_b_body<R, RA, RB, NT, false, STORE>(A, solve_of(one, many), j0, o,
+    pipe_b_body<R, RA, RB, NT, false>(A, one, j0, o,
                                       (uint64_t)blockIdx.x + (uint64_t)blockIdx.y * gridDim.x);
 }
 
@@ -515,7 +502,7 @@ __device__ __forceinline__ void queue_item(int ph, const PipeArgs &A, const Pipe
     if (ph == 0)
         pipe_a_body<R, RA, RB, 256>(A, S, j0, o);
     else
-        pipe_b_body<R, RA, RB, 256, true, false>(A, S, j0, o, slot);
+        pipe_b_body<R, RA, RB, 256, true>(A, S, j0, o, slot);
 }
 
 // Every block serves one queue and takes its items from the queue's head
@@ -622,7 +609,7 @@ __global__ void k_xcc_probe(int *__restrict__ out) {
 // ---------------------------------------------------------------------------
 
 template <typename R, int RA, int RB, int NT>
-static sv_status launch_pipe(int which, hipStream_t st, const PipeSolve &one, const PipeSolve *many, bool store,
+static sv_status launch_pipe(int which, hipStream_t st, const PipeSolve &one,
                              const PipeArgs &A, dim3 grid, size_t lds) {
     // tiles above 64 KiB need a larger dynamic LDS limit; the request plus the
     // kernels' static LDS must stay within the 160 KiB of a workgroup
@@ -631,55 +618,50 @@ static sv_status launch_pipe(int which, hipStream_t st, const PipeSolve &one, co
     if (!attr_done) {
         hipError_t e0 = hipFuncSetAttribute((const void *)k_pipe_a<R, RA, RB, NT>,
                                             hipFuncAttributeMaxDynamicSharedMemorySize, kLim);
-        hipError_t e1 = hipFuncSetAttribute((const void *)k_pipe_b<R, RA, RB, NT, true>,
-                                            hipFuncAttributeMaxDynamicSharedMemorySize, kLim);
-        hipError_t e2 = hipFuncSetAttribute((const void *)k_pipe_b<R, RA, RB, NT, false>,
+        hipError_t e1 = hipFuncSetAttribute((const void *)k_pipe_b<R, RA, RB, NT>,
                                             hipFuncAttributeMaxDynamicSharedMemorySize, kLim);
         (void)hipGetLastError();
-        if (e0 != hipSuccess || e1 != hipSuccess || e2 != hipSuccess)
+        if (e0 != hipSuccess || e1 != hipSuccess)
             return fail(SV_EDEVICE, "cannot raise the LDS limit of the pipeline kernels");
         attr_done = true;
     }
     if (lds > (size_t)kLim) return fail(SV_EUNSUPPORTED, "pipeline tile needs %zu bytes of LDS", lds);
     // algorithmic bytes: the ancilla half is 2^(n_s + n_c) amplitudes; the G1
     // table 2^(n_s + g1)
-    const double half = (double)A.N * (double)(1ull << A.n_c) * sizeof(cvec<R>) * grid.z;
-    const double table = (double)A.N * (double)(1ull << A.g1) * sizeof(cvec<R>) * grid.z;
+    const double half = (double)A.N * (double)(1ull << A.n_c) * sizeof(cvec<R>);
+    const double table = (double)A.N * (double)(1ull << A.g1) * sizeof(cvec<R>);
     if (which == 0) {
         TraceScope ts(st, "pipe_a_init_iqft", table, 0.0);
-        hipLaunchKernelGGL((k_pipe_a<R, RA, RB, NT>), grid, dim3(NT), lds, st, A, one, many);
-    } else if (store) {
-        TraceScope ts(st, "pipe_b_iqft_ry", half + table, 0.0);
-        hipLaunchKernelGGL((k_pipe_b<R, RA, RB, NT, true>), grid, dim3(NT), lds, st, A, one, many);
+        hipLaunchKernelGGL((k_pipe_a<R, RA, RB, NT>), grid, dim3(NT), lds, st, A, one);
     } else {
-        TraceScope ts(st, "pipe_b_batch", table, 0.0);
-        hipLaunchKernelGGL((k_pipe_b<R, RA, RB, NT, false>), grid, dim3(NT), lds, st, A, one, many);
+        TraceScope ts(st, "pipe_b_iqft_ry", half + table, 0.0);
+        hipLaunchKernelGGL((k_pipe_b<R, RA, RB, NT>), grid, dim3(NT), lds, st, A, one);
     }
     SV_HIP(hipGetLastError());
     return SV_OK;
 }
 
 template <typename R, int RA, int RB>
-static sv_status launch_nt(int which, hipStream_t st, const PipeSolve &one, const PipeSolve *many, bool store,
+static sv_status launch_nt(int which, hipStream_t st, const PipeSolve &one,
                            const PipeArgs &A, int nt, dim3 grid, size_t lds) {
-    if (nt == 512) return launch_pipe<R, RA, RB, 512>(which, st, one, many, store, A, grid, lds);
-    return launch_pipe<R, RA, RB, 256>(which, st, one, many, store, A, grid, lds);
+    if (nt == 512) return launch_pipe<R, RA, RB, 512>(which, st, one, A, grid, lds);
+    return launch_pipe<R, RA, RB, 256>(which, st, one, A, grid, lds);
 }
 
 template <typename R>
-static sv_status dispatch_g(int which, hipStream_t st, const PipeSolve &one, const PipeSolve *many, bool store,
+static sv_status dispatch_g(int which, hipStream_t st, const PipeSolve &one,
                             const PipeArgs &A, int g, int nt, dim3 grid, size_t lds) {
     switch (g) {
-    case 1: return launch_nt<R, 1, 0>(which, st, one, many, store, A, nt, grid, lds);
-    case 2: return launch_nt<R, 1, 1>(which, st, one, many, store, A, nt, grid, lds);
-    case 3: return launch_nt<R, 2, 1>(which, st, one, many, store, A, nt, grid, lds);
-    case 4: return launch_nt<R, 2, 2>(which, st, one, many, store, A, nt, grid, lds);
-    case 5: return launch_nt<R, 3, 2>(which, st, one, many, store, A, nt, grid, lds);
-    case 6: return launch_nt<R, 3, 3>(which, st, one, many, store, A, nt, grid, lds);
-    case 7: return launch_nt<R, 4, 3>(which, st, one, many, store, A, nt, grid, lds);
-    case 8: return launch_nt<R, 4, 4>(which, st, one, many, store, A, nt, grid, lds);
-    case 9: return launch_nt<R, 5, 4>(which, st, one, many, store, A, nt, grid, lds);
-    case 10: return launch_nt<R, 5, 5>(which, st, one, many, store, A, nt, grid, lds);
+    case 1: return launch_nt<R, 1, 0>(which, st, one, A, nt, grid, lds);
+    case 2: return launch_nt<R, 1, 1>(which, st, one, A, nt, grid, lds);
+    case 3: return launch_nt<R, 2, 1>(which, st, one, A, nt, grid, lds);
+    case 4: return launch_nt<R, 2, 2>(which, st, one, A, nt, grid, lds);
+    case 5: return launch_nt<R, 3, 2>(which, st, one, A, nt, grid, lds);
+    case 6: return launch_nt<R, 3, 3>(which, st, one, A, nt, grid, lds);
+    case 7: return launch_nt<R, 4, 3>(which, st, one, A, nt, grid, lds);
+    case 8: return launch_nt<R, 4, 4>(which, st, one, A, nt, grid, lds);
+    case 9: return launch_nt<R, 5, 4>(which, st, one, A, nt, grid, lds);
+    case 10: return launch_nt<R, 5, 5>(which, st, one, A, nt, grid, lds);
     }
     return fail(SV_EUNSUPPORTED, "clock group of %d bits", g);
 }
@@ -715,7 +697,7 @@ struct PipePlan {
     size_t lds[2];
 };
 
-static void make_plan(PipePlan &P, int n_s, int n_c, size_t e, const int cl[2], const int nt[2], int nsolves) {
+static void make_plan(PipePlan &P, int n_s, int n_c, size_t e, const int cl[2], const int nt[2]) {
     PipeArgs A;
     A.N = dim_of(n_s);
     A.n_s = n_s;
@@ -738,17 +720,16 @@ static void make_plan(PipePlan &P, int n_s, int n_c, size_t e, const int cl[2], 
         P.nt[w] = nt[w];
         // k_pipe_a writes the G1 table only (G2 value 0)
         const uint64_t tiles = w == 0 ? (A.N >> c) : (A.N >> c) << (n_c - g);
-        P.grid[w] = tiles <= 0x7fffffffull ? dim3((unsigned)tiles, 1, nsolves)
-                                           : dim3(1u << 30, (unsigned)(tiles >> 30), nsolves);
+        P.grid[w] = tiles <= 0x7fffffffull ? dim3((unsigned)tiles)
+                                           : dim3(1u << 30, (unsigned)(tiles >> 30));
         P.lds[w] = pipe_lds(w, c, g, e);
     }
 }
 
 template <typename R>
-static sv_status run_one(hipStream_t st, const PipePlan &P, int w, const PipeSolve &one, const PipeSolve *many,
-                         bool store) {
+static sv_status run_one(hipStream_t st, const PipePlan &P, int w, const PipeSolve &one) {
     const int g = w == 1 ? P.A[w].g2 : P.A[w].g1;
-    return dispatch_g<R>(w, st, one, many, store, P.A[w], g, P.nt[w], P.grid[w], P.lds[w]);
+    return dispatch_g<R>(w, st, one, P.A[w], g, P.nt[w], P.grid[w], P.lds[w]);
 }
 
 // The autotuner: per (dtype, n_s, n_c) time every feasible (columns per
@@ -756,7 +737,7 @@ static sv_status run_one(hipStream_t st, const PipePlan &P, int w, const PipeSol
 // operands of one solve (each kernel is idempotent given its input half)
 // and keep the fastest; results live in the process-wide tuning cache.
 template <typename R>
-static sv_status tune_pipe(hipStream_t st, int n_s, int n_c, const PipeSolve &one, bool store, int cl_out[2],
+static sv_status tune_pipe(hipStream_t st, int n_s, int n_c, const PipeSolve &one, int cl_out[2],
                            int nt_out[2]) {
     const size_t e = sizeof(cvec<R>);
     const int g1 = (n_c + 1) / 2, g2 = n_c - g1;
@@ -782,9 +763,9 @@ static sv_status tune_pipe(hipStream_t st, int n_s, int n_c, const PipeSolve &on
                 cls[w] = cand[i].first;
                 nts[w] = cand[i].second;
                 PipePlan P;
-                make_plan(P, n_s, n_c, e, cls, nts, 1);
+                make_plan(P, n_s, n_c, e, cls, nts);
                 float ms = 0.f;
-                SV_TRY(time_stream(st, 2, &ms, [&]() { return run_one<R>(st, P, w, one, nullptr, store); }));
+                SV_TRY(time_stream(st, 2, &ms, [&]() { return run_one<R>(st, P, w, one); }));
                 if (ms < tbest[i]) tbest[i] = ms;
             }
         int bcl = cl_out[w], bnt = nt_out[w];
@@ -799,36 +780,38 @@ static sv_status tune_pipe(hipStream_t st, int n_s, int n_c, const PipeSolve &on
         nt_out[w] = bnt;
         // the next kernel reads what this one writes: leave its output in place
         PipePlan P;
-        make_plan(P, n_s, n_c, e, cl_out, nt_out, 1);
-        SV_TRY(run_one<R>(st, P, w, one, nullptr, store));
+        make_plan(P, n_s, n_c, e, cl_out, nt_out);
+        SV_TRY(run_one<R>(st, P, w, one));
     }
     return SV_OK;
 }
 
-// launch parameters for a shape: cached, tuned on `one` if allowed, else defaults.
-// A batch's k_pipe_b does not store and is tuned by itself (eigbatch); an entry
-// of the storing kernels serves it too
+// a cached choice of the launch parameters (an entry's third pair belonged to a
+// third kernel; it is kept as zeros so that saved entries of either kind serve)
+static bool pipe_cached(const std::string &key, int cl[2], int nt[2]) {
+    std::vector<int> cached;
+    if (!tune_lookup(key, cached) || cached.size() != 6) return false;
+    for (int w = 0; w < 2; ++w) {
+        cl[w] = cached[2 * w];
+        nt[w] = cached[2 * w + 1];
+    }
+    return true;
+}
+
+static std::string pipe_key(int n_s, int n_c, size_t e) {
+    return std::string("eigpipe/") + (e == 8 ? "c64/" : "c128/") + std::to_string(n_s) + "/" + std::to_string(n_c);
+}
+
+// launch parameters for a shape: cached, tuned on `one` if allowed, else defaults
 template <typename R>
-static sv_status pipe_config_impl(hipStream_t st, int n_s, int n_c, const PipeSolve *tune_on, bool store, int cl[2],
-                                  int nt[2]) {
+static sv_status pipe_config(hipStream_t st, int n_s, int n_c, const PipeSolve &one, int cl[2], int nt[2]) {
     const size_t e = sizeof(cvec<R>);
     const int g1 = (n_c + 1) / 2, g2 = n_c - g1;
-    const std::string shape = std::string(e == 8 ? "c64/" : "c128/") + std::to_string(n_s) + "/" + std::to_string(n_c);
-    std::vector<int> cached;
-    // an eigpipe entry's third pair belonged to a third kernel; it is kept as
-    // zeros so that saved entries of either kind serve
-    if ((!store && tune_lookup("eigbatch/" + shape, cached) && cached.size() == 4) ||
-        (tune_lookup("eigpipe/" + shape, cached) && cached.size() == 6)) {
-        for (int w = 0; w < 2; ++w) {
-            cl[w] = cached[2 * w];
-            nt[w] = cached[2 * w + 1];
-        }
-        return SV_OK;
-    }
-    if (tune_on && autotune_enabled()) {
-        SV_TRY(tune_pipe<R>(st, n_s, n_c, *tune_on, store, cl, nt));
-        if (store) tune_store("eigpipe/" + shape, {cl[0], nt[0], cl[1], nt[1], 0, 0});
-        else tune_store("eigbatch/" + shape, {cl[0], nt[0], cl[1], nt[1]});
+    const std::string key = pipe_key(n_s, n_c, e);
+    if (pipe_cached(key, cl, nt)) return SV_OK;
+    if (autotune_enabled()) {
+        SV_TRY(tune_pipe<R>(st, n_s, n_c, one, cl, nt));
+        tune_store(key, {cl[0], nt[0], cl[1], nt[1], 0, 0});
         return SV_OK;
     }
     for (int w = 0; w < 2; ++w) {
@@ -838,9 +821,12 @@ static sv_status pipe_config_impl(hipStream_t st, int n_s, int n_c, const PipeSo
     return SV_OK;
 }
 
-template <typename R>
-sv_status pipe_config_batch(hipStream_t st, int n_s, int n_c, const PipeSolve *tune_on, int cl[2], int nt[2]) {
-    return pipe_config_impl<R>(st, n_s, n_c, tune_on, false, cl, nt);
+void pipe_config_batch(int n_s, int n_c, size_t elem, int cl[2]) {
+    const int g1 = (n_c + 1) / 2;
+    int nt[2];
+    if (pipe_cached(pipe_key(n_s, n_c, elem), cl, nt)) return;
+    cl[0] = default_cl(n_s, g1, elem);
+    cl[1] = default_cl(n_s, n_c - g1, elem);
 }
 
 template <typename R>
@@ -849,42 +835,21 @@ sv_status pipe_run(sv_state s, int n_s, int n_c, bool sgn, uint64_t gcut, const 
     const size_t e = sizeof(cvec<R>);
     PipeSolve one{s->data, beta, F, part, zpart};
     int cl[2], nt[2];
-    SV_TRY(pipe_config_impl<R>(s->stream, n_s, n_c, &one, true, cl, nt));
+    SV_TRY(pipe_config<R>(s->stream, n_s, n_c, one, cl, nt));
     PipePlan P;
-    make_plan(P, n_s, n_c, e, cl, nt, 1);
+    make_plan(P, n_s, n_c, e, cl, nt);
     for (int w = 0; w < 2; ++w) {
         P.A[w].sgn = sgn ? 1 : 0;
         P.A[w].gcut = gcut;
     }
     *nparts = (uint64_t)P.grid[1].x * P.grid[1].y;
-    for (int w = 0; w < 2; ++w) SV_TRY(run_one<R>(s->stream, P, w, one, nullptr, true));
+    for (int w = 0; w < 2; ++w) SV_TRY(run_one<R>(s->stream, P, w, one));
     return SV_OK;
 }
 template sv_status pipe_run<float>(sv_state, int, int, bool, uint64_t, const double2 *, const uint64_t *, double *,
                                    double *, uint64_t *);
 template sv_status pipe_run<double>(sv_state, int, int, bool, uint64_t, const double2 *, const uint64_t *,
                                     double *, double *, uint64_t *);
-
-// a class of solves sharing (n_s, n_c): the two kernels once each, blockIdx.z =
-// solve; the states are not stored (psi holds the clock rows of k_pipe_a alone)
-template <typename R>
-sv_status pipe_run_batch(hipStream_t st, int n_s, int n_c, const int cl[2], const int nt[2],
-                         const PipeSolve *dev_solves, int nsolves, uint64_t *nparts) {
-    const size_t e = sizeof(cvec<R>);
-    if (nsolves < 1 || nsolves > 65535) return fail(SV_EINVAL, "batch of %d solves", nsolves);
-    PipePlan P;
-    make_plan(P, n_s, n_c, e, cl, nt, nsolves);
-    *nparts = (uint64_t)P.grid[1].x * P.grid[1].y;
-    PipeSolve none{};
-    for (int w = 0; w < 2; ++w) SV_TRY(run_one<R>(st, P, w, none, dev_solves, false));
-    return SV_OK;
-}
-template sv_status pipe_run_batch<float>(hipStream_t, int, int, const int *, const int *, const PipeSolve *, int,
-                                         uint64_t *);
-template sv_status pipe_run_batch<double>(hipStream_t, int, int, const int *, const int *, const PipeSolve *, int,
-                                          uint64_t *);
-template sv_status pipe_config_batch<float>(hipStream_t, int, int, const PipeSolve *, int *, int *);
-template sv_status pipe_config_batch<double>(hipStream_t, int, int, const PipeSolve *, int *, int *);
 
 // ---------------------------------------------------------------------------
 // the work queues' plan: items of about 2^15 amplitudes (runs of consecutive
@@ -918,7 +883,7 @@ sv_status pipe_queue_build(sv_state ctx, hipStream_t st, PipeQueue &q, DevBuf &d
         const QueueClassIn &ci = cls[k];
         const int nt[2] = {256, 256};
         PipePlan P;
-        make_plan(P, ci.n_s, ci.n_c, e, ci.cl, nt, 1);
+        make_plan(P, ci.n_s, ci.n_c, e, ci.cl, nt);
         for (int w = 0; w < 2; ++w) {
             PipeArgs A = P.A[w];
             const int g = w == 1 ? A.g2 : A.g1;

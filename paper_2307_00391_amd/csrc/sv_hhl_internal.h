@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <map>
 #include <vector>
 
 #include "sv_device.h"
@@ -23,8 +24,7 @@ struct DevBuf {
     sv_status ensure(size_t need) { return need <= bytes && p ? SV_OK : alloc(need); }
 };
 
-// per-solve operands of the fused eigen-frame kernels (one solve: passed by
-// value; a batch: a device array indexed by blockIdx.z)
+// per-solve operands of the fused eigen-frame kernels
 struct PipeSolve {
     void *psi;              // the state; of a batched solve, its first pipe_table_rows clock rows
     const double2 *beta;    // V^H b^ (FP64)
@@ -126,11 +126,37 @@ sv_status pipe_queue_build(sv_state ctx, hipStream_t st, PipeQueue &q, DevBuf &d
 template <typename R>
 sv_status pipe_queue_launch(hipStream_t st, const PipeQueue &q, const FinishJob *d_fin);
 
+// batched solves, a column per lane (sv_columns.hip)
+struct ColSolve {
+    const double *lam;      // eigenvalues
+    const double2 *beta;    // V^H b^
+    double *part;           // (P(a = 1), norm) per column and split
+    double *zpart;          // [splits][N]: z_j = beta_j times the sum
+    double T0;
+    uint64_t N;
+};
+struct ColLaunch {
+    int cls0, ncls;         // clock widths of one line length
+    uint32_t blocks;
+    int rb;
+};
+struct ColPlan {
+    const void *d_cls = nullptr;
+    const ColSolve *d_solves = nullptr;
+    std::vector<ColLaunch> launches;
+    double bytes = 0.0, flops = 0.0;
+};
+// log2 of the splits of every clock width, given its number of columns
+std::map<int, int> cols_splits(const std::map<int, uint64_t> &ncols);
 template <typename R>
-sv_status pipe_config_batch(hipStream_t st, int n_s, int n_c, const PipeSolve *tune_on, int cl[2], int nt[2]);
+sv_status cols_build(sv_state ctx, ColPlan &p, DevBuf &buf, const std::vector<int> &ns, const std::vector<int> &nc,
+                     const std::map<int, int> &sp, const std::vector<ColSolve> &solves);
 template <typename R>
-sv_status pipe_run_batch(hipStream_t st, int n_s, int n_c, const int cl[2], const int nt[2],
-                         const PipeSolve *dev_solves, int nsolves, uint64_t *nparts);
+sv_status cols_launch(hipStream_t st, const ColPlan &p);
+
+// the columns per tile of a batched solve's queue items: a cached choice of
+// the shape's single solves, or the default
+void pipe_config_batch(int n_s, int n_c, size_t elem, int cl[2]);
 int pipe_supported(int n_s, int n_c);
 uint64_t pipe_b_blocks_for(int n_s, int n_c, int cl);
 uint64_t pipe_b_blocks(int n_s, int n_c, size_t elem);
