@@ -82,8 +82,8 @@ __device__ __forceinline__ void gst(cvec<R> *p, uint64_t i, cvec<R> v) {
     ((gptr<v2_t<R>>)p)[i] = x;
 }
 
-// non-temporal store for the ancilla = 1 half, which k_pipe_b writes once: far more than the L2 and MALL hold, so they are streamed (the nt bit)
-// instead of cached
+// non-temporal store for the ancilla = 1 half, which k_pipe_b writes once: far
+// more than the L2 and MALL hold, so it is streamed (the nt bit) instead of cached
 template <typename R>
 __device__ __forceinline__ void gst_nt(cvec<R> *p, uint64_t i, cvec<R> v) {
     v2_t<R> x;
@@ -248,11 +248,12 @@ __global__ __launch_bounds__(NT) void k_pipe_a(PipeArgs A, PipeSolve one) {
 // k_pipe_b: inverse cascade on G2 and the inversion rotation
 // ---------------------------------------------------------------------------
 // Writes the state after the rotation (the ancilla = 1 half; not for a
-// batch's work-queue items, PERS: no call shows a batch's states), as 2^-G2 s_y a(y).  In the half the clock's two
-// groups trade places: clock value y1 + (y2 << g1) is row y2 + (y1 << g2), so
-// the rows of a tile (one G1 value) form one block of 2^g2 rows, which
-// streams faster than rows 2^g1 apart (a relabelling of the clock qubits in
-// memory).
+// batch's work-queue items, PERS: no call shows a batch's states), as
+// 2^-G2 s_y a(y).  In the half the qubits are
+// relabelled in memory, from the bottom: the tile's columns, G2, the other
+// column bits, G1, so that a tile is one block of 2^(g2 + cl) amplitudes and
+// streams out whole.  (As 2^g2 rows of 512 B per tile, the stores of a 32-qubit
+// solve took 3.02-3.07 ms.)
 //
 // The projection.  Only the clock sum of each transformed column is needed,
 //   z = sum_y ph(y) (F v)(y),
@@ -267,7 +268,7 @@ __global__ __launch_bounds__(NT) void k_pipe_a(PipeArgs A, PipeSolve one) {
 // a real sum per column, taken while the line is in registers.  A third kernel
 // that read the half back and contracted it with K took 2.5 of the 5.8 ms of a
 // 32-qubit complex64 solve, and 90 of the 247 us of a 26-qubit complex128 one.
-// Bound by the stores: 17.2 GB in 3.02-3.07 ms, 5.6-5.7 TB/s (a plain fill: 6.9).
+// Bound by the stores: 17.2 GB in 2.70 ms, 6.4 TB/s (a plain fill: 6.9).
 //
 // Tile: columns [j0, j0 + C)
 // at G1 value o; a work-queue item (PERS) runs A.iters column blocks j0 + it 2^(pslog + cl).
@@ -323,9 +324,9 @@ __device__ __forceinline__ void pipe_b_body(const PipeArgs &A, const PipeSolve &
     }
     __syncthreads();
     const int nl = C << RA;
-    // clock value o + (l << g1), l = llo + (k << RA), is row l + (o << g2) of
-    // the half: a base for the line and a stride for k
-    const uint64_t ks = 1ull << (RA + A.n_s);
+    // clock value o + (l << g1), l = llo + (k << RA), of column j0 + c is entry
+    // (l << cl) + c of the tile's block: a base for the line and a stride for k
+    const uint64_t ks = 1ull << (RA + A.cl);
     double pa = 0.0, nt = 0.0;
     for (int it = 0; it < iters; ++it) {
         const bool more = PERS && it + 1 < iters;
@@ -341,15 +342,7 @@ __device__ __forceinline__ void pipe_b_body(const PipeArgs &A, const PipeSolve &
         // line's, those of the RB high bits branch into the line's 2^RB
         // entries (a product tree, one level per bit).
         for (int line = threadIdx.x; line < nl; line += NT) {
-            int c = line & (C - 1), llo = line >> A.cl;
-            // a wavefront takes 16 columns of four lines, so that each store
-            // instruction writes four rows of 128 B: that pattern streams
-            // faster than one row of 512 B
-            if (RA >= 2 && A.cl >= 4) {
-                const int wv = line >> 6;
-                c = (line & 15) | ((wv & ((1 << (A.cl - 4)) - 1)) << 4);
-                llo = ((line >> 4) & 3) | ((wv >> (A.cl - 4)) << 2);
-            }
+            const int c = line & (C - 1), llo = line >> A.cl;
             cvec<R> v[1 << RB];
             cvec<R> p = tT[c];
 #pragma unroll
@@ -362,12 +355,20 @@ __device__ __forceinline__ void pipe_b_body(const PipeArgs &A, const PipeSolve &
 #pragma unroll
             for (int bb = 0; bb < RB; ++bb) {
                 const cvec<R> w = om[(RA + bb) * C + c];
-#pragma unroll
-                for (int m = 0; m < (1 << bb); ++m) {
-                    const cvec<R> q = cconjmul<R>(w, TW[tw_off(RA + bb) + llo + (m << RA)]);
+                const int h = 1 << bb;
+                // a + a q and 2 a - (a + a q): six operations; the upper half
+                // of the nodes has the lower half's q, turned by a quarter
+                auto node = [&](int m, cvec<R> q) {
                     const cvec<R> a = v[m];
-                    v[m] = cmul<R>(a, cmake<R>((R)1 + q.x, q.y));
-                    v[m + (1 << bb)] = cmul<R>(a, cmake<R>((R)1 - q.x, -q.y));
+                    const R px = ffma(a.x, q.x, ffma(-a.y, q.y, a.x)), py = ffma(a.x, q.y, ffma(a.y, q.x, a.y));
+                    v[m] = cmake<R>(px, py);
+                    v[m + h] = cmake<R>(ffma((R)2, a.x, -px), ffma((R)2, a.y, -py));
+                };
+#pragma unroll
+                for (int m = 0; m < (h + 1) / 2; ++m) {
+                    const cvec<R> q = cconjmul<R>(w, TW[tw_off(RA + bb) + llo + (m << RA)]);
+                    node(m, q);
+                    if (bb > 0) node(m + h / 2, cmake<R>(q.y, -q.x));
                 }
             }
             // |P|^2 summed over the line in the amplitude precision, weighted by
@@ -377,7 +378,7 @@ __device__ __forceinline__ void pipe_b_body(const PipeArgs &A, const PipeSolve &
             R lpa = 0, lnt = 0, lz = 0;
             const R *s2l = s2t + llo, *srl = srt + llo;
             const cvec<R> bc = be[c];
-            cvec<R> *ps = psi + (A.abit + (((uint64_t)llo + (o << G)) << A.n_s) + j0 + c);
+            cvec<R> *ps = psi + (A.abit + (o << (G + A.n_s)) + (j0 << G) + ((uint64_t)llo << A.cl) + c);
 #pragma unroll
             for (int k = 0; k < (1 << RB); ++k) {
                 const R a2 = v[k].x * v[k].x + v[k].y * v[k].y;
