@@ -10,8 +10,7 @@
 //   SV_BATCH_QUEUE names):
 //   * columns: every eigen-column of every solve in one launch, a column per
 //     lane (sv_columns.hip), then one finishing kernel
-//   * work queues: turn tables (one kernel; it also clears the queue counters),
-//     then the two pipeline kernels' tiles and the finish in one persistent
+//   * work queues: the queue counters cleared, then the two pipeline kernels' tiles and the finish in one persistent
 //     kernel; the solves are spread over one queue per XCC, each item a run of
 //     tiles of one phase of one solve, ordered by a done counter per solve and
 //     phase
@@ -33,36 +32,11 @@
 
 namespace sv {
 
-struct TurnJob {
-    const double *lam;
-    uint64_t *F;
-    double T0;
-    int n_c;
-    uint64_t N;
-};
-
-// all turn tables of the batch (blockIdx.y = solve); also clears the work
-// queue's counters for the launch that follows
-__global__ void k_turn_batch(const TurnJob *__restrict__ jobs, unsigned *__restrict__ cnt, uint64_t ncnt) {
-    for (uint64_t i = ((uint64_t)blockIdx.y * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x; i < ncnt;
-         i += (uint64_t)gridDim.x * gridDim.y * blockDim.x)
+// clears the work queues' counters for the launch that follows
+__global__ void k_clear(unsigned *__restrict__ cnt, uint64_t n) {
+    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x)
         cnt[i] = 0u;
-    const TurnJob J = jobs[blockIdx.y];
-    const uint64_t total = J.N * (uint64_t)J.n_c;
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (uint64_t)gridDim.x * blockDim.x) {
-        const uint64_t j = i / J.n_c;
-        const int k = (int)(i % J.n_c);
-        const double phi = J.lam[j] * J.T0 / (2.0 * M_PI);
-        const double x = ldexp(phi, k);
-        const double f = x - floor(x);
-        const double sc = ldexp(f, 64);
-        J.F[i] = sc >= 18446744073709551616.0 ? 0ull : (uint64_t)sc;
-    }
 }
-
-// workgroups per solve: 64 for a few solves, but no more than about 8192 in all
-// (1024 solves at 64 each took 29 us, nearly all of it idle workgroups)
-static unsigned turn_blocks(int n_solves) { return (unsigned)std::min(64, std::max(8, 8192 / n_solves)); }
 
 // the finish of every solve, one block each (the stream path)
 __global__ __launch_bounds__(256) void k_batch_finish(const FinishJob *__restrict__ jobs) {
@@ -81,7 +55,6 @@ struct sv_batch_s {
     std::vector<DevBuf *> bufs;           // every device allocation of the batch
     DevBuf *arena = nullptr;              // states, tables, partials
     DevBuf *desc = nullptr;               // descriptor arrays
-    const TurnJob *d_turn = nullptr;
     const FinishJob *d_finish = nullptr;     // the finish jobs of the column form
     const FinishJob *d_finish_q = nullptr;   // the same for the work-queue form (its own partial counts)
     double *d_out = nullptr;
@@ -95,7 +68,7 @@ struct sv_batch_s {
     DevBuf qdesc;
     ColPlan cols;
     DevBuf cdesc;
-    unsigned *d_cnt = nullptr;            // queue counters (cleared by the turn-table kernel)
+    unsigned *d_cnt = nullptr;            // queue counters
     uint64_t n_cnt = 0;
     unsigned *d_flag = nullptr;           // set if a queue wait expired
     hipGraph_t graph = nullptr;
@@ -121,8 +94,7 @@ template <typename R>
 static sv_status enqueue_batch(sv_batch b) {
     const hipStream_t st = b->stream;
     if (b->use_queue) {
-        hipLaunchKernelGGL(k_turn_batch, dim3(turn_blocks(b->n_solves), b->n_solves), dim3(256), 0, st, b->d_turn,
-                           b->d_cnt, b->n_cnt);
+        hipLaunchKernelGGL(k_clear, dim3(16), dim3(256), 0, st, b->d_cnt, b->n_cnt);
         SV_HIP(hipGetLastError());
         return pipe_queue_launch<R>(st, b->queue, b->d_finish_q);
     }
@@ -251,12 +223,12 @@ sv_status sv_batch_prepare(sv_batch *out, sv_dtype dt, void *hip_stream, const s
         for (auto &v : bt) v /= cn;
         if ((st = upload(&b->ctx, cex[i]->p, bt.data(), bt.size() * sizeof(double))) != SV_OK) return fail_del(st);
     }
-    // --- arena layout: per solve the sums of the column form; the clock tables,
-    // F and the sums of the queue form; out.  No call shows a batch's states, so
+    // --- arena layout: per solve the sums of the column form; the clock tables
+    // and the sums of the queue form; out.  No call shows a batch's states, so
     // their amplitudes are formed, rotated and projected in registers and not stored
     struct SolveLay {
         int inst, t;
-        size_t cpart, czpart, psi, F, part, zpart;
+        size_t cpart, czpart, psi, part, zpart;
         uint64_t nparts_max;
     };
     std::vector<SolveLay> lay;
@@ -288,7 +260,6 @@ sv_status sv_batch_prepare(sv_batch *out, sv_dtype dt, void *hip_stream, const s
             L.nparts_max = pipe_b_blocks(I.n_s, I.n_c, e);
             const size_t q = form == 0 ? 0 : 1;
             L.psi = take(q * (size_t)pipe_table_rows(I.n_c) * N * e);
-            L.F = take(q * N * I.n_c * sizeof(uint64_t));
             L.part = take(q * 2 * L.nparts_max * sizeof(double));
             L.zpart = take(q * (size_t)pipe_rows(I.n_c) * N * sizeof(double));
             lay.push_back(L);
@@ -314,15 +285,14 @@ sv_status sv_batch_prepare(sv_batch *out, sv_dtype dt, void *hip_stream, const s
     // --- classes by (n_s, n_c)
     std::map<std::pair<int, int>, std::vector<int>> cls;
     for (int k = 0; k < total; ++k) cls[{inst[lay[k].inst].n_s, inst[lay[k].inst].n_c}].push_back(k);
-    // descriptor arena: turn jobs, finish jobs of the two forms
+    // descriptor arena: the finish jobs of the two forms
     b->desc = new DevBuf();
     b->bufs.push_back(b->desc);
-    const size_t tb = (total * sizeof(TurnJob) + 255) & ~(size_t)255, fb = (total * sizeof(FinishJob) + 255) & ~(size_t)255;
-    if ((st = b->desc->alloc(tb + 2 * fb)) != SV_OK) return fail_del(st);
+    const size_t fb = (total * sizeof(FinishJob) + 255) & ~(size_t)255;
+    if ((st = b->desc->alloc(2 * fb)) != SV_OK) return fail_del(st);
     char *dbase = (char *)b->desc->p;
-    b->d_turn = (const TurnJob *)dbase;
-    b->d_finish = (const FinishJob *)(dbase + tb);
-    b->d_finish_q = (const FinishJob *)(dbase + tb + fb);
+    b->d_finish = (const FinishJob *)dbase;
+    b->d_finish_q = (const FinishJob *)(dbase + fb);
     // --- the column form
     std::vector<FinishJob> fin(total);
     {
@@ -347,7 +317,6 @@ sv_status sv_batch_prepare(sv_batch *out, sv_dtype dt, void *hip_stream, const s
     }
     // --- the work queues
     if (form != 0) {
-        std::vector<TurnJob> turn(total);
         std::vector<QueueClassIn> qcls;
         std::vector<int> qsolve_cls(total, 0);
         std::vector<PipeSolve> qsolves(total);
@@ -357,9 +326,8 @@ sv_status sv_batch_prepare(sv_batch *out, sv_dtype dt, void *hip_stream, const s
             pipe_config_batch(n_s, n_c, e, q.cl);
             for (int k : kv.second) {
                 const SolveLay &L = lay[k];
-                turn[k] = TurnJob{(const double *)lamd[L.inst]->p, (uint64_t *)(base + L.F), inst[L.inst].t0[L.t], n_c,
-                                  dim_of(n_s)};
-                qsolves[k] = PipeSolve{base + L.psi, (const double2 *)beta[L.inst]->p, (const uint64_t *)(base + L.F),
+                qsolves[k] = PipeSolve{base + L.psi, (const double2 *)beta[L.inst]->p,
+                                       (const double *)lamd[L.inst]->p, inst[L.inst].t0[L.t],
                                        (double *)(base + L.part), (double *)(base + L.zpart)};
                 qsolve_cls[k] = (int)qcls.size();
                 fin[k].part = qsolves[k].part;
@@ -375,8 +343,7 @@ sv_status sv_batch_prepare(sv_batch *out, sv_dtype dt, void *hip_stream, const s
         if (st == SV_OK) {
             b->have_queue = true;
             for (int k = 0; k < total; ++k) fin[k].nparts = b->queue.nparts[k];
-            if ((st = upload(&b->ctx, (void *)b->d_finish_q, fin.data(), total * sizeof(FinishJob))) != SV_OK ||
-                (st = upload(&b->ctx, (void *)b->d_turn, turn.data(), total * sizeof(TurnJob))) != SV_OK)
+            if ((st = upload(&b->ctx, (void *)b->d_finish_q, fin.data(), total * sizeof(FinishJob))) != SV_OK)
                 return fail_del(st);
         } else if (form == 1 || st != SV_EUNSUPPORTED) {
             return fail_del(st);

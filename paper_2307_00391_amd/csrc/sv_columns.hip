@@ -126,15 +126,8 @@ __global__ __launch_bounds__(256) void k_batch_cols(const ColClass *__restrict__
     if (!live) cm = mp[0];
     const ColSolve S = solves[cm.x];
     const int n_c = T.n_c, L = n_c - RB;
-    // the column's phases, as k_turn_batch forms them; the waves share the bits
-    {
-        const double phi = S.lam[cm.y] * S.T0 / (2.0 * M_PI);
-        for (int b = wv; b < n_c; b += 4) {
-            const double x = ldexp(phi, n_c - 1 - b);
-            const double sc = ldexp(x - floor(x), 64);
-            w[b][lane] = turn_phase<double>(sc >= 18446744073709551616.0 ? 0ull : (uint64_t)sc);
-        }
-    }
+    // the column's phases; the waves share the bits
+    for (int b = wv; b < n_c; b += 4) w[b][lane] = turn_phase<double>(turn_fraction(S.lam[cm.y], S.T0, n_c - 1 - b));
     __syncthreads();
     double2 wt[RB];
 #pragma unroll

@@ -75,10 +75,9 @@ sv_status upload(sv_state s, void *dst, const void *src, size_t bytes) {
     return SV_OK;
 }
 
-// The copy is ordered on the stream; the host waits only for the previous
-// plan's copy out of the staging buffer, not for the passes behind it.
-sv_status upload_plan(sv_state s, void *dst, const void *src, size_t bytes) {
-    if (!bytes) return SV_OK;
+// src in the plan staging buffer, which the device can read; the host waits only
+// for the previous user of the buffer.  Record plan_ev behind the last reader.
+sv_status stage_plan(sv_state s, const void *src, size_t bytes, void **staged) {
     if (!s->plan_ev) SV_HIP(hipEventCreateWithFlags(&s->plan_ev, hipEventDisableTiming));
     else SV_HIP(hipEventSynchronize(s->plan_ev));
     if (s->plan_bytes < bytes) {
@@ -90,7 +89,16 @@ sv_status upload_plan(sv_state s, void *dst, const void *src, size_t bytes) {
         s->plan_bytes = sz;
     }
     memcpy(s->plan_pinned, src, bytes);
-    SV_HIP(hipMemcpyAsync(dst, s->plan_pinned, bytes, hipMemcpyHostToDevice, s->stream));
+    *staged = s->plan_pinned;
+    return SV_OK;
+}
+
+// The copy is ordered on the stream; the host does not wait for the work before it.
+sv_status upload_plan(sv_state s, void *dst, const void *src, size_t bytes) {
+    if (!bytes) return SV_OK;
+    void *p = nullptr;
+    SV_TRY(stage_plan(s, src, bytes, &p));
+    SV_HIP(hipMemcpyAsync(dst, p, bytes, hipMemcpyHostToDevice, s->stream));
     SV_HIP(hipEventRecord(s->plan_ev, s->stream));
     return SV_OK;
 }

@@ -162,7 +162,7 @@ template <typename R, int RA, int RB, int NT>
 __device__ __forceinline__ void pipe_a_body(const PipeArgs &A, const PipeSolve &S, uint64_t j0, uint64_t o) {
     constexpr int G = RA + RB;
     cvec<R> *__restrict__ psi = (cvec<R> *)S.psi;
-    const gptr<const uint64_t> __restrict__ F = (gptr<const uint64_t>)S.F;
+    const gptr<const double> __restrict__ lam = (gptr<const double>)S.lam;
     extern __shared__ unsigned char smem_raw[];
     const int C = 1 << A.cl;
     using D = double;
@@ -179,10 +179,10 @@ __device__ __forceinline__ void pipe_a_body(const PipeArgs &A, const PipeSolve &
         const uint64_t j = j0 + c;
         uint64_t th = 0;
         for (int b = G; b < n_c; ++b)
-            if (o >> (b - G) & 1) th += F[j * n_c + (n_c - 1 - b)];
+            if (o >> (b - G) & 1) th += turn_fraction(lam[j], S.T0, n_c - 1 - b);
         const cvec<D> ph = turn_phase<D>(th);
         cc[c] = cmake<D>(sc * ph.x, sc * ph.y);
-        for (int b = 0; b < G; ++b) om[b * C + c] = turn_phase<D>(F[j * n_c + (n_c - 1 - b)]);
+        for (int b = 0; b < G; ++b) om[b * C + c] = turn_phase<D>(turn_fraction(lam[j], S.T0, n_c - 1 - b));
     }
     // the phases of the G2 bits of every column for k_pipe_b, staged in clock
     // rows 2^g1 + r (r < g2) of the ancilla = 0 half, which the solve leaves
@@ -191,7 +191,7 @@ __device__ __forceinline__ void pipe_a_body(const PipeArgs &A, const PipeSolve &
     for (int e = threadIdx.x; e < g2 * C; e += NT) {
         const int r = e / C, c = e - r * C;
         const uint64_t j = j0 + c;
-        gst<R>(psi, ((((uint64_t)1 << G) + (uint64_t)r) << A.n_s) + j, turn_phase<R>(F[j * n_c + (n_c - 1 - (G + r))]));
+        gst<R>(psi, ((((uint64_t)1 << G) + (uint64_t)r) << A.n_s) + j, turn_phase<R>(turn_fraction(lam[j], S.T0, n_c - 1 - (G + r))));
     }
     __syncthreads();
     // phase A: line = (c, l_hi), register index = bits [0, RA)
@@ -237,8 +237,43 @@ __device__ __forceinline__ void pipe_a_body(const PipeArgs &A, const PipeSolve &
     }
 }
 
+// beta = V^H b for 64 columns of a dense V: a lane per column, the waves share
+// the rows.  b (host memory that the device can read, at most 1024 entries) is
+// staged in LDS.
+template <int NT>
+__device__ __forceinline__ void head_cols(const PipeHead &H, unsigned blk) {
+    extern __shared__ unsigned char smem_raw[];
+    double2 *bs = reinterpret_cast<double2 *>(smem_raw);
+    double2 *part = bs + H.N;
+    constexpr int NW = NT / 64;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    for (uint64_t i = threadIdx.x; i < H.N; i += NT) bs[i] = H.b[i];
+    __syncthreads();
+    const uint64_t j = (uint64_t)blk * 64 + lane;
+    double2 acc = make_double2(0.0, 0.0);
+    if (j < H.N)
+#pragma unroll 8
+        for (uint64_t i = w; i < H.N; i += NW) {
+            const double2 v = H.V[i * H.N + j], x = bs[i];
+            acc.x = fma(v.x, x.x, fma(v.y, x.y, acc.x));       // conj(v) x
+            acc.y = fma(v.x, x.y, fma(-v.y, x.x, acc.y));
+        }
+    part[w * 64 + lane] = acc;
+    __syncthreads();
+    if (w || j >= H.N) return;
+    for (int k = 1; k < NW; ++k) {
+        acc.x += part[k * 64 + lane].x;
+        acc.y += part[k * 64 + lane].y;
+    }
+    H.beta[j] = acc;
+}
+
 template <typename R, int RA, int RB, int NT>
-__global__ __launch_bounds__(NT) void k_pipe_a(PipeArgs A, PipeSolve one) {
+__global__ __launch_bounds__(NT) void k_pipe_a(PipeArgs A, PipeSolve one, PipeHead H) {
+    if (blockIdx.x >= gridDim.x - H.cols) {
+        head_cols<NT>(H, blockIdx.x - (gridDim.x - H.cols));
+        return;
+    }
     uint64_t j0, o;
     tile_coords(A, j0, o);
     pipe_a_body<R, RA, RB, NT>(A, one, j0, o);
@@ -611,7 +646,7 @@ __global__ void k_xcc_probe(int *__restrict__ out) {
 
 template <typename R, int RA, int RB, int NT>
 static sv_status launch_pipe(int which, hipStream_t st, const PipeSolve &one,
-                             const PipeArgs &A, dim3 grid, size_t lds) {
+                             const PipeHead &head, const PipeArgs &A, dim3 grid, size_t lds) {
     // tiles above 64 KiB need a larger dynamic LDS limit; the request plus the
     // kernels' static LDS must stay within the 160 KiB of a workgroup
     constexpr int kLim = 144 * 1024;
@@ -633,7 +668,10 @@ static sv_status launch_pipe(int which, hipStream_t st, const PipeSolve &one,
     const double table = (double)A.N * (double)(1ull << A.g1) * sizeof(cvec<R>);
     if (which == 0) {
         TraceScope ts(st, "pipe_a_init_iqft", table, 0.0);
-        hipLaunchKernelGGL((k_pipe_a<R, RA, RB, NT>), grid, dim3(NT), lds, st, A, one);
+        dim3 g = grid;
+        g.x += head.cols;
+        const size_t need = head.cols ? (head.N + NT) * sizeof(double2) : 0;
+        hipLaunchKernelGGL((k_pipe_a<R, RA, RB, NT>), g, dim3(NT), std::max(lds, need), st, A, one, head);
     } else {
         TraceScope ts(st, "pipe_b_iqft_ry", half + table, 0.0);
         hipLaunchKernelGGL((k_pipe_b<R, RA, RB, NT>), grid, dim3(NT), lds, st, A, one);
@@ -644,25 +682,25 @@ static sv_status launch_pipe(int which, hipStream_t st, const PipeSolve &one,
 
 template <typename R, int RA, int RB>
 static sv_status launch_nt(int which, hipStream_t st, const PipeSolve &one,
-                           const PipeArgs &A, int nt, dim3 grid, size_t lds) {
-    if (nt == 512) return launch_pipe<R, RA, RB, 512>(which, st, one, A, grid, lds);
-    return launch_pipe<R, RA, RB, 256>(which, st, one, A, grid, lds);
+                           const PipeHead &head, const PipeArgs &A, int nt, dim3 grid, size_t lds) {
+    if (nt == 512) return launch_pipe<R, RA, RB, 512>(which, st, one, head, A, grid, lds);
+    return launch_pipe<R, RA, RB, 256>(which, st, one, head, A, grid, lds);
 }
 
 template <typename R>
 static sv_status dispatch_g(int which, hipStream_t st, const PipeSolve &one,
-                            const PipeArgs &A, int g, int nt, dim3 grid, size_t lds) {
+                            const PipeHead &head, const PipeArgs &A, int g, int nt, dim3 grid, size_t lds) {
     switch (g) {
-    case 1: return launch_nt<R, 1, 0>(which, st, one, A, nt, grid, lds);
-    case 2: return launch_nt<R, 1, 1>(which, st, one, A, nt, grid, lds);
-    case 3: return launch_nt<R, 2, 1>(which, st, one, A, nt, grid, lds);
-    case 4: return launch_nt<R, 2, 2>(which, st, one, A, nt, grid, lds);
-    case 5: return launch_nt<R, 3, 2>(which, st, one, A, nt, grid, lds);
-    case 6: return launch_nt<R, 3, 3>(which, st, one, A, nt, grid, lds);
-    case 7: return launch_nt<R, 4, 3>(which, st, one, A, nt, grid, lds);
-    case 8: return launch_nt<R, 4, 4>(which, st, one, A, nt, grid, lds);
-    case 9: return launch_nt<R, 5, 4>(which, st, one, A, nt, grid, lds);
-    case 10: return launch_nt<R, 5, 5>(which, st, one, A, nt, grid, lds);
+    case 1: return launch_nt<R, 1, 0>(which, st, one, head, A, nt, grid, lds);
+    case 2: return launch_nt<R, 1, 1>(which, st, one, head, A, nt, grid, lds);
+    case 3: return launch_nt<R, 2, 1>(which, st, one, head, A, nt, grid, lds);
+    case 4: return launch_nt<R, 2, 2>(which, st, one, head, A, nt, grid, lds);
+    case 5: return launch_nt<R, 3, 2>(which, st, one, head, A, nt, grid, lds);
+    case 6: return launch_nt<R, 3, 3>(which, st, one, head, A, nt, grid, lds);
+    case 7: return launch_nt<R, 4, 3>(which, st, one, head, A, nt, grid, lds);
+    case 8: return launch_nt<R, 4, 4>(which, st, one, head, A, nt, grid, lds);
+    case 9: return launch_nt<R, 5, 4>(which, st, one, head, A, nt, grid, lds);
+    case 10: return launch_nt<R, 5, 5>(which, st, one, head, A, nt, grid, lds);
     }
     return fail(SV_EUNSUPPORTED, "clock group of %d bits", g);
 }
@@ -728,9 +766,9 @@ static void make_plan(PipePlan &P, int n_s, int n_c, size_t e, const int cl[2], 
 }
 
 template <typename R>
-static sv_status run_one(hipStream_t st, const PipePlan &P, int w, const PipeSolve &one) {
+static sv_status run_one(hipStream_t st, const PipePlan &P, int w, const PipeSolve &one, const PipeHead &head = {}) {
     const int g = w == 1 ? P.A[w].g2 : P.A[w].g1;
-    return dispatch_g<R>(w, st, one, P.A[w], g, P.nt[w], P.grid[w], P.lds[w]);
+    return dispatch_g<R>(w, st, one, head, P.A[w], g, P.nt[w], P.grid[w], P.lds[w]);
 }
 
 // The autotuner: per (dtype, n_s, n_c) time every feasible (columns per
@@ -831,10 +869,10 @@ void pipe_config_batch(int n_s, int n_c, size_t elem, int cl[2]) {
 }
 
 template <typename R>
-sv_status pipe_run(sv_state s, int n_s, int n_c, bool sgn, uint64_t gcut, const double2 *beta, const uint64_t *F,
-                   double *part, double *zpart, uint64_t *nparts) {
+sv_status pipe_run(sv_state s, int n_s, int n_c, bool sgn, uint64_t gcut, const PipeHead &head, const double2 *beta, const double *lam,
+                   double T0, double *part, double *zpart, uint64_t *nparts) {
     const size_t e = sizeof(cvec<R>);
-    PipeSolve one{s->data, beta, F, part, zpart};
+    PipeSolve one{s->data, beta, lam, T0, part, zpart};
     int cl[2], nt[2];
     SV_TRY(pipe_config<R>(s->stream, n_s, n_c, one, cl, nt));
     PipePlan P;
@@ -844,13 +882,13 @@ sv_status pipe_run(sv_state s, int n_s, int n_c, bool sgn, uint64_t gcut, const 
         P.A[w].gcut = gcut;
     }
     *nparts = (uint64_t)P.grid[1].x * P.grid[1].y;
-    for (int w = 0; w < 2; ++w) SV_TRY(run_one<R>(s->stream, P, w, one));
+    for (int w = 0; w < 2; ++w) SV_TRY(run_one<R>(s->stream, P, w, one, head));
     return SV_OK;
 }
-template sv_status pipe_run<float>(sv_state, int, int, bool, uint64_t, const double2 *, const uint64_t *, double *,
-                                   double *, uint64_t *);
-template sv_status pipe_run<double>(sv_state, int, int, bool, uint64_t, const double2 *, const uint64_t *,
-                                    double *, double *, uint64_t *);
+template sv_status pipe_run<float>(sv_state, int, int, bool, uint64_t, const PipeHead &, const double2 *,
+                                   const double *, double, double *, double *, uint64_t *);
+template sv_status pipe_run<double>(sv_state, int, int, bool, uint64_t, const PipeHead &, const double2 *,
+                                    const double *, double, double *, double *, uint64_t *);
 
 // ---------------------------------------------------------------------------
 // the work queues' plan: items of about 2^15 amplitudes (runs of consecutive

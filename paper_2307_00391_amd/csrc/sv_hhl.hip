@@ -45,9 +45,8 @@ sv_status cgemm(hipStream_t st, const cvec<R> *in, cvec<R> *out, const cvec<R> *
 template <typename R>
 sv_status ctrl_unitary_impl(sv_state s, const cvec<R> *U, int m, int ctrl, int ctrl_val, int adjoint);
 template <typename R>
-sv_status pipe_run(sv_state s, int n_s, int n_c, bool sgn, uint64_t gcut, const double2 *beta, const uint64_t *F,
-                   double *part,
-                   double *zpart, uint64_t *nparts);
+sv_status pipe_run(sv_state s, int n_s, int n_c, bool sgn, uint64_t gcut, const PipeHead &head,
+                   const double2 *beta, const double *lam, double T0, double *part, double *zpart, uint64_t *nparts);
 
 // --------------------------------------------------------------------------
 // small FP64 kernels
@@ -121,25 +120,12 @@ __global__ void k_axis_transform(double2 *__restrict__ out, const double2 *__res
 }
 
 // F[j][k] = frac(phi_j 2^k) as a 64-bit fraction of a turn, phi_j = lam_j T0 / 2 pi:
-// the same IEEE operations as the host-side table (product, quotient, exact
-// scaling by 2^k, exact floor), so both give the same bits
-__device__ __forceinline__ void turn_table_body(uint64_t *__restrict__ F, const double *__restrict__ lam, double T0,
-                                                int n_c, uint64_t N, uint64_t block, uint64_t blocks) {
-    const uint64_t total = N * (uint64_t)n_c;
-    for (uint64_t i = block * blockDim.x + threadIdx.x; i < total; i += blocks * blockDim.x) {
-        const uint64_t j = i / n_c;
-        const int k = (int)(i % n_c);
-        const double phi = lam[j] * T0 / (2.0 * M_PI);
-        const double x = ldexp(phi, k);
-        const double f = x - floor(x);
-        const double sc = ldexp(f, 64);
-        F[i] = sc >= 18446744073709551616.0 ? 0ull : (uint64_t)sc;
-    }
-}
-
+// the same IEEE operations as the host-side table, so both give the same bits
 __global__ void k_turn_table(uint64_t *__restrict__ F, const double *__restrict__ lam, double T0, int n_c,
                              uint64_t N) {
-    turn_table_body(F, lam, T0, n_c, N, blockIdx.x, gridDim.x);
+    const uint64_t total = N * (uint64_t)n_c;
+    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (uint64_t)gridDim.x * blockDim.x)
+        F[i] = turn_fraction(lam[i / n_c], T0, (int)(i % n_c));
 }
 
 // ---- eigen-frame kernels ---------------------------------------------------
@@ -285,33 +271,11 @@ constexpr int EIG_HEAD = 8 + 2 * EIG_CHUNKS;     // doubles in front of x: scala
 
 static int eig_chunks(uint64_t nparts) { return nparts <= 2048 ? 1 : EIG_CHUNKS; }
 
-__global__ __launch_bounds__(256) void k_eig_sums(double2 *__restrict__ z, const double *__restrict__ zpart,
-                                                  const double2 *__restrict__ beta, uint64_t N, int rows,
-                                                  const double2 *__restrict__ part,
-                                                  uint64_t nparts, int nc, double2 *__restrict__ head) {
-    __shared__ double ws[2][4], wz[3][64];
-    if ((int)blockIdx.x >= nc) {
-        // 64 columns per workgroup, its four waves a quarter of the rows each
-        const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-        const int per = (rows + 3) / 4, r0 = wv * per, r1 = r0 + per < rows ? r0 + per : rows;
-        const uint64_t j = (uint64_t)(blockIdx.x - nc) * 64 + lane;
-        double w[4] = {0.0, 0.0, 0.0, 0.0};
-        if (j < N) {
-            int r = r0;
-            for (; r + 4 <= r1; r += 4)
-#pragma unroll
-                for (int k = 0; k < 4; ++k) w[k] += zpart[(uint64_t)(r + k) * N + j];
-            for (; r < r1; ++r) w[0] += zpart[(uint64_t)r * N + j];
-        }
-        const double f = (w[0] + w[1]) + (w[2] + w[3]);
-        if (wv) wz[wv - 1][lane] = f;
-        __syncthreads();
-        if (wv || j >= N) return;
-        const double t = (f + wz[0][lane]) + (wz[1][lane] + wz[2][lane]);
-        z[j] = make_double2(t * beta[j].x, t * beta[j].y);
-        return;
-    }
-    const uint64_t len = (nparts + nc - 1) / nc, beg = (uint64_t)blockIdx.x * len;
+// stretch blk of nc: head[blk] = its sum (all 256 threads)
+__device__ __forceinline__ void head_sums(const double2 *__restrict__ part, uint64_t nparts, unsigned blk, int nc,
+                                          double2 *__restrict__ head) {
+    __shared__ double ws[2][4];
+    const uint64_t len = (nparts + nc - 1) / nc, beg = (uint64_t)blk * len;
     const uint64_t end = beg + len < nparts ? beg + len : nparts;
     double a = 0.0, n = 0.0;
     for (uint64_t i = beg + threadIdx.x; i < end; i += 256) {
@@ -326,8 +290,75 @@ __global__ __launch_bounds__(256) void k_eig_sums(double2 *__restrict__ z, const
     }
     __syncthreads();
     if (threadIdx.x == 0)
-        head[blockIdx.x] = make_double2((ws[0][0] + ws[0][1]) + (ws[0][2] + ws[0][3]),
-                                        (ws[1][0] + ws[1][1]) + (ws[1][2] + ws[1][3]));
+        head[blk] = make_double2((ws[0][0] + ws[0][1]) + (ws[0][2] + ws[0][3]),
+                                 (ws[1][0] + ws[1][1]) + (ws[1][2] + ws[1][3]));
+}
+
+__global__ __launch_bounds__(256) void k_eig_sums(double2 *__restrict__ z, const double *__restrict__ zpart,
+                                                  const double2 *__restrict__ beta, uint64_t N, int rows,
+                                                  const double2 *__restrict__ part, uint64_t nparts, int nc,
+                                                  double2 *__restrict__ head) {
+    __shared__ double wz[3][64];
+    if ((int)blockIdx.x < nc) {
+        head_sums(part, nparts, blockIdx.x, nc, head);
+        return;
+    }
+    // 64 columns per workgroup, its four waves a quarter of the rows each
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int per = (rows + 3) / 4, r0 = wv * per, r1 = r0 + per < rows ? r0 + per : rows;
+    const uint64_t j = (uint64_t)(blockIdx.x - nc) * 64 + lane;
+    double w[4] = {0.0, 0.0, 0.0, 0.0};
+    if (j < N) {
+        int r = r0;
+        for (; r + 4 <= r1; r += 4)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) w[k] += zpart[(uint64_t)(r + k) * N + j];
+        for (; r < r1; ++r) w[0] += zpart[(uint64_t)r * N + j];
+    }
+    const double f = (w[0] + w[1]) + (w[2] + w[3]);
+    if (wv) wz[wv - 1][lane] = f;
+    __syncthreads();
+    if (wv || j >= N) return;
+    const double t = (f + wz[0][lane]) + (wz[1][lane] + wz[2][lane]);
+    z[j] = make_double2(t * beta[j].x, t * beta[j].y);
+}
+
+// The end of a small solve on a dense plan in one launch, into host memory that
+// the device can write: workgroups [0, nc) the sums, the others x = V z for 16
+// rows each, every one forming z for itself (rows N <= EIG_TAIL; above it the
+// repeated column sums cost more than the launch they save).  With V^H b^ in
+// k_pipe_a's launch and b read from the staging buffer a solve of 11 qubits is
+// three launches and no copy: 31 us, where five launches and two copies took 58.
+constexpr uint64_t EIG_TAIL = 8192, EIG_SMALL = 1024;
+
+__global__ __launch_bounds__(256) void k_eig_tail(double2 *__restrict__ x, const double2 *__restrict__ V,
+                                                  const double *__restrict__ zpart, const double2 *__restrict__ beta,
+                                                  int N, int rows, const double2 *__restrict__ part, uint64_t nparts,
+                                                  int nc, double2 *__restrict__ head) {
+    __shared__ double2 zs[EIG_SMALL];
+    if ((int)blockIdx.x < nc) {
+        head_sums(part, nparts, blockIdx.x, nc, head);
+        return;
+    }
+    for (int j = threadIdx.x; j < N; j += 256) {
+        double w = 0.0;
+        for (int r = 0; r < rows; ++r) w += zpart[(size_t)r * N + j];
+        zs[j] = make_double2(w * beta[j].x, w * beta[j].y);
+    }
+    __syncthreads();
+    const int lane = threadIdx.x & 63, r0 = ((int)blockIdx.x - nc) * 16 + (threadIdx.x >> 6) * 4;
+#pragma unroll
+    for (int r = r0; r < r0 + 4; ++r) {
+        if (r >= N) break;
+        double2 acc = make_double2(0.0, 0.0);
+        for (int t = lane; t < N; t += 64) {
+            const double2 v = V[(size_t)r * N + t], z = zs[t];
+            acc.x = fma(v.x, z.x, fma(-v.y, z.y, acc.x));
+            acc.y = fma(v.x, z.y, fma(v.y, z.x, acc.y));
+        }
+        const double re = wave_sum_f64(acc.x), im = wave_sum_f64(acc.y);
+        if (lane == 0) x[r] = make_double2(re, im);
+    }
 }
 
 // --------------------------------------------------------------------------
@@ -801,8 +832,8 @@ __global__ __launch_bounds__(256) void k_gemv_cols2(double2 *__restrict__ out, c
 }
 
 template <typename VT>
-__device__ __forceinline__ void gemv_cols_body(double2 *__restrict__ out, const VT *__restrict__ V,
-                                               const double2 *__restrict__ b, uint64_t N) {
+__global__ __launch_bounds__(256) void k_gemv_cols(double2 *__restrict__ out, const VT *__restrict__ V,
+                                                   const double2 *__restrict__ b, uint64_t N) {
     __shared__ double2 part[3][64];
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -819,22 +850,6 @@ __device__ __forceinline__ void gemv_cols_body(double2 *__restrict__ out, const 
         const double2 p1 = part[0][lane], p2 = part[1][lane], p3 = part[2][lane];
         out[j] = make_double2((acc.x + p1.x) + (p2.x + p3.x), (acc.y + p1.y) + (p2.y + p3.y));
     }
-}
-
-template <typename VT>
-__global__ __launch_bounds__(256) void k_gemv_cols(double2 *__restrict__ out, const VT *__restrict__ V,
-                                                   const double2 *__restrict__ b, uint64_t N) {
-    gemv_cols_body<VT>(out, V, b, N);
-}
-
-// The head of a solve on a dense plan: workgroups [0, gcols) form beta = V^H b^,
-// the others the turn table (for small systems every launch counts)
-__global__ __launch_bounds__(256) void k_eig_head(double2 *__restrict__ beta, const double2 *__restrict__ V,
-                                                  const double2 *__restrict__ b, uint64_t N, unsigned gcols,
-                                                  uint64_t *__restrict__ F, const double *__restrict__ lam, double T0,
-                                                  int n_c) {
-    if (blockIdx.x < gcols) gemv_cols_body<double2>(beta, V, b, N);
-    else turn_table_body(F, lam, T0, n_c, N, blockIdx.x - gcols, gridDim.x - gcols);
 }
 
 // the dense basis change: out = V in (forward) or V^H in (adjoint), V N x N
@@ -910,6 +925,7 @@ struct Workspace {
 };
 
 static sv_status need(DevBuf &b, size_t bytes) { return b.ensure(bytes); }
+static sv_status eig_result(const double *out, uint64_t N, int nc, sv_hhl_result *res, double *x_out, bool dev);
 static sv_status eig_finish(sv_state s, const EigFrame &E, Workspace &w, uint64_t N, int nc, sv_hhl_result *res,
                             double *x_out, bool dev, double2 *x_dev);
 
@@ -967,7 +983,6 @@ static sv_status eig_frame_run(sv_state s, const EigFrame &E, Workspace &w, cons
     if (nb > 4096) nb = 4096;
     const uint64_t chunk = (half + nb - 1) / nb;
 
-    SV_TRY(need(w.F, N * n_c * sizeof(uint64_t)));
     SV_TRY(need(w.beta, N * sizeof(double2)));
     SV_TRY(need(w.tmp, N * sizeof(double2)));
     SV_TRY(need(w.z, N * sizeof(double2)));
@@ -982,25 +997,25 @@ static sv_status eig_frame_run(sv_state s, const EigFrame &E, Workspace &w, cons
         SV_TRY(need(w.tmp2, 512 * sizeof(double)));
         vec_normalise(st, (double2 *)w.x.p, b_dev, N, (double *)w.tmp2.p, sums + 2);
         SV_HIP(hipGetLastError());
-    } else {
+    }
+    const bool pipe = fused && pipe_supported(n_s, n_c);
+    // a small dense plan: V^H b^ in k_pipe_a's launch (and a host b read from
+    // the staging buffer), the end in one launch
+    const bool small = pipe && !E.Vr && E.n_lo <= 1 && N <= EIG_SMALL;
+    PipeHead head{(double2 *)w.beta.p, (const double2 *)E.V_hi.p, (const double2 *)w.x.p, N,
+                  small ? (unsigned)((N + 63) / 64) : 0u};
+    if (!dev && small) {
+        void *staged = nullptr;
+        SV_TRY(stage_plan(s, bhat.data(), N * sizeof(double2), &staged));
+        head.b = (const double2 *)staged;
+    } else if (!dev) {
         SV_TRY(upload_plan(s, w.x.p, bhat.data(), N * sizeof(double2)));
     }
-    // the turn table, and beta = V^H b^
-    if (!E.Vr && E.n_lo <= 1) {
-        const unsigned gc = (unsigned)((N + 63) / 64);
-        TraceScope _ts(st, "gemv_vh", (double)N * (double)N * sizeof(double2), 8.0 * (double)N * (double)N);
-        hipLaunchKernelGGL(k_eig_head, dim3(gc + grid1(N * n_c)), dim3(256), 0, st, (double2 *)w.beta.p,
-                           (const double2 *)E.V_hi.p, (const double2 *)w.x.p, N, gc, (uint64_t *)w.F.p,
-                           (const double *)E.lam_dev.p, T0, n_c);
-        SV_HIP(hipGetLastError());
-    } else {
-        hipLaunchKernelGGL(k_turn_table, dim3(grid1(N * n_c)), dim3(256), 0, st, (uint64_t *)w.F.p,
-                           (const double *)E.lam_dev.p, T0, n_c, N);
-        SV_HIP(hipGetLastError());
+    // beta = V^H b^
+    if (!small)
         SV_TRY(kron_apply_frame(s, (double2 *)w.beta.p, (const double2 *)w.x.p, (double2 *)w.tmp.p, E, 1, w.gpart));
-    }
 
-    if (fused && pipe_supported(n_s, n_c)) {
+    if (pipe) {
         // fused two-kernel pipeline: (state + inverse QFT on the low clock bits),
         // (inverse QFT high + rotation + the uncompute projected on clock 0)
         const uint64_t nbp = pipe_b_blocks(n_s, n_c, sizeof(cvec<R>));
@@ -1008,16 +1023,34 @@ static sv_status eig_frame_run(sv_state s, const EigFrame &E, Workspace &w, cons
         SV_TRY(need(w.part, 2 * nbp * sizeof(double)));
         SV_TRY(need(w.zpart, (size_t)rows * N * sizeof(double)));
         uint64_t nparts = 0;
-        SV_TRY(pipe_run<R>(s, n_s, n_c, sgn, gcut, (const double2 *)w.beta.p, (const uint64_t *)w.F.p, (double *)w.part.p,
-                           (double *)w.zpart.p, &nparts));
+        SV_TRY(pipe_run<R>(s, n_s, n_c, sgn, gcut, head, (const double2 *)w.beta.p, (const double *)E.lam_dev.p, T0,
+                           (double *)w.part.p, (double *)w.zpart.p, &nparts));
+        if (!dev && small) SV_HIP(hipEventRecord(s->plan_ev, st));
         if (nparts > nbp) return fail(SV_EDEVICE, "pipeline partial count exceeds its buffer");
         const int nc = eig_chunks(nparts);
-        hipLaunchKernelGGL(k_eig_sums, dim3((unsigned)(nc + (N + 63) / 64)), dim3(256), 0, st, (double2 *)w.z.p, (const double *)w.zpart.p,
-                           (const double2 *)w.beta.p, N, rows, (const double2 *)w.part.p, nparts, nc,
-                           (double2 *)(sums + 8));
+        if (!dev && small && (uint64_t)rows * N <= EIG_TAIL) {
+            // the results go straight into the download buffer
+            const size_t bytes = EIG_HEAD * sizeof(double) + N * sizeof(double2);
+            SV_TRY(ensure_pinned(s, bytes));
+            double *out = (double *)s->pinned;
+            hipLaunchKernelGGL(k_eig_tail, dim3((unsigned)(nc + (N + 15) / 16)), dim3(256), 0, st,
+                               (double2 *)(out + EIG_HEAD), (const double2 *)E.V_hi.p, (const double *)w.zpart.p,
+                               (const double2 *)w.beta.p, (int)N, rows, (const double2 *)w.part.p, nparts, nc,
+                               (double2 *)(out + 8));
+            SV_HIP(hipGetLastError());
+            SV_HIP(hipStreamSynchronize(st));
+            return eig_result(out, N, nc, res, x_out, false);
+        }
+        hipLaunchKernelGGL(k_eig_sums, dim3((unsigned)(nc + (N + 63) / 64)), dim3(256), 0, st, (double2 *)w.z.p,
+                           (const double *)w.zpart.p, (const double2 *)w.beta.p, N, rows, (const double2 *)w.part.p, nparts,
+                           nc, (double2 *)(sums + 8));
         SV_HIP(hipGetLastError());
         return eig_finish(s, E, w, N, nc, res, x_out, dev, x_dev);
     }
+    SV_TRY(need(w.F, N * n_c * sizeof(uint64_t)));
+    hipLaunchKernelGGL(k_turn_table, dim3(grid1(N * n_c)), dim3(256), 0, st, (uint64_t *)w.F.p,
+                       (const double *)E.lam_dev.p, T0, n_c, N);
+    SV_HIP(hipGetLastError());
     std::vector<double> cs;
     inversion_table(n_c, cs, sgn, gcut);
     SV_TRY(need(w.cs, cs.size() * sizeof(double)));
@@ -1073,6 +1106,11 @@ static sv_status eig_finish(sv_state s, const EigFrame &E, Workspace &w, uint64_
     }
     std::vector<double> out(EIG_HEAD + (dev ? 0 : 2 * N));
     SV_TRY(download(s, out.data(), sums, out.size() * sizeof(double)));
+    return eig_result(out.data(), N, nc, res, x_out, dev);
+}
+
+// the scalars and the normalised x out of a solve's results (EIG_HEAD doubles, then x)
+static sv_status eig_result(const double *out, uint64_t N, int nc, sv_hhl_result *res, double *x_out, bool dev) {
     res->p_anc = out[0];
     res->norm_total = out[1];
     if (nc) {
@@ -1088,7 +1126,7 @@ static sv_status eig_finish(sv_state s, const EigFrame &E, Workspace &w, uint64_
         if (!(out[3] > 0.0)) return fail(SV_EZERONORM, "post-selected outcome has probability 0");
         return SV_OK;
     }
-    const double *xz = out.data() + EIG_HEAD;
+    const double *xz = out + EIG_HEAD;
     double p = 0.0;
     for (uint64_t j = 0; j < N; ++j) p += xz[2 * j] * xz[2 * j] + xz[2 * j + 1] * xz[2 * j + 1];
     res->p_post = p;

@@ -24,11 +24,29 @@ struct DevBuf {
     sv_status ensure(size_t need) { return need <= bytes && p ? SV_OK : alloc(need); }
 };
 
+// frac(lam T0 / 2 pi 2^k) as a 64-bit fraction of a turn: product, quotient,
+// exact scaling by 2^k, exact floor
+__device__ __forceinline__ uint64_t turn_fraction(double lam, double T0, int k) {
+    const double x = ldexp(lam * T0 / (2.0 * M_PI), k);
+    const double sc = ldexp(x - floor(x), 64);
+    return sc >= 18446744073709551616.0 ? 0ull : (uint64_t)sc;
+}
+
+// the basis change of a small dense system, beta = V^H b, in k_pipe_a's launch:
+// its workgroups behind the tiles take 64 columns each (cols = 0: none)
+struct PipeHead {
+    double2 *beta;
+    const double2 *V, *b;
+    uint64_t N;
+    unsigned cols;
+};
+
 // per-solve operands of the fused eigen-frame kernels
 struct PipeSolve {
     void *psi;              // the state; of a batched solve, its first pipe_table_rows clock rows
     const double2 *beta;    // V^H b^ (FP64)
-    const uint64_t *F;      // turn table [N][n_c]
+    const double *lam;      // eigenvalues
+    double T0;
     double *part;           // k_pipe_b partial sums (2 per block)
     double *zpart;          // k_pipe_b partial column sums [2^g1][N], over beta
 };
