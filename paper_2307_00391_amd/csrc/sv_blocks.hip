@@ -98,13 +98,24 @@ template <typename R>
 __global__ __launch_bounds__(64) void k_block_build(const BBuild *__restrict__ todo, const ROp *__restrict__ ops,
                                                     unsigned char *__restrict__ mats) {
     __shared__ double2 u[16][17];
-    const BBuild &B = todo[blockIdx.x];
+    // the operations come through LDS in chunks: one memory latency each would
+    // be most of the kernel (19 us for the 31 blocks of a 14-qubit circuit)
+    constexpr int CH = 32;
+    static_assert(sizeof(ROp) % 8 == 0, "operations are copied as 8-byte words");
+    __shared__ uint64_t chunk[CH * sizeof(ROp) / 8];
+    const BBuild B = todo[blockIdx.x];
     const int lane = threadIdx.x;
     for (int i = lane; i < 256; i += 64) u[i >> 4][i & 15] = make_double2((i >> 4) == (i & 15) ? 1.0 : 0.0, 0.0);
     uint32_t reach = 1u << (lane & 15);       // rows reached by column lane % 16
-    __syncthreads();
     for (int o = 0; o < B.nops; ++o) {
-        const ROp &f = ops[B.op_off + o];
+        if (o % CH == 0) {
+            __syncthreads();
+            const int n = (int)(sizeof(ROp) / 8) * (B.nops - o < CH ? B.nops - o : CH);
+            const uint64_t *src = (const uint64_t *)(ops + B.op_off + o);
+            for (int i = lane; i < n; i += 64) chunk[i] = src[i];
+            __syncthreads();
+        }
+        const ROp &f = ((const ROp *)chunk)[o % CH];
         if ((B.base & f.gmask) != f.gval) continue;
         if (f.type == OP_PHASE) {
             const double2 ph = make_double2(f.u[0], f.u[1]);
@@ -131,6 +142,7 @@ __global__ __launch_bounds__(64) void k_block_build(const BBuild *__restrict__ t
         }
         __syncthreads();
     }
+    if (!B.nops) __syncthreads();
     unsigned char *M = mats + (size_t)blockIdx.x * MatBytes<R>::stride;
     for (int i = lane; i < 256; i += 64) {
         const int r = i >> 4, c = i & 15;

@@ -411,14 +411,18 @@ static sv_status cgemm_ks(hipStream_t st, const cvec<R> *in, cvec<R> *out, const
         float best = 1e30f;
         // the small shapes only where the large one leaves compute units short
         // of work: on a large product a wavefront per tile takes many times longer
-        for (int c = 0; c < (gm * gn <= 4096 && parts_ok ? 4 : 2); ++c) {
-            float ms = 0.f;
-            SV_TRY(time_stream(st, 2, &ms, [&]() { return launch(c); }));
-            if (ms < best) {
-                best = ms;
-                shape = c;
+        const bool all = gm * gn <= 4096 && parts_ok;
+        // products of a few microseconds: single timings differ by more than the
+        // shapes do, and a wrong pick is up to twice as slow (11 and 20 us)
+        for (int round = 0; round < (all ? 4 : 1); ++round)
+            for (int c = 0; c < (all ? 4 : 2); ++c) {
+                float ms = 0.f;
+                SV_TRY(time_stream(st, all ? 8 : 2, &ms, [&]() { return launch(c); }));
+                if (ms < best) {
+                    best = ms;
+                    shape = c;
+                }
             }
-        }
         tune_store(key, {shape});
     }
     return launch(shape);
