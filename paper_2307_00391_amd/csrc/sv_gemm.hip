@@ -458,7 +458,10 @@ static sv_status ctrl_mask_unitary_at(sv_state s, const cvec<R> *U, int lo, int 
     {
         TraceScope _ts(s->stream, "scatter_rows", 2.0 * (double)total * sizeof(cvec<R>), 0.0);
         const uint64_t gl = total / 1024;
-        if (lo == 0 && m >= 8 && gl >= 1 && gl <= (1u << 23))       // (threads per launch stay below 2^32)
+        // whole rows while a launch is short (1024 rows of 256: 5.5 us, 6.5 with
+        // a deposit per element); the grid-stride copy of k_scatter_rows streams
+        // better when it is long (8192 rows of 1024: 27 us, 37)
+        if (lo == 0 && m >= 8 && gl >= 1 && gl <= 1024)
             hipLaunchKernelGGL(k_scatter_long<R>, dim3((unsigned)gl), dim3(256), 0, s->stream, (cvec<R> *)s->data,
                                (const cvec<R> *)out, m, row_mask, row_fix);
         else
