@@ -391,7 +391,8 @@ int sv_trace_report(char *buf, int len);
  *       local qubits, c contiguous low bits, rb register bits per segment
  *       line: 5 or 4 for complex64, 4 or 3 for complex128; 1: the circuit
  *       runs as matrix-core blocks) per circuit structure; an entry of (k, c)
- *       takes the default rb.
+ *       takes the default rb, a fourth value 1 plans passes of the earliest
+ *       gates.
  * Returns the report length. */
 int sv_tune_report(char *buf, int len);
 /* Sets (n > 0: vals[0..n)) or removes (n == 0) one tuning entry, with the key

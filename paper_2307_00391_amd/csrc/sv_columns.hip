@@ -24,8 +24,8 @@
 // fast as unpacked FP32 ones, and the errors enter |P|^2 twice, alike.  (With
 // two of a line's five levels in FP64: 115 instead of 134 us for the sweep
 // below, and errors up to 1.6 times those of the kernels before.)
-// A sweep of 1024 complex64 solves (n_s 4..10, n_c 8..12): 134 us, about 14
-// vector operations per amplitude; the column tiles of k_pipe_a and k_pipe_b
+// A sweep of 1024 complex64 solves (n_s 4..10, n_c 8..12): 134 us, about 18
+// vector instructions per amplitude; the column tiles of k_pipe_a and k_pipe_b
 // took 850 us at 37 operations, with tables, partial column sums and twiddles
 // through memory.
 #include <math.h>

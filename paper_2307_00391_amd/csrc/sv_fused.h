@@ -218,6 +218,9 @@ struct PlanWindow {
 // cap has to leave room for any one gate next to `base`.
 void plan_windows(const std::vector<PlanItem> &items, int cap, uint64_t base, int item_out, int window_out,
                   int max_ops, std::vector<PlanWindow> &out);
+// the same cut with windows that take the earliest gates until they are full
+void plan_earliest(const std::vector<PlanItem> &items, int cap, uint64_t base, int max_ops,
+                   std::vector<PlanWindow> &out);
 
 // ---- matrix-core passes (sv_blocks.hip) -------------------------------------
 // every gate fits a block of four qubits, and one at least mixes amplitudes

@@ -111,4 +111,31 @@ void plan_windows(const std::vector<PlanItem> &items, int cap, uint64_t base, in
     }
 }
 
+void plan_earliest(const std::vector<PlanItem> &items, int cap, uint64_t base, int max_ops,
+                   std::vector<PlanWindow> &out) {
+    out.clear();
+    std::vector<int> left(items.size()), rest;
+    for (size_t i = 0; i < left.size(); ++i) left[i] = (int)i;
+    while (!left.empty()) {
+        out.emplace_back();
+        PlanWindow &w = out.back();
+        w.set = base;
+        uint64_t blocked = 0;
+        int ops = 0;
+        rest.clear();
+        for (int i : left) {
+            const PlanItem &g = items[i];
+            if (!(g.order & blocked) && popcount64(w.set | g.need) <= cap && ops + g.ops <= max_ops) {
+                w.set |= g.need;
+                ops += g.ops;
+                w.take.push_back(i);
+            } else {
+                blocked |= g.order;
+                rest.push_back(i);
+            }
+        }
+        left.swap(rest);
+    }
+}
+
 }  // namespace sv
