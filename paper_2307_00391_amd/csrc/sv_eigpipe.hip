@@ -8,8 +8,7 @@
 //
 //   k_pipe_a: generate the state after phase estimation (product state over
 //             the clock bits, relabelled so the cascades need no swaps), then
-//             the inverse-QFT cascade on G1 (butterflies in registers, RA
-//             bits at a time, one LDS exchange).  The G1 stages act on G1
+//             the inverse-QFT cascade on G1, in closed form.  The G1 stages act on G1
 //             qubits only, so the result is still a product between the
 //             groups: psi(j, y1, y2) = beta_j T_j(y1) B_j(y2), with T_j the G1
 //             transform of the column's G1 factor and B_j(y2) the product of
@@ -99,31 +98,41 @@ __device__ __forceinline__ cvec<R> cconjmul(cvec<R> a, cvec<R> b) {   // a * con
 __device__ __forceinline__ float ffma(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double ffma(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
-// One inverse cascade stage on a register line v[0..2^RL): pairs differ in bit
-// kb of the register index.  tw is the stage's twiddle table (entry m = phase
-// for the register bits below the stage's qubit equal to m); tidx(k) gives that
-// m for element k.  The 1/sqrt(2) of the Hadamard is left out here and
-// applied once per group by the caller (butterflies are add/sub only).
-// has_tw = false for the lowest qubit of the register (phase 1).
-// The butterfly forms v0 = a0 + a1 conj(w) with four FMAs and
-// v1 = 2 a0 - v0 with two more (six operations instead of eight).
-template <typename R, int RL, typename TIDX>
-__device__ __forceinline__ void stage(cvec<R> (&v)[1 << RL], int kb, const cvec<R> *__restrict__ tw, bool has_tw,
-                                      TIDX tidx) {
+__device__ __forceinline__ int tw_off(int jb) { return (1 << jb) - 1; }
+
+// The inverse cascade of a product state over G = RA + RB clock bits, along one
+// line: the low RA bits are llo, the 2^RB values of the high ones fill v.  Every
+// stage maps a product state to another, so the output at l is
+//   p prod_b (1 + (-1)^(l_b) w_b conj(tw_b(l mod 2^b))),
+// w_b = om[b C] the phase of bit b, tw_b the stage's twiddle (TW).  The factors
+// of the low bits are the line's, those of the high bits branch: a node splits
+// into a + a q and 2 a - (a + a q), six operations, and the upper half of a
+// level's nodes has the lower half's q, turned by a quarter.
+template <typename D, int RA, int RB>
+__device__ __forceinline__ void product_line(cvec<D> (&v)[1 << RB], cvec<D> p, const cvec<D> *__restrict__ om, int C,
+                                             const cvec<D> *__restrict__ TW, int llo) {
 #pragma unroll
-    for (int k0 = 0; k0 < (1 << RL); ++k0) {
-        if (k0 & (1 << kb)) continue;
-        const int k1 = k0 | (1 << kb);
-        cvec<R> a0 = v[k0], a1 = v[k1];
-        if (has_tw) {
-            const cvec<R> w = tw[tidx(k0)];
-            const R rx = ffma(a1.x, w.x, ffma(a1.y, w.y, a0.x));
-            const R ry = ffma(a1.y, w.x, ffma(-a1.x, w.y, a0.y));
-            v[k0] = cmake<R>(rx, ry);
-            v[k1] = cmake<R>(ffma((R)2, a0.x, -rx), ffma((R)2, a0.y, -ry));
-        } else {
-            v[k0] = cmake<R>(a0.x + a1.x, a0.y + a1.y);
-            v[k1] = cmake<R>(a0.x - a1.x, a0.y - a1.y);
+    for (int b = 0; b < RA; ++b) {
+        const cvec<D> q = cconjmul<D>(om[b * C], TW[tw_off(b) + (llo & ((1 << b) - 1))]);
+        const cvec<D> f = (llo >> b & 1) ? cmake<D>((D)1 - q.x, -q.y) : cmake<D>((D)1 + q.x, q.y);
+        p = cmul<D>(p, f);
+    }
+    v[0] = p;
+#pragma unroll
+    for (int bb = 0; bb < RB; ++bb) {
+        const cvec<D> w = om[(RA + bb) * C];
+        const int h = 1 << bb;
+        auto node = [&](int m, cvec<D> q) {
+            const cvec<D> a = v[m];
+            const D px = ffma(a.x, q.x, ffma(-a.y, q.y, a.x)), py = ffma(a.x, q.y, ffma(a.y, q.x, a.y));
+            v[m] = cmake<D>(px, py);
+            v[m + h] = cmake<D>(ffma((D)2, a.x, -px), ffma((D)2, a.y, -py));
+        };
+#pragma unroll
+        for (int m = 0; m < (h + 1) / 2; ++m) {
+            const cvec<D> q = cconjmul<D>(w, TW[tw_off(RA + bb) + llo + (m << RA)]);
+            node(m, q);
+            if (bb > 0) node(m + h / 2, cmake<D>(q.y, -q.x));
         }
     }
 }
@@ -141,7 +150,6 @@ __device__ __forceinline__ void fill_twiddles(cvec<R> *TW, int g, int gbase, uin
         TW[i] = turn_phase<R>((vlow + (m << gbase)) << (63 - j));
     }
 }
-__device__ __forceinline__ int tw_off(int jb) { return (1 << jb) - 1; }
 
 // tile decomposition: column block and the setting of the other group's bits
 __device__ __forceinline__ void tile_coords(const PipeArgs &A, uint64_t &j0, uint64_t &o) {
@@ -157,81 +165,42 @@ __device__ __forceinline__ void tile_coords(const PipeArgs &A, uint64_t &j0, uin
 // In FP64 for both types, rounded once on the store: the table is small (2^g1 of
 // the 2^n_c clock rows), and its errors enter |P|^2 of k_pipe_b twice, alike
 // (complex64 solves of 10 + 10 qubits: rms error of p_post 4.9e-8, 2.0e-7 with a
-// complex64 table).  39 -> 75 us of a 32-qubit solve.
+// complex64 table).  The stages act on a product state, so the table is a
+// product tree per line, like k_pipe_b's, with no tile: 35 us of a 32-qubit
+// solve (75 us with the stages' butterflies through an LDS tile).
 template <typename R, int RA, int RB, int NT>
-__device__ __forceinline__ void pipe_a_body(const PipeArgs &A, const PipeSolve &S, uint64_t j0, uint64_t o) {
+__device__ __forceinline__ void pipe_a_body(const PipeArgs &A, const PipeSolve &S, uint64_t j0) {
     constexpr int G = RA + RB;
     cvec<R> *__restrict__ psi = (cvec<R> *)S.psi;
     const gptr<const double> __restrict__ lam = (gptr<const double>)S.lam;
     extern __shared__ unsigned char smem_raw[];
     const int C = 1 << A.cl;
     using D = double;
-    cvec<D> *tile = reinterpret_cast<cvec<D> *>(smem_raw);          // [2^G][C]
-    cvec<D> *TW = tile + ((size_t)C << G);                           // [2^G - 1] (+1 pad)
-    cvec<D> *om = TW + (1 << G);                                     // [G][C] exp(2 pi i F) of the local bits
-    cvec<D> *cc = om + G * C;                                        // [C] column constants
+    cvec<D> *TW = reinterpret_cast<cvec<D> *>(smem_raw);            // [2^G - 1] (+1 pad)
+    cvec<D> *om = TW + (1 << G);                                     // [G][C] exp(2 pi i F) of the G1 bits
     const int n_c = A.n_c;
     fill_twiddles<D>(TW, G, 0, 0);
-    // the tile holds clock index s = (o << G) | l; bit b of s carries F[j][n_c-1-b].
-    // The G Hadamards below omit their 1/sqrt(2): 2^(-G/2) joins the amplitude scale.
-    const double sc = A.scale * exp2(-0.5 * G);
-    for (int c = threadIdx.x; c < C; c += NT) {
-        const uint64_t j = j0 + c;
-        uint64_t th = 0;
-        for (int b = G; b < n_c; ++b)
-            if (o >> (b - G) & 1) th += turn_fraction(lam[j], S.T0, n_c - 1 - b);
-        const cvec<D> ph = turn_phase<D>(th);
-        cc[c] = cmake<D>(sc * ph.x, sc * ph.y);
-        for (int b = 0; b < G; ++b) om[b * C + c] = turn_phase<D>(turn_fraction(lam[j], S.T0, n_c - 1 - b));
-    }
-    // the phases of the G2 bits of every column for k_pipe_b, staged in clock
-    // rows 2^g1 + r (r < g2) of the ancilla = 0 half, which the solve leaves
-    // unused otherwise (only the rows below 2^g1 hold the G1 table)
-    const int g2 = n_c - G;
-    for (int e = threadIdx.x; e < g2 * C; e += NT) {
-        const int r = e / C, c = e - r * C;
-        const uint64_t j = j0 + c;
-        gst<R>(psi, ((((uint64_t)1 << G) + (uint64_t)r) << A.n_s) + j, turn_phase<R>(turn_fraction(lam[j], S.T0, n_c - 1 - (G + r))));
+    // the phases of every clock bit and column; bit b carries frac(phi_j 2^(n_c-1-b)).
+    // Those of the G2 bits are staged for k_pipe_b in clock rows 2^g1 + r (r < g2)
+    // of the ancilla = 0 half, which the solve leaves unused otherwise (only the
+    // rows below 2^g1 hold the G1 table)
+    for (int e = threadIdx.x; e < n_c * C; e += NT) {
+        const int b = e / C, c = e - b * C;
+        const uint64_t f = turn_fraction(lam[j0 + c], S.T0, n_c - 1 - b);
+        if (b < G) om[e] = turn_phase<D>(f);
+        else gst<R>(psi, ((((uint64_t)1 << G) + (uint64_t)(b - G)) << A.n_s) + j0 + c, turn_phase<R>(f));
     }
     __syncthreads();
-    // phase A: line = (c, l_hi), register index = bits [0, RA)
-    const int nla = C << RB;
-    for (int line = threadIdx.x; line < nla; line += NT) {
-        const int c = line & (C - 1), lhi = line >> A.cl;
-        cvec<D> v[1 << RA];
-        cvec<D> base = cc[c];
-        for (int b = 0; b < RB; ++b)
-            if (lhi >> b & 1) base = cmul<D>(base, om[(RA + b) * C + c]);
-        v[0] = base;
-#pragma unroll
-        for (int b = 0; b < RA; ++b) {
-            const cvec<D> w = om[b * C + c];
-#pragma unroll
-            for (int k = 0; k < (1 << b); ++k) v[k | (1 << b)] = cmul<D>(v[k], w);
-        }
-#pragma unroll
-        for (int jb = 0; jb < RA; ++jb)
-            stage<D, RA>(v, jb, TW + tw_off(jb), jb > 0, [&](int k) { return k & ((1 << jb) - 1); });
-        cvec<D> *lt = tile + ((lhi << RA) << A.cl) + c;
-#pragma unroll
-        for (int k = 0; k < (1 << RA); ++k) lt[k << A.cl] = v[k];
-    }
-    __syncthreads();
-    // phase B: line = (c, l_lo), register index = bits [RA, G)
-    const int nlb = C << RA;
-    for (int line = threadIdx.x; line < nlb; line += NT) {
+    // the G Hadamards below omit their 1/sqrt(2): 2^(-G/2) joins the amplitude scale
+    const cvec<D> root = cmake<D>(A.scale * exp2(-0.5 * G), 0.0);
+    // clock index (k << RA) + llo (G2 value 0): a base for the line and a stride for k
+    const int nl = C << RA;
+    const uint64_t ks = 1ull << (RA + A.n_s);
+    for (int line = threadIdx.x; line < nl; line += NT) {
         const int c = line & (C - 1), llo = line >> A.cl;
         cvec<D> v[1 << RB];
-        cvec<D> *lt = tile + (llo << A.cl) + c;
-#pragma unroll
-        for (int k = 0; k < (1 << RB); ++k) v[k] = lt[(k << RA) << A.cl];
-#pragma unroll
-        for (int jb = RA; jb < G; ++jb)
-            stage<D, RB>(v, jb - RA, TW + tw_off(jb), true,
-                               [&](int k) { return llo + ((k & ((1 << (jb - RA)) - 1)) << RA); });
-        // clock index (o << G) + (k << RA) + llo: a base for the line and a stride for k
-        cvec<R> *p = psi + (((((o << G) + (uint64_t)llo) << A.n_s)) + j0 + c);
-        const uint64_t ks = 1ull << (RA + A.n_s);
+        product_line<D, RA, RB>(v, root, om + c, C, TW, llo);
+        cvec<R> *p = psi + ((uint64_t)llo << A.n_s) + j0 + c;
 #pragma unroll
         for (int k = 0; k < (1 << RB); ++k) gst<R>(p, k * ks, cmake<R>((R)v[k].x, (R)v[k].y));
     }
@@ -276,7 +245,7 @@ __global__ __launch_bounds__(NT) void k_pipe_a(PipeArgs A, PipeSolve one, PipeHe
     }
     uint64_t j0, o;
     tile_coords(A, j0, o);
-    pipe_a_body<R, RA, RB, NT>(A, one, j0, o);
+    pipe_a_body<R, RA, RB, NT>(A, one, j0);
 }
 
 // ---------------------------------------------------------------------------
@@ -367,45 +336,13 @@ __device__ __forceinline__ void pipe_b_body(const PipeArgs &A, const PipeSolve &
         const bool more = PERS && it + 1 < iters;
         const cvec<R> *om = cd + (it & 1) * ncd, *tT = om + G * C, *be = tT + C;
         R *zt = zl + (it & 1) * nl;
-        // the inverse-QFT output on the G2 register of column j at
-        // y = o + l 2^g1, l = llo + (k << RA), from its closed form.  The
-        // input of the G2 stages is T_j(o) times a product state over the G2
-        // bits (phase w_b on bit b), and inverse stage b maps a product state
-        // to a product state: after all of them the amplitude is
-        //   T_j(o) prod_b (1 + (-1)^(l_b) w_b conj(tw_b(l mod 2^b))),
-        // tw_b the stage's twiddle.  The factors of the low RA bits are the
-        // line's, those of the RB high bits branch into the line's 2^RB
-        // entries (a product tree, one level per bit).
+        // the inverse-QFT output on the G2 register of column j at y = o + l 2^g1,
+        // l = llo + (k << RA): the input of the G2 stages is T_j(o) times a product
+        // state over the G2 bits
         for (int line = threadIdx.x; line < nl; line += NT) {
             const int c = line & (C - 1), llo = line >> A.cl;
             cvec<R> v[1 << RB];
-            cvec<R> p = tT[c];
-#pragma unroll
-            for (int b = 0; b < RA; ++b) {
-                const cvec<R> q = cconjmul<R>(om[b * C + c], TW[tw_off(b) + (llo & ((1 << b) - 1))]);
-                const cvec<R> f = (llo >> b & 1) ? cmake<R>((R)1 - q.x, -q.y) : cmake<R>((R)1 + q.x, q.y);
-                p = cmul<R>(p, f);
-            }
-            v[0] = p;
-#pragma unroll
-            for (int bb = 0; bb < RB; ++bb) {
-                const cvec<R> w = om[(RA + bb) * C + c];
-                const int h = 1 << bb;
-                // a + a q and 2 a - (a + a q): six operations; the upper half
-                // of the nodes has the lower half's q, turned by a quarter
-                auto node = [&](int m, cvec<R> q) {
-                    const cvec<R> a = v[m];
-                    const R px = ffma(a.x, q.x, ffma(-a.y, q.y, a.x)), py = ffma(a.x, q.y, ffma(a.y, q.x, a.y));
-                    v[m] = cmake<R>(px, py);
-                    v[m + h] = cmake<R>(ffma((R)2, a.x, -px), ffma((R)2, a.y, -py));
-                };
-#pragma unroll
-                for (int m = 0; m < (h + 1) / 2; ++m) {
-                    const cvec<R> q = cconjmul<R>(w, TW[tw_off(RA + bb) + llo + (m << RA)]);
-                    node(m, q);
-                    if (bb > 0) node(m + h / 2, cmake<R>(q.y, -q.x));
-                }
-            }
+            product_line<R, RA, RB>(v, tT[c], om + c, C, TW, llo);
             // |P|^2 summed over the line in the amplitude precision, weighted by
             // s_y^2 for P(a = 1), by s_y for z and by one for the norm (the
             // rotation keeps each pair's norm); |beta|^2 and the sums over lines
@@ -536,7 +473,7 @@ __device__ __forceinline__ void queue_item(int ph, const PipeArgs &A, const Pipe
                                            uint64_t slot) {
     constexpr int RA = (G + 1) / 2, RB = G / 2;     // the register split of dispatch_g
     if (ph == 0)
-        pipe_a_body<R, RA, RB, 256>(A, S, j0, o);
+        pipe_a_body<R, RA, RB, 256>(A, S, j0);
     else
         pipe_b_body<R, RA, RB, 256, true>(A, S, j0, o, slot);
 }
@@ -722,8 +659,8 @@ static int default_cl(int n_s, int g, size_t elem) {
 
 static size_t pipe_lds(int which, int cl, int g, size_t e) {
     const size_t C = (size_t)1 << cl;
-    if (which == 0)        // the tile, the twiddles, the column phases and constants (FP64)
-        return ((C << g) + ((size_t)1 << g) + (size_t)(g + 1) * C) * sizeof(double2);
+    if (which == 0)        // the twiddles and the column phases (FP64)
+        return (((size_t)1 << g) + (size_t)g * C) * sizeof(double2);
     // the twiddles, two rotation tables, two sets of column data and of line sums
     return ((size_t)1 << g) * e + 2 * ((size_t)1 << g) * (e / 2) + 2 * (size_t)(g + 2) * C * e +
            2 * (C << ((g + 1) / 2)) * (e / 2);
@@ -752,9 +689,7 @@ static void make_plan(PipePlan &P, int n_s, int n_c, size_t e, const int cl[2], 
     for (int w = 0; w < 2; ++w) {
         const int g = w == 1 ? A.g2 : A.g1;
         P.A[w] = A;
-        int c = cl[w];
-        // saved entries may hold wider k_pipe_a tiles than fit in FP64
-        while (w == 0 && c > 0 && pipe_lds(0, c, g, e) > (size_t)PIPE_LDS_LIMIT) --c;
+        const int c = cl[w];
         P.A[w].cl = c;
         P.nt[w] = nt[w];
         // k_pipe_a writes the G1 table only (G2 value 0)
