@@ -49,6 +49,7 @@ typedef double doublex4 __attribute__((ext_vector_type(4)));
 
 constexpr int BLK_MAX_THREADS = 512;
 constexpr int BLK_EXT = 2;             // index bits outside the tile a block may depend on
+constexpr int BLK_UNIT_BITS = 5;       // line bits above the 16 lines of a unit, at most
 
 struct BPass {
     TileLayout t;
@@ -63,7 +64,7 @@ struct BPass {
 struct BBlock {
     uint32_t lb[4];        // amplitude index bit i of the block
     uint32_t cb[4];        // line bits 0..3: the 16 lines of a unit
-    uint32_t ub[5];        // line bits 4..8: the unit
+    uint32_t ub[BLK_UNIT_BITS];   // line bits 4..8: the unit
     int next;              // external index bits
     int ebit[BLK_EXT];
     int mat;               // first of its 2^next matrices
@@ -686,6 +687,11 @@ static sv_status run_blocks_impl(sv_state s, const std::vector<PGate> &gates, in
 }
 
 sv_status run_blocks(sv_state s, const std::vector<PGate> &gates, int k, int c) {
+    // A pinned configuration comes here unchecked.  A block has 4 amplitude, 4
+    // lane and at most 5 unit bits (BBlock::ub), so 13 in all, for both types.
+    k = std::min(k, s->n);
+    if (k < 8 || k > 8 + BLK_UNIT_BITS) return fail(SV_EINVAL, "block tile of %d qubits", k);
+    if (!blocks_eligible(s, gates)) return fail(SV_EINVAL, "a circuit that does not run as blocks of four qubits");
     static bool lds_at_0 = [] {
         bool ok = true;
         for (const void *f : {(const void *)k_blocks<float>, (const void *)k_blocks<double>}) {
@@ -697,8 +703,6 @@ sv_status run_blocks(sv_state s, const std::vector<PGate> &gates, int k, int c) 
         return ok;
     }();
     if (!lds_at_0) return fail(SV_EDEVICE, "the block-pass kernels need their tile at LDS address 0");
-    k = std::min(k, s->n);
-    if (k < 8 || ((size_t)amp_bytes(s->dt) << k) > 131072) return fail(SV_EINVAL, "block tile of %d qubits", k);
     c = std::max(0, std::min(c, k - 4));
     return s->dt == SV_C64 ? run_blocks_impl<float>(s, gates, k, c) : run_blocks_impl<double>(s, gates, k, c);
 }
