@@ -138,7 +138,10 @@ typedef struct {
  * passes as blocks instead: the product of the gates on four qubits as one
  * dense 16 x 16 matrix on the matrix cores.  A pass runs as many workgroups as the device holds at
  * once, each walking a strided run of tiles; SV_FUSED_PERSIST=0 launches one
- * workgroup per tile instead (same results, bit for bit). */
+ * workgroup per tile instead (same results, bit for bit).
+ * The gate list is staged from the host, so the call cannot be captured in a
+ * graph: SV_EUNSUPPORTED while the state's stream is being captured, with
+ * nothing recorded.  (The solves from a host b refuse capture alike.) */
 sv_status sv_apply_circuit(sv_state s, const sv_gate *gates, int n_gates, int max_local);
 
 /* Number of fused passes sv_apply_circuit would run (planning only). */

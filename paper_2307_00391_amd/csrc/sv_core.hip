@@ -75,9 +75,20 @@ sv_status upload(sv_state s, void *dst, const void *src, size_t bytes) {
     return SV_OK;
 }
 
+// The staging buffer is written anew by the next call, so a recorded copy out of
+// it would read that call's plan when the graph is replayed, and plan_ev would
+// stay an event of the capture: such calls are refused before they record anything.
+sv_status refuse_capture(sv_state s) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s->stream, &cap) != hipSuccess) (void)hipGetLastError();
+    if (cap != hipStreamCaptureStatusNone) return fail(SV_EUNSUPPORTED, "the call stages host data and cannot be captured");
+    return SV_OK;
+}
+
 // src in the plan staging buffer, which the device can read; the host waits only
 // for the previous user of the buffer.  Record plan_ev behind the last reader.
 sv_status stage_plan(sv_state s, const void *src, size_t bytes, void **staged) {
+    SV_TRY(refuse_capture(s));
     if (!s->plan_ev) SV_HIP(hipEventCreateWithFlags(&s->plan_ev, hipEventDisableTiming));
     else SV_HIP(hipEventSynchronize(s->plan_ev));
     if (s->plan_bytes < bytes) {

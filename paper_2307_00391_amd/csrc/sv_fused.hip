@@ -905,6 +905,7 @@ sv_status sv_apply_circuit(sv_state s, const sv_gate *gates, int n_gates, int ma
     if (!n_gates) return SV_OK;
     std::vector<PGate> pg;
     SV_TRY(to_pgates(s, gates, n_gates, pg));
+    SV_TRY(refuse_capture(s));
     int k = clamp_k(s, max_local);
     if (k < 3) return fail(SV_EUNSUPPORTED, "state too small for fused passes");
     int c = std::max(0, std::min(low_bits_for(s->dt), k - 2)), rb = 0;

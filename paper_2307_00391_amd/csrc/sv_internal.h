@@ -72,6 +72,8 @@ sv_status norm2_device(sv_state s, uint64_t mask, uint64_t value, double *dev_ou
 sv_status init_b_device(sv_state s, const double2 *b, int n_s, int n_clock_superpose, double scale);
 // the amplitudes with (i & mask) == value divided by sqrt(*prob), as FP64 on the device
 sv_status gather_device(sv_state s, uint64_t mask, uint64_t value, const double *prob, double2 *out);
+// SV_EUNSUPPORTED while the state's stream is being captured
+sv_status refuse_capture(sv_state s);
 // stream-ordered copy to the device through the state's plan staging; returns without waiting
 sv_status stage_plan(sv_state s, const void *src, size_t bytes, void **staged);
 sv_status upload_plan(sv_state s, void *dst, const void *src, size_t bytes);
