@@ -805,9 +805,10 @@ void pipe_config_batch(int n_s, int n_c, size_t elem, int cl[2]) {
 
 template <typename R>
 sv_status pipe_run(sv_state s, int n_s, int n_c, bool sgn, uint64_t gcut, const PipeHead &head, const double2 *beta, const double *lam,
-                   double T0, double *part, double *zpart, uint64_t *nparts) {
+                   double T0, DevBuf &part, double *zpart, uint64_t *nparts) {
     const size_t e = sizeof(cvec<R>);
-    PipeSolve one{s->data, beta, lam, T0, part, zpart};
+    SV_TRY(part.ensure(2 * pipe_b_blocks(n_s, n_c, e) * sizeof(double)));     // every candidate of the tuner
+    PipeSolve one{s->data, beta, lam, T0, (double *)part.p, zpart};
     int cl[2], nt[2];
     SV_TRY(pipe_config<R>(s->stream, n_s, n_c, one, cl, nt));
     PipePlan P;
@@ -817,13 +818,17 @@ sv_status pipe_run(sv_state s, int n_s, int n_c, bool sgn, uint64_t gcut, const 
         P.A[w].gcut = gcut;
     }
     *nparts = (uint64_t)P.grid[1].x * P.grid[1].y;
+    // a default of few columns per tile (complex128, 2^10 clock values per group)
+    // or a pinned one has more tiles than the tuner's candidates
+    SV_TRY(part.ensure(2 * *nparts * sizeof(double)));
+    one.part = (double *)part.p;
     for (int w = 0; w < 2; ++w) SV_TRY(run_one<R>(s->stream, P, w, one, head));
     return SV_OK;
 }
 template sv_status pipe_run<float>(sv_state, int, int, bool, uint64_t, const PipeHead &, const double2 *,
-                                   const double *, double, double *, double *, uint64_t *);
+                                   const double *, double, DevBuf &, double *, uint64_t *);
 template sv_status pipe_run<double>(sv_state, int, int, bool, uint64_t, const PipeHead &, const double2 *,
-                                    const double *, double, double *, double *, uint64_t *);
+                                    const double *, double, DevBuf &, double *, uint64_t *);
 
 // ---------------------------------------------------------------------------
 // the work queues' plan: items of about 2^15 amplitudes (runs of consecutive

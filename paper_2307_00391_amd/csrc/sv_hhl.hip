@@ -46,7 +46,7 @@ template <typename R>
 sv_status ctrl_unitary_impl(sv_state s, const cvec<R> *U, int m, int ctrl, int ctrl_val, int adjoint);
 template <typename R>
 sv_status pipe_run(sv_state s, int n_s, int n_c, bool sgn, uint64_t gcut, const PipeHead &head,
-                   const double2 *beta, const double *lam, double T0, double *part, double *zpart, uint64_t *nparts);
+                   const double2 *beta, const double *lam, double T0, DevBuf &part, double *zpart, uint64_t *nparts);
 
 // --------------------------------------------------------------------------
 // small FP64 kernels
@@ -1018,15 +1018,12 @@ static sv_status eig_frame_run(sv_state s, const EigFrame &E, Workspace &w, cons
     if (pipe) {
         // fused two-kernel pipeline: (state + inverse QFT on the low clock bits),
         // (inverse QFT high + rotation + the uncompute projected on clock 0)
-        const uint64_t nbp = pipe_b_blocks(n_s, n_c, sizeof(cvec<R>));
         const int rows = pipe_rows(n_c);
-        SV_TRY(need(w.part, 2 * nbp * sizeof(double)));
         SV_TRY(need(w.zpart, (size_t)rows * N * sizeof(double)));
         uint64_t nparts = 0;
         SV_TRY(pipe_run<R>(s, n_s, n_c, sgn, gcut, head, (const double2 *)w.beta.p, (const double *)E.lam_dev.p, T0,
-                           (double *)w.part.p, (double *)w.zpart.p, &nparts));
+                           w.part, (double *)w.zpart.p, &nparts));
         if (!dev && small) SV_HIP(hipEventRecord(s->plan_ev, st));
-        if (nparts > nbp) return fail(SV_EDEVICE, "pipeline partial count exceeds its buffer");
         const int nc = eig_chunks(nparts);
         if (!dev && small && (uint64_t)rows * N <= EIG_TAIL) {
             // the results go straight into the download buffer
