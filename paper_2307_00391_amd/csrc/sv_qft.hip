@@ -56,6 +56,7 @@ struct QftStep {
 
 struct QftTile {
     uint64_t nl_mask, fix_val;      // tile number deposit, fixed bits
+    uint64_t tile0;                 // first tile of this launch
     int k;                          // tile bits: [0, c) | r1 bits at p1 | r2 bits at p2
     int c, p1, r1, p2, r2;
     int lo, m;                      // the register
@@ -314,17 +315,16 @@ __device__ __forceinline__ void tile_out(cvec<R> *__restrict__ psi, const QftTil
 // XCD takes a contiguous eighth of the tiles, so that the tiles that share
 // memory pages and 256-byte channels run on one L2 (2.09 -> 1.99 ms for a
 // 24-qubit transform on 2^27 complex64 amplitudes).
-__device__ __forceinline__ uint64_t tile_number() {
-    const uint64_t b = (uint64_t)blockIdx.x + (uint64_t)blockIdx.y * gridDim.x;
-    if (gridDim.y > 1 || (gridDim.x & 7u)) return b;
-    return (b & 7u) * (gridDim.x >> 3) + (b >> 3);
+__device__ __forceinline__ uint64_t tile_number(const QftTile &A) {
+    const uint64_t b = blockIdx.x;
+    return A.tile0 + ((gridDim.x & 7u) ? b : (b & 7u) * (gridDim.x >> 3) + (b >> 3));
 }
 
 // one pass: the steps of one group on every tile
 template <typename R, int SGN, bool DIT>
 __global__ __launch_bounds__(QFT_MAX_THREADS) void k_qft_pass(cvec<R> *__restrict__ psi, QftTile A) {
     extern __shared__ __align__(16) unsigned char smem[];
-    const uint64_t tl = tile_number();
+    const uint64_t tl = tile_number(A);
     uint64_t base = pdep64(tl, A.nl_mask) | A.fix_val;
     uint64_t base2 = base;
     if (A.mid_w) {
@@ -375,7 +375,7 @@ template <typename R>
 __global__ __launch_bounds__(QFT_MAX_THREADS) void k_spectral_mid(cvec<R> *__restrict__ psi, QftTile A, QftTile D,
                                                                   int anc_pos) {
     extern __shared__ __align__(16) unsigned char smem[];
-    const uint64_t tl = tile_number();
+    const uint64_t tl = tile_number(A);
     const uint64_t base = pdep64(tl, A.nl_mask);
     if (!A.direct_in) {
         tile_in<R>(psi, A, base, smem, threadIdx.x, blockDim.x);
@@ -512,11 +512,19 @@ static sv_status group_tile(sv_state s, int lo, int m, int j0, int jn, int kmax,
     return SV_OK;
 }
 
-static void block_of(const QftTile &A, dim3 &grid, unsigned &nt, uint64_t tiles) {
+static unsigned block_of(const QftTile &A) {
     const uint32_t lines = A.k > 4 ? 1u << (A.k - 4) : 1u;
-    nt = lines < 64 ? 64 : lines > (uint32_t)QFT_MAX_THREADS ? (unsigned)QFT_MAX_THREADS : lines;
+    unsigned nt = lines < 64 ? 64 : lines > (uint32_t)QFT_MAX_THREADS ? (unsigned)QFT_MAX_THREADS : lines;
     if (A.mid_w > 1) nt = nt * 2 > (unsigned)QFT_MAX_THREADS ? (unsigned)QFT_MAX_THREADS : nt * 2;
-    grid = tiles <= 0x7fffffffull ? dim3((unsigned)tiles) : dim3(1u << 30, (unsigned)(tiles >> 30));
+    return nt;
+}
+
+// Launches of at most 2^22 workgroups: a grid holds less than 2^32 threads, which
+// small tiles (a small max_local) on a large state would exceed.
+template <typename F>
+static void each_grid(QftTile &A, F launch) {
+    const uint64_t tiles = 1ull << popcount64(A.nl_mask), most = 1ull << 22;
+    for (A.tile0 = 0; A.tile0 < tiles; A.tile0 += most) launch(dim3((unsigned)std::min(tiles, most)));
 }
 
 static size_t tile_bytes(const QftTile &A, sv_dtype dt) {
@@ -524,15 +532,14 @@ static size_t tile_bytes(const QftTile &A, sv_dtype dt) {
 }
 
 template <typename R, int SGN, bool DIT>
-static sv_status launch_qft(sv_state s, const QftTile &A) {
+static sv_status launch_qft(sv_state s, QftTile A) {
     const uint64_t tiles = 1ull << popcount64(A.nl_mask);
-    dim3 grid;
-    unsigned nt;
-    block_of(A, grid, nt, tiles);
     const bool in_regs = A.nsteps == 1 && A.direct_in && A.direct_out;     // never touches LDS
     const size_t lds = in_regs ? 0 : tile_bytes(A, s->dt) * (A.mid_w > 1 ? 2 : 1);
     TraceScope _ts(s->stream, "qft_pass", 2.0 * (double)(tiles << A.k) * sizeof(cvec<R>), 0.0);
-    hipLaunchKernelGGL((k_qft_pass<R, SGN, DIT>), grid, dim3(nt), lds, s->stream, (cvec<R> *)s->data, A);
+    each_grid(A, [&](dim3 grid) {
+        hipLaunchKernelGGL((k_qft_pass<R, SGN, DIT>), grid, dim3(block_of(A)), lds, s->stream, (cvec<R> *)s->data, A);
+    });
     SV_HIP(hipGetLastError());
     return SV_OK;
 }
@@ -668,19 +675,17 @@ sv_status sv_spectral_derivative(sv_state s, int q_lo, int m, int anc, int max_l
     QftTile D = A;
     plan_steps(A, s->dt, 0, g, false);
     plan_steps(D, s->dt, 0, g, true);
-    const uint64_t tiles = 1ull << popcount64(A.nl_mask);
-    dim3 grid;
-    unsigned nt;
-    block_of(A, grid, nt, tiles);
     {
         TraceScope ts(s->stream, "spectral_mid", 2.0 * (double)dim_of(s->n) * amp_bytes(s->dt), 0.0);
         const size_t lds = tile_bytes(A, s->dt);
-        if (s->dt == SV_C64)
-            hipLaunchKernelGGL(k_spectral_mid<float>, grid, dim3(nt), lds, s->stream, (float2 *)s->data, A, D,
-                               tile_position(A, anc));
-        else
-            hipLaunchKernelGGL(k_spectral_mid<double>, grid, dim3(nt), lds, s->stream, (double2 *)s->data, A, D,
-                               tile_position(A, anc));
+        const dim3 nt(block_of(A));
+        const int ap = tile_position(A, anc);
+        each_grid(A, [&](dim3 grid) {
+            if (s->dt == SV_C64)
+                hipLaunchKernelGGL(k_spectral_mid<float>, grid, nt, lds, s->stream, (float2 *)s->data, A, D, ap);
+            else
+                hipLaunchKernelGGL(k_spectral_mid<double>, grid, nt, lds, s->stream, (double2 *)s->data, A, D, ap);
+        });
         SV_HIP(hipGetLastError());
     }
     return run_groups(s, q_lo, m, g, m - g, 1, true, 0, 0, kmax);
