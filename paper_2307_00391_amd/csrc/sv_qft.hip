@@ -186,6 +186,10 @@ __device__ __forceinline__ void radix_line(cvec<R> (&v)[16], const QftStep &S, u
             }
         }
     };
+    // scaled first: the step's sums then stay below 2^(RA/2) times the largest
+    // amplitude, where the unscaled ones reach 2^RA times it and overflow earlier
+#pragma unroll
+    for (int e = 0; e < 16; ++e) v[e] = cmake<R>(v[e].x * sc, v[e].y * sc);
     if (DIT) twiddle();
 #pragma unroll
     for (int q = 0; q < RA; ++q) {
@@ -207,8 +211,6 @@ __device__ __forceinline__ void radix_line(cvec<R> (&v)[16], const QftStep &S, u
             }
         }
     }
-#pragma unroll
-    for (int e = 0; e < 16; ++e) v[e] = cmake<R>(v[e].x * sc, v[e].y * sc);
     if (!DIT) twiddle();
 }
 
