@@ -8,7 +8,7 @@
 // them.  A block costs the same whatever it holds, and a slanted stack of a
 // layered circuit puts 6 to 10 gates in it.  6 layers of U3 and a CNOT ladder
 // on 28 qubits (330 gates, complex64): 20.1 ms as fused passes, 12.6 ms as 50
-// blocks in 6 passes; 8 layers on 14 qubits (complex128): 304 and 104 us.
+// blocks in 6 passes; 8 layers on 14 qubits (complex128): 304 and 102 us.
 //
 // What bounds it: the issue of vector and matrix instructions, 61 and 12 per
 // 16 lines (counters: a SIMD's matrix core is busy 35 % of the pass of 16
@@ -26,8 +26,11 @@
 //
 // A gate whose controls lie outside the tile makes the block's matrix depend
 // on at most two index bits that are fixed in a tile: the block holds a matrix
-// for each of their values.  All matrices are multiplied up in FP64 on the
-// device, one thread per column.
+// for each of their values.  All matrices are multiplied up on the device.
+//
+// Error against extended precision, relative to the fused passes' (rms of 3
+// seeds on 8 to 14 qubits): complex64 0.41-0.47 on layered circuits and
+// 0.67-0.77 on mixed ones, complex128 0.69-0.74 and 0.93-1.02.
 //
 // A tile with an infinite or NaN amplitude takes a scalar path that skips the
 // entries no gate of the block connects, so that such amplitudes spread no
@@ -91,84 +94,131 @@ __device__ __forceinline__ uint32_t bf16_round(float x) {      // finite x
     return (u + 0x7fffu + (u >> 16 & 1u)) >> 16;
 }
 
-// One wavefront per matrix, the matrix in LDS: an op's pairs of rows are spread
-// over the lanes.  (One thread per column with its 16 entries in registers took
-// 28 us for the circuits below, mostly instruction fetch: every op type was
-// unrolled over every register.)
+// sum_i c_i (vh_i + vl_i) of N terms as an unevaluated sum (hi, lo): products by
+// FMA, sums with their rounding errors (Knuth's two-sum).  Nothing may be
+// contracted here beyond the FMAs that are written.
+template <int N>
+__device__ __forceinline__ double2 dd_dot(const double (&c)[N], const double2 (&v)[N]) {
+#pragma clang fp contract(off)
+    double hi = 0.0, lo = 0.0;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const double p = c[i] * v[i].x, e = __builtin_fma(c[i], v[i].y, __builtin_fma(c[i], v[i].x, -p));
+        const double t = hi + p, z = t - hi;
+        lo += ((hi - (t - z)) + (p - z)) + e;
+        hi = t;
+    }
+    const double t = hi + lo;
+    return make_double2(t, lo - (t - hi));
+}
+
+// A matrix entry as the build holds it.  complex64 multiplies its matrices up in
+// FP64 and rounds once; complex128 in pairs of FP64, since what a product of 5
+// gates in FP64 has lost by then is as much as the gates themselves lose when
+// they are applied one by one.
+template <typename R> struct Entry;
+template <> struct Entry<float> {
+    double2 v;
+    __device__ __forceinline__ Entry(double x) : v(make_double2(x, 0.0)) {}
+    __device__ __forceinline__ Entry partner(int sh) const {
+        Entry e(0.0);
+        e.v = make_double2(__shfl_xor(v.x, sh, 64), __shfl_xor(v.y, sh, 64));
+        return e;
+    }
+    // d * this + o * w
+    __device__ __forceinline__ void mix(double2 d, double2 o, const Entry &w) { v = cmac2<double>(d, v, o, w.v); }
+    __device__ __forceinline__ void scale(double2 d) { v = cmul<double>(v, d); }
+    __device__ __forceinline__ double2 value() const { return v; }
+};
+template <> struct Entry<double> {
+    double2 re, im;        // (hi, lo)
+    __device__ __forceinline__ Entry(double x) : re(make_double2(x, 0.0)), im(make_double2(0.0, 0.0)) {}
+    __device__ __forceinline__ Entry partner(int sh) const {
+        Entry e(0.0);
+        e.re = make_double2(__shfl_xor(re.x, sh, 64), __shfl_xor(re.y, sh, 64));
+        e.im = make_double2(__shfl_xor(im.x, sh, 64), __shfl_xor(im.y, sh, 64));
+        return e;
+    }
+    __device__ __forceinline__ void mix(double2 d, double2 o, const Entry &w) {
+        const double2 r = dd_dot<4>({d.x, -d.y, o.x, -o.y}, {re, im, w.re, w.im});
+        im = dd_dot<4>({d.y, d.x, o.y, o.x}, {re, im, w.re, w.im});
+        re = r;
+    }
+    __device__ __forceinline__ void scale(double2 d) {
+        const double2 r = dd_dot<2>({d.x, -d.y}, {re, im});
+        im = dd_dot<2>({d.y, d.x}, {re, im});
+        re = r;
+    }
+    __device__ __forceinline__ double2 value() const { return make_double2(re.x, im.x); }
+};
+
+// One workgroup per matrix, an entry per thread: wave w holds columns 4 w ..
+// 4 w + 3, lane = row + 16 (column % 4), so an op's other row is the lane that
+// differs in the target's bit.  The operations come through LDS in chunks (one
+// memory latency each would be most of the kernel).  14-qubit circuits,
+// complex128 (8 layers and 80 mixed gates, mean): 9.2 us in FP64 pairs; with the
+// matrix in LDS, a wave per matrix and a barrier per op 12.0 us in FP64.
 template <typename R>
-__global__ __launch_bounds__(64) void k_block_build(const BBuild *__restrict__ todo, const ROp *__restrict__ ops,
-                                                    unsigned char *__restrict__ mats) {
-    __shared__ double2 u[16][17];
-    // the operations come through LDS in chunks: one memory latency each would
-    // be most of the kernel (19 us for the 31 blocks of a 14-qubit circuit)
+__global__ __launch_bounds__(256) void k_block_build(const BBuild *__restrict__ todo, const ROp *__restrict__ ops,
+                                                     unsigned char *__restrict__ mats) {
     constexpr int CH = 32;
     static_assert(sizeof(ROp) % 8 == 0, "operations are copied as 8-byte words");
     __shared__ uint64_t chunk[CH * sizeof(ROp) / 8];
     const BBuild B = todo[blockIdx.x];
-    const int lane = threadIdx.x;
-    for (int i = lane; i < 256; i += 64) u[i >> 4][i & 15] = make_double2((i >> 4) == (i & 15) ? 1.0 : 0.0, 0.0);
-    uint32_t reach = 1u << (lane & 15);       // rows reached by column lane % 16
+    const int lane = threadIdx.x & 63, r = lane & 15, c = threadIdx.x >> 4;
+    Entry<R> v(r == c ? 1.0 : 0.0);
+    bool reach = r == c;                      // column c reaches row r
     for (int o = 0; o < B.nops; ++o) {
         if (o % CH == 0) {
             __syncthreads();
             const int n = (int)(sizeof(ROp) / 8) * (B.nops - o < CH ? B.nops - o : CH);
             const uint64_t *src = (const uint64_t *)(ops + B.op_off + o);
-            for (int i = lane; i < n; i += 64) chunk[i] = src[i];
+            for (int i = threadIdx.x; i < n; i += 256) chunk[i] = src[i];
             __syncthreads();
         }
         const ROp &f = ((const ROp *)chunk)[o % CH];
         if ((B.base & f.gmask) != f.gval) continue;
+        const bool on = f.onm >> r & 1u;
         if (f.type == OP_PHASE) {
-            const double2 ph = make_double2(f.u[0], f.u[1]);
-            for (int i = lane; i < 256; i += 64)
-                if (f.onm >> (i >> 4) & 1u) u[i >> 4][i & 15] = cmul<double>(u[i >> 4][i & 15], ph);
-        } else {
-            const int sh = 1 << f.j0;
-            for (int i = lane; i < 128; i += 64) {
-                const int m = (int)insert0((uint32_t)i >> 4, f.j0), p = m | sh, c = i & 15;
-                if (!(f.onm >> m & 1u)) continue;
-                const double2 a = u[m][c], b = u[p][c];
-                if (f.type == OP_X) {
-                    u[m][c] = b;
-                    u[p][c] = a;
-                } else {
-                    u[m][c] = cmac2<double>(make_double2(f.u[0], f.u[1]), a, make_double2(f.u[2], f.u[3]), b);
-                    u[p][c] = cmac2<double>(make_double2(f.u[4], f.u[5]), a, make_double2(f.u[6], f.u[7]), b);
-                }
-            }
-            const uint32_t even = f.j0 == 0 ? 0x5555u : f.j0 == 1 ? 0x3333u : f.j0 == 2 ? 0x0f0fu : 0x00ffu;
-            const uint32_t on = f.onm & even, a = reach & on, b = reach >> sh & on;
-            if (f.type == OP_X) reach = (reach & ~(on | on << sh)) | b | a << sh;
-            else reach |= (a | b) | (a | b) << sh;
+            if (on) v.scale(make_double2(f.u[0], f.u[1]));
+            continue;
         }
-        __syncthreads();
+        const int sh = 1 << f.j0;
+        const Entry<R> w = v.partner(sh);
+        const bool wreach = __shfl_xor((int)reach, sh, 64) != 0;
+        if (!on) continue;
+        if (f.type == OP_X) {
+            v = w;
+            reach = wreach;
+        } else {
+            const int q = r & sh ? 6 : 0;
+            v.mix(make_double2(f.u[q], f.u[q + 1]), make_double2(f.u[q ? 4 : 2], f.u[q ? 5 : 3]), w);
+            reach |= wreach;
+        }
     }
-    if (!B.nops) __syncthreads();
     unsigned char *M = mats + (size_t)blockIdx.x * MatBytes<R>::stride;
-    for (int i = lane; i < 256; i += 64) {
-        const int r = i >> 4, c = i & 15;
-        const double2 v = u[r][c];
-        if (sizeof(R) == 4) {
-            uint32_t *part = (uint32_t *)M;
-            float x = (float)v.x, y = (float)v.y;
-            ((float2 *)(M + MatBytes<R>::full))[i] = make_float2(x, y);
-            // row r of U: rows 2 (r % 8) and 2 (r % 8) + 1 of tile r / 8; column c: K
-            // slots 2 ks, 2 ks + 1 of lane group gc
-            const int tile = r >> 3, row = 2 * (r & 7), gc = (c >> 1) & 3, ks = (c & 1) | (c >> 3 << 1);
+    const double2 z = v.value();
+    if (sizeof(R) == 4) {
+        uint32_t *part = (uint32_t *)M;
+        float x = (float)z.x, y = (float)z.y;
+        ((float2 *)(M + MatBytes<R>::full))[r * 16 + c] = make_float2(x, y);
+        // row r of U: rows 2 (r % 8) and 2 (r % 8) + 1 of tile r / 8; column c: K
+        // slots 2 ks, 2 ks + 1 of lane group gc
+        const int tile = r >> 3, row = 2 * (r & 7), gc = (c >> 1) & 3, ks = (c & 1) | (c >> 3 << 1);
 #pragma unroll
-            for (int p = 0; p < 3; ++p) {
-                const uint32_t hx = bf16_round(x), hy = bf16_round(y);
-                x -= __builtin_bit_cast(float, hx << 16);
-                y -= __builtin_bit_cast(float, hy << 16);
-                uint32_t *at = part + (tile * 3 + p) * 256 + (gc * 16 + row) * 4 + ks;
-                at[0] = hx | (hy ^ 0x8000u) << 16;        // real row: Ur, -Ui
-                at[4] = hy | hx << 16;                    // imaginary row: Ui, Ur
-            }
-        } else {
-            ((double2 *)M)[(c >> 2) * 64 + (c & 3) * 16 + r] = v;
+        for (int p = 0; p < 3; ++p) {
+            const uint32_t hx = bf16_round(x), hy = bf16_round(y);
+            x -= __builtin_bit_cast(float, hx << 16);
+            y -= __builtin_bit_cast(float, hy << 16);
+            uint32_t *at = part + (tile * 3 + p) * 256 + (gc * 16 + row) * 4 + ks;
+            at[0] = hx | (hy ^ 0x8000u) << 16;        // real row: Ur, -Ui
+            at[4] = hy | hx << 16;                    // imaginary row: Ui, Ur
         }
+    } else {
+        ((double2 *)M)[(c >> 2) * 64 + (c & 3) * 16 + r] = z;
     }
-    if (lane < 16) ((uint32_t *)(M + MatBytes<R>::reach))[lane] = reach;
+    const uint64_t all = __ballot(reach);             // rows of the wave's four columns
+    if (r == 0) ((uint32_t *)(M + MatBytes<R>::reach))[c] = (uint32_t)(all >> (lane & 48)) & 0xffffu;
 }
 
 // the matrix operands of a wavefront's lane
@@ -243,24 +293,30 @@ __device__ __forceinline__ void block_lines(const Operand<float> &A, const Unit<
 #pragma unroll
         for (int i = 0; i < 4; ++i) v[n][i] = make_float2(acc[n][i >> 1][2 * (i & 1)], acc[n][i >> 1][2 * (i & 1) + 1]);
 }
+// Each result is the sum of four products' worth of columns per k step, the steps
+// added at the end in pairs: one chain over all 32 products loses up to 1.35
+// times what the gates lose one by one (4 to 5 gates per block), four chains
+// with the matrices above 0.7 to 0.9 times.
 template <int NU>
 __device__ __forceinline__ void block_lines(const Operand<double> &A, const Unit<double> (&x)[NU], double2 (&v)[NU][4]) {
-    doublex4 re[NU], im[NU];
 #pragma unroll
-    for (int n = 0; n < NU; ++n) re[n] = im[n] = doublex4{0, 0, 0, 0};
+    for (int n = 0; n < NU; ++n) {
+        doublex4 re[4], im[4];
 #pragma unroll
-    for (int s = 0; s < 4; ++s)
-#pragma unroll
-        for (int n = 0; n < NU; ++n) {
-            re[n] = __builtin_amdgcn_mfma_f64_16x16x4f64(A.a[s].x, x[n].v[s].x, re[n], 0, 0, 0);
-            im[n] = __builtin_amdgcn_mfma_f64_16x16x4f64(A.a[s].x, x[n].v[s].y, im[n], 0, 0, 0);
-            re[n] = __builtin_amdgcn_mfma_f64_16x16x4f64(-A.a[s].y, x[n].v[s].y, re[n], 0, 0, 0);
-            im[n] = __builtin_amdgcn_mfma_f64_16x16x4f64(A.a[s].y, x[n].v[s].x, im[n], 0, 0, 0);
+        for (int s = 0; s < 4; ++s) {
+            const doublex4 zero = {0, 0, 0, 0};
+            re[s] = __builtin_amdgcn_mfma_f64_16x16x4f64(A.a[s].x, x[n].v[s].x, zero, 0, 0, 0);
+            im[s] = __builtin_amdgcn_mfma_f64_16x16x4f64(A.a[s].x, x[n].v[s].y, zero, 0, 0, 0);
         }
 #pragma unroll
-    for (int n = 0; n < NU; ++n)
+        for (int s = 0; s < 4; ++s) {
+            re[s] = __builtin_amdgcn_mfma_f64_16x16x4f64(-A.a[s].y, x[n].v[s].y, re[s], 0, 0, 0);
+            im[s] = __builtin_amdgcn_mfma_f64_16x16x4f64(A.a[s].y, x[n].v[s].x, im[s], 0, 0, 0);
+        }
 #pragma unroll
-        for (int i = 0; i < 4; ++i) v[n][i] = make_double2(re[n][i], im[n][i]);
+        for (int i = 0; i < 4; ++i)
+            v[n][i] = make_double2((re[0][i] + re[1][i]) + (re[2][i] + re[3][i]), (im[0][i] + im[1][i]) + (im[2][i] + im[3][i]));
+    }
 }
 
 // The tile of an infinite or NaN amplitude: 16 lanes per line, one result row
@@ -277,17 +333,27 @@ __device__ __forceinline__ void block_careful(const BBlock &b, const unsigned ch
     for (uint32_t line = threadIdx.x >> 4; line < lines; line += blockDim.x >> 4) {
         uint32_t s0 = 0;
         for (int i = 0; i < 9; ++i) s0 ^= line >> i & 1u ? (i < 4 ? b.cb[i] : b.ub[i - 4]) : 0u;
-        cvec<R> acc = cmake<R>(0, 0);
-        bool any = false;
+        // added four columns at a time and in pairs, as on the fast path
+        auto add = [](cvec<R> &a, bool &any, cvec<R> b) {
+            a = any ? cmake<R>(a.x + b.x, a.y + b.y) : b;
+            any = true;
+        };
+        cvec<R> acc = cmake<R>(0, 0), half = acc, part = acc;
+        bool any = false, hany = false, pany = false;
 #pragma unroll 1
         for (int c = 0; c < 16; ++c) {
             const cvec<R> z = lds_ld<R>(slot(s0, c));
             const cvec<R> u = sizeof(R) == 4 ? ((const cvec<R> *)(M + MatBytes<R>::full))[r * 16 + c]
                                              : ((const cvec<R> *)M)[(c >> 2) * 64 + (c & 3) * 16 + r];
-            if (!(reach[c] >> r & 1u)) continue;
-            const cvec<R> p = u.x == (R)1 && u.y == (R)0 ? z : cmul<R>(u, z);
-            acc = any ? cmake<R>(acc.x + p.x, acc.y + p.y) : p;
-            any = true;
+            if (reach[c] >> r & 1u) add(part, pany, u.x == (R)1 && u.y == (R)0 ? z : cmul<R>(u, z));
+            if ((c & 3) == 3) {
+                if (pany) add(half, hany, part);
+                pany = false;
+            }
+            if ((c & 7) == 7) {
+                if (hany) add(acc, any, half);
+                hany = false;
+            }
         }
         lds_st<R>(slot(s0, r), acc);
     }
@@ -663,8 +729,11 @@ static sv_status run_blocks_impl(sv_state s, const std::vector<PGate> &gates, in
         return st;
     }
     unsigned char *mats = dev + blob.size();
-    hipLaunchKernelGGL(k_block_build<R>, dim3((unsigned)todo.size()), dim3(64), 0, s->stream,
-                       (const BBuild *)(dev + bp + bb), (const ROp *)(dev + bp + bb + bt), mats);
+    {
+        TraceScope _ts(s->stream, "block_build", (double)(bo + todo.size() * MatBytes<R>::stride), 0.0);
+        hipLaunchKernelGGL(k_block_build<R>, dim3((unsigned)todo.size()), dim3(256), 0, s->stream,
+                           (const BBuild *)(dev + bp + bb), (const ROp *)(dev + bp + bb + bt), mats);
+    }
     int cus = 0;
     (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, s->device);
     for (size_t i = 0; i < passes.size(); ++i) {

@@ -295,7 +295,8 @@ sv_status cols_build(sv_state ctx, ColPlan &p, DevBuf &buf, const std::vector<in
             map.resize(l.groups * 64, make_uint2(~0u, 0u));
             SV_TRY(upload(ctx, d + l.map, map.data(), map.size() * sizeof(uint2)));
             const uint64_t nb = l.groups << sp.at(n_c);
-            if (blocks + nb > 0x7fffffffull) return fail(SV_EUNSUPPORTED, "batch of too many columns");
+            // (a grid holds less than 2^32 threads)
+            if (blocks + nb >= 1ull << 24) return fail(SV_EUNSUPPORTED, "batch of too many columns");
             cls.push_back(ColClass{(const double *)(d + l.W), (const double *)(d + l.E), d + l.S, (const uint2 *)(d + l.map), n_c,
                                    sp.at(n_c), (uint32_t)blocks, (uint32_t)nb});
             blocks += nb;
