@@ -134,9 +134,9 @@ typedef struct {
  * state instead of g.  Gates are only moved past gates on disjoint qubits;
  * the result equals the in-order product.  max_local <= 0 lets the
  * autotuner choose k.  With max_local = 0, a circuit whose gates touch at most
- * four qubits each and not only permute or scale amplitudes may run its
- * passes as blocks instead: the product of the gates on four qubits as one
- * dense 16 x 16 matrix on the matrix cores.  A pass runs as many workgroups as the device holds at
+ * four qubits each, are unitary and not only permute or scale amplitudes may
+ * run its passes as blocks instead: the product of the gates on four qubits as
+ * one dense 16 x 16 matrix on the matrix cores.  A pass runs as many workgroups as the device holds at
  * once, each walking a strided run of tiles; SV_FUSED_PERSIST=0 launches one
  * workgroup per tile instead (same results, bit for bit).
  * The gate list is staged from the host, so the call cannot be captured in a

@@ -15,8 +15,9 @@
 // blocks, 0.196 ms per block on 28 qubits); a pass's HBM traffic hides behind
 // them from about four blocks on.
 //
-// complex64: both operands are split into three bf16 parts, x = h + m + l
-// exactly (each part is the rounded rest, 8 bits at a time), and the six
+// complex64: both operands are split into three bf16 parts, x = h + m + l (each
+// part is the rounded rest, 8 bits at a time; exact in the range BlkScale keeps
+// the amplitudes in and for matrix entries of 2^-110 and more), and the six
 // products h h, h m, m h, m m, h l, l h are accumulated in FP32, smallest
 // first, by v_mfma_f32_16x16x32_bf16: K = 32 is the 16 amplitudes' real and
 // imaginary parts, so one instruction forms the real parts of 16 lines.  What
@@ -32,8 +33,8 @@
 // seeds on 8 to 14 qubits): complex64 0.41-0.47 on layered circuits and
 // 0.67-0.77 on mixed ones, complex128 0.69-0.74 and 0.93-1.02.
 //
-// A tile with an infinite or NaN amplitude takes a scalar path that skips the
-// entries no gate of the block connects, so that such amplitudes spread no
+// A tile with an infinite, NaN or huge amplitude takes a scalar path that skips
+// the entries no gate of the block connects, so that such amplitudes spread no
 // further than the gates carry them.
 #include <math.h>
 #include <string.h>
@@ -319,7 +320,29 @@ __device__ __forceinline__ void block_lines(const Operand<double> &A, const Unit
     }
 }
 
-// The tile of an infinite or NaN amplitude: 16 lanes per line, one result row
+// The range of the fast path.  A tile's amplitudes are scaled up on the way in and
+// back on the way out.  complex64, by 2^24: the parts of an FP32 number are then
+// multiples of 2^-125, where the matrix cores flush what is below 2^-126 to zero
+// (unscaled, a state of amplitudes near 2^-115 came out with a relative error of
+// 3e-6, one near 2^-120 with 1e-4).  complex128, by 2^32: the products of
+// denormal amplitudes lose nothing before they are added.  Tiles with an
+// amplitude that is not finite or above 2^95 (complex128: 2^983), from which a
+// tile's norm could leave the range of the operands, take the careful path;
+// `probe` times such an amplitude, or the sum of such products, overflows.
+// The cost is 4 multiplications per amplitude and pass, below 1 %.
+template <typename R> struct BlkScale;
+template <> struct BlkScale<float> {
+    static constexpr float probe = 0x1p33f;
+    static __device__ __forceinline__ float2 in(float2 z) { return make_float2(z.x * 0x1p24f, z.y * 0x1p24f); }
+    static __device__ __forceinline__ float2 out(float2 z) { return make_float2(z.x * 0x1p-24f, z.y * 0x1p-24f); }
+};
+template <> struct BlkScale<double> {
+    static constexpr double probe = 0x1p41;
+    static __device__ __forceinline__ double2 in(double2 z) { return make_double2(z.x * 0x1p32, z.y * 0x1p32); }
+    static __device__ __forceinline__ double2 out(double2 z) { return make_double2(z.x * 0x1p-32, z.y * 0x1p-32); }
+};
+
+// A tile outside that range: 16 lanes per line, one result row
 // each, entry by entry over the entries the block's gates connect (an entry 1
 // copies).  A line's reads all come before its writes in the same wavefront.
 // Written for few registers: it shares the kernel with the fast path.
@@ -420,7 +443,7 @@ __global__ __launch_bounds__(BLK_MAX_THREADS, 2) void k_blocks(cvec<R> *__restri
         const uint64_t base = pdep64(tl, P.t.nl_mask);
         Operand<R> A, An;
         An.load(matrix(blocks[P.blk_off], base), lane);
-        R chk = 0;       // 0, or NaN once an amplitude is not finite
+        R chk = 0;       // not finite once an amplitude is not, or too large
         if (big) {
             for (uint32_t t0 = 0; t0 < T; t0 += nt * U) {
                 const uint64_t g0 = base | gthr | scatter_t(t0, c, r, hpos);
@@ -430,22 +453,27 @@ __global__ __launch_bounds__(BLK_MAX_THREADS, 2) void k_blocks(cvec<R> *__restri
                 for (int u = 0; u < U; ++u) buf[u] = psi[g0 | uoff(u)];
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
-                    chk = fma(buf[u].x, (R)0, chk);
-                    chk = fma(buf[u].y, (R)0, chk);
-                    lds_st<R>(s0 ^ uswz(u), buf[u]);
+                    chk = fma(buf[u].x, BlkScale<R>::probe, chk);
+                    chk = fma(buf[u].y, BlkScale<R>::probe, chk);
+                    lds_st<R>(s0 ^ uswz(u), BlkScale<R>::in(buf[u]));
                 }
             }
         } else {
             for (uint32_t t = threadIdx.x; t < T; t += nt) {
                 const cvec<R> z = psi[base | scatter_t(t, c, r, hpos)];
-                chk = fma(z.x, (R)0, chk);
-                chk = fma(z.y, (R)0, chk);
-                lds_st<R>(swz<R>(t) * (uint32_t)sizeof(cvec<R>), z);
+                chk = fma(z.x, BlkScale<R>::probe, chk);
+                chk = fma(z.y, BlkScale<R>::probe, chk);
+                lds_st<R>(swz<R>(t) * (uint32_t)sizeof(cvec<R>), BlkScale<R>::in(z));
             }
         }
-        if (chk != chk) *fl = 1;
+        if (!isfinite(chk)) *fl = 1;
         __syncthreads();
         const bool careful = __builtin_amdgcn_readfirstlane((int)*fl) != 0;
+        if (careful) {       // the amplitudes as they are, read again
+            for (uint32_t t = threadIdx.x; t < T; t += nt)
+                lds_st<R>(swz<R>(t) * (uint32_t)sizeof(cvec<R>), psi[base | scatter_t(t, c, r, hpos)]);
+            __syncthreads();
+        }
 
         for (int bi = 0; bi < P.nblk; ++bi) {
             const BBlock &b = blocks[P.blk_off + bi];
@@ -535,8 +563,10 @@ __global__ __launch_bounds__(BLK_MAX_THREADS, 2) void k_blocks(cvec<R> *__restri
             __syncthreads();
         }
         if (careful && threadIdx.x == 0) *fl = 0;
-
-        if (big) {
+        if (careful) {
+            for (uint32_t t = threadIdx.x; t < T; t += nt)
+                psi[base | scatter_t(t, c, r, hpos)] = lds_ld<R>(swz<R>(t) * (uint32_t)sizeof(cvec<R>));
+        } else if (big) {
             for (uint32_t t0 = 0; t0 < T; t0 += nt * U) {
                 const uint64_t g0 = base | gthr | scatter_t(t0, c, r, hpos);
                 const uint32_t s0 = (sthr ^ swz<R>(t0)) * (uint32_t)sizeof(cvec<R>);
@@ -544,11 +574,11 @@ __global__ __launch_bounds__(BLK_MAX_THREADS, 2) void k_blocks(cvec<R> *__restri
 #pragma unroll
                 for (int u = 0; u < U; ++u) buf[u] = lds_ld<R>(s0 ^ uswz(u));
 #pragma unroll
-                for (int u = 0; u < U; ++u) psi[g0 | uoff(u)] = buf[u];
+                for (int u = 0; u < U; ++u) psi[g0 | uoff(u)] = BlkScale<R>::out(buf[u]);
             }
         } else {
             for (uint32_t t = threadIdx.x; t < T; t += nt)
-                psi[base | scatter_t(t, c, r, hpos)] = lds_ld<R>(swz<R>(t) * (uint32_t)sizeof(cvec<R>));
+                psi[base | scatter_t(t, c, r, hpos)] = BlkScale<R>::out(lds_ld<R>(swz<R>(t) * (uint32_t)sizeof(cvec<R>)));
         }
         if (tl + gridDim.x < ntiles) __syncthreads();
     }
@@ -558,11 +588,20 @@ __global__ __launch_bounds__(BLK_MAX_THREADS, 2) void k_blocks(cvec<R> *__restri
 // host side
 // ---------------------------------------------------------------------------
 
+// both singular values 1, as far as the entries of a complex64 gate hold it
+static bool unitary_gate(const double (&u)[8]) {
+    const double a = u[0] * u[0] + u[1] * u[1] + u[2] * u[2] + u[3] * u[3], b = u[4] * u[4] + u[5] * u[5] + u[6] * u[6] + u[7] * u[7];
+    const double re = u[0] * u[4] + u[1] * u[5] + u[2] * u[6] + u[3] * u[7], im = u[1] * u[4] - u[0] * u[5] + u[3] * u[6] - u[2] * u[7];
+    return fabs(a - 1.0) < 1e-5 && fabs(b - 1.0) < 1e-5 && fabs(re) < 1e-5 && fabs(im) < 1e-5;
+}
+
+// (Gates that are not unitary take the vector passes: the range of the blocks'
+// operands rests on rows of norm 1.)
 bool blocks_eligible(sv_state s, const std::vector<PGate> &gates) {
     if (s->n < 8) return false;
     bool mixes = false;
     for (const PGate &g : gates) {
-        if (popcount64(g.qubits) > 4) return false;
+        if (popcount64(g.qubits) > 4 || (g.kind == 0 && !unitary_gate(g.u))) return false;
         mixes |= g.kind == 0;
     }
     return mixes;

@@ -223,7 +223,7 @@ void plan_earliest(const std::vector<PlanItem> &items, int cap, uint64_t base, i
                    std::vector<PlanWindow> &out);
 
 // ---- matrix-core passes (sv_blocks.hip) -------------------------------------
-// every gate fits a block of four qubits, and one at least mixes amplitudes
+// every gate is unitary and fits a block of four qubits, and one at least mixes amplitudes
 bool blocks_eligible(sv_state s, const std::vector<PGate> &gates);
 // passes and blocks they come to on tiles of k qubits with the lowest c in them
 int count_block_passes(const std::vector<PGate> &gates, int k, int c);
