@@ -8,6 +8,7 @@
 // MFMAs: re += ar br - ai bi, im += ar bi + ai br.
 #include <string.h>
 
+#include <algorithm>
 #include <string>
 #include <vector>
 
@@ -377,7 +378,7 @@ static sv_status cgemm_ks(hipStream_t st, const cvec<R> *in, cvec<R> *out, const
     const uint64_t wblocks = (wtiles + 3) / 4;
     // the tile shape: 64 x 64 per workgroup (0), 16 x 16 per wavefront (1), or
     // k in parts: 16 x 16 in four (2), 32 x 32 in two (3).  Tuned per shape by
-    // timing all on this call's operands (the product is out of place, so it
+    // timing them on this call's operands (the product is out of place, so it
     // can be run again), cached; without tuning, parts wherever the 64 x 64
     // tiles would not fill the chip, the smaller ones up to two per compute unit.
     const std::string key = std::string("cgemm/") + (sizeof(R) == 4 ? "c64/" : "c128/") + std::to_string(M) + "/" +
@@ -401,27 +402,37 @@ static sv_status cgemm_ks(hipStream_t st, const cvec<R> *in, cvec<R> *out, const
         return SV_OK;
     };
     std::vector<int> cached;
-    // (grids of at most 2^23 workgroups in x: threads per launch stay below 2^32)
+    // (grids of at most 2^22 workgroups in x: threads per launch stay below 2^32)
     const bool parts_ok = (M + 15) / 16 <= (1ull << 22) && N <= (1 << 19);
     int shape = gm * gn < 256 && parts_ok ? (wtiles <= 512 ? 2 : 3) : 0;
     if (tune_lookup(key, cached) && cached.size() == 1 && (cached[0] == 0 || cached[0] == 1 ||
                                                            (parts_ok && (cached[0] == 2 || cached[0] == 3)))) {
         shape = cached[0];
     } else if (autotune_enabled() && wblocks <= 0x7fffffffull) {
-        float best = 1e30f;
-        // the small shapes only where the large one leaves compute units short
-        // of work: on a large product a wavefront per tile takes many times longer
-        const bool all = gm * gn <= 4096 && parts_ok;
-        // products of a few microseconds: single timings differ by more than the
-        // shapes do, and a wrong pick is up to twice as slow (11 and 20 us)
-        for (int round = 0; round < (all ? 4 : 1); ++round)
-            for (int c = 0; c < (all ? 4 : 2); ++c) {
-                float ms = 0.f;
-                SV_TRY(time_stream(st, all ? 8 : 2, &ms, [&]() { return launch(c); }));
-                if (ms < best) {
-                    best = ms;
-                    shape = c;
-                }
+        // The parts only up to four 64 x 64 tiles per compute unit: beyond, the
+        // large shape is the faster one (shapes 0 and 3, complex64 and complex128:
+        // 128 tiles 65 34 99 51 us, 512: 181 185 308 322, 1024: 320 358 721 636,
+        // 2048: 625 706 1164 1279).  One timing each as a first pass; products of a few microseconds
+        // vary by more than the shapes differ and a wrong pick is up to twice as
+        // slow (11 and 20 us), so those within half of the best are timed twice
+        // more, which stays below a millisecond.
+        const int ncand = gm * gn <= 1024 && parts_ok ? 4 : 2;
+        float t[4] = {1e30f, 1e30f, 1e30f, 1e30f}, best = 1e30f;
+        auto time = [&](int c, int reps) -> sv_status {
+            float ms = 0.f;
+            SV_TRY(time_stream(st, reps, &ms, [&]() { return launch(c); }));
+            t[c] = std::min(t[c], ms);
+            return SV_OK;
+        };
+        for (int c = 0; c < ncand; ++c) SV_TRY(time(c, 2));
+        const float first = *std::min_element(t, t + 4);
+        for (int round = 0; round < 2 && first < 0.05f; ++round)
+            for (int c = 0; c < ncand; ++c)
+                if (t[c] < 1.5f * first) SV_TRY(time(c, 4));
+        for (int c = 0; c < ncand; ++c)
+            if (t[c] < best) {
+                best = t[c];
+                shape = c;
             }
         tune_store(key, {shape});
     }
