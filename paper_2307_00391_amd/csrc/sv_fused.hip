@@ -705,16 +705,18 @@ static void fusion_default(sv_state s, const std::vector<PGate> &pg, int &k, int
 // amplitudes and more): the candidates are k local qubits in {K-1, K} (K the
 // default, bounded by the LDS) times c contiguous low bits in {C-1, C, C+1}
 // (C the default, c <= k - 2) times rb register bits per segment line (the
-// default and one fewer).  Each candidate's plan is made for the whole
-// circuit and its first passes are timed on a scratch copy of the state (the
-// state itself is not touched): the first pass, plus the mean of up to eight
-// others spread over the plan times their number.  When the two best
-// estimates are within 10 %, both run their whole plan, and the faster is kept.  Cached per dtype, size and circuit
-// structure (gate kinds and qubits, not angles) as (k, c, rb), with a fourth value 1
-// for windows of the earliest gates; an entry of
-// (k, c) takes the default rb, rb = 1 stands for matrix-core blocks, which run
-// beside the candidates above where every gate fits one.  SV_FUSED_LOWBITS pins
-// c and skips the tuning.
+// default and one fewer) times the planner (windows, and windows of the
+// earliest gates where those come to at most a fifth more passes), and
+// matrix-core blocks where every gate fits one.  Each candidate's first passes
+// are timed on a scratch copy of the state (the state itself is not touched):
+// the first pass, plus the mean of up to eight others spread over the plan times
+// their number; the best few run their whole plan, and the fastest is kept.  A first call costs about 30 runs of the circuit (28
+// qubits, complex64: 6 layers 0.31 s, 120 mixed gates 0.33 s; 0.55 and 0.33 with
+// a warm-up for every run and the first planner and the vector passes alone).  Cached per dtype,
+// size and circuit structure (gate kinds and qubits, not angles) as (k, c, rb),
+// with a fourth value 1 for windows of the earliest gates; an entry of (k, c)
+// takes the default rb, rb = 1 stands for blocks.  SV_FUSED_LOWBITS pins c and
+// skips the tuning.
 static uint64_t circuit_signature(const std::vector<PGate> &pg) {
     uint64_t h = 1469598103934665603ull;
     auto mix = [&](uint64_t v) {
@@ -774,99 +776,146 @@ sv_status fusion_config(sv_state s, const std::vector<PGate> &pg, int &k, int &c
     // Candidates: tile depth k, contiguous low bits c and register bits per
     // segment line rb.  Fewer register bits mean more segments but far fewer
     // registers, so a smaller tile can run three or more workgroups per CU.
+    // Circuits of few gates per qubit come to as many passes, or nearly, with
+    // windows of the earliest gates, and those may run a little faster (25
+    // qubits, complex64: 106 mixed gates 1217 us in 10 passes against 1249 in 9,
+    // 77 gates 922 against 942, 7 passes each; 120 gates 1285 in 9 against 1233
+    // in 8; 28 qubits, complex128, 120 gates: 24.2 against 24.8 ms, with another
+    // c): where they are at most a fifth more they are candidates too.
     // A plan's time is estimated from its first pass (which holds the most
-    // ops) plus a sample of the others scaled to their number.
+    // ops) plus a sample of the others scaled to their number.  The runs are
+    // queued one behind the other, so that the host plans the next while they
+    // run; below 27 qubits, where a run may be shorter than its planning, an
+    // untimed one goes ahead of each.
     const int K = k, C = c, RB0 = s->dt == SV_C64 ? 5 : 4;
     struct Cand {
         float est;
         int k, c, rb;
+        bool early;
+        float scale1;              // est = ms of span 0 + scale1 x ms of span 1
+        size_t ev;                 // first of its three events
     };
     std::vector<Cand> cands;
-    float best = 1e30f;
-    for (int rr = RB0; rr >= RB0 - 1 && st == SV_OK; --rr) {
-        for (int kk = K - 1; kk <= K && st == SV_OK; ++kk) {
-            if (kk < 3 || kk < rr) continue;
-            for (int cc = C - 1; cc <= C + 1 && st == SV_OK; ++cc) {
-                if (cc < 0 || cc > kk - 2) continue;
-                std::vector<HostPass> passes;
-                plan(s->n, kk, cc, pg, passes);
-                if (passes.empty()) continue;
-                // the first pass, and up to eight of the others spread evenly
-                // over the plan (pass times vary several-fold along it)
-                const size_t N = passes.size(), S = N - 1 < 8 ? N - 1 : 8;
-                std::vector<HostPass> first(passes.begin(), passes.begin() + 1), sample;
-                for (size_t j = 0; j < S; ++j) sample.push_back(passes[1 + j * (N - 1) / S]);
-                float ms0 = 0.f, ms1 = 0.f;
-                st = time_stream(s->stream, 1, &ms0, [&]() {
-                    return s->dt == SV_C64 ? launch_passes<float>(t, first, rr) : launch_passes<double>(t, first, rr);
-                });
-                if (st == SV_OK && S > 0)
-                    st = time_stream(s->stream, 1, &ms1, [&]() {
-                        return s->dt == SV_C64 ? launch_passes<float>(t, sample, rr) : launch_passes<double>(t, sample, rr);
-                    });
-                const float est = ms0 + (S > 0 ? ms1 * (float)(N - 1) / (float)S : 0.f);
-                if (st == SV_OK) cands.push_back({est, kk, cc, rr});
+    std::vector<hipEvent_t> ev;
+    auto mark = [&]() -> sv_status {
+        hipEvent_t x = nullptr;
+        SV_HIP(hipEventCreate(&x));
+        ev.push_back(x);
+        SV_HIP(hipEventRecord(x, s->stream));
+        return SV_OK;
+    };
+    auto run_plan = [&](std::vector<HostPass> &p, int r) {
+        return s->dt == SV_C64 ? launch_passes<float>(t, p, r) : launch_passes<double>(t, p, r);
+    };
+    // the estimates of the candidates from `from` on
+    auto read_times = [&](size_t from) -> sv_status {
+        SV_HIP(hipStreamSynchronize(s->stream));
+        for (size_t i = from; i < cands.size(); ++i) {
+            float ms[2] = {0.f, 0.f};
+            for (int q = 0; q < 2; ++q) SV_HIP(hipEventElapsedTime(&ms[q], ev[cands[i].ev + q], ev[cands[i].ev + q + 1]));
+            cands[i].est = ms[0] + cands[i].scale1 * ms[1];
+        }
+        return SV_OK;
+    };
+    const bool brief = s->n < 27;
+    auto tune = [&]() -> sv_status {
+        bool warm = false;
+        for (int rr = RB0; rr >= RB0 - 1; --rr)
+            for (int kk = K - 1; kk <= K; ++kk)
+                for (int cc = std::max(0, C - 1); cc <= C + 1; ++cc) {
+                    if (kk < 3 || kk < rr || cc > kk - 2) continue;
+                    std::vector<HostPass> p[2];
+                    for (int e = 0; e < 2; ++e) plan(s->n, kk, cc, pg, p[e], e == 1);
+                    for (int e = 0; e < 2; ++e) {
+                        const size_t N = p[e].size();
+                        if (!N || (e && N * 5 > p[0].size() * 6)) continue;
+                        // the first pass, and up to eight of the others spread evenly
+                        // over the plan (pass times vary several-fold along it)
+                        const size_t S = N - 1 < 8 ? N - 1 : 8;
+                        std::vector<HostPass> first(p[e].begin(), p[e].begin() + 1), sample;
+                        for (size_t j = 0; j < S; ++j) sample.push_back(p[e][1 + j * (N - 1) / S]);
+                        if (brief || !warm) SV_TRY(run_plan(first, rr));
+                        warm = true;
+                        cands.push_back({0.f, kk, cc, rr, e == 1, S ? (float)(N - 1) / (float)S : 0.f, ev.size()});
+                        SV_TRY(mark());
+                        SV_TRY(run_plan(first, rr));
+                        SV_TRY(mark());
+                        if (S) SV_TRY(run_plan(sample, rr));
+                        SV_TRY(mark());
+                    }
+                }
+        SV_TRY(read_times(0));
+        // matrix-core blocks: the whole circuit, or on large states a prefix of it
+        // (at least four gates per qubit), scaled, behind a few gates that load the
+        // kernels; a second tile only where the first comes within a third of the
+        // vector passes
+        if (!fusion_pinned() && blocks_eligible(s, pg)) {
+            const size_t part = s->n <= 28 ? pg.size() : std::min(pg.size(), (size_t)(4 * s->n));
+            const std::vector<PGate> head(pg.begin(), pg.begin() + (long)part);
+            const std::vector<PGate> few(pg.begin(), pg.begin() + (long)std::min<size_t>(part, 8));
+            float vec = 1e30f;
+            for (const Cand &q : cands) vec = std::min(vec, q.est);
+            for (int cc = s->dt == SV_C64 ? 3 : 2, e = cc + 1; cc <= e && blocks_eligible(s, head); ++cc) {
+                if (brief) SV_TRY(run_blocks(t, head, K, cc));
+                else if (cc < e && blocks_eligible(s, few)) SV_TRY(run_blocks(t, few, K, cc));
+                cands.push_back({0.f, K, cc, RB_BLOCKS, false, (float)pg.size() / (float)part, ev.size()});
+                SV_TRY(mark());
+                SV_TRY(mark());
+                SV_TRY(run_blocks(t, head, K, cc));
+                SV_TRY(mark());
+                SV_TRY(read_times(cands.size() - 1));
+                if (cands.back().est > 1.33f * vec) break;
             }
         }
-    }
-    // matrix-core blocks: the whole circuit, or on large states a prefix of it
-    // (at least four gates per qubit), scaled
-    if (st == SV_OK && !fusion_pinned() && blocks_eligible(s, pg)) {
-        const size_t part = s->n <= 28 ? pg.size() : std::min(pg.size(), (size_t)(4 * s->n));
-        const std::vector<PGate> head(pg.begin(), pg.begin() + (long)part);
-        for (int cc = s->dt == SV_C64 ? 3 : 2, e = cc + 1; cc <= e && st == SV_OK && blocks_eligible(s, head); ++cc) {
-            float ms = 0.f;
-            st = time_stream(s->stream, 1, &ms, [&]() { return run_blocks(t, head, K, cc); });
-            if (st == SV_OK) cands.push_back({ms * (float)pg.size() / (float)part, K, cc, RB_BLOCKS});
+        if (cands.empty()) return SV_OK;
+        // The samples tell estimates apart to about 2 % (6 % below half a
+        // millisecond; to 10 % between the kinds: windows, windows of the earliest
+        // gates, blocks): the best few within that run their whole plan, in turn,
+        // and the fastest is kept.
+        std::sort(cands.begin(), cands.end(), [](const Cand &x, const Cand &y) { return x.est < y.est; });
+        const bool tiny = cands[0].est < 0.5f;
+        std::vector<size_t> fin;
+        for (size_t i = 0; i < cands.size() && cands[i].est <= 1.1f * cands[0].est; ++i) {
+            bool seen = false;
+            for (size_t j : fin) seen |= (cands[j].rb == RB_BLOCKS) == (cands[i].rb == RB_BLOCKS) && cands[j].early == cands[i].early;
+            if (!seen || (fin.size() < (tiny ? 7 : 4) && cands[i].est <= (tiny ? 1.06f : 1.02f) * cands[0].est)) fin.push_back(i);
         }
-    }
-    // the two best estimates, when within 10 % of each other (closer than the
-    // sample can tell apart), both run their whole plan, and the faster is kept
-    std::sort(cands.begin(), cands.end(), [](const Cand &x, const Cand &y) { return x.est < y.est; });
-    const size_t nfull = cands.size() > 1 && cands[1].est <= 1.1f * cands[0].est ? 2 : 1;
-    if (nfull == 1 && !cands.empty()) {
-        k = cands[0].k;
-        c = cands[0].c;
-        rb = cands[0].rb;
-    }
-    for (size_t i = 0; i < cands.size() && i < nfull && nfull > 1 && st == SV_OK; ++i) {
-        const Cand &cd = cands[i];
-        std::vector<HostPass> passes;
-        if (cd.rb != RB_BLOCKS) plan(s->n, cd.k, cd.c, pg, passes);
-        float ms = 0.f;
-        st = time_stream(s->stream, 1, &ms, [&]() {
-            if (cd.rb == RB_BLOCKS) return run_blocks(t, pg, cd.k, cd.c);
-            return s->dt == SV_C64 ? launch_passes<float>(t, passes, cd.rb) : launch_passes<double>(t, passes, cd.rb);
-        });
-        if (st == SV_OK && ms < best) {
-            best = ms;
-            k = cd.k;
-            c = cd.c;
-            rb = cd.rb;
-        }
-    }
-    // circuits of few gates per qubit come to as many passes, or nearly, with
-    // windows of the earliest gates, and those may run a little faster (25
-    // qubits, complex64: 106 mixed gates 1217 us in 10 passes against 1249 in 9,
-    // 77 gates 922 against 942, 7 passes each; 120 gates 1285 in 9 against 1233
-    // in 8): where they are at most a fifth more, both run whole, in turn
-    if (st == SV_OK && rb != RB_BLOCKS && !cands.empty()) {
-        std::vector<HostPass> p[2];
-        for (int e = 0; e < 2; ++e) plan(s->n, k, c, pg, p[e], e == 1);
-        if (p[1].size() * 5 <= p[0].size() * 6) {
-            float ms[2] = {1e30f, 1e30f};
-            for (int round = 0; round < 3; ++round)
-                for (int e = 0; e < 2 && st == SV_OK; ++e) {
-                    float m = 0.f;
-                    st = time_stream(s->stream, 1, &m, [&]() {
-                        return s->dt == SV_C64 ? launch_passes<float>(t, p[e], rb) : launch_passes<double>(t, p[e], rb);
-                    });
-                    if (m < ms[e]) ms[e] = m;
+        size_t best = 0;
+        if (fin.size() > 1) {
+            std::vector<std::vector<HostPass>> p(fin.size());
+            for (size_t i = 0; i < fin.size(); ++i)
+                if (cands[fin[i]].rb != RB_BLOCKS) plan(s->n, cands[fin[i]].k, cands[fin[i]].c, pg, p[i], cands[fin[i]].early);
+            auto whole = [&](size_t i) -> sv_status {
+                const Cand &q = cands[fin[i]];
+                return q.rb == RB_BLOCKS ? run_blocks(t, pg, q.k, q.c) : run_plan(p[i], q.rb);
+            };
+            const size_t e0 = ev.size(), n = fin.size(), runs = n * (tiny ? 4 : 1);
+            if (brief) SV_TRY(whole(n - 1));
+            SV_TRY(mark());
+            for (size_t j = 0; j < runs; ++j) {
+                SV_TRY(whole(j % n));
+                SV_TRY(mark());
+            }
+            SV_HIP(hipStreamSynchronize(s->stream));
+            float least = 1e30f;
+            for (size_t j = 0; j < runs; ++j) {
+                float m = 0.f;
+                SV_HIP(hipEventElapsedTime(&m, ev[e0 + j], ev[e0 + j + 1]));
+                if (m < least) {
+                    least = m;
+                    best = fin[j % n];
                 }
-            early = ms[1] < ms[0];
+            }
         }
-    }
+        k = cands[best].k;
+        c = cands[best].c;
+        rb = cands[best].rb;
+        early = cands[best].early;
+        return SV_OK;
+    };
+    if (st == SV_OK) st = tune();
     hipStreamSynchronize(s->stream);
+    for (hipEvent_t x : ev) (void)hipEventDestroy(x);
     sv_free(t);
     hipFree(scratch);
     if (st != SV_OK) return st;

@@ -1,11 +1,13 @@
 """A first call tunes its launch parameters; what that costs stays in proportion
-to the call.  The bounds are about three times what is measured (a dense unitary
-of 10 qubits on 24: 13 calls' time)."""
+to the call.  Measured: a dense unitary of 10 qubits on 24: the time of 13 calls,
+a circuit of 120 gates on 28 qubits: of 29."""
 import time
 
+import numpy as np
 import pytest
 
 from paper_2307_00391_amd import binding as B
+from paper_2307_00391_amd import inputs
 
 pytestmark = pytest.mark.gpu
 
@@ -36,3 +38,23 @@ def test_dense_unitary_of_half_a_millisecond():
                                       lambda: B.sv_tune_set(f"cgemm/c64/{1 << (n - 1 - m)}/{1 << m}/{1 << m}/0", []))
     s.close()
     assert first <= 40 * steady
+
+
+def test_circuit_of_a_dozen_milliseconds():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    n = 28
+    gates = B.make_gates(inputs.random_circuit(np.random.default_rng(5), n, 120))
+    s = B.State(n, "c64")
+    B.sv_init_basis(s.h, 1)
+    key = []
+
+    def forget():
+        key[:] = [ln.split()[0] for ln in B.sv_tune_report().splitlines() if ln.startswith(f"fused/c64/{n}/")]
+        for k in key:
+            B.sv_tune_set(k, [])
+
+    first, steady = _first_and_steady(torch, lambda: B.sv_apply_circuit(s.h, gates), forget)
+    s.close()
+    assert key and first <= 40 * steady
