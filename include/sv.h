@@ -383,7 +383,11 @@ int sv_trace_report(char *buf, int len);
 
 /* The autotuner's current choices, one line per tuned shape:
  * "op/dtype/shape... values".  Tuning runs on first use of a shape
- * (SV_AUTOTUNE=0: defaults); SV_TUNE_CACHE=<file> persists the choices.
+ * (SV_AUTOTUNE=0: defaults); SV_TUNE_CACHE=<file> persists the choices, behind
+ * a line "format 2".  Entries of a file without that line were chosen among
+ * fewer forms: while tuning is on, those that may name a slower one now are
+ * timed anew (a configuration is pinned by sv_tune_set, or by a file that
+ * carries the line).
  *   eigpipe/<dtype>/<n_s>/<n_c>  fused eigen-frame kernels: (log2 columns
  *       per tile, threads per workgroup) for each of the two kernels, and a
  *       third pair that is not read;
