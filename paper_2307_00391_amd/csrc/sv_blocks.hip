@@ -642,29 +642,22 @@ static void blocks_of(const std::vector<PGate> &gates, const PlanWindow &w, uint
     plan_windows(items, 4, 0, BLK_EXT, BLK_EXT, 1 << 20, bw);
 }
 
-int count_block_passes(const std::vector<PGate> &gates, int k, int c) {
-    std::vector<PlanWindow> wins;
-    block_passes(gates, k, c, wins);
-    return (int)wins.size();
-}
-
-int count_blocks(sv_state s, const std::vector<PGate> &gates, int k, int c) {
-    std::vector<PlanWindow> wins, bw;
-    block_passes(gates, k, c, wins);
-    int n = 0;
-    for (const PlanWindow &w : wins) {
+void plan_blocks(int n, const std::vector<PGate> &gates, int k, int c, BlockPlan &plan) {
+    plan.k = k;
+    plan.c = c;
+    plan.nblocks = 0;
+    block_passes(gates, k, c, plan.wins);
+    plan.blocks.resize(plan.wins.size());
+    for (size_t i = 0; i < plan.wins.size(); ++i) {
         TileLayout t;
-        tile_layout(s->n, k, w.set, t);
-        blocks_of(gates, w, ~t.nl_mask & ((1ull << s->n) - 1ull), bw);
-        n += (int)bw.size();
+        tile_layout(n, k, plan.wins[i].set, t);
+        blocks_of(gates, plan.wins[i], ~t.nl_mask & ((1ull << n) - 1ull), plan.blocks[i]);
+        plan.nblocks += (int)plan.blocks[i].size();
     }
-    return n;
 }
 
 template <typename R>
-static sv_status run_blocks_impl(sv_state s, const std::vector<PGate> &gates, int k, int c) {
-    std::vector<PlanWindow> wins, bw;
-    block_passes(gates, k, c, wins);
+static sv_status run_blocks_impl(sv_state s, const std::vector<PGate> &gates, const BlockPlan &plan) {
     std::vector<BPass> passes;
     std::vector<BBlock> blocks;
     std::vector<BBuild> todo;
@@ -672,14 +665,14 @@ static sv_status run_blocks_impl(sv_state s, const std::vector<PGate> &gates, in
     std::vector<FOp> fops;
     const uint64_t all = (1ull << s->n) - 1ull;
     const int e = sizeof(R) == 4 ? 5 : 4;
-    for (const PlanWindow &w : wins) {
+    for (size_t wi = 0; wi < plan.wins.size(); ++wi) {
+        const PlanWindow &w = plan.wins[wi];
         BPass P;
         memset(&P, 0, sizeof P);
-        tile_layout(s->n, k, w.set, P.t);
+        tile_layout(s->n, plan.k, w.set, P.t);
         P.blk_off = (int)blocks.size();
         const uint64_t L = ~P.t.nl_mask & all;
-        blocks_of(gates, w, L, bw);
-        for (const PlanWindow &q : bw) {
+        for (const PlanWindow &q : plan.blocks[wi]) {
             BBlock b;
             memset(&b, 0, sizeof b);
             uint32_t S = 0;
@@ -800,6 +793,12 @@ sv_status run_blocks(sv_state s, const std::vector<PGate> &gates, int k, int c) 
     k = std::min(k, s->n);
     if (k < 8 || k > 8 + BLK_UNIT_BITS) return fail(SV_EINVAL, "block tile of %d qubits", k);
     if (!blocks_eligible(s, gates)) return fail(SV_EINVAL, "a circuit that does not run as blocks of four qubits");
+    BlockPlan plan;
+    plan_blocks(s->n, gates, k, std::max(0, std::min(c, k - 4)), plan);
+    return run_blocks(s, gates, plan);
+}
+
+sv_status run_blocks(sv_state s, const std::vector<PGate> &gates, const BlockPlan &plan) {
     static bool lds_at_0 = [] {
         bool ok = true;
         for (const void *f : {(const void *)k_blocks<float>, (const void *)k_blocks<double>}) {
@@ -811,8 +810,7 @@ sv_status run_blocks(sv_state s, const std::vector<PGate> &gates, int k, int c) 
         return ok;
     }();
     if (!lds_at_0) return fail(SV_EDEVICE, "the block-pass kernels need their tile at LDS address 0");
-    c = std::max(0, std::min(c, k - 4));
-    return s->dt == SV_C64 ? run_blocks_impl<float>(s, gates, k, c) : run_blocks_impl<double>(s, gates, k, c);
+    return s->dt == SV_C64 ? run_blocks_impl<float>(s, gates, plan) : run_blocks_impl<double>(s, gates, plan);
 }
 
 }  // namespace sv

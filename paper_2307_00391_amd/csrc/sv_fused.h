@@ -225,10 +225,15 @@ void plan_earliest(const std::vector<PlanItem> &items, int cap, uint64_t base, i
 // ---- matrix-core passes (sv_blocks.hip) -------------------------------------
 // every gate is unitary and fits a block of four qubits, and one at least mixes amplitudes
 bool blocks_eligible(sv_state s, const std::vector<PGate> &gates);
-// passes and blocks they come to on tiles of k qubits with the lowest c in them
-int count_block_passes(const std::vector<PGate> &gates, int k, int c);
-int count_blocks(sv_state s, const std::vector<PGate> &gates, int k, int c);
-// tiles of 2^k amplitudes with the lowest c index bits in them
+struct BlockPlan {
+    int k, c, nblocks;
+    std::vector<PlanWindow> wins;                  // the passes
+    std::vector<std::vector<PlanWindow>> blocks;   // of each pass (gates: places in its window)
+};
+// on tiles of k qubits with the lowest c in them: 8 <= k <= 13, c <= k - 4, eligible gates
+void plan_blocks(int n, const std::vector<PGate> &gates, int k, int c, BlockPlan &plan);
+sv_status run_blocks(sv_state s, const std::vector<PGate> &gates, const BlockPlan &plan);
+// the same for a configuration that may be pinned
 sv_status run_blocks(sv_state s, const std::vector<PGate> &gates, int k, int c);
 
 }  // namespace sv

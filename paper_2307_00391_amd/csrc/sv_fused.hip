@@ -681,24 +681,34 @@ constexpr int RB_BLOCKS = 1;
 static bool fusion_pinned() { return getenv("SV_FUSED_LOWBITS") || getenv("SV_FUSED_RB"); }
 
 // The configuration without tuning, for states below 2^22 amplitudes (larger
-// ones: the vector passes).  Times here are launches, latencies and the
-// serial run of a tile's gates, and blocks shorten the last: 4 layers of U3 +
-// CNOT ladder take 56 against 134 us on 14 qubits and 119 against 251 us on 20
-// (complex64), 80 mixed gates 113 against 135 and 135 against 157 us.  In
-// complex128 a block costs four times as much, so from 19 qubits on blocks
-// with few gates lose (20 qubits, 80 mixed gates, two gates per block: 195
-// against 153 us; the layers, five per block: 150 against 226 us).
+// ones: the vector passes).  Times here are launches, latencies and the serial
+// run of a tile's gates, and blocks shorten the last.  Fitted to 684 circuits (1
+// to 8 layers, 4 to 300 mixed gates, 20 to 150 NOTs and swaps or 8 to 200 phases
+// with 1 to 20 dense gates, 8 to 21 qubits, both types), in us: a dense gate
+// costs the vector passes 1.0, a NOT or swap 0.6, a phase 0.3; blocks cost 16
+// for the build and its gap, 2 per further pass (8 where the vector passes' tile
+// holds the whole state) and, where they fill the chip, their arithmetic: 3 per
+// block on 21 qubits in complex128, 0.5 in complex64, half of it per qubit less
+// (complex128 from 19 qubits on: and at least three gates per block; 600 mixed
+// gates on 20 qubits, two and a half per block, 1240 against 1153).
+// The rule's pick takes 0.5 % longer than the faster one on average, at most 24 %
+// (13 of 55 us); always blocks: 6 % and 75 %.  Examples (blocks,
+// vector passes): 8 layers on 14 qubits, complex128, 105 and 304 us; 80 mixed
+// gates on 18 qubits, complex64, 123 and 153; one dense gate and 60 phases on 21
+// qubits, complex128, 107 and 63; 16 mixed gates on 14 qubits 43 and 36.
 // The tile grows with the state, so that small states still spread over many
 // compute units: 14 qubits, complex64, k = 8 .. 13: 72 71 54 56 57 71 us; 20
 // qubits: 337 243 179 122 119 117 us.
-static void fusion_default(sv_state s, const std::vector<PGate> &pg, int &k, int &c, int &rb) {
-    if (s->n >= 22 || !blocks_eligible(s, pg)) return;
+static bool fusion_default(sv_state s, const std::vector<PGate> &pg, BlockPlan &plan) {
+    if (s->n >= 22 || fusion_pinned() || !blocks_eligible(s, pg)) return false;
     const bool wide = s->dt == SV_C128;
-    const int bk = std::min(wide ? 12 : 13, std::max(std::min(s->n, 10), s->n / 2 + (wide ? 2 : 3)));
-    if (wide && s->n >= 19 && count_blocks(s, pg, bk, 3) * 3 > (int)pg.size()) return;
-    k = bk;
-    c = 3;
-    rb = RB_BLOCKS;
+    double saved = -16.0;
+    for (const PGate &g : pg) saved += g.kind == 0 ? 1.0 : g.kind == 3 ? 0.3 : 0.6;
+    if (saved <= 0.0) return false;
+    plan_blocks(s->n, pg, std::min(wide ? 12 : 13, std::max(std::min(s->n, 10), s->n / 2 + (wide ? 2 : 3))), 3, plan);
+    saved -= (s->n <= default_max_local(s->dt) ? 8.0 : 2.0) * ((double)plan.wins.size() - 1.0);
+    if (wide && s->n >= 19 && plan.nblocks * 3 > (int)pg.size()) return false;
+    return saved > ldexp(wide ? 3.0 : 0.5, s->n - 21) * plan.nblocks;
 }
 
 // The fusion autotuner (sv_apply_circuit with max_local = 0, states of 2^22
@@ -738,11 +748,7 @@ static uint64_t circuit_signature(const std::vector<PGate> &pg) {
 }
 
 sv_status fusion_config(sv_state s, const std::vector<PGate> &pg, int &k, int &c, int &rb, bool &early) {
-    if (s->n < 22) {
-        if (!fusion_pinned()) fusion_default(s, pg, k, c, rb);
-        return SV_OK;
-    }
-    if (getenv("SV_FUSED_LOWBITS")) return SV_OK;
+    if (s->n < 22 || getenv("SV_FUSED_LOWBITS")) return SV_OK;
     char sig[32];
     snprintf(sig, sizeof sig, "%016llx", (unsigned long long)circuit_signature(pg));
     const std::string key = std::string("fused/") + (s->dt == SV_C64 ? "c64/" : "c128/") + std::to_string(s->n) + "/" + sig;
@@ -939,9 +945,9 @@ int sv_plan_passes(int n_qubits, sv_dtype dt, const sv_gate *gates, int n_gates,
     if (to_pgates(&tmp, gates, n_gates, pg) != SV_OK) return -1;
     int k = max_local > 0 ? max_local : default_max_local(dt);
     if (k > n_qubits) k = n_qubits;
-    int c = std::min(low_bits_for(dt), k - 2), rb = 0;
-    if (max_local == 0 && !fusion_pinned()) fusion_default(&tmp, pg, k, c, rb);
-    if (rb == RB_BLOCKS) return count_block_passes(pg, k, c);
+    const int c = std::min(low_bits_for(dt), k - 2);
+    BlockPlan blocks;
+    if (max_local == 0 && fusion_default(&tmp, pg, blocks)) return (int)blocks.wins.size();
     std::vector<HostPass> passes;
     plan(n_qubits, k, c, pg, passes);
     return (int)passes.size();
@@ -959,7 +965,11 @@ sv_status sv_apply_circuit(sv_state s, const sv_gate *gates, int n_gates, int ma
     if (k < 3) return fail(SV_EUNSUPPORTED, "state too small for fused passes");
     int c = std::max(0, std::min(low_bits_for(s->dt), k - 2)), rb = 0;
     bool early = false;
-    if (max_local == 0) SV_TRY(fusion_config(s, pg, k, c, rb, early));
+    if (max_local == 0) {
+        BlockPlan blocks;
+        if (fusion_default(s, pg, blocks)) return run_blocks(s, pg, blocks);
+        SV_TRY(fusion_config(s, pg, k, c, rb, early));
+    }
     if (rb == RB_BLOCKS) return run_blocks(s, pg, k, c);
     std::vector<HostPass> passes;
     plan(s->n, k, c, pg, passes, early);
