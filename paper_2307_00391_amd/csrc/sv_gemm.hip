@@ -469,10 +469,13 @@ static sv_status ctrl_mask_unitary_at(sv_state s, const cvec<R> *U, int lo, int 
     {
         TraceScope _ts(s->stream, "scatter_rows", 2.0 * (double)total * sizeof(cvec<R>), 0.0);
         const uint64_t gl = total / 1024;
-        // whole rows while a launch is short (1024 rows of 256: 5.5 us, 6.5 with
-        // a deposit per element); the grid-stride copy of k_scatter_rows streams
-        // better when it is long (8192 rows of 1024: 27 us, 37)
-        if (lo == 0 && m >= 8 && gl >= 1 && gl <= 1024)
+        // whole rows while a launch is short; the grid-stride copy of k_scatter_rows
+        // streams better when it is long.  Copies of 2^18 .. 2^22 elements, rows of
+        // 256 (whole rows and, behind, elements): complex64 6.5 7.0, 7.5 8.2, 10.9
+        // 10.9, 13.9 12.7, 23.5 19.7 us, complex128 7.2 8.3, 9.5 9.9, 10.6 10.1,
+        // 15.1 14.8, 24.4 24.1; rows of 1024: 6.3 7.7, 6.7 6.7, 10.4 8.2, 12.5 11.1,
+        // 21.1 17.8 and 6.6 9.4, 7.1 9.5, 9.8 9.0, 14.1 14.0, 24.5 23.4.
+        if (lo == 0 && m >= 8 && gl >= 1 && gl <= 512)
             hipLaunchKernelGGL(k_scatter_long<R>, dim3((unsigned)gl), dim3(256), 0, s->stream, (cvec<R> *)s->data,
                                (const cvec<R> *)out, m, row_mask, row_fix);
         else
