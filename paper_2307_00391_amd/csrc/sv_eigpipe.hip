@@ -31,9 +31,10 @@
 // Inverse cascade stage on register qubit j (relative to the clock register):
 //   a1 *= conj(phase), then (a0 + a1, a0 - a1)/sqrt 2
 // with phase = exp(2 pi i (v mod 2^j) / 2^(j+1)), v the register value: the
-// controlled phases of the textbook QFT circuit that target qubit j.  The
-// local part comes from a table of 2^g roots of unity, the part due to bits
-// outside the tile is one exact-turn phase per stage and tile.
+// controlled phases of the textbook QFT circuit that target qubit j.  On a
+// product state no stage has to be run: each contributes one factor per line
+// (product_line), with the stage's roots from a table per group and the bits
+// below the group, fixed for a tile, folded into it.
 #include <math.h>
 
 #include <algorithm>
@@ -46,7 +47,6 @@
 
 namespace sv {
 
-
 struct PipeArgs {
     uint64_t N;          // 2^n_s columns
     int n_s, n_c;
@@ -56,8 +56,7 @@ struct PipeArgs {
     double scale;        // 2^(-n_c/2)
     int sgn;             // signed (two's-complement) clock for the inversion
     uint64_t gcut;       // 0: inversion sin = 1/y; >= 1: gapped-phase-estimation flag, sin = [|y| >= gcut]
-    int pslog, iters;    // work-queue items: log2 of the column-block stride in blocks (0);
-                         // column blocks per item
+    int iters;           // work-queue items: consecutive column blocks per item
 };
 
 // HBM pointers of a solve, in the global address space: the pointers come
@@ -275,7 +274,7 @@ __global__ __launch_bounds__(NT) void k_pipe_a(PipeArgs A, PipeSolve one, PipeHe
 // Bound by the stores: 17.2 GB in 2.70 ms, 6.4 TB/s (a plain fill: 6.9).
 //
 // Tile: columns [j0, j0 + C)
-// at G1 value o; a work-queue item (PERS) runs A.iters column blocks j0 + it 2^(pslog + cl).
+// at G1 value o; a work-queue item (PERS) runs A.iters column blocks j0 + it 2^cl.
 // The FP64 partial pair goes to slot `slot`.
 template <typename R, int RA, int RB, int NT, bool PERS>
 __device__ __forceinline__ void pipe_b_body(const PipeArgs &A, const PipeSolve &S, uint64_t j0, uint64_t o,
@@ -299,7 +298,7 @@ __device__ __forceinline__ void pipe_b_body(const PipeArgs &A, const PipeSolve &
     R *zl = reinterpret_cast<R *>(cd + 2 * ncd);
     __shared__ double red[2][NT / 64];
     const int iters = PERS ? A.iters : 1;
-    const uint64_t jstep = PERS ? 1ull << (A.pslog + A.cl) : 0;
+    const uint64_t jstep = PERS ? 1ull << A.cl : 0;
     const int g1 = A.g1, n_c = A.n_c;
     auto col_data = [&](int e, uint64_t j) -> cvec<R> {
         const int b = e / C, cq = e - b * C;
@@ -684,7 +683,6 @@ static void make_plan(PipePlan &P, int n_s, int n_c, size_t e, const int cl[2], 
     A.scale = 1.0 / sqrt((double)(1ull << n_c));
     A.sgn = 0;
     A.gcut = 0;
-    A.pslog = 0;
     A.iters = 1;
     for (int w = 0; w < 2; ++w) {
         const int g = w == 1 ? A.g2 : A.g1;
@@ -873,7 +871,6 @@ sv_status pipe_queue_build(sv_state ctx, hipStream_t st, PipeQueue &q, DevBuf &d
             // a run of column blocks reads each next block's column data ahead
             if (w > 0)
                 while ((uint64_t)iters < nb && (((uint64_t)iters * 2 * C) << g) <= (1ull << 15)) iters *= 2;
-            A.pslog = 0;
             A.iters = iters;
             qc[k].A[w] = A;
             qc[k].g[w] = g;

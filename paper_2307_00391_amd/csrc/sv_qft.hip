@@ -37,8 +37,7 @@
 #include <algorithm>
 #include <vector>
 
-#include "sv_device.h"
-#include "sv_internal.h"
+#include "sv_fused.h"
 
 namespace sv {
 
@@ -63,7 +62,7 @@ struct QftTile {
     int nsteps;
     int direct_in, direct_out;      // first / last step moves HBM <-> registers itself
     int rev_tp, rev_w;              // bit reversal of the tile field [rev_tp, rev_tp + rev_w) on the way out
-    int mid_lo, mid_w;              // the mirrored middle bits (two tiles per workgroup), mid_w = 0: none
+    int mid_lo, mid_w;              // the mirrored middle bits, two or more (two tiles per workgroup); mid_w = 0: none
     QftStep st[QFT_MAX_STEPS];
 };
 
@@ -74,14 +73,6 @@ __device__ __forceinline__ uint64_t tile_index(const QftTile &A, uint32_t t) {
     if (A.r2) g |= (uint64_t)(h >> A.r1) << A.p2;
     return g;
 }
-
-// LDS slot: the low bits XOR-ed with the folded higher ones, as for the fused
-// gate passes (threads whose amplitudes sit 2^p apart meet distinct banks)
-__host__ __device__ __forceinline__ uint32_t qswz(uint32_t t, int e) {
-    const uint32_t m = (1u << e) - 1u, h = t >> e;
-    return t ^ ((h ^ (h >> e) ^ (h >> (2 * e))) & m);
-}
-template <typename R> constexpr int QE = sizeof(R) == 4 ? 5 : 4;
 
 // exp(2 pi i t / 2^64): the nearest quarter turn exactly, the rest (at most an
 // eighth of a turn) by the Taylor series of sine and cosine, cut where the
@@ -224,7 +215,7 @@ __device__ __forceinline__ void tile_step(cvec<R> *__restrict__ psi, const QftTi
 #pragma unroll
         for (int i = 0; i < 4; ++i) bt = ((bt >> S.ipos[i]) << (S.ipos[i] + 1)) | (bt & ((1u << S.ipos[i]) - 1u));
         const uint64_t gl = base | tile_index(A, bt);
-        const uint32_t sl = qswz(bt, QE<R>) * (uint32_t)sizeof(cvec<R>);
+        const uint32_t sl = swz<R>(bt) * (uint32_t)sizeof(cvec<R>);
         cvec<R> v[16];
         if (in) {
 #pragma unroll
@@ -287,9 +278,9 @@ __device__ __forceinline__ void tile_in(const cvec<R> *__restrict__ psi, const Q
 #pragma unroll
         for (int u = 0; u < U; ++u) b[u] = psi[base | tile_index(A, t + u * nt)];
 #pragma unroll
-        for (int u = 0; u < U; ++u) *(cvec<R> *)(lds + qswz(t + u * nt, QE<R>) * sizeof(cvec<R>)) = b[u];
+        for (int u = 0; u < U; ++u) *(cvec<R> *)(lds + swz<R>(t + u * nt) * sizeof(cvec<R>)) = b[u];
     }
-    for (; t < T; t += nt) *(cvec<R> *)(lds + qswz(t, QE<R>) * sizeof(cvec<R>)) = psi[base | tile_index(A, t)];
+    for (; t < T; t += nt) *(cvec<R> *)(lds + swz<R>(t) * sizeof(cvec<R>)) = psi[base | tile_index(A, t)];
 }
 
 // tile element t receives the element whose field is t's field reversed
@@ -300,7 +291,7 @@ __device__ __forceinline__ void tile_out(cvec<R> *__restrict__ psi, const QftTil
     const uint32_t T = 1u << A.k, fm = (1u << A.rev_w) - 1u;
     auto src = [&](uint32_t t) {
         if (A.rev_w) t = (t & ~(fm << A.rev_tp)) | ((__brev((t >> A.rev_tp) & fm) >> (32 - A.rev_w)) << A.rev_tp);
-        return *(const cvec<R> *)(lds + qswz(t, QE<R>) * sizeof(cvec<R>));
+        return *(const cvec<R> *)(lds + swz<R>(t) * sizeof(cvec<R>));
     };
     uint32_t t = th;
     for (; t + (U - 1) * nt < T; t += U * nt) {
@@ -347,7 +338,7 @@ __global__ __launch_bounds__(QFT_MAX_THREADS) void k_qft_pass(cvec<R> *__restric
     }
     // mirrored tiles: the upper half of the workgroup has the second one
     // (nothing to do where a tile is its own mirror)
-    const uint32_t nt = A.mid_w > 1 ? blockDim.x / 2 : blockDim.x;
+    const uint32_t nt = A.mid_w ? blockDim.x / 2 : blockDim.x;
     const uint32_t q = threadIdx.x / nt, th = threadIdx.x % nt;
     const bool on = q == 0 || base2 != base;
     const uint32_t tbytes = (A.k < 4 ? 16u : 1u << A.k) * (uint32_t)sizeof(cvec<R>);
@@ -398,8 +389,8 @@ __global__ __launch_bounds__(QFT_MAX_THREADS) void k_spectral_mid(cvec<R> *__res
         const bool pos = k < half;
         const double sd = (double)(pos ? k : 2 * half - k) / den;      // exactly 1 at the largest |k'|
         const R sn = (R)sd, cs = (R)sqrt(fmax(0.0, 1.0 - sd * sd));
-        cvec<R> *q0 = (cvec<R> *)(smem + qswz(t, QE<R>) * sizeof(cvec<R>));
-        cvec<R> *q1 = (cvec<R> *)(smem + qswz(t | ab, QE<R>) * sizeof(cvec<R>));
+        cvec<R> *q0 = (cvec<R> *)(smem + swz<R>(t) * sizeof(cvec<R>));
+        cvec<R> *q1 = (cvec<R> *)(smem + swz<R>(t | ab) * sizeof(cvec<R>));
         const cvec<R> a0 = *q0, a1 = *q1;
         const cvec<R> b0 = cmake<R>(cs * a0.x - sn * a1.x, cs * a0.y - sn * a1.y);
         const cvec<R> b1 = cmake<R>(sn * a0.x + cs * a1.x, sn * a0.y + cs * a1.y);
@@ -477,7 +468,7 @@ static void plan_steps(QftTile &A, sv_dtype dt, int j0, int jn, bool dit) {
         for (int b = 0, p = 0; p < kv; ++p)
             if (used >> p & 1) S.ipos[b++] = p;
         for (int b = 0; b < 4; ++b) {
-            S.lb[b] = qswz(1u << pos[b], e) * eb;
+            S.lb[b] = swz_e(1u << pos[b], e) * eb;
             S.gb[b] = pos[b] < A.k ? 1ull << index_position(A, pos[b]) : 0ull;
             if (b >= R && (S.gb[b] >> A.lo & ((1ull << at) - 1ull))) S.dep = 1;
         }
@@ -517,7 +508,7 @@ static sv_status group_tile(sv_state s, int lo, int m, int j0, int jn, int kmax,
 static unsigned block_of(const QftTile &A) {
     const uint32_t lines = A.k > 4 ? 1u << (A.k - 4) : 1u;
     unsigned nt = lines < 64 ? 64 : lines > (uint32_t)QFT_MAX_THREADS ? (unsigned)QFT_MAX_THREADS : lines;
-    if (A.mid_w > 1) nt = nt * 2 > (unsigned)QFT_MAX_THREADS ? (unsigned)QFT_MAX_THREADS : nt * 2;
+    if (A.mid_w) nt = nt * 2 > (unsigned)QFT_MAX_THREADS ? (unsigned)QFT_MAX_THREADS : nt * 2;
     return nt;
 }
 
@@ -537,7 +528,7 @@ template <typename R, int SGN, bool DIT>
 static sv_status launch_qft(sv_state s, QftTile A) {
     const uint64_t tiles = 1ull << popcount64(A.nl_mask);
     const bool in_regs = A.nsteps == 1 && A.direct_in && A.direct_out;     // never touches LDS
-    const size_t lds = in_regs ? 0 : tile_bytes(A, s->dt) * (A.mid_w > 1 ? 2 : 1);
+    const size_t lds = in_regs ? 0 : tile_bytes(A, s->dt) * (A.mid_w ? 2 : 1);
     TraceScope _ts(s->stream, "qft_pass", 2.0 * (double)(tiles << A.k) * sizeof(cvec<R>), 0.0);
     each_grid(A, [&](dim3 grid) {
         hipLaunchKernelGGL((k_qft_pass<R, SGN, DIT>), grid, dim3(block_of(A)), lds, s->stream, (cvec<R> *)s->data, A);
@@ -630,7 +621,7 @@ static sv_status run_qft_ordered(sv_state s, int lo, int m, int sgn, int max_loc
     A.rev_w = 2 * g;
     A.direct_out = 0;
     A.mid_lo = lo + g;
-    A.mid_w = m - 2 * g;
+    A.mid_w = m - 2 * g;      // at least 2: m > kmax - c and 2 g < kmax - c
     return launch_pass(s, A, sgn, false);
 }
 
