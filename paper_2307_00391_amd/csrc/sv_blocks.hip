@@ -16,8 +16,8 @@
 // them from about four blocks on.
 //
 // complex64: both operands are split into three bf16 parts, x = h + m + l (each
-// part is the rounded rest, 8 bits at a time; exact in the range BlkScale keeps
-// the amplitudes in and for matrix entries of 2^-110 and more), and the six
+// part is the rounded rest, 8 bits at a time; exact in the range BlkRange keeps
+// a tile's larger amplitudes in and for matrix entries of 2^-110 and more), and the six
 // products h h, h m, m h, m m, h l, l h are accumulated in FP32, smallest
 // first, by v_mfma_f32_16x16x32_bf16: K = 32 is the 16 amplitudes' real and
 // imaginary parts, so one instruction forms the real parts of 16 lines.  What
@@ -320,26 +320,33 @@ __device__ __forceinline__ void block_lines(const Operand<double> &A, const Unit
     }
 }
 
-// The range of the fast path.  A tile's amplitudes are scaled up on the way in and
-// back on the way out.  complex64, by 2^24: the parts of an FP32 number are then
-// multiples of 2^-125, where the matrix cores flush what is below 2^-126 to zero
-// (unscaled, a state of amplitudes near 2^-115 came out with a relative error of
-// 3e-6, one near 2^-120 with 1e-4).  complex128, by 2^32: the products of
-// denormal amplitudes lose nothing before they are added.  Tiles with an
-// amplitude that is not finite or above 2^95 (complex128: 2^983), from which a
-// tile's norm could leave the range of the operands, take the careful path;
-// `probe` times such an amplitude, or the sum of such products, overflows.
-// The cost is 4 multiplications per amplitude and pass, below 1 %.
-template <typename R> struct BlkScale;
-template <> struct BlkScale<float> {
-    static constexpr float probe = 0x1p33f;
-    static __device__ __forceinline__ float2 in(float2 z) { return make_float2(z.x * 0x1p24f, z.y * 0x1p24f); }
-    static __device__ __forceinline__ float2 out(float2 z) { return make_float2(z.x * 0x1p-24f, z.y * 0x1p-24f); }
+// The range of the fast path, by a tile's largest component.  From 2^95 on
+// (complex128: 2^983; infinities and NaN among it), where a tile's norm could
+// leave the range of the operands: the careful path.  Below 2^-60 (2^-900): the
+// tile is scaled by 2^64 (2^512) in LDS and back on the way out, for the matrix
+// cores flush the bf16 parts below 2^-126 to zero, so that a state of amplitudes
+// near 2^-115 came out with a relative error of 3e-6, one near 2^-120 with 1e-4
+// (and products of denormal doubles lose their last bits).  What is flushed
+// beside larger amplitudes is below 2^-62 of the tile's largest.  `look` gathers
+// the largest component, NaN included: one instruction per amplitude, three for
+// complex128 (on the high words).
+template <typename R> struct BlkRange;
+template <> struct BlkRange<float> {
+    using key = float;
+    static constexpr float high = 0x1p95f, low = 0x1p-60f, up = 0x1p64f, down = 0x1p-64f;
+    static __device__ __forceinline__ float look(float m, float2 z) {
+        return __builtin_elementwise_maximum(__builtin_elementwise_maximum(m, __builtin_fabsf(z.x)), __builtin_fabsf(z.y));
+    }
+    static __device__ __forceinline__ bool below(float m, float limit) { return m < limit; }
+    static __device__ __forceinline__ bool zero(float m) { return m == 0.f; }       // nothing to scale
 };
-template <> struct BlkScale<double> {
-    static constexpr double probe = 0x1p41;
-    static __device__ __forceinline__ double2 in(double2 z) { return make_double2(z.x * 0x1p32, z.y * 0x1p32); }
-    static __device__ __forceinline__ double2 out(double2 z) { return make_double2(z.x * 0x1p-32, z.y * 0x1p-32); }
+template <> struct BlkRange<double> {
+    using key = uint32_t;
+    static constexpr double high = 0x1p983, low = 0x1p-900, up = 0x1p512, down = 0x1p-512;
+    static __device__ __forceinline__ uint32_t word(double x) { return (uint32_t)__double2hiint(x) & 0x7fffffffu; }
+    static __device__ __forceinline__ uint32_t look(uint32_t m, double2 z) { return max(max(m, word(z.x)), word(z.y)); }
+    static __device__ __forceinline__ bool below(uint32_t m, double limit) { return m < word(limit); }
+    static __device__ __forceinline__ bool zero(uint32_t) { return false; }         // (0: denormals too)
 };
 
 // A tile outside that range: 16 lanes per line, one result row
@@ -384,7 +391,7 @@ __device__ __forceinline__ void block_careful(const BBlock &b, const unsigned ch
 
 // One pass.  Workgroups walk the tiles in strides of the grid.  A wavefront
 // takes units of 16 lines; the next block's matrix is loaded while this one's
-// units run.  Dynamic LDS: the tile, then a flag (no static LDS, so the tile
+// units run.  Dynamic LDS: the tile, then three flags (no static LDS, so the tile
 // starts at address 0).
 // (The next tile read into registers under the last block gained nothing:
 // 13.9 against 13.0 ms on the 28-qubit circuit.)
@@ -403,7 +410,7 @@ __global__ __launch_bounds__(BLK_MAX_THREADS, 2) void k_blocks(cvec<R> *__restri
     const uint32_t upw = (T >> 8) / (uint32_t)nw;
     const int lw = __builtin_ctz((unsigned)nw);
     lptr<uint32_t> fl = (lptr<uint32_t>)(uintptr_t)flag;
-    if (threadIdx.x == 0) *fl = 0;
+    if (threadIdx.x == 0) fl[0] = fl[1] = fl[2] = 0;
     __syncthreads();
 
     constexpr int U = sizeof(R) == 4 ? 8 : 4;
@@ -443,7 +450,7 @@ __global__ __launch_bounds__(BLK_MAX_THREADS, 2) void k_blocks(cvec<R> *__restri
         const uint64_t base = pdep64(tl, P.t.nl_mask);
         Operand<R> A, An;
         An.load(matrix(blocks[P.blk_off], base), lane);
-        R chk = 0;       // not finite once an amplitude is not, or too large
+        typename BlkRange<R>::key most = 0;
         if (big) {
             for (uint32_t t0 = 0; t0 < T; t0 += nt * U) {
                 const uint64_t g0 = base | gthr | scatter_t(t0, c, r, hpos);
@@ -453,25 +460,33 @@ __global__ __launch_bounds__(BLK_MAX_THREADS, 2) void k_blocks(cvec<R> *__restri
                 for (int u = 0; u < U; ++u) buf[u] = psi[g0 | uoff(u)];
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
-                    chk = fma(buf[u].x, BlkScale<R>::probe, chk);
-                    chk = fma(buf[u].y, BlkScale<R>::probe, chk);
-                    lds_st<R>(s0 ^ uswz(u), BlkScale<R>::in(buf[u]));
+                    most = BlkRange<R>::look(most, buf[u]);
+                    lds_st<R>(s0 ^ uswz(u), buf[u]);
                 }
             }
         } else {
             for (uint32_t t = threadIdx.x; t < T; t += nt) {
                 const cvec<R> z = psi[base | scatter_t(t, c, r, hpos)];
-                chk = fma(z.x, BlkScale<R>::probe, chk);
-                chk = fma(z.y, BlkScale<R>::probe, chk);
-                lds_st<R>(swz<R>(t) * (uint32_t)sizeof(cvec<R>), BlkScale<R>::in(z));
+                most = BlkRange<R>::look(most, z);
+                lds_st<R>(swz<R>(t) * (uint32_t)sizeof(cvec<R>), z);
             }
         }
-        if (!isfinite(chk)) *fl = 1;
+        // (a NaN is not below the limit)
+        const bool ok = BlkRange<R>::below(most, BlkRange<R>::high), small = BlkRange<R>::below(most, BlkRange<R>::low);
+        const uint64_t huge = __ballot(!ok), plain = __ballot(!small), some = __ballot(small && !BlkRange<R>::zero(most));
+        if (lane == 0) {
+            if (huge) fl[0] = 1;
+            if (plain) fl[1] = 1;
+            if (some) fl[2] = 1;
+        }
         __syncthreads();
-        const bool careful = __builtin_amdgcn_readfirstlane((int)*fl) != 0;
-        if (careful) {       // the amplitudes as they are, read again
-            for (uint32_t t = threadIdx.x; t < T; t += nt)
-                lds_st<R>(swz<R>(t) * (uint32_t)sizeof(cvec<R>), psi[base | scatter_t(t, c, r, hpos)]);
+        const bool careful = __builtin_amdgcn_readfirstlane((int)fl[0]) != 0;
+        const bool scaled = !__builtin_amdgcn_readfirstlane((int)fl[1]) && __builtin_amdgcn_readfirstlane((int)fl[2]);
+        if (scaled) {
+            for (uint32_t t = threadIdx.x; t < T; t += nt) {
+                const cvec<R> z = lds_ld<R>(t * (uint32_t)sizeof(cvec<R>));
+                lds_st<R>(t * (uint32_t)sizeof(cvec<R>), cmake<R>(z.x * BlkRange<R>::up, z.y * BlkRange<R>::up));
+            }
             __syncthreads();
         }
 
@@ -562,10 +577,12 @@ __global__ __launch_bounds__(BLK_MAX_THREADS, 2) void k_blocks(cvec<R> *__restri
             }
             __syncthreads();
         }
-        if (careful && threadIdx.x == 0) *fl = 0;
-        if (careful) {
-            for (uint32_t t = threadIdx.x; t < T; t += nt)
-                psi[base | scatter_t(t, c, r, hpos)] = lds_ld<R>(swz<R>(t) * (uint32_t)sizeof(cvec<R>));
+        if (threadIdx.x == 0) fl[0] = fl[1] = fl[2] = 0;
+        if (scaled) {
+            for (uint32_t t = threadIdx.x; t < T; t += nt) {
+                const cvec<R> z = lds_ld<R>(swz<R>(t) * (uint32_t)sizeof(cvec<R>));
+                psi[base | scatter_t(t, c, r, hpos)] = cmake<R>(z.x * BlkRange<R>::down, z.y * BlkRange<R>::down);
+            }
         } else if (big) {
             for (uint32_t t0 = 0; t0 < T; t0 += nt * U) {
                 const uint64_t g0 = base | gthr | scatter_t(t0, c, r, hpos);
@@ -574,11 +591,11 @@ __global__ __launch_bounds__(BLK_MAX_THREADS, 2) void k_blocks(cvec<R> *__restri
 #pragma unroll
                 for (int u = 0; u < U; ++u) buf[u] = lds_ld<R>(s0 ^ uswz(u));
 #pragma unroll
-                for (int u = 0; u < U; ++u) psi[g0 | uoff(u)] = BlkScale<R>::out(buf[u]);
+                for (int u = 0; u < U; ++u) psi[g0 | uoff(u)] = buf[u];
             }
         } else {
             for (uint32_t t = threadIdx.x; t < T; t += nt)
-                psi[base | scatter_t(t, c, r, hpos)] = BlkScale<R>::out(lds_ld<R>(swz<R>(t) * (uint32_t)sizeof(cvec<R>)));
+                psi[base | scatter_t(t, c, r, hpos)] = lds_ld<R>(swz<R>(t) * (uint32_t)sizeof(cvec<R>));
         }
         if (tl + gridDim.x < ntiles) __syncthreads();
     }
