@@ -59,7 +59,10 @@ sv_status ensure_pinned(sv_state s, size_t bytes) {
     if (s->pinned) SV_HIP(hipHostFree(s->pinned));
     s->pinned = nullptr;
     s->pinned_bytes = 0;
-    size_t sz = std::max<size_t>(bytes, 1 << 16);
+    // room for a solve's scalars beside its vector: a Kronecker plan's matrices, which
+    // size the buffer, hold as many bytes as its solves' vectors, and a second
+    // allocation cost the first solve of such a plan 0.4 ms
+    size_t sz = std::max<size_t>(bytes, 1 << 16) + 4096;
     SV_HIP(hipHostMalloc(&s->pinned, sz, hipHostMallocDefault));
     s->pinned_bytes = sz;
     return SV_OK;
@@ -85,9 +88,10 @@ sv_status refuse_capture(sv_state s) {
     return SV_OK;
 }
 
-// src in the plan staging buffer, which the device can read; the host waits only
-// for the previous user of the buffer.  Record plan_ev behind the last reader.
-sv_status stage_plan(sv_state s, const void *src, size_t bytes, void **staged) {
+// The copy is ordered on the stream; the host waits only for the previous user of
+// the staging buffer, not for the work before it.
+sv_status upload_plan(sv_state s, void *dst, const void *src, size_t bytes) {
+    if (!bytes) return SV_OK;
     SV_TRY(refuse_capture(s));
     if (!s->plan_ev) SV_HIP(hipEventCreateWithFlags(&s->plan_ev, hipEventDisableTiming));
     else SV_HIP(hipEventSynchronize(s->plan_ev));
@@ -100,16 +104,7 @@ sv_status stage_plan(sv_state s, const void *src, size_t bytes, void **staged) {
         s->plan_bytes = sz;
     }
     memcpy(s->plan_pinned, src, bytes);
-    *staged = s->plan_pinned;
-    return SV_OK;
-}
-
-// The copy is ordered on the stream; the host does not wait for the work before it.
-sv_status upload_plan(sv_state s, void *dst, const void *src, size_t bytes) {
-    if (!bytes) return SV_OK;
-    void *p = nullptr;
-    SV_TRY(stage_plan(s, src, bytes, &p));
-    SV_HIP(hipMemcpyAsync(dst, p, bytes, hipMemcpyHostToDevice, s->stream));
+    SV_HIP(hipMemcpyAsync(dst, s->plan_pinned, bytes, hipMemcpyHostToDevice, s->stream));
     SV_HIP(hipEventRecord(s->plan_ev, s->stream));
     return SV_OK;
 }

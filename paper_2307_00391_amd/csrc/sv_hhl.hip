@@ -987,8 +987,6 @@ static sv_status eig_frame_run(sv_state s, const EigFrame &E, Workspace &w, cons
     SV_TRY(need(w.tmp, N * sizeof(double2)));
     SV_TRY(need(w.z, N * sizeof(double2)));
     SV_TRY(need(w.x, N * sizeof(double2)));
-    SV_TRY(need(w.part, 2 * nb * sizeof(double)));
-    SV_TRY(need(w.zpart, (size_t)g2.y * 4 * N * sizeof(double2)));
     SV_TRY(need(w.out, EIG_HEAD * sizeof(double) + N * sizeof(double2)));
     double *sums = (double *)w.out.p;
     const bool dev = b_dev != nullptr;
@@ -999,17 +997,28 @@ static sv_status eig_frame_run(sv_state s, const EigFrame &E, Workspace &w, cons
         SV_HIP(hipGetLastError());
     }
     const bool pipe = fused && pipe_supported(n_s, n_c);
+    if (!pipe) {
+        SV_TRY(need(w.part, 2 * nb * sizeof(double)));
+        SV_TRY(need(w.zpart, (size_t)g2.y * 4 * N * sizeof(double2)));
+    }
     // a small dense plan: V^H b^ in k_pipe_a's launch (and a host b read from
-    // the staging buffer), the end in one launch
+    // pinned memory), the end in one launch
     const bool small = pipe && !E.Vr && E.n_lo <= 1 && N <= EIG_SMALL;
     PipeHead head{(double2 *)w.beta.p, (const double2 *)E.V_hi.p, (const double2 *)w.x.p, N,
                   small ? (unsigned)((N + 63) / 64) : 0u};
-    if (!dev && small) {
-        void *staged = nullptr;
-        SV_TRY(stage_plan(s, bhat.data(), N * sizeof(double2), &staged));
-        head.b = (const double2 *)staged;
-    } else if (!dev) {
-        SV_TRY(upload_plan(s, w.x.p, bhat.data(), N * sizeof(double2)));
+    if (!dev) {
+        SV_TRY(refuse_capture(s));
+        if (!pipe) {
+            SV_TRY(upload(s, w.x.p, bhat.data(), N * sizeof(double2)));
+        } else {
+            // b^ goes in and the results come out through one pinned buffer, which
+            // nothing else uses in between: large enough for both from the start, so
+            // that a new plan's first solve allocates it once
+            SV_TRY(ensure_pinned(s, EIG_HEAD * sizeof(double) + N * sizeof(double2)));
+            memcpy(s->pinned, bhat.data(), N * sizeof(double2));
+            if (small) head.b = (const double2 *)s->pinned;
+            else SV_HIP(hipMemcpyAsync(w.x.p, s->pinned, N * sizeof(double2), hipMemcpyHostToDevice, st));
+        }
     }
     // beta = V^H b^
     if (!small)
@@ -1023,12 +1032,9 @@ static sv_status eig_frame_run(sv_state s, const EigFrame &E, Workspace &w, cons
         uint64_t nparts = 0;
         SV_TRY(pipe_run<R>(s, n_s, n_c, sgn, gcut, head, (const double2 *)w.beta.p, (const double *)E.lam_dev.p, T0,
                            w.part, (double *)w.zpart.p, &nparts));
-        if (!dev && small) SV_HIP(hipEventRecord(s->plan_ev, st));
         const int nc = eig_chunks(nparts);
         if (!dev && small && (uint64_t)rows * N <= EIG_TAIL) {
             // the results go straight into the download buffer
-            const size_t bytes = EIG_HEAD * sizeof(double) + N * sizeof(double2);
-            SV_TRY(ensure_pinned(s, bytes));
             double *out = (double *)s->pinned;
             hipLaunchKernelGGL(k_eig_tail, dim3((unsigned)(nc + (N + 15) / 16)), dim3(256), 0, st,
                                (double2 *)(out + EIG_HEAD), (const double2 *)E.V_hi.p, (const double *)w.zpart.p,

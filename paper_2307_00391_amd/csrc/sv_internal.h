@@ -75,7 +75,6 @@ sv_status gather_device(sv_state s, uint64_t mask, uint64_t value, const double 
 // SV_EUNSUPPORTED while the state's stream is being captured
 sv_status refuse_capture(sv_state s);
 // stream-ordered copy to the device through the state's plan staging; returns without waiting
-sv_status stage_plan(sv_state s, const void *src, size_t bytes, void **staged);
 sv_status upload_plan(sv_state s, void *dst, const void *src, size_t bytes);
 // uniformly controlled Ry from a device table of (cos, sin) in the state's
 // precision; fm / fv: fixed bits (the target at 0, controls at their values)
