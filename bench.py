@@ -12,7 +12,9 @@ runs sv_hhl_run_device from the right-hand side to the post-selected solution,
 both resident in HBM (the same solve from host buffers is reported beside it).
 
 value = gate-amplitude updates per second (paper_2307_00391_amd.metrics.
-hhl_updates, eigen-frame count).  The JSON line also carries: the HBM rate
+hhl_updates, eigen-frame count: the circuit's gates, of which the fused kernels
+evaluate runs in closed form, the uncompute and its projection as an inner
+product).  The JSON line also carries: the HBM rate
 of the whole step, the per-kernel roofline of the dominant kernel (HIP
 events around its launches on its own stream, during the timed steps), the
 33-qubit U3 + CNOT-ladder throughput probe, the matrix-core rate of the dense

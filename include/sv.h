@@ -423,7 +423,7 @@ const char *sv_last_eigensolver(void);
  * Ry(t) = [[cos t/2, -sin t/2], [sin t/2, cos t/2]] with
  * cos^2(t/2) = zero-child / node weight, controlled on those qubits taking
  * the value p (no gate for a node of weight 0).  A diagonal over the
- * register then restores arg(b_r).  All angles are computed on the host in
+ * register then restores arg(b_r).  All angles are computed on the device in
  * FP64 and rounded once to the state's precision.
  *   mode 0: the circuit gate by gate: |0...0>, one Ry on the top qubit, one
  *           uniformly controlled Ry pass per further level, the diagonal;
@@ -649,9 +649,9 @@ sv_status sv_batch_prepare(sv_batch *out, sv_dtype dt, void *hip_stream, const s
 sv_status sv_batch_run(sv_batch b, int use_graph, double *results);
 int sv_batch_num_solves(sv_batch b);
 /* The batch's launch form: 1 the work-queue kernel, 0 the columns, -1
- * for a NULL batch.  ms_streams / ms_queue (may be NULL): the graph
- * replay times of the two forms measured at prepare (0 when not timed: pinned,
- * cached, or tuning off). */
+ * for a NULL batch.  ms_streams (the columns) / ms_queue (may be NULL): the
+ * graph replay times of the two forms measured at prepare (0 when not timed:
+ * pinned, cached, or tuning off). */
 int sv_batch_form(sv_batch b, float *ms_streams, float *ms_queue);
 sv_status sv_batch_free(sv_batch b);
 

@@ -786,7 +786,7 @@ sv_status fusion_config(sv_state s, const std::vector<PGate> &pg, int &k, int &c
     // windows of the earliest gates, and those may run a little faster (25
     // qubits, complex64: 106 mixed gates 1217 us in 10 passes against 1249 in 9,
     // 77 gates 922 against 942, 7 passes each; 120 gates 1285 in 9 against 1233
-    // in 8; 28 qubits, complex128, 120 gates: 24.2 against 24.8 ms, with another
+    // in 7; 28 qubits, complex128, 120 gates: 24.2 against 24.8 ms, with another
     // c): where they are at most a fifth more they are candidates too.
     // A plan's time is estimated from its first pass (which holds the most
     // ops) plus a sample of the others scaled to their number.  The runs are

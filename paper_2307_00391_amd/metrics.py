@@ -63,7 +63,10 @@ def hhl_updates(n_s: int, n_c: int, mode: int) -> dict:
     the ancilla = 1 half only (the other half is discarded by the
     post-selection); the final Hadamard layer is evaluated only for the
     clock = 0 outcome it is projected on, counted as one update per
-    amplitude of the half.
+    amplitude of the half.  This is the circuit's work, whatever evaluates it:
+    the fused kernels form the transform's amplitudes as product trees and the
+    uncompute with its projection as an inner product with them, and a batch
+    stores no state.
     """
     n = n_s + n_c + 1
     full, half, quarter = 2.0 ** n, 2.0 ** (n - 1), 2.0 ** (n - 2)
