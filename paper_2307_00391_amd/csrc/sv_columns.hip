@@ -20,10 +20,10 @@
 // below: the root prod_(b < L) (low bits once per o, the next three per line),
 // then the top bits as a product tree, a node splitting into a + a q and
 // 2 a - (a + a q) (six operations), with the 32nd roots of the line bits as
-// constants.  All but the leaves in FP64 for both types: FP64 FMAs issue as
-// fast as unpacked FP32 ones, and the errors enter |P|^2 twice, alike.  (With
-// two of a line's five levels in FP64: 115 instead of 134 us for the sweep
-// below, and errors up to 1.6 times those of the kernels before.)
+// constants.  All but the leaves and their sums in FP64 for both types, since
+// the errors enter |P|^2 twice, alike.  (With two of a line's five levels in FP64:
+// 115 instead of 134 us for the sweep below, and up to three times the errors;
+// all of it in FP64: 160-178 us.)
 // A sweep of 1024 complex64 solves (n_s 4..10, n_c 8..12): 134 us, about 18
 // vector instructions per amplitude; the column tiles of k_pipe_a and k_pipe_b
 // took 850 us at 37 operations, with tables, partial column sums and twiddles
@@ -161,21 +161,27 @@ __global__ __launch_bounds__(256) void k_batch_cols(const ColClass *__restrict__
 #pragma unroll
             for (int kb = 0; kb < RB - 1; ++kb)
                 tree_level<double>(kb, Q(kb), [&](int m, double2 q) { split<double>(v[m], q, v[m], v[m + (1 << kb)]); });
-            // the leaves k = m and m + 2^(RB-1): the sums
-            R lz = 0, lpa = 0, lnt = 0;
+            // the leaves k = m and m + 2^(RB-1): the sums, in FP32 in four chains (one
+            // chain of a line's 32 terms rounds the peak's share up to 31 times: rms
+            // error of p_post over 1152 solves of 9 clock bits 2.75e-7, four chains
+            // 1.35e-7, the column tiles before 2.19e-7; the launch takes as long)
+            constexpr int NCH = sizeof(R) == 4 ? 4 : 1;
+            R lz[4] = {0, 0, 0, 0}, lpa[4] = {0, 0, 0, 0}, lnt[4] = {0, 0, 0, 0};
             const double2 qd = Q(RB - 1);
             tree_level<R>(RB - 1, cmake<R>((R)qd.x, (R)qd.y), [&](int m, cvec<R> q) {
                 constexpr int h = 1 << (RB - 1);
                 cvec<R> p, n;
                 split<R>(cmake<R>((R)v[m].x, (R)v[m].y), q, p, n);
                 const R p2 = cfma(p.x, p.x, p.y * p.y), n2 = cfma(n.x, n.x, n.y * n.y);
-                lnt += p2 + n2;
-                lz = cfma(Sl[2 * m], p2, cfma(Sl[2 * (m + h)], n2, lz));
-                lpa = cfma(Sl[2 * m + 1], p2, cfma(Sl[2 * (m + h) + 1], n2, lpa));
+                const int q4 = m & (NCH - 1);
+                lnt[q4] += p2 + n2;
+                lz[q4] = cfma(Sl[2 * m], p2, cfma(Sl[2 * (m + h)], n2, lz[q4]));
+                lpa[q4] = cfma(Sl[2 * m + 1], p2, cfma(Sl[2 * (m + h) + 1], n2, lpa[q4]));
             });
-            z += (double)lz;
-            pa += (double)lpa;
-            nt += (double)lnt;
+            auto total = [](const R (&x)[4]) { return (double)(NCH == 1 ? x[0] : (x[0] + x[1]) + (x[2] + x[3])); };
+            z += total(lz);
+            pa += total(lpa);
+            nt += total(lnt);
         }
     }
     if (wv) {
