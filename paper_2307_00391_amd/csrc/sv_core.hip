@@ -353,11 +353,13 @@ template <typename R> static inline cvec<R> hc(const double *u) {
 // Reduction partials of norm2_into: at most this many blocks.
 constexpr int NORM_MAX_PARTS = 4096;
 
-// 8 amplitudes per thread: 2^19 amplitudes on 256 workgroups take 5 us, where
-// 64 per thread (32 workgroups) took 16
+// 8 amplitudes per thread up to 1024 workgroups (2^19 amplitudes: 5 us on 256
+// workgroups, 16 on 32), then 64: four workgroups per compute unit stream as fast,
+// and the sum over 4096 partials costs more than it gains (2^24 complex128
+// amplitudes: 54 us with 1024 workgroups, 58 with 4096).
 static uint64_t norm_blocks(uint64_t count) {
-    const uint64_t per_block = 256 * 8;
-    const uint64_t nb = (count + per_block - 1) / per_block;
+    auto blocks = [&](uint64_t per_thread) { return (count + 256 * per_thread - 1) / (256 * per_thread); };
+    const uint64_t nb = std::max(std::min<uint64_t>(blocks(8), 1024), blocks(64));
     return nb > (uint64_t)NORM_MAX_PARTS ? (uint64_t)NORM_MAX_PARTS : (nb ? nb : 1);
 }
 
